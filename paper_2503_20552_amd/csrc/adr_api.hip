@@ -14,7 +14,7 @@ hipError_t launch_decode_stream(const DecodeParams &p, int d, bool fp8, hipStrea
 hipError_t read_stream_faults(unsigned long long *count);
 bool decode_stream_supports(int d, int G, int B);
 bool decode_valu_supports(int d, int G);
-bool decode_mfma_supports(int d, int G);
+bool decode_mfma_supports(int d, int G, int Hkv);
 hipError_t launch_lse_merge(const MergeParams &p, hipStream_t stream);
 hipError_t launch_stream_read(const void *src, size_t bytes, void *sink, hipStream_t stream);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t stream);
@@ -251,32 +251,68 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     if (want == ADR_KERNEL_VALU)
         return adr::decode_valu_supports(d, G) ? KERNEL_VALU : -ADR_ERR_UNSUPPORTED;
     if (want == ADR_KERNEL_MFMA_GRID)
-        return !fp8 && adr::decode_mfma_supports(d, G) ? KERNEL_GRID : -ADR_ERR_UNSUPPORTED;
+        return !fp8 && d == 128 && adr::decode_mfma_supports(d, G, cache->Hkv) ? KERNEL_GRID : -ADR_ERR_UNSUPPORTED;
     if (want == ADR_KERNEL_MFMA) {
         if (adr::decode_stream_supports(d, G, B))
             return KERNEL_STREAM;
-        return !fp8 && adr::decode_mfma_supports(d, G) ? KERNEL_GRID : -ADR_ERR_UNSUPPORTED;
+        return !fp8 && d == 128 && adr::decode_mfma_supports(d, G, cache->Hkv) ? KERNEL_GRID : -ADR_ERR_UNSUPPORTED;
     }
     if (want != ADR_KERNEL_AUTO)
         return -ADR_ERR_UNSUPPORTED;
-    // Measured on MI355X: the resident-workgroup kernel wins on split passes with many items
-    // (groups of up to four heads always; wider groups from 2048 (request, kv-head) pairs
-    // on: +11 % at 256 requests x 8 kv-heads, G = 8; about even at a quarter of that);
-    // whole-row items and small passes of wide groups run faster one workgroup per item, unless
-    // the bound on the lengths allows more than 32 partitions per row: that kernel's grid is sized
-    // from the bound, and on the 70B-shaped workload under a bound of 32 K tokens its workgroups
-    // without a partition make it 90 us against the resident kernel's 84 us (73 us under the
-    // lengths' own maximum).
+    // Measured on MI355X (us per launch, partitions as pass_cut below makes them).  With few
+    // (request, kv-head) pairs the hardware's own hand-out of one workgroup per item, three to a
+    // compute unit, beats the resident workgroups' set-up, hand-over and tail:
+    //     pairs                        8     64    320   1024 (G = 4)  1024 (G = 8)
+    //     one workgroup per item       6     18     44    197            72
+    //     resident workgroups         30     35     54    206            79
+    // From 2048 on the two meet (397 and 398 with G = 4) and the resident kernel pulls ahead as rows
+    // grow (1610 against 1650 with 4096 pairs of mean length 5000), except in groups of one
+    // head, where items of a partition each stay ahead up to 4096 pairs (236 against 248 at 2048).
     const bool splits = partition_tokens > 0 && max_seq_len > partition_tokens;
-    const bool many = (int64_t)B * cache->Hkv >= 2048 || max_parts_for(max_seq_len, partition_tokens) > 32;
+    const int64_t pairs = (int64_t)B * cache->Hkv;
+    const bool many = pairs >= (G == 1 ? 4096 : 2048);
     // An fp8 cache has the resident-workgroup kernel and the vector-ALU one only.
-    if ((fp8 || (splits && (G <= 4 || many))) && adr::decode_stream_supports(d, G, B))
+    if ((fp8 || (splits && many)) && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
-    if (!fp8 && adr::decode_mfma_supports(d, G))
+    // d = 64: 106 against 117 us (128 requests, 8 kv-heads, G = 4); not yet compared beyond 2048 pairs.
+    if (!fp8 && (d == 128 || pairs < 2048) && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
     if (adr::decode_valu_supports(d, G))
         return KERNEL_VALU;
     return -ADR_ERR_UNSUPPORTED;
+}
+
+// The partitions a pass works with, where the caller leaves both the kernel and the merge to the call:
+// what lies in the workspace in between is then the library's own affair (it never takes more than
+// the caller's partitions would).  `min_part` > 0: rows are cut finer than `tokens`, see row_partition.
+struct PassCut {
+    int tokens, min_part;
+};
+
+PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int partition_tokens, unsigned flags)
+{
+    PassCut cut = {partition_tokens, 0};
+    if (partition_tokens <= 0 || kernel == KERNEL_VALU ||
+        (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS)))
+        return cut;
+    // Rows of the cache one workgroup walks at a time (two kv-heads of 64 elements are taken together).
+    const int64_t rows = (int64_t)B * (kernel == KERNEL_GRID && cache->d == 64 ? cache->Hkv / 2 : cache->Hkv);
+    if (rows >= 1024) {
+        // Enough rows to fill the chip: an item's fixed cost (its chain of length, page table and first
+        // page, and its combine) is paid half as often with 1024 tokens as with 512, and there are half
+        // the partial results to merge.  1024 pairs: 202 against 210 us with the merge; 2048 pairs: 398
+        // against 418 (one workgroup per item) and 398 against 411 (resident).
+        if (partition_tokens < 1024)
+            cut.tokens = partition_tokens * ((1024 + partition_tokens - 1) / partition_tokens);
+    } else if (kernel == KERNEL_GRID) {
+        // Too few: with up to 96 rows partitions of 128 tokens (8 pairs of 2000 tokens: 9.5 us with the
+        // merge against 12.9 with 512; 64 pairs: 22.5 against 26), up to 1024 rows no more than 512
+        // tokens (256 pairs: 40.6 against 49.3 us with 1024).
+        const int finest = rows <= 96 ? 128 : 512;
+        if (partition_tokens > finest)
+            cut.min_part = finest;
+    }
+    return cut;
 }
 
 constexpr unsigned kFlagBits = 0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_WORKSPACE_READY |
@@ -323,7 +359,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     const int64_t max_parts = max_parts_for(max_seq_len, partition_tokens);
     if ((int64_t)B * cache->Hkv * (max_parts + 1) > 0x7fffffffLL) // (+1: the grids take an odd number per row)
         return ADR_ERR_SHAPE;
-    const bool split = partition_tokens > 0 && max_parts > 1;
+    bool split = partition_tokens > 0 && max_parts > 1;
     const WorkspacePlan plan = plan_workspace(B, Hq, d, max_seq_len, partition_tokens);
     if (static_scratch) { // the library's own array stands in for the caller's workspace
         if (plan.total() > (size_t)ADR_STATIC_SCRATCH_BYTES)
@@ -345,6 +381,9 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         return ADR_ERR_WORKSPACE;
     if (B == 0)
         return ADR_OK;
+    const PassCut cut = pass_cut(cache, kernel, B, split ? partition_tokens : 0, flags);
+    const int cut_parts = (int)max_parts_for(max_seq_len, cut.tokens);
+    split = split && cut_parts > 1;
 
     adr::DecodeParams p;
     p.q = (const uint16_t *)q;
@@ -373,9 +412,10 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     p.Hkv = cache->Hkv;
     p.G = G;
     p.num_pages = cache->num_pages;
-    p.partition_tokens = split ? partition_tokens : 0;
-    p.max_parts = split ? (int)max_parts : 1;
+    p.partition_tokens = split ? cut.tokens : 0;
+    p.max_parts = split ? cut_parts : 1;
     p.max_seq_len = max_seq_len;
+    p.min_part = split ? cut.min_part : 0;
     p.out_f32 = out_dtype == ADR_F32;
     p.scale_log2e = scale * adr::kLog2e;
     p.coalesce = !(flags & ADR_SINGLE_PARTITION_ITEMS);
@@ -432,9 +472,10 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         mp.part_lse = p.part_lse;
         mp.part_offsets = nullptr;
         mp.seq_lens = seq_lens;
-        mp.partition_tokens = partition_tokens;
-        mp.max_parts = (int)max_parts;
+        mp.partition_tokens = p.partition_tokens;
+        mp.max_parts = p.max_parts;
         mp.max_seq_len = max_seq_len;
+        mp.min_part = p.min_part;
         mp.B = B;
         mp.heads = Hq;
         mp.d = d;
@@ -514,6 +555,7 @@ int adr_decode_merge(void *out, adr_dtype out_dtype, float *lse, const int32_t *
     mp.partition_tokens = partition_tokens;
     mp.max_parts = (int)max_parts;
     mp.max_seq_len = max_seq_len;
+    mp.min_part = 0;
     mp.B = B;
     mp.heads = Hq;
     mp.d = d;
@@ -545,6 +587,7 @@ int adr_lse_merge(void *out, adr_dtype out_dtype, float *lse_out, const float *p
     mp.partition_tokens = 0;
     mp.max_parts = 0;
     mp.max_seq_len = 0;
+    mp.min_part = 0;
     mp.B = B;
     mp.heads = heads;
     mp.d = d;

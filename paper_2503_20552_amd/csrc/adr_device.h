@@ -65,6 +65,7 @@ struct DecodeParams {
     int partition_tokens; // 0 = whole sequence in one pass
     int max_parts;        // partitions per request the grid was sized for (>= 1)
     int max_seq_len;
+    int min_part;         // > 0: rows are cut finer than partition_tokens, down to this many (row_partition)
     int out_f32;          // 1: out is fp32, 0: bf16
     int coalesce;         // the resident kernel may take runs of partitions as one item
     float scale_log2e;    // softmax scale * log2(e): scores are kept in base 2
@@ -82,6 +83,7 @@ struct MergeParams {
     const int32_t *seq_lens;     // implicit layout: request b owns partitions
     int partition_tokens;        //   [b*max_parts, b*max_parts + ceil(min(seq_len,max_seq_len)/partition_tokens))
     int max_parts, max_seq_len;  //   and rows with <= 1 partition are left alone
+    int min_part;                //   (row_partition)
     int B, heads, d, out_f32;
     const uint32_t *status;      // call status block of the pass that wrote the partials, or nullptr: when
                                  // its expired-waits word is not zero every row gets NaN
@@ -141,6 +143,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f)
         return (u >> 16) | 0x40u;
     u += 0x7fffu + ((u >> 16) & 1u);
     return u >> 16;
+}
+
+// Two fp32 -> two bf16, round to nearest even (one instruction on gfx950).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -230,6 +240,17 @@ __device__ __forceinline__ int parts_of(int L, int partition_tokens)
     if (partition_tokens <= 0 || L <= 0)
         return 1;
     return (L + partition_tokens - 1) / partition_tokens;
+}
+
+// Tokens per partition of a row of L tokens.  A pass too small to fill the chip cuts a row finer than
+// the caller's partition, into as many partitions as the workspace has places for (max_parts, from
+// the bound on the lengths), but not below min_part tokens; min_part = 0 leaves the caller's.
+__device__ __forceinline__ int row_partition(int L, int partition_tokens, int max_parts, int min_part)
+{
+    if (min_part == 0)
+        return partition_tokens;
+    const int even = ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1);
+    return min(max(even, min_part), partition_tokens);
 }
 
 // Combine the kWaves per-wave partial results staged in LDS and write either

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const MergeParams p)
         count = p.part_offsets[b + 1] - first;
     } else {
         const int L = max(min(p.seq_lens[b], p.max_seq_len), 0);
-        count = parts_of(L, p.partition_tokens);
+        count = parts_of(L, row_partition(L, p.partition_tokens, p.max_parts, p.min_part));
         first = b * p.max_parts;
         if (count <= 1)
             return; // the attention kernel already wrote this row's final result

@@ -106,15 +106,23 @@ __device__ __forceinline__ u32x4 fp8x8_to_bf16x8(u32x2 w) { return u32x4{w[0], w
 //   ka           A operand of QK^T (see decode_mfma.hip), one register group per step
 //   score_scale  softmax scale * log2(e) (* the page's K scale for an fp8 cache)
 //   p_scale      1, or the page's V scale for an fp8 cache: O += (P * p_scale) V
+//   PAIR         the tile's rows are two kv-heads of 64 elements side by side; `upper`: this lane's
+//                head belongs to the second of them.  Each kv-head has a sum of its own (no product
+//                of one head's query with the other's keys, which may hold an infinity)
+template <bool PAIR = false>
 __device__ __forceinline__ void attend_page(WaveState &st, PageRegs &pg, const u32x4 (&ka)[4],
                                             const u32x4 (&qb)[4], float score_scale, float p_scale,
-                                            int tok, int t1, int j)
+                                            int tok, int t1, int j, bool upper = false)
 {
-    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, s_up = s;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[kk]),
-                                                    __builtin_bit_cast(bf16x8, qb[kk]), s, 0, 0, 0);
+    for (int kk = 0; kk < 4; ++kk) {
+        f32x4 &acc = PAIR && kk >= 2 ? s_up : s;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[kk]),
+                                                      __builtin_bit_cast(bf16x8, qb[kk]), acc, 0, 0, 0);
+    }
+    if (PAIR && upper)
+        s = s_up;
     // tok = index of the first of this lane's four tokens (4j + i)
     const bool tail = tok - 4 * j + kPageSize > t1;
     float sc[4];
@@ -147,20 +155,24 @@ __device__ __forceinline__ void attend_page(WaveState &st, PageRegs &pg, const u
                 st.o[e][i] *= a;
         }
     }
-    uint32_t ph[4], pl[4];
+    // Weights as bf16 terms, element i <-> token 4j+i.  Two heads' worth of a pair row carry three terms
+    // (24 bits: what the vector-ALU kernel, which serves the same shapes, keeps in fp32), others two.
+    constexpr int TERMS = PAIR ? 3 : 2;
+    u32x2 w[TERMS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float pw = fast_exp2(sc[i] - st.m);
-        st.l += pw;
-        pw *= p_scale;
-        ph[i] = __float_as_uint(pw) & 0xffff0000u;            // bf16 head (truncated)
-        pl[i] = __float_as_uint(pw - __uint_as_float(ph[i])); // remainder, exact in fp32
+    for (int h = 0; h < 2; ++h) {
+        float p0 = fast_exp2(sc[2 * h] - st.m), p1 = fast_exp2(sc[2 * h + 1] - st.m);
+        st.l += p0;
+        st.l += p1;
+        p0 *= p_scale;
+        p1 *= p_scale;
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) {
+            w[t][h] = pack_bf16(p0, p1);
+            p0 -= bf16_lo(w[t][h]); // exact
+            p1 -= bf16_hi(w[t][h]);
+        }
     }
-    u32x2 ah, al; // four bf16 each: element i <-> token 4j+i
-    ah[0] = (ph[0] >> 16) | ph[1];
-    ah[1] = (ph[2] >> 16) | ph[3];
-    al[0] = (pl[0] >> 16) | (pl[1] & 0xffff0000u);
-    al[1] = (pl[2] >> 16) | (pl[3] & 0xffff0000u);
 
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -168,10 +180,10 @@ __device__ __forceinline__ void attend_page(WaveState &st, PageRegs &pg, const u
         u32x2 vb;
         vb[0] = __builtin_amdgcn_perm(pg.v[1][e >> 1], pg.v[0][e >> 1], sel);
         vb[1] = __builtin_amdgcn_perm(pg.v[3][e >> 1], pg.v[2][e >> 1], sel);
-        st.o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-            __builtin_bit_cast(s16x4, ah), __builtin_bit_cast(s16x4, vb), st.o[e], 0, 0, 0);
-        st.o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-            __builtin_bit_cast(s16x4, al), __builtin_bit_cast(s16x4, vb), st.o[e], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t)
+            st.o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                __builtin_bit_cast(s16x4, w[t]), __builtin_bit_cast(s16x4, vb), st.o[e], 0, 0, 0);
     }
 }
 

@@ -199,6 +199,19 @@ def test_kernel_choice_is_reported_by_the_library():
     assert lib.adr_kernel_name(0) == b""
 
 
+def test_small_passes_take_one_workgroup_per_item():
+    lib = adr.load_library()
+    def choice(c, B, Hq, part=512, flags=0):
+        return lib.adr_decode_kernel_choice(ctypes.byref(c), B, Hq, 8192, part, flags)
+    gqa, half = cache(Hkv=8), cache(Hkv=8, d=64)
+    assert choice(gqa, 1, 32) == choice(gqa, 255, 32) == adr.KERNEL_MFMA_GRID and choice(gqa, 256, 16) == adr.KERNEL_MFMA
+    assert choice(cache(Hkv=32), 64, 32) == adr.KERNEL_MFMA_GRID and choice(cache(Hkv=32), 128, 32) == adr.KERNEL_MFMA
+    assert choice(half, 255, 32) == choice(half, 1, 64, part=0) == adr.KERNEL_MFMA_GRID
+    assert choice(cache(Hkv=1, d=64), 8, 8) == choice(half, 256, 64) == adr.KERNEL_VALU     # no pair; a large pass
+    assert choice(cache(Hkv=2, d=64), 8, 32) == choice(cache(Hkv=2, d=64), 8, 6) == -UNSUP  # groups of 16 and 3: as before
+    assert choice(half, 8, 32, flags=adr.KERNEL_MFMA_GRID) == choice(half, 8, 32, flags=adr.KERNEL_MFMA) == -UNSUP
+
+
 def test_cu_mask_stream_and_fault_count_reject_bad_arguments():
     lib = adr.load_library()
     handle = ctypes.c_void_p()

@@ -1,0 +1,90 @@
+"""GPU parity of the one-workgroup-per-item kernel where the library picks it by itself: two kv-heads of
+64 elements taken side by side, rows cut finer or coarser than the caller's partitions, waves with more
+tiles than one load of the page table brings, and the edges of tiles, waves and partitions in between."""
+import types
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_20552_amd as adr
+import workloads as W
+from gpu_util import ATOL, compare, dev, gpu_attention, oracle_attention, say
+
+pytestmark = pytest.mark.gpu
+
+# around the edges of a tile, of a workgroup's four waves, of partitions of 64, 128 and 512 tokens
+EDGES = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 511, 512, 513, 1023, 1024, 1025]
+
+
+def make(seed, Hq, Hkv, d, lens_after, page_size=16):
+    lens_after = np.asarray(lens_after, dtype=np.int32)
+    wl = W.Workload(96, "item", B=len(lens_after), Hq=Hq, Hkv=Hkv, d=d, lengths="given", page_size=page_size)
+    b = W.make_batch(wl, device="cpu", headroom_tokens=1, seed_offset=seed, lens_before=np.maximum(lens_after - 1, 0))
+    # (the slot of a row's last token, which no append has filled here, holds a value and not the poison)
+    k, v = torch.nan_to_num(b.k_cache.float(), nan=0.25), torch.nan_to_num(b.v_cache.float(), nan=-0.5)
+    return types.SimpleNamespace(wl=wl, q=b.q, k_cache=k.to(torch.bfloat16), v_cache=v.to(torch.bfloat16),
+                                 block_table=b.block_table, seq_lens=lens_after)
+
+
+def check(b, what, **kw):
+    args = (dev(b.q), dev(b.k_cache), dev(b.v_cache), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
+    say(what)
+    out, lse = gpu_attention(*args, **kw)
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    assert compare(out, lse, ref, ref_lse, what=what)[0] <= ATOL
+    again, lse_again = gpu_attention(*args, **kw)
+    assert torch.equal(out, again) and torch.equal(lse, lse_again)
+    return out, lse
+
+
+@pytest.mark.parametrize("G,Hkv", [(1, 2), (4, 8), (8, 2), (2, 6)])
+@pytest.mark.parametrize("partition_tokens", [0, 64, 512])
+@pytest.mark.parametrize("page_size", [16, 64])
+def test_heads_of_64_in_pairs(G, Hkv, partition_tokens, page_size):
+    b = make(G + Hkv, G * Hkv, Hkv, 64, EDGES, page_size)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    assert adr.adr_decode_kernel_choice(cache, len(EDGES), G * Hkv, 1025, partition_tokens) == adr.KERNEL_MFMA_GRID
+    check(b, "pairs G=%d Hkv=%d part=%d page=%d" % (G, Hkv, partition_tokens, page_size),
+          partition_tokens=partition_tokens)
+
+
+def test_a_kv_head_with_infinities_leaves_its_neighbour_alone():
+    b = make(7, 8, 2, 64, [40, 700])
+    k = b.k_cache.clone()
+    k[:, :, 1, 5] = float("inf")
+    args = (dev(b.q), dev(b.k_cache), dev(b.v_cache), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
+    say("infinities in the second of two kv-heads")
+    clean, _ = gpu_attention(*args, partition_tokens=64)
+    dirty, _ = gpu_attention(args[0], dev(k), *args[2:], partition_tokens=64)
+    assert torch.equal(clean[:, :4], dirty[:, :4]) and not torch.equal(clean[:, 4:], dirty[:, 4:])
+
+
+@pytest.mark.parametrize("Hkv,G", [(1, 4), (8, 2)])                # 1 .. 96 rows of the cache: partitions of 128
+@pytest.mark.parametrize("bound", [None, 8192])                    # places of the workspace: 3 or 16 a row
+def test_a_small_pass_is_cut_finer_than_the_callers_partitions(Hkv, G, bound):
+    b = make(11 + Hkv, G * Hkv, Hkv, 128, [1, 128, 129, 2047, 2048, 2049, 0, 300, 1100][:9 if Hkv == 8 else 4])
+    if bound:                                                     # the table has to describe that many tokens
+        wide = np.zeros((b.block_table.shape[0], bound // 16), dtype=np.int32)
+        wide[:, :b.block_table.shape[1]] = b.block_table
+        b.block_table = wide
+    out, _ = check(b, "finer Hkv=%d bound=%s" % (Hkv, bound), partition_tokens=1024, max_seq_len=bound)
+    args = (dev(b.q), dev(b.k_cache), dev(b.v_cache), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
+    whole, _ = gpu_attention(*args, partition_tokens=1024, max_seq_len=bound, flags=adr.SINGLE_PARTITION_ITEMS)
+    assert (not torch.equal(out, whole)) and (out - whole).abs().max().item() < 1e-4
+
+
+def test_a_large_pass_is_cut_coarser_than_the_callers_partitions():
+    b = make(13, 16, 16, 128, np.resize(EDGES + [1500, 2100], 64))       # 1024 rows of the cache
+    out, _ = check(b, "coarser", partition_tokens=48)
+    args = (dev(b.q), dev(b.k_cache), dev(b.v_cache), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
+    fine, _ = gpu_attention(*args, partition_tokens=48, flags=adr.SINGLE_PARTITION_ITEMS)
+    assert (not torch.equal(out, fine)) and (out - fine).abs().max().item() < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("page_size", [16, 32])
+def test_a_wave_with_more_tiles_than_one_load_of_the_table_brings(d, page_size):
+    # 64 tiles of 16 tokens for each of four waves: 4096 tokens, and its double
+    check(make(17, 4, 2, d, [4095, 4096, 4097, 8192 + 17, 33], page_size), "long unsplit rows d=%d" % d,
+          partition_tokens=0)
