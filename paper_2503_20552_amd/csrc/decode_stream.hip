@@ -506,20 +506,19 @@ __device__ __forceinline__ PairWeights pair_softmax(WaveState &st, PageRegs &pb,
                 st.o[e][i] *= a;
         }
     }
-    uint32_t ph[8], pl[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float pw = fast_exp2(sc[i] - st.m);
-        st.l += pw;
-        pw *= i < 4 ? p_scale_a : p_scale_b;
-        ph[i] = __float_as_uint(pw) & 0xffff0000u;            // bf16 head (truncated)
-        pl[i] = __float_as_uint(pw - __uint_as_float(ph[i])); // remainder, exact in fp32
-    }
+    // A bf16 head and a bf16 remainder, both rounded by the conversion instruction: 17 bits of each weight
+    // without a bias (cut off instead, the remainder made every result 8e-6 too small: error against 64
+    // bits 8.7e-6 before, 2.3e-6 now; the time is the same).
     PairWeights w;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
-        w.ah[h] = (ph[2 * h] >> 16) | ph[2 * h + 1];
-        w.al[h] = (pl[2 * h] >> 16) | (pl[2 * h + 1] & 0xffff0000u);
+        float p0 = fast_exp2(sc[2 * h] - st.m), p1 = fast_exp2(sc[2 * h + 1] - st.m);
+        st.l += p0;
+        st.l += p1;
+        p0 *= h < 2 ? p_scale_a : p_scale_b;
+        p1 *= h < 2 ? p_scale_a : p_scale_b;
+        w.ah[h] = pack_bf16(p0, p1);
+        w.al[h] = pack_bf16(p0 - bf16_lo(w.ah[h]), p1 - bf16_hi(w.ah[h])); // (the differences are exact)
     }
     return w;
 }
@@ -803,20 +802,17 @@ __device__ __forceinline__ void single_page_fp8(WaveState &st, const u32x2 (&k8)
                 st.o[e][i] *= a;
         }
     }
-    uint32_t ph[4], pl[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float pw = fast_exp2(sc[i] - st.m);
-        st.l += pw;
-        pw *= p_scale;
-        ph[i] = __float_as_uint(pw) & 0xffff0000u;
-        pl[i] = __float_as_uint(pw - __uint_as_float(ph[i]));
-    }
     u32x2 ah, al;
-    ah[0] = (ph[0] >> 16) | ph[1];
-    ah[1] = (ph[2] >> 16) | ph[3];
-    al[0] = (pl[0] >> 16) | (pl[1] & 0xffff0000u);
-    al[1] = (pl[2] >> 16) | (pl[3] & 0xffff0000u);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float p0 = fast_exp2(sc[2 * h] - st.m), p1 = fast_exp2(sc[2 * h + 1] - st.m);
+        st.l += p0;
+        st.l += p1;
+        p0 *= p_scale;
+        p1 *= p_scale;
+        ah[h] = pack_bf16(p0, p1);
+        al[h] = pack_bf16(p0 - bf16_lo(ah[h]), p1 - bf16_hi(ah[h]));
+    }
     const uint32_t keep = tail ? tail_mask_fp8(tok, t1) : 0xffffffffu; // rows past the end may hold anything
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
