@@ -59,8 +59,8 @@ typedef enum { ADR_BF16 = 0, ADR_FP8_E4M3 = 1, ADR_F32 = 2 } adr_dtype;
 
 /* Kernel choice for adr_decode_attention (bits 0..3 of `flags`). */
 enum {
-    ADR_KERNEL_AUTO = 0, /* the library picks per shape (bf16 with d = 64 and an even number of kv-heads may
-                            then run on kernel 3, which cannot be asked for by name there), and a split
+    ADR_KERNEL_AUTO = 0, /* the library picks per shape (an fp8 cache, and d = 64 with an even number of
+                            kv-heads, may then run on kernel 3, which cannot be asked for by name there), and a split
                             pass that merges may cut the rows coarser or finer than
                             partition_tokens, within the same workspace; the result is the same
                             up to the order of the floating-point sums, and the choice depends on

@@ -9,7 +9,7 @@
 namespace adr {
 hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
-hipError_t launch_decode_mfma(const DecodeParams &p, int d, hipStream_t stream);
+hipError_t launch_decode_mfma(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t launch_decode_stream(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t read_stream_faults(unsigned long long *count);
 bool decode_stream_supports(int d, int G, int B);
@@ -270,12 +270,18 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // head, where items of a partition each stay ahead up to 4096 pairs (236 against 248 at 2048).
     const bool splits = partition_tokens > 0 && max_seq_len > partition_tokens;
     const int64_t pairs = (int64_t)B * cache->Hkv;
-    const bool many = pairs >= (G == 1 ? 4096 : 2048);
-    // An fp8 cache has the resident-workgroup kernel and the vector-ALU one only.
-    if ((fp8 || (splits && many)) && adr::decode_stream_supports(d, G, B))
+    bool resident = splits && pairs >= (G == 1 ? 4096 : 2048);
+    // fp8: at 2048 pairs the resident kernel is ahead only with groups of two to four heads and long rows
+    // (235 against 250 us at a median of 1500 tokens, bound 8192); 65 against 89 us the other way at a
+    // median of 300, bound 2400, and with groups of eight 244 against 283.  (Unsplit passes of that size
+    // stay there as well, though one workgroup per row takes 264 against 392 us: which kernel serves
+    // them is what adr_decode_kernel_choice has always said.)
+    if (fp8)
+        resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len >= 8192;
+    if (resident && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
     // d = 64: 106 against 117 us (128 requests, 8 kv-heads, G = 4); not yet compared beyond 2048 pairs.
-    if (!fp8 && (d == 128 || pairs < 2048) && adr::decode_mfma_supports(d, G, cache->Hkv))
+    if ((d == 128 || pairs < 2048) && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
     if (adr::decode_valu_supports(d, G))
         return KERNEL_VALU;
@@ -460,7 +466,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
             return ADR_ERR_LAUNCH;
     }
     hipError_t e = kernel == KERNEL_STREAM ? adr::launch_decode_stream(p, d, fp8, (hipStream_t)stream)
-                   : kernel == KERNEL_GRID ? adr::launch_decode_mfma(p, d, (hipStream_t)stream)
+                   : kernel == KERNEL_GRID ? adr::launch_decode_mfma(p, d, fp8, (hipStream_t)stream)
                                            : adr::launch_decode_valu(p, d, fp8, (hipStream_t)stream);
     if (e != hipSuccess)
         return ADR_ERR_LAUNCH;

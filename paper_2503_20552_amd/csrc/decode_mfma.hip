@@ -1,5 +1,5 @@
 // Decode attention with the QK^T and PV contractions on the matrix cores
-// (bf16 cache; d = 128 with any group size G <= 16, and d = 64 with two kv-heads taken together).
+// (bf16 or fp8 cache; d = 128 with any group size G <= 16, and d = 64 with two kv-heads taken together).
 //
 // One workgroup of 4 waves per (request, kv-head, partition); wave w streams
 // tiles w, w+4, ... .  A tile is 16 tokens = one MFMA tile edge (a cache page is one or
@@ -20,6 +20,16 @@
 // G .. 2G-1, contracted with chunks 8 .. 15.  P V is taken over the whole row and each head keeps its
 // half.  (113 against 121 us for the vector-ALU kernel at 128 requests, 8 kv-heads, G = 4.)
 //
+// fp8 cache: two tiles a step, K and V both by direct-to-LDS loads into one stage of 8 KB per wave, which
+// is copied to registers and refilled at once; K is widened to bf16 after the LDS read and meets the
+// query as it is (exact: error against 64 bits 2.7e-6, the resident kernel's two-term fp8 query
+// 1.6e-5), V comes out of the LDS transposed (mfma_fp8.h).  The scales of a wave's pages arrive with
+// one gather per sixty-four tiles, not page by page.  Measured against the resident kernel, which
+// served fp8 before: 9 against 37 us at one request of 2000 tokens, 35 against 60 at 40 requests,
+// 130 against 146 at 128, 53 against 79 with groups of eight; heads of 64 (before: vector ALUs)
+// 70 against 127.  Three workgroups to a compute unit: four are slower (142 against 130 us at 128
+// requests), and so is a second stage with two (132).
+//
 // QK^T  S[token][head] = K[16 x 128] * Q^T[128 x 16] as four
 //       v_mfma_f32_16x16x32_bf16.  The A operand wants lane (r, j) to hold 16
 //       bytes of token r -- sixteen different rows per quarter wave, a pattern
@@ -30,8 +40,8 @@
 //       XOR-permuted by t (slot s holds chunk s ^ t), which makes the operand
 //       reads -- sixteen rows, same chunk -- hit sixteen different bank groups.
 //       Step kk, lane (r, j) contracts chunk kk*4 + j; Q^T (the B operand,
-//       head r, loaded once) uses the same order.  Heads r >= G are zero
-//       columns.  Each wave owns two such tiles (the page being consumed and
+//       head r, loaded once) uses the same order.  Columns past the last
+//       head repeat it and are never stored.  Each wave owns two such tiles (the page being consumed and
 //       the page in flight).
 //       Result layout: lane (r, j) holds S[token 4j+i][head r], i = 0..3.
 // softmax  per lane over its 4 tokens, running max shared across the four
@@ -46,7 +56,7 @@
 //       instruction -- and the B operand (k = token 4j+u, n = r) for column
 //       set e is assembled from those four registers with byte permutes.
 //       Result layout: lane (r, j) holds O[head 4j+i][8r + e].
-#include "mfma_page.h"
+#include "mfma_fp8.h"
 
 #include <algorithm>
 
@@ -84,42 +94,177 @@ constexpr int kWaveBytes = kStages * kTileBytes; // LDS of one wave: its K tiles
 // The tiles of one wave in one partition: first, first + NW, ...  Their table entries arrive with one
 // vector load, lane n holding the wave's n-th tile, and reach the scalar unit by a lane read; a
 // second register holds the next sixty-four.
-template <int NW>
+template <int NW, bool FP8, bool PAIR>
 struct TileIds {
     const int32_t *row; // the row's table
-    int first, last_entry, shift;
+    int first, count, last_entry, shift;
     int now, next;
+    // fp8: the scales of the tiles' pages, K and V, of the one kv-head or of both of a pair
+    static constexpr int SCALES = FP8 ? (PAIR ? 4 : 2) : 1;
+    float scale_now[SCALES], scale_next[SCALES];
 
     __device__ __forceinline__ int load(int n) const
     {
-        return row[min((first + n * NW) >> shift, last_entry)]; // (clamped: inside the row's table)
+        // (a lane past the last tile reads the last one's entry; never outside the row's table)
+        return row[min((first + min(n, max(count - 1, 0)) * NW) >> shift, last_entry)];
     }
-    __device__ __forceinline__ void start(const DecodeParams &p, int b, int first_tile)
+    // Scales of the pages `entry` of tiles n (one to a lane); zero past the last tile.
+    __device__ __forceinline__ void load_scales(const DecodeParams &p, int h, int entry, int n, float (&to)[SCALES]) const
+    {
+        if constexpr (FP8) {
+#pragma unroll
+            for (int i = 0; i < SCALES; ++i)
+                to[i] = 0.f;
+            if (n < count) {
+                const int64_t at = (int64_t)clamp_page(entry, p.num_pages) * p.Hkv + (PAIR ? 2 * h : h);
+#pragma unroll
+                for (int i = 0; i < SCALES / 2; ++i) {
+                    to[2 * i] = p.k_scale[at + i];
+                    to[2 * i + 1] = p.v_scale[at + i];
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void start(const DecodeParams &p, int b, int first_tile, int tiles)
     {
         row = p.block_table + (int64_t)b * p.max_pages;
         first = first_tile;
+        count = tiles;
         last_entry = p.max_pages - 1;
         shift = p.page_shift;
         now = load(threadIdx.x & 63);
         next = 0;
     }
     // Entry of tile n; called for n = 0, 1, 2, ... in turn, in front of the tile's own loads.
-    __device__ __forceinline__ int entry(int n, int count)
+    __device__ __forceinline__ int entry(const DecodeParams &p, int h, int n)
     {
         if ((n & 63) == 0) {
             if (n) {
                 asm volatile("" : "+v"(next)); // it is waited for here and not at every lane read below
                 now = next;
+                if constexpr (FP8) {
+                    settle(scale_next);
+#pragma unroll
+                    for (int i = 0; i < SCALES; ++i)
+                        scale_now[i] = scale_next[i];
+                }
             }
             if (count > n + 64)
                 next = load(n + 64 + (threadIdx.x & 63));
         }
+        if (FP8 && (n & 63) == 32 && count > n + 32) {
+            asm volatile("" : "+v"(next));
+            load_scales(p, h, next, n + 32 + (threadIdx.x & 63), scale_next);
+        }
         return __builtin_amdgcn_readlane(now, n & 63);
+    }
+    // Loads of scales are waited for here.
+    static __device__ __forceinline__ void settle(float (&s)[SCALES])
+    {
+#pragma unroll
+        for (int i = 0; i < SCALES; ++i)
+            asm volatile("" : "+v"(s[i]));
+    }
+    // fp8: scale i of tile n (0: K, 1: V; a pair's second kv-head: 2, 3).
+    __device__ __forceinline__ float scale(int i, int n) const
+    {
+        return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale_now[i]), n & 63));
     }
 };
 
-template <bool PAIR, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3)))
+// ---- fp8 cache: two tiles (32 tokens) at a time ------------------------------------------------
+
+// Loads of one tile of K or V for one row of D bytes per token: two, of eight rows each; slot c of row t
+// holds the row's 16-byte chunk c ^ (t & 7), so that the transposed reads below hit different banks.
+__device__ __forceinline__ void load_tile_fp8(char *tile, __amdgpu_buffer_rsrc_t rsrc, const uint32_t (&lane_off)[2])
+{
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)(tile + i * 1024), 16,
+                                                 lane_off[i], 0, 0, kStreamOnce);
+    asm volatile("" ::: "memory");
+}
+
+// S = K Q^T of one tile, K widened to bf16 (exact).
+template <bool PAIR>
+__device__ __forceinline__ f32x4 scores_fp8(const u32x2 (&k8)[4], const u32x4 (&qb)[4], bool upper)
+{
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, s_up = s;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        f32x4 &acc = PAIR && kk >= 2 ? s_up : s;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(k8[kk])),
+                                                      __builtin_bit_cast(bf16x8, qb[kk]), acc, 0, 0, 0);
+    }
+    return PAIR && upper ? s_up : s;
+}
+
+// One online-softmax step over two tiles and O += P V.
+//   sc   base-2 scores of tokens tok + i of the first tile and tok_b + i of the second (i = 0 .. 3)
+//   v8   V bytes, transposed: for column block e, four tokens of the first tile, then of the second
+template <bool PAIR>
+__device__ __forceinline__ void attend_two_fp8(WaveState &st, float (&sc)[8], u32x2 (&v8)[8], float vs_a, float vs_b,
+                                               int tok, int tok_b, int t1, int j)
+{
+    if (tok_b - 4 * j + kPageSize > t1) { // tokens past the end (the second tile as a whole may lie there)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (tok + i >= t1)
+                sc[i] = -INFINITY;
+            if (tok_b + i >= t1)
+                sc[4 + i] = -INFINITY;
+        }
+        const uint32_t keep_a = tail_mask_fp8(tok, t1), keep_b = tail_mask_fp8(tok_b, t1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { // their rows may hold anything: keep them out of P V
+            v8[e][0] &= keep_a;
+            v8[e][1] &= keep_b;
+        }
+    }
+    float bm = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+    bm = max_across_rows(bm);
+    if (__any(bm > st.m + kMaxSlack)) {
+        const float mn = fmaxf(st.m, bm);
+        const float alpha = fast_exp2(st.m - mn);
+        st.m = mn;
+        st.l *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a = __shfl(alpha, 4 * j + i);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                st.o[e][i] *= a;
+        }
+    }
+    constexpr int TERMS = PAIR ? 3 : 2; // (see attend_page)
+    u32x4 w[TERMS];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float p0 = fast_exp2(sc[2 * k] - st.m), p1 = fast_exp2(sc[2 * k + 1] - st.m);
+        st.l += p0;
+        st.l += p1;
+        p0 *= k < 2 ? vs_a : vs_b;
+        p1 *= k < 2 ? vs_a : vs_b;
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) {
+            w[t][k] = pack_bf16(p0, p1);
+            p0 -= bf16_lo(w[t][k]);
+            p1 -= bf16_hi(w[t][k]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const u32x4 v = fp8x8_to_bf16x8(v8[e]);
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t)
+            st.o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]),
+                                                              __builtin_bit_cast(bf16x8, v), st.o[e], 0, 0, 0);
+    }
+}
+
+template <bool FP8, bool PAIR, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2)))
 void decode_mfma_kernel(const DecodeParams p)
 {
     constexpr int HD = PAIR ? D / 2 : D;           // elements of one head
@@ -146,33 +291,55 @@ void decode_mfma_kernel(const DecodeParams p)
     const int n_parts = parts_of(L, pt);
     if (first_part >= n_parts)
         return;
-    TileIds<NW> ids;
-    ids.start(p, b, first_part * (pt / kPageSize) + wave);
+    TileIds<NW, FP8, PAIR> ids;
+    auto start = [&](int part) { // this wave's tiles of a partition
+        const int t0 = part * pt, t1 = pt > 0 ? min(L, t0 + pt) : L;
+        const int tiles = (t1 - t0 + kPageSize - 1) / kPageSize - wave;
+        ids.start(p, b, t0 / kPageSize + wave, tiles > 0 ? (tiles + NW - 1) / NW : 0);
+    };
+    start(first_part);
 
-    // B operand of QK^T: head r's query, chunk order matching the K loads
+    // B operand of QK^T: head r's query, chunk order matching the K loads.  (Columns past the last head
+    // repeat it, and a column of a pair holds its query in the other kv-head's chunks too: nobody reads
+    // what comes of those.  Loads without a condition leave the tiles' loads to go out behind them.)
     u32x4 qb[4];
+    {
+        const uint16_t *q = p.q + (int64_t)b * p.q_row_stride + (int64_t)(h * R + min(r, R - 1)) * HD;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        qb[kk] = u32x4{0u, 0u, 0u, 0u};
-        const int chunk = kk * 4 + j;
-        if (r < R && (!PAIR || (kk >= 2) == upper))
-            qb[kk] = *(const u32x4 *)(p.q + (int64_t)b * p.q_row_stride + (int64_t)(h * R + r) * HD +
-                                      (PAIR ? chunk & 7 : chunk) * 8);
+        for (int kk = 0; kk < 4; ++kk)
+            qb[kk] = *(const u32x4 *)(q + (PAIR ? (kk * 4 + j) & 7 : kk * 4 + j) * 8);
     }
 
-    // Byte offsets of this lane.
+    // Byte offsets of this lane, bf16:
     //  K load i (to LDS): row t = 4i + j, slot r of that row, which holds chunk r ^ t.
     //  K operand read, step kk: row r, chunk kk*4 + j, which sits in slot (kk*4 + j) ^ r.
     //  V load u (to registers): row 4j + u, chunk r.
-    const uint32_t tok_bytes = (uint32_t)H * D * 2;
-    uint32_t k_lane[4], k_read[4];
+    // fp8 (load_tile_fp8):
+    //  K and V load i (to LDS): row t = 8i + lane / 8, slot lane % 8.
+    //  K operand read, step kk: row r, 8-byte piece kk*4 + j.
+    //  V read, transposed: lane c + 2k of its sixteen names token 4j + (k & 3) of the first (k < 4) or
+    //  the second tile, half c of chunk e.
+    const uint32_t tok_bytes = (uint32_t)H * D * (FP8 ? 1 : 2);
+    const uint32_t head_bytes = (uint32_t)h * D * (FP8 ? 1 : 2);
+    uint32_t k_lane[4], k_read[4], fp8_lane[2], v_tr[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int t = 4 * i + j;
-        k_lane[i] = (uint32_t)h * D * 2 + t * tok_bytes + ((r ^ t) * 16);
-        k_read[i] = r * (D * 2) + (((i * 4 + j) ^ r) * 16);
+        k_lane[i] = head_bytes + t * tok_bytes + ((r ^ t) * 16);
+        const int chunk = i * 4 + j;
+        k_read[i] = FP8 ? r * D + (((chunk >> 1) ^ (r & 7)) * 16) + (chunk & 1) * 8 : r * (D * 2) + ((chunk ^ r) * 16);
     }
-    const uint32_t v_lane = (uint32_t)h * D * 2 + 4 * j * tok_bytes + r * 16;
+    const uint32_t v_lane = head_bytes + 4 * j * tok_bytes + r * 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        fp8_lane[i] = head_bytes + (8 * i + (lane >> 3)) * tok_bytes + (((lane & 7) ^ (lane >> 3)) * 16);
+    {
+        const int row = 4 * j + ((r >> 1) & 3), tile = 2 + (r >> 3); // the stage's tiles: K, K, V, V
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v_tr[e] = lds_address(lds_raw) + wave * kWaveBytes + tile * kFp8TileBytes + row * D +
+                      ((e ^ (row & 7)) << 4) + 8 * (r & 1);
+    }
     const uint32_t page_bytes = kPageSize * tok_bytes;
     const char *kc = (const char *)p.k_cache;
     const char *vc = (const char *)p.v_cache;
@@ -181,8 +348,7 @@ void decode_mfma_kernel(const DecodeParams p)
     for (int part = first_part;;) {
         const int t0 = part * pt;
         const int t1 = pt > 0 ? min(L, t0 + pt) : L;
-        const int tiles = (t1 - t0 + kPageSize - 1) / kPageSize - wave;
-        const int count = tiles > 0 ? (tiles + NW - 1) / NW : 0; // this wave's tiles
+        const int count = ids.count;
 
         WaveState st;
 #pragma unroll
@@ -197,7 +363,7 @@ void decode_mfma_kernel(const DecodeParams p)
         // descriptor of zero bytes: the loads return zeros and fetch nothing), which
         // keeps the number of loads in flight fixed: "all but the newest eight" is
         // always the tile to consume.
-        if (count > 0) {
+        if constexpr (!FP8) if (count > 0) {
             PageRegs A, B;
             u32x4 ka[4];
             auto issue = [&](int n, PageRegs &regs, char *tile) {
@@ -205,7 +371,7 @@ void decode_mfma_kernel(const DecodeParams p)
                 int page = 0;
                 if (n < count) {
                     const int t = ids.first + n * NW;
-                    page = pool_tile_checked(ids.entry(n, count), t, p.num_pages, p.page_shift, p.bounds, b);
+                    page = pool_tile_checked(ids.entry(p, h, n), t, p.num_pages, p.page_shift, p.bounds, b);
                     range = page_bytes;
                 }
                 load_page(regs, tile, page_rsrc(kc, page, page_bytes, range), page_rsrc(vc, page, page_bytes, range),
@@ -231,6 +397,59 @@ void decode_mfma_kernel(const DecodeParams p)
             }
         }
 
+        // fp8: one stage of two tiles of K and of V.  It is copied to registers as soon as it is whole and the
+        // next two tiles are on their way while these are attended (twelve waves to a compute unit
+        // keep up to 96 KB in flight).
+        if constexpr (FP8) if (count > 0) {
+            auto issue = [&](int n) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    uint32_t range = 0;
+                    int page = 0;
+                    if (n + t < count) {
+                        page = pool_tile_checked(ids.entry(p, h, n + t), ids.first + (n + t) * NW, p.num_pages,
+                                                 p.page_shift, p.bounds, b);
+                        range = page_bytes;
+                    }
+                    load_tile_fp8(mine + t * kFp8TileBytes, page_rsrc(kc, page, page_bytes, range), fp8_lane);
+                    load_tile_fp8(mine + (2 + t) * kFp8TileBytes, page_rsrc(vc, page, page_bytes, range), fp8_lane);
+                }
+            };
+            ids.load_scales(p, h, ids.now, lane, ids.scale_now);
+            issue(0);
+            ids.settle(ids.scale_now);
+            int tok = t0 + wave * kPageSize + 4 * j;
+            for (int n = 0; n < count; n += 2) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                u32x2 ka[4], kb[4], v8[8];
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    ka[kk] = *(const u32x2 *)(mine + k_read[kk]);
+                    kb[kk] = *(const u32x2 *)(mine + kFp8TileBytes + k_read[kk]);
+                }
+                lds_read_tr8_x8_wait(v_tr, v8);
+                settle_k(ka, kb);
+                // The scales of these two tiles (zero for a tile that is none), before the ids move on.
+                // (n is even, so tile n + 1 belongs to the same sixty-four lanes.)
+                float ks[2], vs[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    ks[t] = p.scale_log2e * (PAIR && upper ? ids.scale(ids.SCALES - 2, n + t) : ids.scale(0, n + t));
+                    vs[t] = PAIR && upper ? ids.scale(ids.SCALES - 1, n + t) : ids.scale(1, n + t);
+                }
+                issue(n + 2);
+                const f32x4 sa = scores_fp8<PAIR>(ka, qb, upper), sb = scores_fp8<PAIR>(kb, qb, upper);
+                float sc[8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sc[i] = sa[i] * ks[0];
+                    sc[4 + i] = sb[i] * ks[1];
+                }
+                attend_two_fp8<PAIR>(st, sc, v8, vs[0], vs[1], tok, tok + NW * kPageSize, t1, j);
+                tok += 2 * NW * kPageSize;
+            }
+        }
+
         // The wave's share of the result takes the place of its own K tiles (no load is on its way to
         // them any more, and no other wave reads them).  [R][D] floats, R <= 16.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -244,8 +463,14 @@ void decode_mfma_kernel(const DecodeParams p)
         for (int i = 0; i < 4; ++i) {
             const int g = 4 * j + i;
             if (g < R) {
-                *(f32x4 *)(so + g * D + 8 * r) = f32x4{st.o[0][i], st.o[1][i], st.o[2][i], st.o[3][i]};
-                *(f32x4 *)(so + g * D + 8 * r + 4) = f32x4{st.o[4][i], st.o[5][i], st.o[6][i], st.o[7][i]};
+                if constexpr (FP8) { // st.o[e] holds column 16e + r (a bf16 cache: 8r + e)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        so[g * D + 16 * e + r] = st.o[e][i];
+                } else {
+                    *(f32x4 *)(so + g * D + 8 * r) = f32x4{st.o[0][i], st.o[1][i], st.o[2][i], st.o[3][i]};
+                    *(f32x4 *)(so + g * D + 8 * r + 4) = f32x4{st.o[4][i], st.o[5][i], st.o[6][i], st.o[7][i]};
+                }
             }
         }
         __syncthreads();
@@ -298,25 +523,36 @@ void decode_mfma_kernel(const DecodeParams p)
         part += stride;
         if (part >= n_parts)
             break;
-        ids.start(p, b, part * (pt / kPageSize) + wave);
+        start(part);
         __syncthreads(); // the next partition's K tiles go where the per-wave results lie
     }
 }
 
 bool decode_mfma_supports(int d, int G, int Hkv);
 
-hipError_t launch_decode_mfma(const DecodeParams &p, int d, hipStream_t stream)
+hipError_t launch_decode_mfma(const DecodeParams &p, int d, bool fp8, hipStream_t stream)
 {
     if (!decode_mfma_supports(d, p.G, p.Hkv))
         return hipErrorInvalidValue;
     const bool pair = d == D / 2;
-    const dim3 grid((unsigned)((int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv) * grid_stride(p.max_parts)));
-    constexpr int NW = kWaves;
-    const size_t lds = (size_t)NW * (kWaveBytes + 16 * 2 * sizeof(float));
-    if (pair)
-        decode_mfma_kernel<true, NW><<<grid, NW * 64, lds, stream>>>(p);
+    const int64_t rows = (int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv);
+    const dim3 grid((unsigned)(rows * grid_stride(p.max_parts)));
+    auto go = [&](auto kernel, int waves) {
+        kernel<<<grid, waves * 64, (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float)), stream>>>(p);
+    };
+    // Eight waves to an item where whole rows are items and may be long: a row is then at the mercy of
+    // the few waves that share it (us, 4 and 8 waves: 64 requests x 32 kv-heads of up to 4096 tokens 277
+    // and 238, 128 x 8 of up to 8192 260 and 240, heads of 64 202 and 152, fp8 171 and 157; with rows of up
+    // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61).
+    const bool wide = p.partition_tokens == 0 && p.max_seq_len >= 4096;
+    if (fp8 && pair)
+        wide ? go(decode_mfma_kernel<true, true, 8>, 8) : go(decode_mfma_kernel<true, true, 4>, 4);
+    else if (fp8)
+        wide ? go(decode_mfma_kernel<true, false, 8>, 8) : go(decode_mfma_kernel<true, false, 4>, 4);
+    else if (pair)
+        wide ? go(decode_mfma_kernel<false, true, 8>, 8) : go(decode_mfma_kernel<false, true, 4>, 4);
     else
-        decode_mfma_kernel<false, NW><<<grid, NW * 64, lds, stream>>>(p);
+        wide ? go(decode_mfma_kernel<false, false, 8>, 8) : go(decode_mfma_kernel<false, false, 4>, 4);
     return hipGetLastError();
 }
 

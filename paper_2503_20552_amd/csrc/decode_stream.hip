@@ -61,6 +61,7 @@
 // device words.  They are zero whenever no launch is using them: the last workgroup
 // to finish puts them back to zero.
 #include "mfma_page.h"
+#include "mfma_fp8.h"
 
 #include <algorithm>
 #include <atomic>
@@ -214,11 +215,6 @@ __device__ __forceinline__ Item decode_ticket(const Shared &sh, const StreamPara
 // The flag accesses are written as instructions by hand: the compiler would
 // otherwise guard an atomic LDS access with a wait for all direct-to-LDS loads.
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
-__device__ __forceinline__ uint32_t lds_address(const void *p)
-{
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
 
 __device__ __forceinline__ int flag_read(const int *word)
 {
@@ -598,33 +594,6 @@ struct QueryFp8 {
     float unscale;      // 2^-s, this lane's head
 };
 
-// The transposed reads are written by hand, all eight of a step in one statement, and nothing waits for
-// them there: the compiler would guard each one (it cannot tell the read's target from the ring
-// slots that direct-to-LDS loads are still filling) with a wait for EVERY load in flight, which
-// is exactly what the ring must not do.  The stage read here has landed (wait_groups); the results
-// are valid after the caller's wait for the LDS (settle_copies below), which takes them as operands
-// so that nothing reads them earlier.
-__device__ __forceinline__ void lds_read_tr8_x8(const uint32_t (&addr)[8], u32x2 (&v)[8])
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("ds_read_b64_tr_b8 %0, %8 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %1, %9 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %2, %10 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %3, %11 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %4, %12 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %5, %13 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %6, %14 offset:%16\n\t"
-                 "ds_read_b64_tr_b8 %7, %15 offset:%16"
-                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-                 : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]), "v"(addr[5]), "v"(addr[6]),
-                   "v"(addr[7]), "n"(Geo<true>::kTile)
-                 : "memory");
-#else
-    for (int e = 0; e < 8; ++e)
-        v[e] = u32x2{addr[e], 0u};
-#endif
-}
-
 // Wait for every LDS read of this wave.  What was read (transposed V pieces, K bytes, scales) goes
 // through the statement, so that no use of it is scheduled above the wait, and the compiler, which
 // inserts its own waits for the reads it knows of in front of this statement, has none left to
@@ -742,14 +711,6 @@ __device__ __forceinline__ void pair_scores_fp8(f32x4 &sa, f32x4 &sb, const u32x
         sa = mfma_fp8(ka[kk], q.lo[kk], sa);
         sb = mfma_fp8(kb[kk], q.lo[kk], sb);
     }
-}
-
-// A word of four bytes that clears, in a V operand, the tokens of this lane at or past t1 (tok =
-// index of the lane's first token).
-__device__ __forceinline__ uint32_t tail_mask_fp8(int tok, int t1)
-{
-    return (tok + 0 < t1 ? 0x000000ffu : 0u) | (tok + 1 < t1 ? 0x0000ff00u : 0u) | (tok + 2 < t1 ? 0x00ff0000u : 0u) |
-           (tok + 3 < t1 ? 0xff000000u : 0u);
 }
 
 // O += P V over two pages, column blocks E0 .. E1 - 1; v8: the pair's bytes (four tokens of the

@@ -24,14 +24,20 @@ def make(seed, Hq, Hkv, d, lens_after, page_size=16):
     # (the slot of a row's last token, which no append has filled here, holds a value and not the poison)
     k, v = torch.nan_to_num(b.k_cache.float(), nan=0.25), torch.nan_to_num(b.v_cache.float(), nan=-0.5)
     return types.SimpleNamespace(wl=wl, q=b.q, k_cache=k.to(torch.bfloat16), v_cache=v.to(torch.bfloat16),
-                                 block_table=b.block_table, seq_lens=lens_after)
+                                 block_table=b.block_table, seq_lens=lens_after, used=b.used)
 
 
-def check(b, what, **kw):
+def check(b, what, fp8=False, **kw):
+    ref_kw = {}
+    if fp8:     # pages no row owns keep NaN codes and NaN scales
+        b.k_cache, ks = W.quantize_pool_fp8(b.k_cache, b.used)
+        b.v_cache, vs = W.quantize_pool_fp8(b.v_cache, b.used)
+        kw.update(k_scale=dev(ks), v_scale=dev(vs))
+        ref_kw = dict(k_scale=W.bits(ks), v_scale=W.bits(vs))
     args = (dev(b.q), dev(b.k_cache), dev(b.v_cache), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
     say(what)
     out, lse = gpu_attention(*args, **kw)
-    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale, **ref_kw)
     assert compare(out, lse, ref, ref_lse, what=what)[0] <= ATOL
     again, lse_again = gpu_attention(*args, **kw)
     assert torch.equal(out, again) and torch.equal(lse, lse_again)
@@ -82,9 +88,27 @@ def test_a_large_pass_is_cut_coarser_than_the_callers_partitions():
     assert (not torch.equal(out, fine)) and (out - fine).abs().max().item() < 1e-4
 
 
+@pytest.mark.parametrize("d,G,Hkv", [(128, 1, 3), (128, 4, 8), (128, 16, 2), (64, 4, 8), (64, 8, 2), (64, 1, 2)])
+@pytest.mark.parametrize("partition_tokens", [0, 64, 512])
+@pytest.mark.parametrize("page_size", [16, 64])
+def test_fp8_cache(d, G, Hkv, partition_tokens, page_size):
+    b = make(19 + G + Hkv, G * Hkv, Hkv, d, EDGES, page_size)
+    check(b, "fp8 d=%d G=%d Hkv=%d part=%d page=%d" % (d, G, Hkv, partition_tokens, page_size), fp8=True,
+          partition_tokens=partition_tokens)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("page_size", [16, 32])
-def test_a_wave_with_more_tiles_than_one_load_of_the_table_brings(d, page_size):
-    # 64 tiles of 16 tokens for each of four waves: 4096 tokens, and its double
-    check(make(17, 4, 2, d, [4095, 4096, 4097, 8192 + 17, 33], page_size), "long unsplit rows d=%d" % d,
+@pytest.mark.parametrize("lens", [[2047, 33, 1], [4095, 4096, 4097, 3000], [8191, 8192, 8193, 8192 + 512, 8192 + 529, 33]])
+def test_a_wave_with_more_tiles_than_one_load_of_the_table_brings(fp8, d, page_size, lens):
+    # unsplit rows: 64 tiles of 16 tokens for each of four (a bound below 4096) or eight waves
+    check(make(17, 4, 2, d, lens, page_size), "unsplit rows d=%d fp8=%s up to %d" % (d, fp8, max(lens)), fp8=fp8,
           partition_tokens=0)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_four_waves_with_more_tiles_than_one_load_of_the_table_brings(fp8):
+    # one partition of 4608 tokens: 72 tiles for each of four waves, and a ragged second partition
+    b = make(23, 4, 2, 128, [4609, 4096, 4608, 100, 6000])
+    check(b, "long partitions fp8=%s" % fp8, fp8=fp8, partition_tokens=4608, flags=adr.SINGLE_PARTITION_ITEMS)
