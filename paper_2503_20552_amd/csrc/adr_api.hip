@@ -4,6 +4,7 @@
 #include "../../include/adr.h"
 #include "adr_device.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace adr {
@@ -289,35 +290,54 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
 }
 
 // The partitions a pass works with, where the caller leaves both the kernel and the merge to the call:
-// what lies in the workspace in between is then the library's own affair (it never takes more than
-// the caller's partitions would).  `min_part` > 0: rows are cut finer than `tokens`, see row_partition.
+// what lies in the workspace in between is then the library's own affair (it never takes more places
+// than the caller's partitions would).
 struct PassCut {
-    int tokens, min_part;
+    int tokens;    // per partition, when cut is 0
+    int max_parts; // partitions of a row at most
+    int cut;       // > 0: see row_partition
 };
 
-PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int partition_tokens, unsigned flags)
+PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, int partition_tokens, unsigned flags)
 {
-    PassCut cut = {partition_tokens, 0};
+    PassCut cut = {partition_tokens, (int)max_parts_for(max_seq_len, partition_tokens), 0};
     if (partition_tokens <= 0 || kernel == KERNEL_VALU ||
         (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS)))
         return cut;
     // Rows of the cache one workgroup walks at a time (two kv-heads of 64 elements are taken together).
     const int64_t rows = (int64_t)B * (kernel == KERNEL_GRID && cache->d == 64 ? cache->Hkv / 2 : cache->Hkv);
-    if (rows >= 1024) {
-        // Enough rows to fill the chip: an item's fixed cost (its chain of length, page table and first
-        // page, and its combine) is paid half as often with 1024 tokens as with 512, and there are half
-        // the partial results to merge.  1024 pairs: 202 against 210 us with the merge; 2048 pairs: 398
-        // against 418 (one workgroup per item) and 398 against 411 (resident).
-        if (partition_tokens < 1024)
+    if (kernel == KERNEL_STREAM) {
+        // With enough rows for its workgroups: an item's fixed cost is paid half as often with 1024
+        // tokens as with 512, and there are half the partial results to merge (398 against 411 us at
+        // 2048 pairs, fp8 237 against 254).
+        if (rows >= 2048 && partition_tokens < 1024) {
             cut.tokens = partition_tokens * ((1024 + partition_tokens - 1) / partition_tokens);
-    } else if (kernel == KERNEL_GRID) {
-        // Too few: with up to 96 rows partitions of 128 tokens (8 pairs of 2000 tokens: 9.5 us with the
-        // merge against 12.9 with 512; 64 pairs: 22.5 against 26), up to 1024 rows no more than 512
-        // tokens (256 pairs: 40.6 against 49.3 us with 1024).
-        const int finest = rows <= 96 ? 128 : 512;
-        if (partition_tokens > finest)
-            cut.min_part = finest;
+            cut.max_parts = (int)max_parts_for(max_seq_len, cut.tokens);
+        }
+        return cut;
     }
+    // One workgroup per item.  Short rows are not cut at all, which spares the merge (1 row of 300 tokens
+    // 5.9 us against 7.4 in partitions of 128; 1600 rows of 100, bound 800, 32 against 35).
+    if (max_seq_len <= (rows >= 1024 ? 1024 : 512)) {
+        cut.max_parts = 1;
+        return cut;
+    }
+    // Otherwise into what makes about 1200 items of the pass (rows taken to be a quarter as long as the
+    // bound on the average), 128 to 1024 tokens each and not below a 96th of the bound: fewer leave
+    // compute units idle, more pay an item's fixed cost (its chain of length, page table and first page,
+    // its combine, its place in the merge) for nothing.  us with the merge, partitions of 128 / 256
+    // / 512 / 1024 tokens:
+    //     rows                   8              64               256              1024
+    //     1000 tokens     8 /  9 / 11 / 11   14 / 14 / 14 / 18   30 / 30 / 32 / 31   111 / 100 /  97 / 100
+    //     3000 tokens     9 / 10 / 12 / 18   25 / 25 / 27 / 33   83 / 75 / 74 / 79   327 / 297 / 280 / 266
+    //     30000 tokens   31 / 28 / 26 / 25  208 /185 /171 /166
+    // (an fp8 cache likewise).  The same length for every row: cut in proportion to their own lengths
+    // instead, rows of mixed lengths end in long items (85 against 78 us at 1024 rows of heavy-tailed
+    // lengths, 48 against 43 at 296).
+    const int64_t aim = std::max<int64_t>(std::min<int64_t>(std::max<int64_t>(rows * max_seq_len / 4800, 128), 1024),
+                                          max_seq_len / 96);
+    cut.cut = (int)((aim + 64) / 128 * 128); // whole pairs of tiles for each of four waves
+    cut.max_parts = (int)std::min<int64_t>(max_parts_for(max_seq_len, cut.cut), cut.max_parts);
     return cut;
 }
 
@@ -387,9 +407,8 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         return ADR_ERR_WORKSPACE;
     if (B == 0)
         return ADR_OK;
-    const PassCut cut = pass_cut(cache, kernel, B, split ? partition_tokens : 0, flags);
-    const int cut_parts = (int)max_parts_for(max_seq_len, cut.tokens);
-    split = split && cut_parts > 1;
+    const PassCut cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
+    split = split && cut.max_parts > 1;
 
     adr::DecodeParams p;
     p.q = (const uint16_t *)q;
@@ -419,9 +438,9 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     p.G = G;
     p.num_pages = cache->num_pages;
     p.partition_tokens = split ? cut.tokens : 0;
-    p.max_parts = split ? cut_parts : 1;
+    p.max_parts = split ? cut.max_parts : 1;
     p.max_seq_len = max_seq_len;
-    p.min_part = split ? cut.min_part : 0;
+    p.cut = split ? cut.cut : 0;
     p.out_f32 = out_dtype == ADR_F32;
     p.scale_log2e = scale * adr::kLog2e;
     p.coalesce = !(flags & ADR_SINGLE_PARTITION_ITEMS);
@@ -481,7 +500,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         mp.partition_tokens = p.partition_tokens;
         mp.max_parts = p.max_parts;
         mp.max_seq_len = max_seq_len;
-        mp.min_part = p.min_part;
+        mp.cut = p.cut;
         mp.B = B;
         mp.heads = Hq;
         mp.d = d;
@@ -561,7 +580,7 @@ int adr_decode_merge(void *out, adr_dtype out_dtype, float *lse, const int32_t *
     mp.partition_tokens = partition_tokens;
     mp.max_parts = (int)max_parts;
     mp.max_seq_len = max_seq_len;
-    mp.min_part = 0;
+    mp.cut = 0;
     mp.B = B;
     mp.heads = Hq;
     mp.d = d;
@@ -593,7 +612,7 @@ int adr_lse_merge(void *out, adr_dtype out_dtype, float *lse_out, const float *p
     mp.partition_tokens = 0;
     mp.max_parts = 0;
     mp.max_seq_len = 0;
-    mp.min_part = 0;
+    mp.cut = 0;
     mp.B = B;
     mp.heads = heads;
     mp.d = d;

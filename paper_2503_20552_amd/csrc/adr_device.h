@@ -65,12 +65,13 @@ struct DecodeParams {
     int partition_tokens; // 0 = whole sequence in one pass
     int max_parts;        // partitions per request the grid was sized for (>= 1)
     int max_seq_len;
-    int min_part;         // > 0: rows are cut finer than partition_tokens, down to this many (row_partition)
+    int cut;              // > 0: rows are cut into partitions of that many tokens where it can be (row_partition)
     int out_f32;          // 1: out is fp32, 0: bf16
     int coalesce;         // the resident kernel may take runs of partitions as one item
     float scale_log2e;    // softmax scale * log2(e): scores are kept in base 2
     uint32_t *control;    // control area of the call (status block first), or nullptr: the static pool
     int spin_limit;       // polls before a wait on another wave is declared failed
+    int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
     BoundsRecord *bounds; // debug builds: where out-of-range entries are recorded (else nullptr)
 };
@@ -83,7 +84,7 @@ struct MergeParams {
     const int32_t *seq_lens;     // implicit layout: request b owns partitions
     int partition_tokens;        //   [b*max_parts, b*max_parts + ceil(min(seq_len,max_seq_len)/partition_tokens))
     int max_parts, max_seq_len;  //   and rows with <= 1 partition are left alone
-    int min_part;                //   (row_partition)
+    int cut;                     //   (row_partition)
     int B, heads, d, out_f32;
     const uint32_t *status;      // call status block of the pass that wrote the partials, or nullptr: when
                                  // its expired-waits word is not zero every row gets NaN
@@ -242,15 +243,13 @@ __device__ __forceinline__ int parts_of(int L, int partition_tokens)
     return (L + partition_tokens - 1) / partition_tokens;
 }
 
-// Tokens per partition of a row of L tokens.  A pass too small to fill the chip cuts a row finer than
-// the caller's partition, into as many partitions as the workspace has places for (max_parts, from
-// the bound on the lengths), but not below min_part tokens; min_part = 0 leaves the caller's.
-__device__ __forceinline__ int row_partition(int L, int partition_tokens, int max_parts, int min_part)
+// Tokens per partition of a row of L tokens.  cut = 0: the caller's partitions.  Otherwise the library
+// cuts by itself: `cut` tokens, or more where the row would need more than max_parts places.
+__device__ __forceinline__ int row_partition(int L, int partition_tokens, int max_parts, int cut)
 {
-    if (min_part == 0)
+    if (cut == 0)
         return partition_tokens;
-    const int even = ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1);
-    return min(max(even, min_part), partition_tokens);
+    return max(cut, ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1));
 }
 
 // Combine the kWaves per-wave partial results staged in LDS and write either

@@ -81,13 +81,14 @@ __device__ __forceinline__ void read_k_operand(u32x4 (&ka)[4], const char *ktile
 // therefore odd.  (2) Workgroups that find nothing still cost about a nanosecond each, and a loose
 // bound makes tens of thousands of them: the stride stops at kGridStrideMax, and rows with more
 // partitions (rare where this kernel is chosen) have their workgroups loop.
+// (Where there are few rows, a long one needs its workgroups: the limit is then 4096 of them in all.)
 constexpr int kGridStrideMax = 33;
-__host__ __device__ inline int grid_stride(int max_parts)
+static int grid_stride(int64_t rows, int max_parts)
 {
-    const int n = max_parts < kGridStrideMax ? max_parts : kGridStrideMax;
+    const int64_t most = std::max<int64_t>(kGridStrideMax, 4096 / rows);
+    const int n = (int)std::min<int64_t>(max_parts, most);
     return n > 1 ? (n | 1) : n;
 }
-
 
 constexpr int kWaveBytes = kStages * kTileBytes; // LDS of one wave: its K tiles, then its share of the result
 
@@ -281,13 +282,13 @@ void decode_mfma_kernel(const DecodeParams p)
     const int j = lane >> 4;
     const bool upper = PAIR && r >= G;
 
-    const int stride = grid_stride(p.max_parts);
+    const int stride = p.grid_stride;
     const int h = blockIdx.x % H;
     const int first_part = (blockIdx.x / H) % stride;
     const int b = blockIdx.x / (H * stride);
 
     const int L = max(min(((const __attribute__((address_space(4))) int32_t *)p.seq_lens)[b], p.max_seq_len), 0);
-    const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.min_part);
+    const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut);
     const int n_parts = parts_of(L, pt);
     if (first_part >= n_parts)
         return;
@@ -530,13 +531,15 @@ void decode_mfma_kernel(const DecodeParams p)
 
 bool decode_mfma_supports(int d, int G, int Hkv);
 
-hipError_t launch_decode_mfma(const DecodeParams &p, int d, bool fp8, hipStream_t stream)
+hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipStream_t stream)
 {
+    DecodeParams p = params;
     if (!decode_mfma_supports(d, p.G, p.Hkv))
         return hipErrorInvalidValue;
     const bool pair = d == D / 2;
     const int64_t rows = (int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv);
-    const dim3 grid((unsigned)(rows * grid_stride(p.max_parts)));
+    p.grid_stride = grid_stride(rows, p.max_parts);
+    const dim3 grid((unsigned)(rows * p.grid_stride));
     auto go = [&](auto kernel, int waves) {
         kernel<<<grid, waves * 64, (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float)), stream>>>(p);
     };
