@@ -1,4 +1,5 @@
-"""ctypes binding of include/adr.h.  Argument marshalling only."""
+"""Binding of include/adr.h.  Argument marshalling only: plain calls of the enqueueing functions go through
+the native module _marshal (csrc/marshal.cpp), everything else -- and every refusal -- through ctypes here."""
 from __future__ import annotations
 
 import contextlib
@@ -75,6 +76,7 @@ class _CBoundsRecord(ctypes.Structure):
 _lib = None
 _release_lib = None
 _debug_lib = None
+_marshal = None
 
 
 def library_path() -> str:
@@ -99,16 +101,30 @@ def debug_library():
 
 
 def load_library():
-    """Load libadr.so; fails loudly when it has not been built."""
-    global _lib, _release_lib
+    """Load libadr.so and the native marshalling; fails loudly when they have not been built."""
+    global _lib, _release_lib, _marshal
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise ImportError(
             "%s is missing: build it with `python -m paper_2503_20552_amd.build` "
             "(there is no fallback path)" % _LIB_PATH)
+    try:
+        from . import _marshal as native
+    except ImportError as e:
+        raise ImportError("the native marshalling module is missing or does not load: build it with "
+                          "`python -m paper_2503_20552_amd.build`") from e
+    _marshal = native
     _lib = _release_lib = _declare(ctypes.CDLL(_LIB_PATH))
     return _lib
+
+
+_FAST = ("adr_decode_attention", "adr_decode_step", "adr_kv_append", "adr_lse_merge", "adr_pack_qkv", "adr_scatter_rows")
+
+
+def _set_addresses(lib):
+    """What the native marshalling calls: the entry points' addresses in this library."""
+    lib.address_of = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _FAST}
 
 
 def _declare(lib):
@@ -178,6 +194,7 @@ def _declare(lib):
     lib.adr_graph_table_launch.argtypes = [vp, i32, vp]
     lib.adr_graph_table_destroy.restype = i32
     lib.adr_graph_table_destroy.argtypes = [vp]
+    _set_addresses(lib)
     return lib
 
 
@@ -201,6 +218,10 @@ def adr_stream_destroy(handle: int) -> None:
 
 def adr_pack_qkv(dst: torch.Tensor, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, stream=None) -> None:
     """dst [B, >= (Hq+2Hkv)*d] bf16 <- q | k | v (each [B, heads, d], row-strided views allowed)."""
+    lib = load_library()
+    status = _marshal.pack_qkv(lib.address_of["adr_pack_qkv"], dst, q, k, v, stream)
+    if status is not None:
+        return _check(status, "adr_pack_qkv")
     qp, qs = _rows_view(q, "q")
     kp, ks = _rows_view(k, "k")
     vp_, vs = _rows_view(v, "v")
@@ -210,18 +231,22 @@ def adr_pack_qkv(dst: torch.Tensor, q: torch.Tensor, k: torch.Tensor, v: torch.T
         raise ValueError("dst must be bf16 [B, width] with contiguous rows")
     if k.shape != v.shape or k.shape[0] != B or k.shape[2] != d or dst.shape[1] < (Hq + 2 * Hkv) * d:
         raise ValueError("shape mismatch")
-    _check(load_library().adr_pack_qkv(dst.data_ptr(), dst.stride(0), qp, qs, kp, ks, vp_, vs, B, Hq, Hkv, d,
+    _check(lib.adr_pack_qkv(dst.data_ptr(), dst.stride(0), qp, qs, kp, ks, vp_, vs, B, Hq, Hkv, d,
                                        _stream_handle(stream)), "adr_pack_qkv")
 
 
 def adr_scatter_rows(dst: torch.Tensor, src: torch.Tensor, row_index: torch.Tensor, stream=None) -> None:
     """dst[row_index[i]] = src[i] for 2-D bf16 tensors with contiguous rows of equal width."""
+    lib = load_library()
+    status = _marshal.scatter_rows(lib.address_of["adr_scatter_rows"], dst, src, row_index, stream)
+    if status is not None:
+        return _check(status, "adr_scatter_rows")
     for t in (dst, src):
         if t.dtype != torch.bfloat16 or t.dim() != 2 or t.stride(1) != 1:
             raise ValueError("dst and src must be bf16 [rows, width] with contiguous rows")
     if dst.shape[1] != src.shape[1] or row_index.dtype != torch.int32 or row_index.numel() != src.shape[0]:
         raise ValueError("shape mismatch")
-    _check(load_library().adr_scatter_rows(dst.data_ptr(), dst.stride(0), dst.shape[0], src.data_ptr(),
+    _check(lib.adr_scatter_rows(dst.data_ptr(), dst.stride(0), dst.shape[0], src.data_ptr(),
                                            src.stride(0), row_index.data_ptr(), src.shape[0], src.shape[1],
                                            _stream_handle(stream)), "adr_scatter_rows")
 
@@ -372,6 +397,9 @@ def _check(status: int, where: str):
 def adr_kv_append(cache: KVCache, k_new: torch.Tensor, v_new: torch.Tensor,
                   block_table: torch.Tensor, positions: torch.Tensor, stream=None) -> None:
     lib = load_library()
+    status = _marshal.kv_append(lib.address_of["adr_kv_append"], KVCache, cache, k_new, v_new, block_table, positions, stream)
+    if status is not None:
+        return _check(status, "adr_kv_append")
     cs = cache.c_struct()
     kp, kstride = _rows_view(k_new, "k_new")
     vp, vstride = _rows_view(v_new, "v_new")
@@ -419,6 +447,10 @@ def adr_decode_attention(out: torch.Tensor, q: torch.Tensor, cache: KVCache,
                          lse: Optional[torch.Tensor] = None, flags: int = KERNEL_AUTO,
                          stream=None) -> None:
     lib = load_library()
+    status = _marshal.decode_attention(lib.address_of["adr_decode_attention"], KVCache, out, q, cache, block_table,
+                                       seq_lens, scale, max_seq_len, partition_tokens, workspace, lse, flags, stream)
+    if status is not None:
+        return _check(status, "adr_decode_attention")
     cs = cache.c_struct()
     odt, lse_ptr, qp, qstride, B, Hq, ws_ptr, ws_bytes = _attention_args(out, q, cache, block_table, seq_lens,
                                                                          workspace, lse)
@@ -455,6 +487,10 @@ def adr_decode_step(out: torch.Tensor, q: torch.Tensor, k_new: torch.Tensor, v_n
                     lse: Optional[torch.Tensor] = None, flags: int = KERNEL_AUTO,
                     stream=None) -> None:
     lib = load_library()
+    status = _marshal.decode_step(lib.address_of["adr_decode_step"], KVCache, out, q, k_new, v_new, cache, block_table,
+                                  seq_lens, scale, max_seq_len, partition_tokens, workspace, lse, flags, stream)
+    if status is not None:
+        return _check(status, "adr_decode_step")
     cs = cache.c_struct()
     odt, lse_ptr, qp, qstride, B, Hq, ws_ptr, ws_bytes = _attention_args(out, q, cache, block_table, seq_lens,
                                                                          workspace, lse)
@@ -492,6 +528,9 @@ def adr_lse_merge(out: torch.Tensor, part_o: torch.Tensor, part_lse: torch.Tenso
                   part_offsets: torch.Tensor, lse_out: Optional[torch.Tensor] = None,
                   stream=None) -> None:
     lib = load_library()
+    status = _marshal.lse_merge(lib.address_of["adr_lse_merge"], out, part_o, part_lse, part_offsets, lse_out, stream)
+    if status is not None:
+        return _check(status, "adr_lse_merge")
     B, heads, d = out.shape
     odt = ADR_BF16 if out.dtype == torch.bfloat16 else ADR_F32
     if out.dtype not in (torch.bfloat16, torch.float32) or not out.is_contiguous():

@@ -2,6 +2,9 @@
 
     python -m paper_2503_20552_amd.build [--debug]
 
+Also built: _marshal.so, the binding's argument marshalling (csrc/marshal.cpp, a CPython module
+against torch's headers; host code only).
+
 Each .hip file under csrc/ is compiled to an object in csrc/_build/ and the
 objects are linked into paper_2503_20552_amd/libadr.so.  --debug builds the same
 sources with -DADR_DEBUG_BOUNDS into libadr_debug.so (objects in csrc/_build/debug/):
@@ -46,6 +49,24 @@ def _compile(name: str, obj_dir: str = OBJ, extra=()) -> str:
     return obj
 
 
+MARSHAL = os.path.join(HERE, "_marshal.so")
+
+
+def build_marshal() -> str:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                           "-isystem", os.path.join(root, "include"),
+                           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
+                           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 def build(verbose: bool = True, debug: bool = False) -> str:
     obj_dir = os.path.join(OBJ, "debug") if debug else OBJ
     lib = DEBUG_LIB if debug else LIB
@@ -57,6 +78,8 @@ def build(verbose: bool = True, debug: bool = False) -> str:
     tmp = lib + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, lib)
+    if not debug:
+        build_marshal()
     if verbose:
         print("built", lib, "from", ", ".join(names))
     return lib
