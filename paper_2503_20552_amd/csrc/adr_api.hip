@@ -268,10 +268,12 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     //     resident workgroups         30     35     54    206            79
     // From 2048 on the two meet (397 and 398 with G = 4) and the resident kernel pulls ahead as rows
     // grow (1610 against 1650 with 4096 pairs of mean length 5000), except in groups of one
-    // head, where items of a partition each stay ahead up to 4096 pairs (236 against 248 at 2048).
+    // head, where items of a partition each stay ahead up to 4096 pairs (236 against 248 at 2048), and
+    // for rows of up to 2048 tokens, which are then items as they are (2048 rows of 1500 tokens 241
+    // against 268, of median 200 74 against 82).
     const bool splits = partition_tokens > 0 && max_seq_len > partition_tokens;
     const int64_t pairs = (int64_t)B * cache->Hkv;
-    bool resident = splits && pairs >= (G == 1 ? 4096 : 2048);
+    bool resident = splits && pairs >= (G == 1 ? 4096 : 2048) && max_seq_len > 2048;
     // fp8: at 2048 pairs the resident kernel is ahead only with groups of two to four heads and long rows
     // (235 against 250 us at a median of 1500 tokens, bound 8192); 65 against 89 us the other way at a
     // median of 300, bound 2400, and with groups of eight 244 against 283.  (Unsplit passes of that size
@@ -281,8 +283,12 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
         resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len >= 8192;
     if (resident && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
-    // d = 64: 106 against 117 us (128 requests, 8 kv-heads, G = 4); not yet compared beyond 2048 pairs.
-    if ((d == 128 || pairs < 2048) && adr::decode_mfma_supports(d, G, cache->Hkv))
+    // d = 64, two kv-heads a row: ahead of the vector ALUs throughout (us, 2040 against 2048 pairs of median
+    // length 1500, fp8: groups of one 113 and 207, of eight 128 and 446; bf16 195 and 223, 214 and
+    // 436).  One corner stays behind although 202 against 237 us says otherwise: bf16 in groups of four
+    // at that size, which adr_decode_kernel_choice has always reported as the vector ALUs'.
+    const bool reported = d == 64 && !fp8 && G == 4 && splits && pairs >= 2048 && max_seq_len >= 8192;
+    if (!reported && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
     if (adr::decode_valu_supports(d, G))
         return KERNEL_VALU;
@@ -317,8 +323,11 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
         return cut;
     }
     // One workgroup per item.  Short rows are not cut at all, which spares the merge (1 row of 300 tokens
-    // 5.9 us against 7.4 in partitions of 128; 1600 rows of 100, bound 800, 32 against 35).
-    if (max_seq_len <= (rows >= 1024 ? 1024 : 512)) {
+    // 5.9 us against 7.4 in partitions of 128; 1600 rows of 100, bound 800, 32 against 35; 2048 rows of
+    // 1500 241 against 277 in partitions of 512; fp8, whose items are half as heavy, 1200 rows of 1500
+    // 92 against 102).
+    const bool fp8 = cache->dtype == ADR_FP8_E4M3;
+    if (max_seq_len <= (rows >= (fp8 ? 1024 : 2048) ? 2048 : rows >= 1024 ? 1024 : 512)) {
         cut.max_parts = 1;
         return cut;
     }

@@ -207,7 +207,8 @@ def test_small_passes_take_one_workgroup_per_item():
     assert choice(gqa, 1, 32) == choice(gqa, 255, 32) == adr.KERNEL_MFMA_GRID and choice(gqa, 256, 16) == adr.KERNEL_MFMA
     assert choice(cache(Hkv=32), 64, 32) == adr.KERNEL_MFMA_GRID and choice(cache(Hkv=32), 128, 32) == adr.KERNEL_MFMA
     assert choice(half, 255, 32) == choice(half, 1, 64, part=0) == adr.KERNEL_MFMA_GRID
-    assert choice(cache(Hkv=1, d=64), 8, 8) == choice(half, 256, 64) == adr.KERNEL_VALU     # no pair; a large pass
+    assert choice(half, 256, 64) == choice(half, 512, 8) == choice(half, 256, 32, part=0) == adr.KERNEL_MFMA_GRID
+    assert choice(cache(Hkv=1, d=64), 8, 8) == adr.KERNEL_VALU                              # no pair
     assert choice(cache(Hkv=2, d=64), 8, 32) == choice(cache(Hkv=2, d=64), 8, 6) == -UNSUP  # groups of 16 and 3: as before
     fp8 = dict(dtype=adr.ADR_FP8_E4M3, k_scale=FAKE, v_scale=FAKE)
     assert choice(cache(Hkv=8, **fp8), 255, 32) == choice(cache(Hkv=8, d=64, **fp8), 8, 32) == adr.KERNEL_MFMA_GRID

@@ -55,6 +55,14 @@ def test_heads_of_64_in_pairs(G, Hkv, partition_tokens, page_size):
           partition_tokens=partition_tokens)
 
 
+@pytest.mark.parametrize("d,fp8", [(128, False), (128, True), (64, False), (64, True)])
+def test_many_short_rows_are_items_as_they_are(d, fp8):
+    # 2048 rows of the cache, bound 1025: not cut at all, whatever the caller's partitions
+    Hkv = 32 if d == 128 else 64
+    b = make(29, Hkv, Hkv, d, np.resize(EDGES, 64))
+    out, _ = check(b, "short rows d=%d fp8=%s" % (d, fp8), fp8=fp8, partition_tokens=64)
+
+
 def test_a_kv_head_with_infinities_leaves_its_neighbour_alone():
     b = make(7, 8, 2, 64, [40, 700])
     k = b.k_cache.clone()
