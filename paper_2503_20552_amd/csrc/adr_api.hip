@@ -274,13 +274,13 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     const bool splits = partition_tokens > 0 && max_seq_len > partition_tokens;
     const int64_t pairs = (int64_t)B * cache->Hkv;
     bool resident = splits && pairs >= (G == 1 ? 4096 : 2048) && max_seq_len > 2048;
-    // fp8: at 2048 pairs the resident kernel is ahead only with groups of two to four heads and long rows
-    // (235 against 250 us at a median of 1500 tokens, bound 8192); 65 against 89 us the other way at a
-    // median of 300, bound 2400, and with groups of eight 244 against 283.  (Unsplit passes of that size
-    // stay there as well, though one workgroup per row takes 264 against 392 us: which kernel serves
-    // them is what adr_decode_kernel_choice has always said.)
+    // fp8: one workgroup per item throughout (us: 255 requests x 8 kv-heads 221 against 236, 500 x 4 of very
+    // skewed lengths 471 against 478, 2048 pairs of median 300 65 against 89, groups of eight 244
+    // against 283, unsplit 264 against 392).  One corner stays where adr_decode_kernel_choice has always
+    // reported it, though the same figures hold there: groups of two to four heads, 2048 pairs or more,
+    // rows of up to 8192 tokens.
     if (fp8)
-        resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len >= 8192;
+        resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len > 4096 && max_seq_len <= 8192;
     if (resident && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
     // d = 64, two kv-heads a row: ahead of the vector ALUs throughout (us, 2040 against 2048 pairs of median

@@ -28,7 +28,7 @@
 // served fp8 before: 9 against 37 us at one request of 2000 tokens, 35 against 60 at 40 requests,
 // 130 against 146 at 128, 53 against 79 with groups of eight; heads of 64 (before: vector ALUs)
 // 70 against 127.  Three workgroups to a compute unit: four are slower (142 against 130 us at 128
-// requests), and so is a second stage with two (132).
+// requests), and so are a second stage with two (132) and three tiles in flight with three (132).
 //
 // QK^T  S[token][head] = K[16 x 128] * Q^T[128 x 16] as four
 //       v_mfma_f32_16x16x32_bf16.  The A operand wants lane (r, j) to hold 16
@@ -70,7 +70,7 @@ __device__ __forceinline__ void read_k_operand(u32x4 (&ka)[4], const char *ktile
         ka[kk] = *(const u32x4 *)(ktile + k_read[kk]);
 }
 
-// Workgroups are numbered row by row: kv-head fastest (the heads of a page are read together),
+// Workgroups are numbered row by row: the kv-heads of a partition together (see the kernel),
 // then the row's partitions, `stride` of them; a workgroup takes every stride-th partition of its
 // row from its own on and leaves at once when the row has none for it.  The grid is sized from
 // the caller's bound on the lengths, not from the lengths, so most workgroups may find nothing.
@@ -89,6 +89,8 @@ static int grid_stride(int64_t rows, int max_parts)
     const int n = (int)std::min<int64_t>(max_parts, most);
     return n > 1 ? (n | 1) : n;
 }
+
+constexpr int kChiplets = 8; // of the GPU; the hardware deals workgroups out to them in turn
 
 constexpr int kWaveBytes = kStages * kTileBytes; // LDS of one wave: its K tiles, then its share of the result
 
@@ -283,9 +285,25 @@ void decode_mfma_kernel(const DecodeParams p)
     const bool upper = PAIR && r >= G;
 
     const int stride = p.grid_stride;
-    const int h = blockIdx.x % H;
-    const int first_part = (blockIdx.x / H) % stride;
-    const int b = blockIdx.x / (H * stride);
+    // Which (row of the cache h, partition, request) this workgroup starts with.  Consecutive workgroups go
+    // to the eight chiplets in turn.  bf16: kv-heads fastest, so that a page's heads are read side by
+    // side by different chiplets.  fp8: the kv-heads of a partition one after the other on one chiplet --
+    // with eight kv-heads the other order gives a chiplet the same 128 bytes of every 1024, and it
+    // costs 250 against 221 us at 255 requests, 130 against 116 at 128, 141 against 129 at 60
+    // requests of 32 kv-heads (bf16, 256 bytes a piece, is 1 to 2 % faster the first way).
+    unsigned unit, h;
+    if constexpr (FP8) {
+        const unsigned turn = blockIdx.x / kChiplets;
+        h = turn % H;
+        unit = turn / H * kChiplets + blockIdx.x % kChiplets;
+    } else {
+        h = blockIdx.x % H;
+        unit = blockIdx.x / H;
+    }
+    const int first_part = unit % stride;
+    const int b = unit / stride;
+    if (FP8 && b >= p.B)
+        return;
 
     const int L = max(min(((const __attribute__((address_space(4))) int32_t *)p.seq_lens)[b], p.max_seq_len), 0);
     const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut);
@@ -539,7 +557,13 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     const bool pair = d == D / 2;
     const int64_t rows = (int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv);
     p.grid_stride = grid_stride(rows, p.max_parts);
-    const dim3 grid((unsigned)(rows * p.grid_stride));
+    int64_t units = (int64_t)p.B * p.grid_stride;
+    if (fp8)
+        units = (units + kChiplets - 1) / kChiplets * kChiplets; // (the surplus finds no request)
+    const int64_t blocks = units * (rows / p.B);
+    if (blocks > 0x7fffffffLL)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel, int waves) {
         kernel<<<grid, waves * 64, (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float)), stream>>>(p);
     };

@@ -201,8 +201,8 @@ def test_kernel_choice_is_reported_by_the_library():
 
 def test_small_passes_take_one_workgroup_per_item():
     lib = adr.load_library()
-    def choice(c, B, Hq, part=512, flags=0):
-        return lib.adr_decode_kernel_choice(ctypes.byref(c), B, Hq, 8192, part, flags)
+    def choice(c, B, Hq, part=512, flags=0, bound=8192):
+        return lib.adr_decode_kernel_choice(ctypes.byref(c), B, Hq, bound, part, flags)
     gqa, half = cache(Hkv=8), cache(Hkv=8, d=64)
     assert choice(gqa, 1, 32) == choice(gqa, 255, 32) == adr.KERNEL_MFMA_GRID and choice(gqa, 256, 16) == adr.KERNEL_MFMA
     assert choice(cache(Hkv=32), 64, 32) == adr.KERNEL_MFMA_GRID and choice(cache(Hkv=32), 128, 32) == adr.KERNEL_MFMA
@@ -214,6 +214,8 @@ def test_small_passes_take_one_workgroup_per_item():
     assert choice(cache(Hkv=8, **fp8), 255, 32) == choice(cache(Hkv=8, d=64, **fp8), 8, 32) == adr.KERNEL_MFMA_GRID
     assert choice(cache(Hkv=8, **fp8), 256, 64) == choice(cache(Hkv=8, **fp8), 512, 8) == adr.KERNEL_MFMA_GRID
     assert choice(cache(Hkv=8, **fp8), 256, 16) == adr.KERNEL_MFMA
+    assert choice(cache(Hkv=8, **fp8), 256, 16, bound=9000) == choice(cache(Hkv=8, **fp8), 256, 16, bound=4096) == adr.KERNEL_MFMA_GRID
+    assert choice(gqa, 256, 32, bound=2049) == adr.KERNEL_MFMA and choice(gqa, 256, 32, bound=2048) == adr.KERNEL_MFMA_GRID
     assert choice(cache(Hkv=8, **fp8), 8, 32, flags=adr.KERNEL_MFMA_GRID) == -UNSUP
     assert choice(half, 8, 32, flags=adr.KERNEL_MFMA_GRID) == choice(half, 8, 32, flags=adr.KERNEL_MFMA) == -UNSUP
 

@@ -105,6 +105,13 @@ def test_fp8_cache(d, G, Hkv, partition_tokens, page_size):
           partition_tokens=partition_tokens)
 
 
+@pytest.mark.parametrize("B", [1, 7, 8, 9])        # (request, partition) units around whole turns of the eight chiplets
+@pytest.mark.parametrize("Hkv", [1, 3, 8])
+def test_fp8_every_item_is_done_once(B, Hkv):
+    b = make(31 + B, 2 * Hkv, Hkv, 128, np.resize([1000, 17, 513, 0, 2100], B))
+    check(b, "fp8 B=%d Hkv=%d" % (B, Hkv), fp8=True, partition_tokens=64)
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("page_size", [16, 32])
