@@ -975,9 +975,10 @@ void decode_stream_kernel(const StreamParams sp)
     const __amdgpu_buffer_rsrc_t vs_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(FP8 ? (const void *)p.v_scale : (const void *)kc), 0, scale_range, 0x00020000);
     const int pages_per_part = (sp.pt << cshift) / kPageSize; // 2^26 when the pass is not split (part is 0 then)
-    // "Page" below is a 16-token tile of the pool; a cache page is 1 << tsh of them (the
-    // instantiations with a fixed ring depth serve 16-token pages only).
-    const int tsh = STAGES > 0 ? 0 : p.page_shift;
+    // "Page" below is a 16-token tile of the pool; a cache page is 1 << tsh of them.  (Every
+    // instantiation takes the shift at run time: pages of 64 tokens on the fixed ring depths 402
+    // against 404 us, pages of 16 the same 399 with the shift as without.)
+    const int tsh = p.page_shift;
 
     const Waits waits = {&sh.failed, p.spin_limit};
     Item C = fetch(sh.rec[0], 0, waits);
@@ -1606,14 +1607,13 @@ hipError_t launch_rows(const DecodeParams &p, int d, bool fp8, int chunk, hipStr
     if (grid > (int64_t)cus * per_cu)
         grid = (int64_t)cus * per_cu;
     const dim3 blocks((unsigned)grid);
-    const bool fixed_depth = p.page_shift == 0;
-    if (fp8 && stages == 3 && fixed_depth)
+    if (fp8 && stages == 3)
         decode_stream_kernel<true, 3><<<blocks, kThreads, lds, stream>>>(sp);
     else if (fp8)
         decode_stream_kernel<true, 0><<<blocks, kThreads, lds, stream>>>(sp);
-    else if (stages == 4 && fixed_depth)
+    else if (stages == 4)
         decode_stream_kernel<false, 4><<<blocks, kThreads, lds, stream>>>(sp);
-    else if (stages == 3 && fixed_depth) // groups of five to eight heads
+    else if (stages == 3) // groups of five to eight heads
         decode_stream_kernel<false, 3><<<blocks, kThreads, lds, stream>>>(sp);
     else
         decode_stream_kernel<false, 0><<<blocks, kThreads, lds, stream>>>(sp);
