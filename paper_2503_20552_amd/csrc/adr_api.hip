@@ -281,6 +281,9 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // rows of up to 8192 tokens.
     if (fp8)
         resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len > 4096 && max_seq_len <= 8192;
+    // The test aid is about the resident kernel's waits: where it is asked for, that kernel serves.
+    if (flags & ADR_DEBUG_EXPIRE_WAITS)
+        resident = fp8 || (splits && (G <= 4 || pairs >= 2048 || max_parts_for(max_seq_len, partition_tokens) > 32));
     if (resident && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
     // d = 64, two kv-heads a row: ahead of the vector ALUs throughout (us, 2040 against 2048 pairs of median

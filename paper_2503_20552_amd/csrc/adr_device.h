@@ -154,6 +154,27 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
+// Two non-negative fp32 numbers p as sums of TERMS bf16 ones (pairs as the matrix instructions take them):
+// heads cut off, the last term rounded.  17 bits of p in two terms, all 24 in three; rounding leaves no
+// bias.  Every term is kept at 2^-126 or above (as 16-bit integers: the terms are not negative, and NaN
+// stays NaN), so that a weight times an infinite value stays infinite: with remainders that are zero or
+// negative it would be NaN.
+template <int TERMS>
+__device__ __forceinline__ void split_weights(float p0, float p1, uint32_t (&w)[TERMS])
+{
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+        const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+        w[t] = t + 1 < TERMS ? (u0 >> 16) | (u1 & 0xffff0000u) : pack_bf16(p0, p1);
+        if (t + 1 < TERMS) {
+            p0 -= __uint_as_float(u0 & 0xffff0000u); // exact
+            p1 -= __uint_as_float(u1 & 0xffff0000u);
+        }
+        w[t] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, w[t]), u16x2{0x0080, 0x0080}));
+    }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

@@ -50,7 +50,7 @@
 //       v_mfma_f32_16x16x16_bf16 per page (one per e = 0..7, dcol = 8r + e).
 //       The S layout above IS the A-operand layout (row = head r, k = token
 //       4j+i), so P never moves between lanes.  P is split into a bf16 head
-//       and a bf16 remainder, both rounded (two MFMAs), so the weights keep 17 significant
+//       and a rounded bf16 remainder (two MFMAs), so the weights keep 17 significant
 //       bits (PAIR: three terms, all 24).  V is loaded in its natural layout -- lane (r, j), load u: the 16
 //       bytes of token 4j+u at chunk r, i.e. four complete 256-byte rows per
 //       instruction -- and the B operand (k = token 4j+u, n = r) for column
@@ -249,12 +249,11 @@ __device__ __forceinline__ void attend_two_fp8(WaveState &st, float (&sc)[8], u3
         st.l += p1;
         p0 *= k < 2 ? vs_a : vs_b;
         p1 *= k < 2 ? vs_a : vs_b;
+        uint32_t terms[TERMS];
+        split_weights<TERMS>(p0, p1, terms);
 #pragma unroll
-        for (int t = 0; t < TERMS; ++t) {
-            w[t][k] = pack_bf16(p0, p1);
-            p0 -= bf16_lo(w[t][k]);
-            p1 -= bf16_hi(w[t][k]);
-        }
+        for (int t = 0; t < TERMS; ++t)
+            w[t][k] = terms[t];
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {

@@ -502,9 +502,7 @@ __device__ __forceinline__ PairWeights pair_softmax(WaveState &st, PageRegs &pb,
                 st.o[e][i] *= a;
         }
     }
-    // A bf16 head and a bf16 remainder, both rounded by the conversion instruction: 17 bits of each weight
-    // without a bias (cut off instead, the remainder made every result 8e-6 too small: error against 64
-    // bits 8.7e-6 before, 2.3e-6 now; the time is the same).
+    // (The remainder is rounded: cut off like the head, it made every result 8e-6 too small.)
     PairWeights w;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
@@ -513,8 +511,10 @@ __device__ __forceinline__ PairWeights pair_softmax(WaveState &st, PageRegs &pb,
         st.l += p1;
         p0 *= h < 2 ? p_scale_a : p_scale_b;
         p1 *= h < 2 ? p_scale_a : p_scale_b;
-        w.ah[h] = pack_bf16(p0, p1);
-        w.al[h] = pack_bf16(p0 - bf16_lo(w.ah[h]), p1 - bf16_hi(w.ah[h])); // (the differences are exact)
+        uint32_t terms[2];
+        split_weights<2>(p0, p1, terms);
+        w.ah[h] = terms[0];
+        w.al[h] = terms[1];
     }
     return w;
 }
@@ -771,8 +771,10 @@ __device__ __forceinline__ void single_page_fp8(WaveState &st, const u32x2 (&k8)
         st.l += p1;
         p0 *= p_scale;
         p1 *= p_scale;
-        ah[h] = pack_bf16(p0, p1);
-        al[h] = pack_bf16(p0 - bf16_lo(ah[h]), p1 - bf16_hi(ah[h]));
+        uint32_t terms[2];
+        split_weights<2>(p0, p1, terms);
+        ah[h] = terms[0];
+        al[h] = terms[1];
     }
     const uint32_t keep = tail ? tail_mask_fp8(tok, t1) : 0xffffffffu; // rows past the end may hold anything
 #pragma unroll

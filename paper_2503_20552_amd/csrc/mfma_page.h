@@ -166,12 +166,11 @@ __device__ __forceinline__ void attend_page(WaveState &st, PageRegs &pg, const u
         st.l += p1;
         p0 *= p_scale;
         p1 *= p_scale;
+        uint32_t terms[TERMS];
+        split_weights<TERMS>(p0, p1, terms);
 #pragma unroll
-        for (int t = 0; t < TERMS; ++t) {
-            w[t][h] = pack_bf16(p0, p1);
-            p0 -= bf16_lo(w[t][h]); // exact
-            p1 -= bf16_hi(w[t][h]);
-        }
+        for (int t = 0; t < TERMS; ++t)
+            w[t][h] = terms[t];
     }
 
 #pragma unroll

@@ -74,6 +74,25 @@ def test_a_kv_head_with_infinities_leaves_its_neighbour_alone():
     assert torch.equal(clean[:, :4], dirty[:, :4]) and not torch.equal(clean[:, 4:], dirty[:, 4:])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kernel", [adr.KERNEL_AUTO, adr.KERNEL_MFMA])
+@pytest.mark.parametrize("partition_tokens", [0, 64])
+def test_an_infinite_value_stays_infinite(d, kernel, partition_tokens):
+    if d == 64 and kernel == adr.KERNEL_MFMA:
+        pytest.skip("the resident kernel serves d = 128")
+    b = make(9, 16, 4, d, [1, 40, 700, 1300])
+    v = b.v_cache.clone()
+    v[:, :, :, 5] = float("inf")            # every weight's every term meets one
+    v[:, 3, :, 7] = -float("inf")
+    args = (dev(b.q), dev(b.k_cache), dev(v), dev(b.block_table), dev(b.seq_lens), b.wl.scale)
+    say("infinite values d=%d kernel=%d part=%d" % (d, kernel, partition_tokens))
+    out, lse = gpu_attention(*args, partition_tokens=partition_tokens, flags=kernel)
+    plain, plain_lse = gpu_attention(args[0], args[1], dev(b.v_cache), *args[3:], partition_tokens=partition_tokens, flags=kernel)
+    assert (out[..., 5] == float("inf")).all() and (out[1:, :, 7] == -float("inf")).all()
+    rest = [i for i in range(d) if i not in (5, 7)]
+    assert torch.equal(out[..., rest], plain[..., rest]) and torch.equal(lse, plain_lse)
+
+
 @pytest.mark.parametrize("Hkv,G", [(1, 4), (8, 2)])                # 1 .. 96 rows of the cache: partitions of 128
 @pytest.mark.parametrize("bound", [None, 8192])                    # places of the workspace: 3 or 16 a row
 def test_a_small_pass_is_cut_finer_than_the_callers_partitions(Hkv, G, bound):
