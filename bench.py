@@ -45,12 +45,10 @@ HBM_PEAK_GBS = 8000.0
 # line reports traffic null rather than a stale number.
 MEASURED_TRAFFIC_BYTES = {
     # (workload, kernel[, "fp8"]): (bytes per launch, hash of csrc/ at the time, summary under profiles/)
-    (3, 'decode_stream_kernel'): (2344273634, '6766cd555ffaca53', 'profiles/decode_stream_kernel_workload3.md'),
-    (5, 'decode_stream_kernel'): (10533352777, '6766cd555ffaca53', 'profiles/decode_stream_kernel_workloads2_5_bf16.md'),
-    (2, 'decode_stream_kernel'): (1447104494, '6766cd555ffaca53', 'profiles/decode_stream_kernel_workloads2_5_bf16.md'),
-    (5, 'decode_stream_kernel', 'fp8'): (5456117949, '6766cd555ffaca53', 'profiles/decode_stream_kernel_workload5_fp8.md'),
-    (3, 'decode_stream_kernel', 'fp8'): (1214961475, '6766cd555ffaca53', 'profiles/decode_stream_kernel_workload5_fp8.md'),
-    (4, 'decode_mfma_kernel'): (347841203, '6766cd555ffaca53', 'profiles/decode_mfma_kernel_workload4.md'),
+    (3, 'decode_stream_kernel'): (2332288190, '4d5d4cd461082fda', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (3, 'decode_mfma_kernel', 'fp8'): (1184535298, '4d5d4cd461082fda', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (4, 'decode_mfma_kernel'): (343502318, '4d5d4cd461082fda', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (2, 'decode_mfma_kernel'): (1439955515, '4d5d4cd461082fda', 'profiles/traffic_of_the_benchmark_kernels.md'),
 }
 
 
