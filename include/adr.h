@@ -87,8 +87,9 @@ enum {
     ADR_SINGLE_PARTITION_ITEMS = 32,
     /* The caller vouches that the workspace's control area (its last bytes, see
      * adr_decode_workspace_bytes) is all zero: it was cleared by an earlier call on this workspace
-     * that has completed, and every call leaves it zero.  Saves adr_decode_attention the small
-     * kernel that clears it first (adr_decode_step never needs one).  On an area that is not zero
+     * that has completed, and every call leaves it zero, whichever kernel serves it.  Saves
+     * adr_decode_attention the small kernel that clears it ahead of the resident one
+     * (adr_decode_step never needs one).  On an area that is not zero
      * the results are wrong or NaN. */
     ADR_WORKSPACE_READY = 64,
     /* Test aid: the resident matrix-core kernel's waits on other waves expire at once, as if its

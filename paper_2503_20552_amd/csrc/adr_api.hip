@@ -461,10 +461,12 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     if (bounds_record(&p.bounds) != ADR_OK)
         return ADR_ERR_LAUNCH;
 
-    // The control area must be all zero when the resident kernel starts and when a merge reads the
-    // status block.  Kernels that never touch it leave the merge without a status to read.
-    const bool uses_control = p.control && (kernel == KERNEL_STREAM || (flags & ADR_PARTIALS_ONLY));
-    const bool clear_control = uses_control && !(flags & ADR_WORKSPACE_READY);
+    // The control area must be all zero when the resident kernel starts, when a merge reads the status
+    // block, and behind every call that was not told it is (adr.h: a later call may then vouch for it, or
+    // the status be read): the append kernel clears it on its way, or else a kernel that never touches it
+    // does, or else a small kernel ahead of the resident one.
+    const bool clear_control = p.control && !(flags & ADR_WORKSPACE_READY);
+    p.clear_words = clear_control && !nt && kernel != KERNEL_STREAM ? plan.control_words() : 0;
 
     // The new token goes in first: the append kernel, with the token index taken from seq_lens.
     if (nt) {
@@ -491,7 +493,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         ap.bounds = p.bounds;
         if (adr::launch_kv_append(ap, fp8, (hipStream_t)stream) != hipSuccess)
             return ADR_ERR_LAUNCH;
-    } else if (clear_control) {
+    } else if (clear_control && kernel == KERNEL_STREAM) {
         control_clear_kernel<<<1, 64, 0, (hipStream_t)stream>>>(p.control, plan.control_words());
         if (hipGetLastError() != hipSuccess)
             return ADR_ERR_LAUNCH;
@@ -517,7 +519,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         mp.heads = Hq;
         mp.d = d;
         mp.out_f32 = p.out_f32;
-        mp.status = uses_control ? p.control : nullptr;
+        mp.status = kernel == KERNEL_STREAM ? p.control : nullptr; // the others have no wait that could expire
         e = adr::launch_lse_merge(mp, (hipStream_t)stream);
         if (e != hipSuccess)
             return ADR_ERR_LAUNCH;

@@ -70,6 +70,7 @@ struct DecodeParams {
     int coalesce;         // the resident kernel may take runs of partitions as one item
     float scale_log2e;    // softmax scale * log2(e): scores are kept in base 2
     uint32_t *control;    // control area of the call (status block first), or nullptr: the static pool
+    int clear_words;      // of `control`, zeroed by a kernel that does not use it (clear_control)
     int spin_limit;       // polls before a wait on another wave is declared failed
     int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
@@ -271,6 +272,16 @@ __device__ __forceinline__ int row_partition(int L, int partition_tokens, int ma
     if (cut == 0)
         return partition_tokens;
     return max(cut, ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1));
+}
+
+// Every call leaves its control area zero, whichever kernel serves it: a later call on the workspace may
+// vouch for it, merge partials by its status block or read that.  A kernel that never touches the area
+// has its first workgroup zero it on the way (no launch of its own; nothing of this call reads it).
+__device__ __forceinline__ void clear_control(const DecodeParams &p)
+{
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < p.clear_words; i += blockDim.x)
+            p.control[i] = 0u;
 }
 
 // Combine the kWaves per-wave partial results staged in LDS and write either

@@ -274,6 +274,7 @@ void decode_mfma_kernel(const DecodeParams p)
     const int H = PAIR ? p.Hkv >> 1 : p.Hkv;       // rows of D elements per token
     const int R = PAIR ? 2 * G : G;                // query heads that use one of them
 
+    clear_control(p);
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     float *ml = (float *)(lds_raw + NW * kWaveBytes); // [NW][16][2]: running max, denominator of each head
 
