@@ -155,25 +155,25 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
-// Two non-negative fp32 numbers p as sums of TERMS bf16 ones (pairs as the matrix instructions take them):
-// heads cut off, the last term rounded.  17 bits of p in two terms, all 24 in three; rounding leaves no
-// bias.  Every term is kept at 2^-126 or above (as 16-bit integers: the terms are not negative, and NaN
-// stays NaN), so that a weight times an infinite value stays infinite: with remainders that are zero or
-// negative it would be NaN.
+// Two fp32 weights p (times a page's V scale, of either sign) as sums of TERMS bf16 ones, pairs as the matrix
+// instructions take them: 17 bits of p in two terms, all 24 in three; the last is rounded, which leaves
+// no bias.  The heads are cut off one unit in the last place below p, so what remains has p's sign and is
+// never zero: a head that is p itself would leave 0, and 0 times an infinite value is NaN.  (The sum is
+// the same: where the cut-off bits are zero the remainder is a power of two.)  Weights below 2^-94
+// are cut off as they are, since a remainder made up there would be no normal bf16 number; a weight of
+// zero is all zeros.
 template <int TERMS>
 __device__ __forceinline__ void split_weights(float p0, float p1, uint32_t (&w)[TERMS])
 {
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t below0 = fabsf(p0) >= 0x1p-94f ? 1u : 0u, below1 = fabsf(p1) >= 0x1p-94f ? 1u : 0u;
 #pragma unroll
-    for (int t = 0; t < TERMS; ++t) {
-        const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
-        w[t] = t + 1 < TERMS ? (u0 >> 16) | (u1 & 0xffff0000u) : pack_bf16(p0, p1);
-        if (t + 1 < TERMS) {
-            p0 -= __uint_as_float(u0 & 0xffff0000u); // exact
-            p1 -= __uint_as_float(u1 & 0xffff0000u);
-        }
-        w[t] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, w[t]), u16x2{0x0080, 0x0080}));
+    for (int t = 0; t + 1 < TERMS; ++t) {
+        const uint32_t h0 = (__float_as_uint(p0) - below0) & 0xffff0000u, h1 = (__float_as_uint(p1) - below1) & 0xffff0000u;
+        w[t] = (h0 >> 16) | h1;
+        p0 -= __uint_as_float(h0); // exact
+        p1 -= __uint_as_float(h1);
     }
+    w[TERMS - 1] = pack_bf16(p0, p1);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
