@@ -463,10 +463,11 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
 
     // The control area must be all zero when the resident kernel starts, when a merge reads the status
     // block, and behind every call that was not told it is (adr.h: a later call may then vouch for it, or
-    // the status be read): the append kernel clears it on its way, or else a kernel that never touches it
-    // does, or else a small kernel ahead of the resident one.
+    // the status be read).  A kernel that never touches it clears it on its way; ahead of the resident
+    // one the append kernel does, or else a small kernel.
     const bool clear_control = p.control && !(flags & ADR_WORKSPACE_READY);
-    p.clear_words = clear_control && !nt && kernel != KERNEL_STREAM ? plan.control_words() : 0;
+    const bool clear_ahead = clear_control && kernel == KERNEL_STREAM;
+    p.clear_words = clear_control && !clear_ahead ? plan.control_words() : 0;
 
     // The new token goes in first: the append kernel, with the token index taken from seq_lens.
     if (nt) {
@@ -488,12 +489,12 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         ap.Hkv = cache->Hkv;
         ap.d = d;
         ap.B = B;
-        ap.clear_words = clear_control ? p.control : nullptr; // on its way, for the kernels behind it
-        ap.n_clear_words = clear_control ? plan.control_words() : 0;
+        ap.clear_words = clear_ahead ? p.control : nullptr; // on its way, for the kernels behind it
+        ap.n_clear_words = clear_ahead ? plan.control_words() : 0;
         ap.bounds = p.bounds;
         if (adr::launch_kv_append(ap, fp8, (hipStream_t)stream) != hipSuccess)
             return ADR_ERR_LAUNCH;
-    } else if (clear_control && kernel == KERNEL_STREAM) {
+    } else if (clear_ahead) {
         control_clear_kernel<<<1, 64, 0, (hipStream_t)stream>>>(p.control, plan.control_words());
         if (hipGetLastError() != hipSuccess)
             return ADR_ERR_LAUNCH;

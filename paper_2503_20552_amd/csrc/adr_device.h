@@ -276,7 +276,10 @@ __device__ __forceinline__ int row_partition(int L, int partition_tokens, int ma
 
 // Every call leaves its control area zero, whichever kernel serves it: a later call on the workspace may
 // vouch for it, merge partials by its status block or read that.  A kernel that never touches the area
-// has its first workgroup zero it on the way (no launch of its own; nothing of this call reads it).
+// has its first workgroup, which always has a partition to attend, zero it as its last act: no launch of its own,
+// and nothing of this call reads it.  (At the kernel's start every workgroup without a partition would pay for
+// the question, 84 against 79 us with 64 K of them, and in the append kernel it stands ahead of the
+// look-up of the position: 11.9 against 11.4 us for a step of one request.)
 __device__ __forceinline__ void clear_control(const DecodeParams &p)
 {
     if (blockIdx.x == 0)

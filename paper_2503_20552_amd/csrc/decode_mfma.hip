@@ -274,7 +274,6 @@ void decode_mfma_kernel(const DecodeParams p)
     const int H = PAIR ? p.Hkv >> 1 : p.Hkv;       // rows of D elements per token
     const int R = PAIR ? 2 * G : G;                // query heads that use one of them
 
-    clear_control(p);
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     float *ml = (float *)(lds_raw + NW * kWaveBytes); // [NW][16][2]: running max, denominator of each head
 
@@ -545,6 +544,7 @@ void decode_mfma_kernel(const DecodeParams p)
         start(part);
         __syncthreads(); // the next partition's K tiles go where the per-wave results lie
     }
+    clear_control(p);
 }
 
 bool decode_mfma_supports(int d, int G, int Hkv);

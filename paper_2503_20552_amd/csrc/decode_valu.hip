@@ -59,7 +59,6 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
     constexpr int TPL = 64 / LPT;       // token rows per load instruction
     constexpr int U = kPageSize / TPL;  // load instructions per page
 
-    clear_control(p);
     const int Hkv = p.Hkv;
     // (an odd number of workgroups per row and kv-head: consecutive workgroups go to the compute
     // units in turn, and with an even number a row's few real ones fall on the same units row after row)
@@ -217,6 +216,7 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
     }
     __syncthreads();
     combine_waves_and_store<D>(p, sm, sl, so, G, b, kvh, part, n_parts);
+    clear_control(p);
 }
 
 #define ADR_VALU_CASE(DD, GG)                                                                     \
