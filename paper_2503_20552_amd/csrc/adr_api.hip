@@ -273,14 +273,11 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // against 268, of median 200 74 against 82).
     const bool splits = partition_tokens > 0 && max_seq_len > partition_tokens;
     const int64_t pairs = (int64_t)B * cache->Hkv;
-    bool resident = splits && pairs >= (G == 1 ? 4096 : 2048) && max_seq_len > 2048;
-    // fp8: one workgroup per item throughout (us: 255 requests x 8 kv-heads 221 against 236, 500 x 4 of very
-    // skewed lengths 471 against 478, 2048 pairs of median 300 65 against 89, groups of eight 244
-    // against 283, unsplit 264 against 392).  One corner stays where adr_decode_kernel_choice has always
-    // reported it, though the same figures hold there: groups of two to four heads, 2048 pairs or more,
-    // rows of up to 8192 tokens.
-    if (fp8)
-        resident = pairs >= 2048 && G >= 2 && G <= 4 && max_seq_len > 4096 && max_seq_len <= 8192;
+    // fp8: one workgroup per item throughout (us per step, one workgroup per item and resident ones: 256
+    // requests x 8 kv-heads of median length 1500 226 and 240, of median 1000 154 and 168, of 3000 tokens
+    // 288 and 300, of 300 49 and 71; groups of two 211 and 232, of eight 244 and 326; whole rows 256
+    // and 405; 512 requests of median 1500 the same, 442).
+    bool resident = !fp8 && splits && pairs >= (G == 1 ? 4096 : 2048) && max_seq_len > 2048;
     // The test aid is about the resident kernel's waits: where it is asked for, that kernel serves.
     if (flags & ADR_DEBUG_EXPIRE_WAITS)
         resident = fp8 || (splits && (G <= 4 || pairs >= 2048 || max_parts_for(max_seq_len, partition_tokens) > 32));
@@ -288,10 +285,8 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
         return KERNEL_STREAM;
     // d = 64, two kv-heads a row: ahead of the vector ALUs throughout (us, 2040 against 2048 pairs of median
     // length 1500, fp8: groups of one 113 and 207, of eight 128 and 446; bf16 195 and 223, 214 and
-    // 436).  One corner stays behind although 202 against 237 us says otherwise: bf16 in groups of four
-    // at that size, which adr_decode_kernel_choice has always reported as the vector ALUs'.
-    const bool reported = d == 64 && !fp8 && G == 4 && splits && pairs >= 2048 && max_seq_len >= 8192;
-    if (!reported && adr::decode_mfma_supports(d, G, cache->Hkv))
+    // 436, of four 206 and 239).
+    if (adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
     if (adr::decode_valu_supports(d, G))
         return KERNEL_VALU;

@@ -63,6 +63,23 @@ def test_many_short_rows_are_items_as_they_are(d, fp8):
     out, _ = check(b, "short rows d=%d fp8=%s" % (d, fp8), fp8=fp8, partition_tokens=64)
 
 
+def widen(b, bound):
+    """The table has to describe as many tokens as the bound."""
+    wide = np.zeros((b.block_table.shape[0], -(-bound // b.wl.page_size)), dtype=np.int32)
+    wide[:, :b.block_table.shape[1]] = b.block_table
+    b.block_table = wide
+
+
+@pytest.mark.parametrize("d,G,fp8", [(128, 2, True), (128, 4, True), (64, 4, False)])
+@pytest.mark.parametrize("partition_tokens", [0, 512])
+def test_many_rows_under_an_ordinary_bound(d, G, fp8, partition_tokens):
+    Hkv = 32 if d == 128 else 64                                   # 2048 rows of the cache
+    b = make(37, G * Hkv, Hkv, d, np.resize(EDGES + [1500, 2100], 64))
+    widen(b, 8192)
+    check(b, "many rows d=%d G=%d fp8=%s part=%d" % (d, G, fp8, partition_tokens), fp8=fp8, partition_tokens=partition_tokens,
+          max_seq_len=8192)
+
+
 def test_a_kv_head_with_infinities_leaves_its_neighbour_alone():
     b = make(7, 8, 2, 64, [40, 700])
     k = b.k_cache.clone()
