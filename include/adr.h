@@ -70,9 +70,11 @@ enum {
                             (request, partition, kv-head) items; batches of more than 512 rows
                             go out as one launch per 512 rows */
     ADR_KERNEL_MFMA_GRID = 3, /* matrix cores, one workgroup per (request, partition, kv-head), for up
-                                 to 33 partitions of a request (workgroups loop over the partitions
+                                 to 33 partitions of a request or as many as make 4096 workgroups
+                                 (nine with very many requests; workgroups loop over the partitions
                                  of longer ones); its grid is sized from max_seq_len, so a bound far
-                                 above the lengths costs it time; bf16 cache only */
+                                 above the lengths costs it some time.  By name for d = 128 and a bf16
+                                 cache; ADR_KERNEL_AUTO takes it for fp8 and for d = 64 too */
     /* Bit 4: run the partition pass only and leave the merge to a later
      * adr_decode_merge call on the same workspace (rows with one partition are
      * still written to `out` directly).  Lets a caller place the two passes on

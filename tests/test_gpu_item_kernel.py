@@ -163,3 +163,18 @@ def test_four_waves_with_more_tiles_than_one_load_of_the_table_brings(fp8):
     # one partition of 4608 tokens: 72 tiles for each of four waves, and a ragged second partition
     b = make(23, 4, 2, 128, [4609, 4096, 4608, 100, 6000])
     check(b, "long partitions fp8=%s" % fp8, fp8=fp8, partition_tokens=4608, flags=adr.SINGLE_PARTITION_ITEMS)
+
+
+# Workgroups per row: 33; what makes 68000 of them with 2061 rows or more; what makes 4096 with 124 or fewer.  Rows of one
+# partition more or less than that, and of several times as many, under a bound that allows any number.
+@pytest.mark.parametrize("B,Hkv,stride", [(40, 8, 33), (512, 8, 17), (1100, 8, 9), (2, 2, 1025)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_rows_with_more_partitions_than_workgroups(B, Hkv, stride, fp8):
+    long = [16 * (stride + i) + j for i in (-1, 0, 1) for j in (0, 1)] + [16 * 3 * stride]
+    lens = np.resize([1, 16, 17, 40, 300], B) if B > 8 else np.array(long[3:5])
+    if B > 8:
+        lens[np.arange(len(long)) * 5] = long
+    b = make(43 + B, Hkv, Hkv, 128, lens)
+    widen(b, 32768)
+    flags = adr.SINGLE_PARTITION_ITEMS if fp8 else adr.KERNEL_MFMA_GRID       # the caller's partitions
+    check(b, "looping workgroups B=%d Hkv=%d fp8=%s" % (B, Hkv, fp8), fp8=fp8, partition_tokens=16, max_seq_len=32768, flags=flags)
