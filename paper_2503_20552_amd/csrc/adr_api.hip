@@ -300,11 +300,12 @@ struct PassCut {
     int tokens;    // per partition, when cut is 0
     int max_parts; // partitions of a row at most
     int cut;       // > 0: see row_partition
+    uint32_t share;
 };
 
 PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, int partition_tokens, unsigned flags)
 {
-    PassCut cut = {partition_tokens, (int)max_parts_for(max_seq_len, partition_tokens), 0};
+    PassCut cut = {partition_tokens, (int)max_parts_for(max_seq_len, partition_tokens), 0, 0};
     if (partition_tokens <= 0 || kernel == KERNEL_VALU ||
         (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS)))
         return cut;
@@ -330,10 +331,9 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
         return cut;
     }
     // Otherwise into what makes about 1200 items of the pass (rows taken to be a quarter as long as the
-    // bound on the average), 128 to 1024 tokens each and not below a 96th of the bound: fewer leave
-    // compute units idle, more pay an item's fixed cost (its chain of length, page table and first page,
-    // its combine, its place in the merge) for nothing.  us with the merge, partitions of 128 / 256
-    // / 512 / 1024 tokens:
+    // bound on the average), 128 to 1024 tokens each: fewer leave compute units idle, more pay an item's
+    // fixed cost (its chain of length, page table and first page, its combine, its place in the merge)
+    // for nothing.  us with the merge, partitions of 128 / 256 / 512 / 1024 tokens:
     //     rows                   8              64               256              1024
     //     1000 tokens     8 /  9 / 11 / 11   14 / 14 / 14 / 18   30 / 30 / 32 / 31   111 / 100 /  97 / 100
     //     3000 tokens     9 / 10 / 12 / 18   25 / 25 / 27 / 33   83 / 75 / 74 / 79   327 / 297 / 280 / 266
@@ -341,9 +341,16 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
     // (an fp8 cache likewise).  The same length for every row: cut in proportion to their own lengths
     // instead, rows of mixed lengths end in long items (85 against 78 us at 1024 rows of heavy-tailed
     // lengths, 48 against 43 at 296).
-    const int64_t aim = std::max<int64_t>(std::min<int64_t>(std::max<int64_t>(rows * max_seq_len / 4800, 128), 1024),
-                                          max_seq_len / 96);
-    cut.cut = (int)((aim + 64) / 128 * 128); // whole pairs of tiles for each of four waves
+    const auto share = [&](int64_t items) { // of a row's length, in units of 2^-32: `items` of the pass if all were as long
+        return (uint32_t)std::min<int64_t>((rows << 32) / items, 0xffffffffLL);
+    };
+    cut.cut = adr::share_of_row(std::min(max_seq_len, adr::kCutLongRow), share(4800));
+    // What the bound says beyond 8192 tokens is not taken for the rows' length (a serving system passes its
+    // context limit): longer rows are cut by their own, to 3600 items if all were like them and 96 of a row
+    // at most while that leaves partitions of 1024 tokens.  us per step, bound 131072 (1048576), partitions that grow with the
+    // bound and these: one request of 2000 tokens 19.5 (22.7) and 10.7, of 20000 25.7 (115) and 23; 16 of 2000
+    // 50 (56) and 30; 40 of median 1000 66 (93) and 50.
+    cut.share = std::max(share(3600), (uint32_t)(((uint64_t)1 << 32) / 96));
     cut.max_parts = (int)std::min<int64_t>(max_parts_for(max_seq_len, cut.cut), cut.max_parts);
     return cut;
 }
@@ -448,6 +455,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     p.max_parts = split ? cut.max_parts : 1;
     p.max_seq_len = max_seq_len;
     p.cut = split ? cut.cut : 0;
+    p.cut_share = cut.share;
     p.out_f32 = out_dtype == ADR_F32;
     p.scale_log2e = scale * adr::kLog2e;
     p.coalesce = !(flags & ADR_SINGLE_PARTITION_ITEMS);
@@ -511,6 +519,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         mp.max_parts = p.max_parts;
         mp.max_seq_len = max_seq_len;
         mp.cut = p.cut;
+        mp.cut_share = p.cut_share;
         mp.B = B;
         mp.heads = Hq;
         mp.d = d;
@@ -591,6 +600,7 @@ int adr_decode_merge(void *out, adr_dtype out_dtype, float *lse, const int32_t *
     mp.max_parts = (int)max_parts;
     mp.max_seq_len = max_seq_len;
     mp.cut = 0;
+    mp.cut_share = 0;
     mp.B = B;
     mp.heads = Hq;
     mp.d = d;
@@ -623,6 +633,7 @@ int adr_lse_merge(void *out, adr_dtype out_dtype, float *lse_out, const float *p
     mp.max_parts = 0;
     mp.max_seq_len = 0;
     mp.cut = 0;
+    mp.cut_share = 0;
     mp.B = B;
     mp.heads = heads;
     mp.d = d;

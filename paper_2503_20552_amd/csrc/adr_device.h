@@ -65,7 +65,8 @@ struct DecodeParams {
     int partition_tokens; // 0 = whole sequence in one pass
     int max_parts;        // partitions per request the grid was sized for (>= 1)
     int max_seq_len;
-    int cut;              // > 0: rows are cut into partitions of that many tokens where it can be (row_partition)
+    int cut;              // > 0: rows are cut into partitions of that many tokens or more (row_partition)
+    uint32_t cut_share;   //   of a long row's length, in units of 2^-32
     int out_f32;          // 1: out is fp32, 0: bf16
     int coalesce;         // the resident kernel may take runs of partitions as one item
     float scale_log2e;    // softmax scale * log2(e): scores are kept in base 2
@@ -86,6 +87,7 @@ struct MergeParams {
     int partition_tokens;        //   [b*max_parts, b*max_parts + ceil(min(seq_len,max_seq_len)/partition_tokens))
     int max_parts, max_seq_len;  //   and rows with <= 1 partition are left alone
     int cut;                     //   (row_partition)
+    uint32_t cut_share;
     int B, heads, d, out_f32;
     const uint32_t *status;      // call status block of the pass that wrote the partials, or nullptr: when
                                  // its expired-waits word is not zero every row gets NaN
@@ -266,12 +268,21 @@ __device__ __forceinline__ int parts_of(int L, int partition_tokens)
 }
 
 // Tokens per partition of a row of L tokens.  cut = 0: the caller's partitions.  Otherwise the library
-// cuts by itself: `cut` tokens, or more where the row would need more than max_parts places.
-__device__ __forceinline__ int row_partition(int L, int partition_tokens, int max_parts, int cut)
+// cuts by itself (pass_cut): `cut` tokens, a share of the row's own length where it is a long one, or more
+// where it would need more than max_parts places.
+constexpr int kCutLeast = 128, kCutMost = 1024; // (whole pairs of tiles for each of four waves)
+constexpr int kCutLongRow = 8192;
+__host__ __device__ __forceinline__ int share_of_row(int L, uint32_t share) // to the next multiple of kCutLeast
+{
+    const uint64_t n = (((uint64_t)(uint32_t)L * share >> 32) + kCutLeast / 2) / kCutLeast * kCutLeast;
+    return n < kCutLeast ? kCutLeast : n < kCutMost ? (int)n : kCutMost;
+}
+__device__ __forceinline__ int row_partition(int L, int partition_tokens, int max_parts, int cut, uint32_t share)
 {
     if (cut == 0)
         return partition_tokens;
-    return max(cut, ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1));
+    const int places = ((L + max_parts - 1) / max_parts + kPageSize - 1) & ~(kPageSize - 1);
+    return max(L > kCutLongRow ? max(cut, share_of_row(L, share)) : cut, places);
 }
 
 // Every call leaves its control area zero, whichever kernel serves it: a later call on the workspace may

@@ -312,7 +312,7 @@ void decode_mfma_kernel(const DecodeParams p)
     const unsigned least = p.cut > 0 ? p.cut : p.partition_tokens;
     if (first_part > 0 && first_part * least >= (unsigned)L)
         return;
-    const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut);
+    const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut, p.cut_share);
     const int n_parts = parts_of(L, pt);
     if (first_part >= n_parts)
         return;

@@ -178,3 +178,39 @@ def test_rows_with_more_partitions_than_workgroups(B, Hkv, stride, fp8):
     widen(b, 32768)
     flags = adr.SINGLE_PARTITION_ITEMS if fp8 else adr.KERNEL_MFMA_GRID       # the caller's partitions
     check(b, "looping workgroups B=%d Hkv=%d fp8=%s" % (B, Hkv, fp8), fp8=fp8, partition_tokens=16, max_seq_len=32768, flags=flags)
+
+
+def partitions_of_a_pass(b, fp8, bound):
+    """How many partitions a merging call with AUTO leaves in its workspace: the words of it that are written."""
+    q, shape = dev(b.q), b.q.shape
+    scales = [torch.ones(b.k_cache.shape[0], b.wl.Hkv, device="cuda:0") for _ in range(2)] if fp8 else (None, None)
+    data = [dev(torch.randint(0, 0x40, x.shape, dtype=torch.uint8)) if fp8 else dev(x) for x in (b.k_cache, b.v_cache)]
+    ws = torch.full((adr.adr_decode_workspace_bytes(*shape, bound, 512) // 4,), float("nan"), device="cuda:0")
+    table = torch.zeros(shape[0], bound // 16, dtype=torch.int32, device="cuda:0")
+    table[:, :b.block_table.shape[1]] = dev(b.block_table)
+    adr.adr_decode_attention(torch.empty(shape, device="cuda:0"), q, adr.KVCache(*data, *scales), table, dev(b.seq_lens), b.wl.scale,
+                             bound, 512, ws)
+    torch.cuda.synchronize()
+    control = 64 * (1 + -(-shape[0] // 512))
+    return int((~torch.isnan(ws[:-control])).sum()) / (shape[1] * (shape[2] + 1))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_a_bound_far_above_the_lengths_does_not_coarsen_the_cut(d, fp8):
+    few = make(47, 8, 8, d, [2000, 1000, 1700])                # partitions of 128 tokens
+    say("cut under loose bounds d=%d fp8=%s" % (d, fp8))
+    assert [partitions_of_a_pass(few, fp8, n) for n in (8192, 32768, 131072, 1 << 20)] == [16 + 8 + 14] * 4
+    for b in (make(48, 8, 8, d, [20000]), make(49, 8, 8, d, np.resize([1500, 3000], 40))):
+        callers = int((-(-b.seq_lens // 512)).sum())
+        for n in (32768, 131072, 1 << 20):
+            assert partitions_of_a_pass(b, fp8, n) >= callers
+
+
+@pytest.mark.parametrize("d,fp8", [(128, False), (128, True), (64, False)])
+@pytest.mark.parametrize("bound", [8200, 32768, 1 << 20])
+@pytest.mark.parametrize("lens", [[8191, 8192, 8193, 8320, 8321, 0, 1], [20000, 300], [16385, 12000] + [40] * 30])
+def test_rows_around_the_length_from_which_they_are_cut_by_their_own(d, fp8, bound, lens):
+    b = make(53, 8, 2, d, np.minimum(lens, bound))
+    widen(b, bound)
+    check(b, "long rows d=%d fp8=%s bound=%d %s" % (d, fp8, bound, lens[:3]), fp8=fp8, partition_tokens=512, max_seq_len=bound)
