@@ -283,10 +283,17 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
         resident = fp8 || (splits && (G <= 4 || pairs >= 2048 || max_parts_for(max_seq_len, partition_tokens) > 32));
     if (resident && adr::decode_stream_supports(d, G, B))
         return KERNEL_STREAM;
-    // d = 64, two kv-heads a row: ahead of the vector ALUs throughout (us, 2040 against 2048 pairs of median
-    // length 1500, fp8: groups of one 113 and 207, of eight 128 and 446; bf16 195 and 223, 214 and
-    // 436, of four 206 and 239).
-    if (adr::decode_mfma_supports(d, G, cache->Hkv))
+    // d = 64, two kv-heads a row: ahead of the vector ALUs in groups of two heads or more (us, 2040 against 2048
+    // pairs of median length 1500, fp8: groups of eight 128 and 446; bf16 of eight 214 and 436, of four 206
+    // and 239; four requests of 300 tokens in groups of four 9 and 12) and in large passes of groups of one (fp8
+    // 113 and 207, bf16 195 and 223).  Small passes of groups of one are the vector ALUs': with few
+    // items a workgroup's own chain of steps is all there is, and theirs is shorter (four requests x 8
+    // kv-heads of up to 512 tokens 10.2 and 8.6, fp8 11.8 and 9.4; one of 2000 in partitions of 512 12.9
+    // and 11.2).  Up to 32768 tokens that holds for 244 of 252 shapes measured, by 15 % in the median; with
+    // twice as many an fp8 cache is behind in one of four, and from 4096 tokens on whole rows get eight waves
+    // (31 against 46).
+    const bool few = d == 64 && G == 1 && pairs * max_seq_len <= 32768 && max_seq_len < 4096;
+    if (!few && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
     if (adr::decode_valu_supports(d, G))
         return KERNEL_VALU;

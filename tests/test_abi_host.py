@@ -212,6 +212,12 @@ def test_small_passes_take_one_workgroup_per_item():
     assert choice(half, 255, 32) == choice(half, 1, 64, part=0) == adr.KERNEL_MFMA_GRID
     assert choice(half, 256, 64) == choice(half, 512, 8) == choice(half, 256, 32, part=0) == adr.KERNEL_MFMA_GRID
     assert choice(cache(Hkv=1, d=64), 8, 8) == adr.KERNEL_VALU                              # no pair
+    # groups of one head of 64: the vector ALUs have the shorter chain while there are few items (8.6 against 10.2 us
+    # at 4 requests x 8 kv-heads of up to 512 tokens)
+    for part in (0, 512):
+        assert choice(half, 4, 8, part=part, bound=1024) == choice(half, 1, 8, part=part, bound=4095) == adr.KERNEL_VALU
+        assert choice(half, 4, 8, part=part, bound=1025) == choice(half, 1, 8, part=part, bound=4096) == adr.KERNEL_MFMA_GRID
+        assert choice(half, 1, 16, part=part, bound=100) == adr.KERNEL_MFMA_GRID
     assert choice(cache(Hkv=2, d=64), 8, 32) == choice(cache(Hkv=2, d=64), 8, 6) == -UNSUP  # groups of 16 and 3: as before
     fp8 = dict(dtype=adr.ADR_FP8_E4M3, k_scale=FAKE, v_scale=FAKE)
     assert choice(cache(Hkv=8, **fp8), 255, 32) == choice(cache(Hkv=8, d=64, **fp8), 8, 32) == adr.KERNEL_MFMA_GRID

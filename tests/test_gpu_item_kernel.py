@@ -214,3 +214,13 @@ def test_rows_around_the_length_from_which_they_are_cut_by_their_own(d, fp8, bou
     b = make(53, 8, 2, d, np.minimum(lens, bound))
     widen(b, bound)
     check(b, "long rows d=%d fp8=%s bound=%d %s" % (d, fp8, bound, lens[:3]), fp8=fp8, partition_tokens=512, max_seq_len=bound)
+
+
+@pytest.mark.parametrize("bound,kernel", [(1024, adr.KERNEL_VALU), (1025, adr.KERNEL_MFMA_GRID)])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("partition_tokens", [0, 512])
+def test_small_passes_of_single_heads_of_64(bound, kernel, fp8, partition_tokens):
+    b = make(59, 8, 8, 64, [bound, 17, 0, 700])
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    assert adr.adr_decode_kernel_choice(cache, 4, 8, bound, partition_tokens) == kernel
+    check(b, "single heads of 64, bound=%d fp8=%s part=%d" % (bound, fp8, partition_tokens), fp8=fp8, partition_tokens=partition_tokens)
