@@ -5,6 +5,8 @@ from __future__ import annotations
 import contextlib
 import ctypes
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -101,7 +103,7 @@ def debug_library():
 
 
 def load_library():
-    """Load libadr.so and the native marshalling; fails loudly when they have not been built."""
+    """Load libadr.so; fails loudly when it has not been built."""
     global _lib, _release_lib, _marshal
     if _lib is not None:
         return _lib
@@ -109,14 +111,31 @@ def load_library():
         raise ImportError(
             "%s is missing: build it with `python -m paper_2503_20552_amd.build` "
             "(there is no fallback path)" % _LIB_PATH)
-    try:
-        from . import _marshal as native
-    except ImportError as e:
-        raise ImportError("the native marshalling module is missing or does not load: build it with "
-                          "`python -m paper_2503_20552_amd.build`") from e
-    _marshal = native
+    _marshal = _native_marshalling()
     _lib = _release_lib = _declare(ctypes.CDLL(_LIB_PATH))
     return _lib
+
+
+class _LeavesAll:
+    """Stands in for the native marshalling where it cannot be used: every call is left to ctypes."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_marshalling():
+    """The module _marshal, if it is there and was built for this Python and this torch (it works on torch's
+    tensors directly).  Without it the same calls go through ctypes, 9 to 12 us slower each."""
+    wanted = "%s torch %s" % (sys.implementation.cache_tag, torch.__version__)
+    try:
+        from . import _marshal as native
+        why = "it was built for %s, this is %s" % (getattr(native, "built_for", "something else"), wanted)
+        if getattr(native, "built_for", None) == wanted:
+            return native
+    except ImportError as e:
+        why = str(e)
+    warnings.warn("calls are marshalled in Python, which costs each about 10 us: the native module _marshal is not used (%s); "
+                  "`python -m paper_2503_20552_amd.build` builds it" % why, RuntimeWarning, stacklevel=3)
+    return _LeavesAll()
 
 
 _FAST = ("adr_decode_attention", "adr_decode_step", "adr_kv_append", "adr_lse_merge", "adr_pack_qkv", "adr_scatter_rows")

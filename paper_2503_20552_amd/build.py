@@ -59,6 +59,7 @@ def build_marshal() -> str:
     tmp = MARSHAL + ".tmp%d" % os.getpid()
     subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
                            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                           '-DADR_BUILT_FOR="%s torch %s"' % (sys.implementation.cache_tag, torch.__version__),
                            "-isystem", os.path.join(root, "include"),
                            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
                            "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", tmp,

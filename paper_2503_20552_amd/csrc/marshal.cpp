@@ -61,7 +61,7 @@ void *stream_handle(PyObject *o, const at::Tensor &on)
 {
     PyObject *handle;
     if (o == Py_None) {
-        need(on.is_cuda()); // (torch has set the device up, then)
+        need(on.is_cuda() && get_device && get_raw_stream); // (torch has set the device up, then)
         PyObject *device = PyObject_CallNoArgs(get_device);
         handle = device ? PyObject_CallOneArg(get_raw_stream, device) : nullptr;
         Py_XDECREF(device);
@@ -353,10 +353,13 @@ PyMODINIT_FUNC PyInit__marshal()
     PyObject *torch_c = PyImport_ImportModule("torch._C");
     if (!torch_c)
         return nullptr;
-    get_device = PyObject_GetAttrString(torch_c, "_cuda_getDevice");
+    get_device = PyObject_GetAttrString(torch_c, "_cuda_getDevice"); // (a torch without them: such calls are left alone)
     get_raw_stream = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
+    PyErr_Clear();
     Py_DECREF(torch_c);
-    if (!get_device || !get_raw_stream)
-        return nullptr;
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    // What it was built for: the binding leaves it aside under any other Python or torch.
+    if (m && PyModule_AddStringConstant(m, "built_for", ADR_BUILT_FOR) != 0)
+        Py_CLEAR(m);
+    return m;
 }

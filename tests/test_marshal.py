@@ -1,6 +1,9 @@
 """The native marshalling against the ctypes path it stands in for: for plain calls the C entry point must
 receive the same arguments from both, and what the ctypes path refuses the native one must leave to it."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -162,3 +165,37 @@ def test_the_status_becomes_the_exception():
     with pytest.raises(adr.AdrError) as e:
         fn(**a)
     assert e.value.status == 2 and "adr_decode_step" in str(e.value)
+
+
+WITHOUT = """
+import sys, types, warnings
+class Hide:
+    def find_spec(self, name, path=None, target=None):
+        if name == "paper_2503_20552_amd._marshal":
+            raise ImportError("hidden")
+{how}
+import torch
+import paper_2503_20552_amd as adr
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert adr.adr_graph_capacity(5, 16, 64) == 16 and adr.adr_version() > 0
+assert len(seen) == 1 and "_marshal" in str(seen[0].message), seen
+k = torch.zeros(7, 16, 2, 64, dtype=torch.bfloat16)
+q = torch.zeros(3, 8, 64, dtype=torch.bfloat16)
+try:
+    adr.adr_decode_attention(q.clone(), q, adr.KVCache(k, k.clone()), torch.zeros(3, 5, dtype=torch.int32),
+                             torch.zeros(3, dtype=torch.int32), 0.25, 80, 24, stream=1 << 40)
+except adr.AdrError as e:
+    assert e.status == 2       # not a multiple of the page size: the C entry point's own refusal
+else:
+    raise AssertionError
+"""
+
+
+@pytest.mark.parametrize("how", ["sys.meta_path.insert(0, Hide())",
+                                 "sys.modules['paper_2503_20552_amd._marshal'] = types.ModuleType('_marshal')"])
+def test_the_library_works_without_the_native_marshalling(how):
+    """Missing, or built for another Python or torch: the same calls go through ctypes, after one warning."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", WITHOUT.format(how=how)], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
