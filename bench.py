@@ -9,7 +9,8 @@ pass and the log-sum-exp merge (--separate-append: adr_kv_append, then
 adr_decode_attention).  Sequences grow by one token per step.
 Prints ONE JSON line: whole-job attended-KV bandwidth (algorithmic bytes of K
 and V attended per second, inputs resident in HBM), the roofline of the
-dominant kernel from HIP events on the launch stream, the fp64 oracle timed
+attention pass (the dominant kernel and its merge, as the timed step runs them)
+from HIP events on the launch stream, the fp64 oracle timed
 on the host cores as a baseline, and (object "corun") the same attention steps
 next to a compute-bound neighbour: a bf16 8192^3 matrix product on a second
 stream, with the compute units shared freely and split by queue masks, for the
@@ -196,17 +197,17 @@ def main():
             if events is None:
                 adr.adr_decode_attention(out, st["q"], cache, st["table"], seq, wl.scale, st["max_len"],
                                          part, ws, None, kf)
-            else:   # the same three kernels in the same order, with events around the partition pass and the merge
-                # (the workspace's control area is clear: every earlier call left it so, which saves the
-                # attention call its clearing kernel, as the append does inside adr_decode_step)
-                e0, e1, e2 = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+            else:   # the kernels of adr_decode_step in the same order, with events around the attention pass: the partition
+                # kernel and the merge together, since a call that keeps its partials apart (ADR_PARTIALS_ONLY)
+                # cuts the rows in another way.  (The workspace's control area is clear: every earlier call
+                # left it so, which saves the attention call a clearing kernel, as the append does inside
+                # adr_decode_step.)
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
                 e0.record()
                 adr.adr_decode_attention(out, st["q"], cache, st["table"], seq, wl.scale, st["max_len"],
-                                         part, ws, None, kf | adr.PARTIALS_ONLY | adr.WORKSPACE_READY)
+                                         part, ws, None, kf | adr.WORKSPACE_READY)
                 e1.record()
-                adr.adr_decode_merge(out, seq, st["max_len"], part, ws)
-                e2.record()
-                events.append((e0, e1, e2))
+                events.append((e0, e1))
 
     if args.probe_copy:
         src = torch.zeros(1 << 30, dtype=torch.uint8, device="cuda:0")
@@ -236,13 +237,12 @@ def main():
     kv_bytes = attended_tokens * bytes_per_token
     value = kv_bytes / elapsed / 1e9
 
-    # the same K steps again, instrumented: HIP events on the launch stream around each pass
+    # the same K steps again, instrumented: HIP events on the launch stream around each attention pass
     events = []
     for s in range(Wm, Wm + K):
         one_step(s, events)
     torch.cuda.synchronize()
-    attn_ms = np.array([e0.elapsed_time(e1) for e0, e1, _ in events])
-    merge_ms = np.array([e1.elapsed_time(e2) for _, e1, e2 in events])
+    attn_ms = np.array([e0.elapsed_time(e1) for e0, e1 in events])
     bytes_per_launch = kv_bytes / (layers * K)
     achieved = bytes_per_launch / (attn_ms.mean() * 1e-3) / 1e9
     # the library says which kernel it runs for this shape
@@ -256,12 +256,11 @@ def main():
     roofline = {"bound": "hbm", "kernel": kernel_name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "traffic_source": traffic_source,
-                "avg_kernel_ms": round(float(attn_ms.mean()), 5),
-                "median_kernel_ms": round(float(np.median(attn_ms)), 5), "launches": int(len(attn_ms)),
-                "algorithmic_bytes_per_launch": int(bytes_per_launch),
-                "merge_avg_ms": round(float(merge_ms.mean()), 5)}
-    log("partition pass %.4f ms avg (min %.4f, max %.4f), merge %.4f ms avg" % (
-        attn_ms.mean(), attn_ms.min(), attn_ms.max(), merge_ms.mean()))
+                "timed": "the kernel and the merge behind it", "avg_pass_ms": round(float(attn_ms.mean()), 5),
+                "median_pass_ms": round(float(np.median(attn_ms)), 5), "launches": int(len(attn_ms)),
+                "algorithmic_bytes_per_launch": int(bytes_per_launch)}
+    log("attention pass (partition kernel and merge) %.4f ms avg (min %.4f, max %.4f)" % (
+        attn_ms.mean(), attn_ms.min(), attn_ms.max()))
 
     corun = None
     if not args.no_corun and not fp8 and wl.d == 128:
