@@ -224,3 +224,66 @@ def test_small_passes_of_single_heads_of_64(bound, kernel, fp8, partition_tokens
     cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
     assert adr.adr_decode_kernel_choice(cache, 4, 8, bound, partition_tokens) == kernel
     check(b, "single heads of 64, bound=%d fp8=%s part=%d" % (bound, fp8, partition_tokens), fp8=fp8, partition_tokens=partition_tokens)
+
+
+VARIANTS = [(128, 4, 2, False), (128, 2, 3, True), (64, 4, 2, False), (64, 2, 4, True)]
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", VARIANTS)
+@pytest.mark.parametrize("partition_tokens,page_size", [(16, 16), (48, 16), (64, 64), (512, 32)])
+@pytest.mark.parametrize("apart", [False, True])
+def test_the_callers_partitions(d, G, Hkv, fp8, partition_tokens, page_size, apart):
+    """Calls that keep the caller's partitions (fewer tiles than waves among them): items of one partition each, and
+    partials left in the workspace for adr_decode_merge."""
+    b = make(61 + d, G * Hkv, Hkv, d, EDGES, page_size)
+    scales = ()
+    if fp8:
+        b.k_cache, ks = W.quantize_pool_fp8(b.k_cache, b.used)
+        b.v_cache, vs = W.quantize_pool_fp8(b.v_cache, b.used)
+        scales = (ks, vs)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache), *map(dev, scales))
+    bound, shape = int(b.seq_lens.max()), b.q.shape
+    flags = adr.PARTIALS_ONLY if apart else adr.SINGLE_PARTITION_ITEMS
+    assert adr.adr_decode_kernel_choice(cache, shape[0], shape[1], bound, partition_tokens, flags) == adr.KERNEL_MFMA_GRID
+    out = torch.full(shape, float("nan"), device="cuda:0")
+    lse = torch.full(shape[:2], float("nan"), device="cuda:0")
+    ws = torch.full((adr.adr_decode_workspace_bytes(*shape, bound, partition_tokens) // 4,), float("nan"), device="cuda:0")
+    say("callers' partitions d=%d fp8=%s part=%d page=%d apart=%s" % (d, fp8, partition_tokens, page_size, apart))
+    table, lens = dev(b.block_table), dev(b.seq_lens)
+    adr.adr_decode_attention(out, dev(b.q), cache, table, lens, b.wl.scale, bound, partition_tokens, ws, lse, flags)
+    if apart:
+        adr.adr_decode_merge(out, lens, bound, partition_tokens, ws, lse)
+    torch.cuda.synchronize()
+    ref_kw = dict(k_scale=W.bits(scales[0]), v_scale=W.bits(scales[1])) if fp8 else {}
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale, **ref_kw)
+    assert compare(out, lse, ref, ref_lse, what="callers' partitions")[0] <= ATOL
+    written = int((~torch.isnan(ws[:-64 * 2])).sum()) / (shape[1] * (d + 1))      # rows of one partition go to `out`
+    counts = -(-b.seq_lens // partition_tokens)
+    assert written == counts[counts > 1].sum()
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", VARIANTS[1:])
+def test_debug_build_records_out_of_range_entries(d, G, Hkv, fp8):
+    b = make(67, G * Hkv, Hkv, d, [40, 41, 201])
+    table = b.block_table.copy()
+    table[1, 0] = -5                               # clamps to page 0
+    table[2, 3] = len(b.k_cache) + 1000            # clamps to the last page
+    k, v, kw = b.k_cache, b.v_cache, {}
+    if fp8:
+        every = np.ones(len(b.k_cache), dtype=bool)    # (the clamped pages are read)
+        k, ks = W.quantize_pool_fp8(b.k_cache, every)
+        v, vs = W.quantize_pool_fp8(b.v_cache, every)
+        kw = dict(k_scale=dev(ks), v_scale=dev(vs))
+    args = (dev(b.q), dev(k), dev(v), dev(table), dev(b.seq_lens), b.wl.scale)
+    say("debug build d=%d fp8=%s" % (d, fp8))
+    release, release_lse = gpu_attention(*args, partition_tokens=64, **kw)
+    with adr.debug_library():
+        adr.adr_debug_bounds_status(reset=True)
+        debug, debug_lse = gpu_attention(*args, partition_tokens=64, **kw)
+        rec = adr.adr_debug_bounds_status(reset=True)
+        assert rec["kind"] == 1 and rec["count"] >= 2
+        assert (rec["row"], rec["index"], rec["value"]) in ((1, 0, -5), (2, 3, len(b.k_cache) + 1000))
+        clean = dev(np.clip(table, 0, len(b.k_cache) - 1).astype(np.int32))
+        again, _ = gpu_attention(*args[:3], clean, *args[4:], partition_tokens=64, **kw)
+        assert adr.adr_debug_bounds_status()["count"] == 0
+    assert torch.equal(release, debug) and torch.equal(release_lse, debug_lse) and torch.equal(release, again)
