@@ -64,7 +64,8 @@ enum {
                             pass that merges may cut the rows coarser or finer than
                             partition_tokens, within the same workspace; the result is the same
                             up to the order of the floating-point sums, and the choice depends on
-                            the arguments alone */
+                            the arguments alone, B and max_seq_len among them: a row's last bits may
+                            differ between batches of other sizes or under other bounds */
     ADR_KERNEL_VALU = 1, /* vector-ALU dot products: d in {64, 128}, G in {1, 2, 4, 8} */
     ADR_KERNEL_MFMA = 2, /* matrix-core QK^T and PV (d = 128): resident workgroups pulling
                             (request, partition, kv-head) items; batches of more than 512 rows
@@ -96,13 +97,18 @@ enum {
     ADR_WORKSPACE_READY = 64,
     /* Test aid: the resident matrix-core kernel's waits on other waves expire at once, as if its
      * hand-shakes were broken.  Every kernel still runs to its end; the call's rows come back as
-     * NaN and adr_decode_read_status reports the expired waits. */
+     * NaN and adr_decode_read_status reports the expired waits.  The other kernels have no such
+     * waits, so with ADR_KERNEL_AUTO the flag also changes the choice: an fp8 cache and split bf16
+     * passes in groups of up to four heads (or of many pairs or partitions) take the resident
+     * kernel, and a call it does not serve runs as without the flag. */
     ADR_DEBUG_EXPIRE_WAITS = 128
 };
 /* Bits 16..27 of `flags`: size the resident kernel's grid for n compute units (1..4095) instead
  * of asking the stream for its compute-unit mask.  Needed while a graph is being recorded for a
  * masked stream: a recording stream cannot be asked, and the grid is then sized for the whole
- * chip. */
+ * chip.  The other kernels' workgroups are dealt out inside the mask by the hardware, whatever
+ * their number; a caller that wants a pass on an unmasked stream held to n units names the
+ * resident kernel (ADR_KERNEL_MFMA). */
 #define ADR_GRID_CUS(n) (((unsigned)(n) & 0xFFFu) << 16)
 
 /* The paged KV cache of ONE layer ("cache blocks", Sec. 3.2.1).  K and V are
@@ -172,8 +178,8 @@ size_t adr_decode_workspace_bytes(int B, int Hq, int d, int max_seq_len, int par
  *
  * Page ids are clamped into [0,num_pages) before use; table entries past
  * ceil(seq_len/page_size) are never dereferenced.  Results are bit-identical
- * from run to run for fixed inputs, partition_tokens and flags, and do not
- * depend on where pages sit in the pool.
+ * from run to run for fixed inputs and arguments, and do not depend on where
+ * pages sit in the pool.
  */
 int adr_decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q,
                          int64_t q_row_stride, const adr_kv_cache *cache,

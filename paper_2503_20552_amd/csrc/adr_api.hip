@@ -276,7 +276,9 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // fp8: one workgroup per item throughout (us per step, one workgroup per item and resident ones: 256
     // requests x 8 kv-heads of median length 1500 226 and 240, of median 1000 154 and 168, of 3000 tokens
     // 288 and 300, of 300 49 and 71; groups of two 211 and 232, of eight 244 and 326; whole rows 256
-    // and 405; 512 requests of median 1500 the same, 442).
+    // and 405; 512 requests of median 1500 the same, 442).  One shape is the other way round, 512 requests in
+    // groups of four of which one in ten has 32000 to 65000 tokens (1.01 and 0.98 ms); heavy-tailed lengths
+    // under the same bound are not (162 and 177), and the arguments do not tell the two apart.
     bool resident = !fp8 && splits && pairs >= (G == 1 ? 4096 : 2048) && max_seq_len > 2048;
     // The test aid is about the resident kernel's waits: where it is asked for, that kernel serves.
     if (flags & ADR_DEBUG_EXPIRE_WAITS)
@@ -285,7 +287,8 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
         return KERNEL_STREAM;
     // d = 64, two kv-heads a row: ahead of the vector ALUs in groups of two heads or more (us, 2040 against 2048
     // pairs of median length 1500, fp8: groups of eight 128 and 446; bf16 of eight 214 and 436, of four 206
-    // and 239; four requests of 300 tokens in groups of four 9 and 12) and in large passes of groups of one (fp8
+    // and 239; four requests of 300 tokens in groups of four 9 and 12; small fp8 passes in groups of two 5 %
+    // behind, large ones 20 % ahead) and in large passes of groups of one (fp8
     // 113 and 207, bf16 195 and 223).  Small passes of groups of one are the vector ALUs': with few
     // items a workgroup's own chain of steps is all there is, and theirs is shorter (four requests x 8
     // kv-heads of up to 512 tokens 10.2 and 8.6, fp8 11.8 and 9.4; one of 2000 in partitions of 512 12.9

@@ -18,12 +18,13 @@
 // row of d = 128.  An item is both heads; their query heads fill the columns of one tile, the first
 // kv-head's in columns 0 .. G-1, contracted with chunks 0 .. 7 of a row, the second's in columns
 // G .. 2G-1, contracted with chunks 8 .. 15.  P V is taken over the whole row and each head keeps its
-// half.  (113 against 121 us for the vector-ALU kernel at 128 requests, 8 kv-heads, G = 4.)
+// half.  (113 against 121 us for the vector-ALU kernel at 128 requests, 8 kv-heads, G = 4; small
+// passes of groups of one are that kernel's.)
 //
 // fp8 cache: two tiles a step, K and V both by direct-to-LDS loads into one stage of 8 KB per wave, which
 // is copied to registers and refilled at once; K is widened to bf16 after the LDS read and meets the
-// query as it is (exact: error against 64 bits 2.7e-6, the resident kernel's two-term fp8 query
-// 1.6e-5), V comes out of the LDS transposed (mfma_fp8.h).  The scales of a wave's pages arrive with
+// query as it is (exact: error against 64 bits 5e-6, the resident kernel's two-term fp8 query
+// 1.7e-5), V comes out of the LDS transposed (mfma_fp8.h).  The scales of a wave's pages arrive with
 // one gather per sixty-four tiles, not page by page.  Measured against the resident kernel, which
 // served fp8 before: 9 against 37 us at one request of 2000 tokens, 35 against 60 at 40 requests,
 // 130 against 146 at 128, 53 against 79 with groups of eight; heads of 64 (before: vector ALUs)

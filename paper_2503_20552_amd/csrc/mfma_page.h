@@ -1,7 +1,9 @@
-// Pieces shared by the two matrix-core decode kernels (d = 128, bf16 cache):
-// per-page buffer descriptors, the K tile's LDS layout, and the per-page
-// arithmetic S = K Q^T -> online softmax -> O += P V.  See decode_mfma.hip for
-// the operand layouts.
+// Pieces shared by the two matrix-core decode kernels: per-page buffer
+// descriptors, the running state of a wave and the widening of fp8, for every cache; the
+// K tile's LDS layout, its loads and the per-page arithmetic S = K Q^T -> online
+// softmax -> O += P V, for a bf16 cache and rows of 128 elements (one head, or two of
+// 64).  The fp8 counterparts are in mfma_fp8.h and the kernels.  See decode_mfma.hip
+// for the operand layouts.
 #pragma once
 
 #include "adr_device.h"
