@@ -188,20 +188,23 @@ def main():
             pos, seq = st["positions"][s], st["seq_lens"][s]
         kf = flags if kernel_flags is None else kernel_flags
         for li, cache in enumerate(st["caches"]):
-            if events is None and not args.separate_append:
+            if not args.separate_append:
                 # append and attention in one call (the token index is seq - 1 = pos)
+                if events is not None:
+                    events.append(tuple(torch.cuda.Event(enable_timing=True) for _ in range(2)))
+                    events[-1][0].record()
                 adr.adr_decode_step(out, st["q"], st["k_new"], st["v_new"], cache, st["table"], seq, wl.scale,
                                     st["max_len"], part, ws, None, kf)
+                if events is not None:
+                    events[-1][1].record()
                 continue
             adr.adr_kv_append(cache, st["k_new"], st["v_new"], st["table"], pos)
             if events is None:
                 adr.adr_decode_attention(out, st["q"], cache, st["table"], seq, wl.scale, st["max_len"],
                                          part, ws, None, kf)
-            else:   # the kernels of adr_decode_step in the same order, with events around the attention pass: the partition
-                # kernel and the merge together, since a call that keeps its partials apart (ADR_PARTIALS_ONLY)
-                # cuts the rows in another way.  (The workspace's control area is clear: every earlier call
-                # left it so, which saves the attention call a clearing kernel, as the append does inside
-                # adr_decode_step.)
+            else:   # events around the attention call: the partition kernel and the merge together, since a call
+                # that keeps its partials apart (ADR_PARTIALS_ONLY) cuts the rows in another way.  (The workspace's
+                # control area is clear: every earlier call left it so, which saves the call a clearing kernel.)
                 e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
                 e0.record()
                 adr.adr_decode_attention(out, st["q"], cache, st["table"], seq, wl.scale, st["max_len"],
@@ -237,7 +240,7 @@ def main():
     kv_bytes = attended_tokens * bytes_per_token
     value = kv_bytes / elapsed / 1e9
 
-    # the same K steps again, instrumented: HIP events on the launch stream around each attention pass
+    # the same K steps again, instrumented: HIP events on the launch stream around each layer's call
     events = []
     for s in range(Wm, Wm + K):
         one_step(s, events)
@@ -246,8 +249,8 @@ def main():
     bytes_per_launch = kv_bytes / (layers * K)
     achieved = bytes_per_launch / (attn_ms.mean() * 1e-3) / 1e9
     # the library says which kernel it runs for this shape
-    kernel_name = adr.adr_kernel_name(adr.adr_decode_kernel_choice(st["caches"][0], wl.B, wl.Hq, st["max_len"],
-                                                                   part, flags))
+    choice = adr.adr_decode_kernel_choice if args.separate_append else adr.adr_decode_step_kernel_choice
+    kernel_name = adr.adr_kernel_name(choice(st["caches"][0], wl.B, wl.Hq, st["max_len"], part, flags))
     traffic, traffic_source = None, None
     default_shape = layers == wl.layers and part == wl.partition_tokens and not args.length_bound
     entry = MEASURED_TRAFFIC_BYTES.get((wl.ident, kernel_name, "fp8") if fp8 else (wl.ident, kernel_name))
@@ -256,11 +259,12 @@ def main():
     roofline = {"bound": "hbm", "kernel": kernel_name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "traffic_source": traffic_source,
-                "timed": "the kernel and the merge behind it", "avg_pass_ms": round(float(attn_ms.mean()), 5),
+                "timed": "adr_decode_attention" if args.separate_append else "adr_decode_step, the append kernel included",
+                "avg_pass_ms": round(float(attn_ms.mean()), 5),
                 "median_pass_ms": round(float(np.median(attn_ms)), 5), "launches": int(len(attn_ms)),
                 "algorithmic_bytes_per_launch": int(bytes_per_launch)}
-    log("attention pass (partition kernel and merge) %.4f ms avg (min %.4f, max %.4f)" % (
-        attn_ms.mean(), attn_ms.min(), attn_ms.max()))
+    log("attention pass (%s) %.4f ms avg (min %.4f, max %.4f)" % (
+        roofline["timed"], attn_ms.mean(), attn_ms.min(), attn_ms.max()))
 
     corun = None
     if not args.no_corun and not fp8 and wl.d == 128:

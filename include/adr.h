@@ -64,8 +64,10 @@ enum {
                             pass that merges may cut the rows coarser or finer than
                             partition_tokens, within the same workspace; the result is the same
                             up to the order of the floating-point sums, and the choice depends on
-                            the arguments alone, B and max_seq_len among them: a row's last bits may
-                            differ between batches of other sizes or under other bounds */
+                            the arguments alone, B and max_seq_len among them, in large batches (see
+                            adr_decode_step) the cut on all lengths of the batch: a row's last bits
+                            may differ between batches of other sizes or lengths or under other
+                            bounds */
     ADR_KERNEL_VALU = 1, /* vector-ALU dot products: d in {64, 128}, G in {1, 2, 4, 8} */
     ADR_KERNEL_MFMA = 2, /* matrix-core QK^T and PV (d = 128): resident workgroups pulling
                             (request, partition, kv-head) items; batches of more than 512 rows
@@ -160,7 +162,8 @@ size_t adr_decode_workspace_bytes(int B, int Hq, int d, int max_seq_len, int par
  * t over the first seq_lens[b] cached tokens of request b, K_t/V_t taken from
  * kv-head h/G (Sec. 2.1 step (2); the kernel the executor of Sec. 3.1 runs).
  *
- *   out        [B][Hq][d], bf16 or fp32 (out_dtype), contiguous.
+ *   out        [B][Hq][d], bf16 or fp32 (out_dtype), contiguous.  Holds counters of the call
+ *              before it holds the result (not where it overlaps q or the new tokens).
  *   lse        optional fp32 [B][Hq]: natural-log log-sum-exp of the scaled scores.
  *   q          bf16 [B][Hq][d], request rows q_row_stride ELEMENTS apart.
  *   seq_lens   int32 [B]: tokens attended (the length AFTER the append, so the
@@ -221,6 +224,14 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  *   k_new, v_new  bf16 [B][Hkv][d], rows new_row_stride ELEMENTS apart (views into the grouped
  *                 q|k|v buffer are fine), 16-byte aligned; read only.
  *   everything else as in adr_decode_attention; seq_lens is the length AFTER the append.
+ *
+ * In a split pass of 768 (request, kv-head) pairs or more (pairs of kv-heads where d = 64) and at
+ * most 2048 requests, under ADR_KERNEL_AUTO and with at least four partitions allowed, the append
+ * kernel also orders the requests by length and cuts them by the tokens the batch really has, and
+ * one workgroup per item serves them in that order, also where adr_decode_attention takes the
+ * resident kernel (which ADR_KERNEL_MFMA names; ADR_GRID_CUS keeps it, too): `out` then equals the
+ * two calls' up to the order of the floating-point sums.  adr_decode_attention plans such passes
+ * the same where it would take one workgroup per item anyway.
  *
  * The append kernel runs first, then the attention kernels, all on `stream`; the call saves the
  * caller the positions array (it is seq_lens - 1) and one trip through the binding.  k_new /
@@ -414,11 +425,15 @@ int adr_stream_fault_count(uint64_t *count);
 /*
  * Which kernel a pass of this shape and these flags runs on: ADR_KERNEL_VALU, ADR_KERNEL_MFMA
  * (the resident matrix-core kernel) or ADR_KERNEL_MFMA_GRID, or minus an adr_status when the
- * arguments are rejected.  The same decision adr_decode_attention takes.  adr_kernel_name gives
+ * arguments are rejected.  The same decision adr_decode_attention takes;
+ * adr_decode_step_kernel_choice tells adr_decode_step's (an `out` that overlaps q or the new tokens
+ * left aside: such a call runs as adr_decode_attention's).  adr_kernel_name gives
  * the kernel's name as profilers show it (without template arguments); "" for other values.
  */
 int adr_decode_kernel_choice(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int partition_tokens,
                              unsigned flags);
+int adr_decode_step_kernel_choice(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int partition_tokens,
+                                  unsigned flags);
 const char *adr_kernel_name(int kernel);
 
 /*

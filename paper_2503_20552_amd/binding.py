@@ -35,7 +35,7 @@ EXPORTS = ("adr_kv_append", "adr_decode_workspace_bytes", "adr_decode_attention"
            "adr_decode_step",
            "adr_decode_merge", "adr_lse_merge", "adr_probe_stream_read", "adr_probe_copy",
            "adr_stream_create_cu_mask", "adr_stream_destroy", "adr_stream_fault_count",
-           "adr_decode_read_status", "adr_decode_kernel_choice", "adr_kernel_name", "adr_debug_bounds_status",
+           "adr_decode_read_status", "adr_decode_kernel_choice", "adr_decode_step_kernel_choice", "adr_kernel_name", "adr_debug_bounds_status",
            "adr_offload_bound_mem", "adr_offload_bound_comp", "adr_offload_bound", "adr_need_offload",
            "adr_graph_capacity", "adr_pack_qkv", "adr_scatter_rows",
            "adr_graph_table_create", "adr_graph_table_capacity", "adr_graph_table_launch", "adr_graph_table_destroy",
@@ -201,6 +201,8 @@ def _declare(lib):
     lib.adr_decode_read_status.argtypes = [vp, sz, i32, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_uint32)]
     lib.adr_decode_kernel_choice.restype = i32
     lib.adr_decode_kernel_choice.argtypes = [ctypes.POINTER(_CCache), i32, i32, i32, i32, u32]
+    lib.adr_decode_step_kernel_choice.restype = i32
+    lib.adr_decode_step_kernel_choice.argtypes = lib.adr_decode_kernel_choice.argtypes
     lib.adr_kernel_name.restype = ctypes.c_char_p
     lib.adr_kernel_name.argtypes = [i32]
     lib.adr_debug_bounds_status.restype = i32
@@ -331,6 +333,16 @@ def adr_decode_kernel_choice(cache: "KVCache", B: int, Hq: int, max_seq_len: int
                                                  int(flags))
     if rc < 0:
         raise AdrError(-rc, "adr_decode_kernel_choice")
+    return int(rc)
+
+
+def adr_decode_step_kernel_choice(cache: "KVCache", B: int, Hq: int, max_seq_len: int, partition_tokens: int,
+                                  flags: int = KERNEL_AUTO) -> int:
+    cs = cache.c_struct()
+    rc = load_library().adr_decode_step_kernel_choice(ctypes.byref(cs), B, Hq, int(max_seq_len), int(partition_tokens),
+                                                      int(flags))
+    if rc < 0:
+        raise AdrError(-rc, "adr_decode_step_kernel_choice")
     return int(rc)
 
 

@@ -3,12 +3,14 @@
 // readers at the end synchronise; that is what they are for.)
 #include "../../include/adr.h"
 #include "adr_device.h"
+#include "plan.h"
 
 #include <algorithm>
 #include <atomic>
 
 namespace adr {
 hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream);
+hipError_t launch_plan(const PlanParams &p, const MeetWords &meet, int B, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t launch_decode_stream(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
@@ -16,6 +18,7 @@ hipError_t read_stream_faults(unsigned long long *count);
 bool decode_stream_supports(int d, int G, int B);
 bool decode_valu_supports(int d, int G);
 bool decode_mfma_supports(int d, int G, int Hkv);
+int merge_slices(int64_t rows, int max_parts);
 hipError_t launch_lse_merge(const MergeParams &p, hipStream_t stream);
 hipError_t launch_stream_read(const void *src, size_t bytes, void *sink, hipStream_t stream);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t stream);
@@ -79,6 +82,12 @@ __global__ void control_clear_kernel(uint32_t *words, int n)
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x)
         words[i] = 0u;
+}
+
+// Do `a` and `b` share a byte?
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
 
 // ---- per-device addresses of this file's static device data -------------------------------
@@ -221,6 +230,8 @@ int adr_kv_append(const adr_kv_cache *cache, const void *k_new, const void *v_ne
     p.B = B;
     p.clear_words = nullptr;
     p.n_clear_words = 0;
+    p.meet.out = nullptr;
+    p.plan.items = nullptr;
     if (bounds_record(&p.bounds) != ADR_OK)
         return ADR_ERR_LAUNCH;
     const hipError_t e =
@@ -365,6 +376,32 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
     return cut;
 }
 
+// Is a split pass planned on the device (plan.h), and served by one workgroup per item then?  Where there are
+// at least as many rows as the chip holds workgroups: us a step, in the batch's order and planned, 256 requests x 8
+// kv-heads of median length 1500 406 (the resident kernel) and 379, fp8 223 and 208, of 3000 tokens 525 and 498, 160 of
+// up to 3000 178 and 163, 128 of heavy-tailed lengths 78 and 69, 1500 of median 200 408 and 350; with 296 to 600
+// rows the two are within 2 % either way (49.0 and 49.5, 110.4 and 111.5, 125.5 and 126.5, fp8 57 and 61).
+// The list takes the place of one partition per row, so that there must be some.
+// Without an append kernel to plan on its way a kernel of its own does, and passes for the resident kernel stay
+// with it (adr_decode_kernel_choice).
+bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B, int Hq, int max_seq_len,
+               int partition_tokens, unsigned flags, bool step)
+{
+    p.items = nullptr;
+    const int H = cache->d == 64 ? cache->Hkv / 2 : cache->Hkv;
+    const int64_t max_parts = max_parts_for(max_seq_len, partition_tokens);
+    if (kernel == KERNEL_VALU || (kernel == KERNEL_STREAM && (!step || (flags >> 16))) ||
+        (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_DEBUG_EXPIRE_WAITS)) ||
+        B > 2048 || (int64_t)B * H < adr::kSlots || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
+        return false;
+    p.heads_per_slot = (float)H / adr::kSlots;
+    p.B = B;
+    p.max_seq_len = max_seq_len;
+    p.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
+    p.max_items = (int)adr::plan_places(B, H, max_seq_len);
+    return (size_t)p.max_items * sizeof(adr::u32x4) <= (size_t)B * Hq * cache->d * sizeof(float);
+}
+
 constexpr unsigned kFlagBits = 0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_WORKSPACE_READY |
                                ADR_DEBUG_EXPIRE_WAITS | (0xFFFu << 16);
 
@@ -403,7 +440,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     const int G = Hq / cache->Hkv;
     const int d = cache->d;
     const bool fp8 = cache->dtype == ADR_FP8_E4M3;
-    const int kernel = choose_kernel(cache, B, Hq, max_seq_len, partition_tokens, flags);
+    int kernel = choose_kernel(cache, B, Hq, max_seq_len, partition_tokens, flags);
     if (kernel < 0)
         return -kernel;
     const int64_t max_parts = max_parts_for(max_seq_len, partition_tokens);
@@ -431,8 +468,38 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         return ADR_ERR_WORKSPACE;
     if (B == 0)
         return ADR_OK;
-    const PassCut cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
-    split = split && cut.max_parts > 1;
+    // One workgroup per item: the wave that brings a row's last partition may merge it (decode_mfma.hip).  The arrivals
+    // are counted in `out`, which must not be an input then (an executor may well attend in place).
+    adr::MeetWords meet = {out, Hq, d * (out_dtype == ADR_F32 ? 4 : 2)};
+    const size_t out_bytes = (size_t)B * Hq * meet.stride;
+    bool meets = split && !(flags & ADR_PARTIALS_ONLY) &&
+                 !overlap(out, out_bytes, q, ((size_t)(B - 1) * q_row_stride + (size_t)Hq * d) * 2);
+    if (nt && meets) {
+        const size_t new_bytes = ((size_t)(B - 1) * nt->row_stride + (size_t)cache->Hkv * d) * 2;
+        meets = !overlap(out, out_bytes, nt->k, new_bytes) && !overlap(out, out_bytes, nt->v, new_bytes);
+    }
+    PassCut cut;
+    adr::PlanParams list;
+    list.items = nullptr;
+    if (meets && plan_pass(list, cache, kernel, B, Hq, max_seq_len, partition_tokens, flags, nt != nullptr)) {
+        kernel = KERNEL_GRID;
+        cut = {partition_tokens, list.max_parts, 0, 0};
+        list.items = (adr::u32x4 *)((char *)workspace + (size_t)B * list.max_parts * Hq * d * sizeof(float));
+        list.seq_lens = seq_lens;
+    } else {
+        cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
+        split = split && cut.max_parts > 1;
+        // Without a plan, where an append kernel clears the words on its way and the chip holds all items at once: an
+        // item of a split row keeps its place until its results are in memory and counted, 3 us with the
+        // memory busy, and elsewhere others wait for that place (us a step, merged by a kernel of its own and
+        // inside: one request of 2000 tokens 10.1 and 9.5, of 8000 13.7 and 13.0; 37 of median 1000 51.2 and 54.5, fp8 256 of
+        // 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
+        // (24 of them: 15.2 and 15.7, three rows of 24 33.5 and 36.9).
+        meets = meets && split && nt && kernel == KERNEL_GRID && cut.max_parts <= 16 &&
+                (int64_t)B * cache->Hkv * cut.max_parts <= adr::kSlots;
+    }
+    if (!meets)
+        meet.out = nullptr;
 
     adr::DecodeParams p;
     p.q = (const uint16_t *)q;
@@ -482,6 +549,10 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     const bool clear_ahead = clear_control && kernel == KERNEL_STREAM;
     p.clear_words = clear_control && !clear_ahead ? plan.control_words() : 0;
 
+    p.meet = !meets ? 0 : list.items ? 1 : adr::merge_slices((int64_t)B * Hq, cut.max_parts);
+    p.items = list.items;
+    p.max_items = list.items ? list.max_items : 0;
+
     // The new token goes in first: the append kernel, with the token index taken from seq_lens.
     if (nt) {
         adr::AppendParams ap;
@@ -504,6 +575,8 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         ap.B = B;
         ap.clear_words = clear_ahead ? p.control : nullptr; // on its way, for the kernels behind it
         ap.n_clear_words = clear_ahead ? plan.control_words() : 0;
+        ap.meet = meet;
+        ap.plan = list;
         ap.bounds = p.bounds;
         if (adr::launch_kv_append(ap, fp8, (hipStream_t)stream) != hipSuccess)
             return ADR_ERR_LAUNCH;
@@ -511,13 +584,16 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         control_clear_kernel<<<1, 64, 0, (hipStream_t)stream>>>(p.control, plan.control_words());
         if (hipGetLastError() != hipSuccess)
             return ADR_ERR_LAUNCH;
+    } else if (meets) {
+        if (adr::launch_plan(list, meet, B, (hipStream_t)stream) != hipSuccess)
+            return ADR_ERR_LAUNCH;
     }
     hipError_t e = kernel == KERNEL_STREAM ? adr::launch_decode_stream(p, d, fp8, (hipStream_t)stream)
                    : kernel == KERNEL_GRID ? adr::launch_decode_mfma(p, d, fp8, (hipStream_t)stream)
                                            : adr::launch_decode_valu(p, d, fp8, (hipStream_t)stream);
     if (e != hipSuccess)
         return ADR_ERR_LAUNCH;
-    if (split && !(flags & ADR_PARTIALS_ONLY)) {
+    if (split && !meets && !(flags & ADR_PARTIALS_ONLY)) {
         adr::MergeParams mp;
         mp.out = out;
         mp.lse_out = lse;
@@ -661,6 +737,14 @@ int adr_decode_kernel_choice(const adr_kv_cache *cache, int B, int Hq, int max_s
     if (B < 0 || Hq <= 0 || Hq % cache->Hkv != 0 || max_seq_len < 0 || partition_tokens < 0)
         return -ADR_ERR_SHAPE;
     return choose_kernel(cache, B, Hq, max_seq_len, partition_tokens, flags);
+}
+
+int adr_decode_step_kernel_choice(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int partition_tokens,
+                                  unsigned flags)
+{
+    const int kernel = adr_decode_kernel_choice(cache, B, Hq, max_seq_len, partition_tokens, flags);
+    adr::PlanParams list;
+    return kernel > 0 && plan_pass(list, cache, kernel, B, Hq, max_seq_len, partition_tokens, flags, true) ? (int)KERNEL_GRID : kernel;
 }
 
 const char *adr_kernel_name(int kernel)

@@ -74,6 +74,9 @@ struct DecodeParams {
     int clear_words;      // of `control`, zeroed by a kernel that does not use it (clear_control)
     int spin_limit;       // polls before a wait on another wave is declared failed
     int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
+    int meet;             //   > 0: the last partition of a row to arrive merges it, in that many slices (arrivals are counted in `out`)
+    const u32x4 *items;   //   its items in the order they are to be taken (plan.h), or nullptr: by row and stride
+    int max_items;        //     places in `items`
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
     BoundsRecord *bounds; // debug builds: where out-of-range entries are recorded (else nullptr)
 };
@@ -93,6 +96,26 @@ struct MergeParams {
                                  // its expired-waits word is not zero every row gets NaN
 };
 
+// Where a split pass counts the partitions of a row that have arrived: the first word of each head's row of `out`, which
+// the wave that merges the row overwrites at last.  Zeroed ahead of the attention kernel.
+struct MeetWords {
+    void *out;       // or nullptr: nothing is counted
+    int heads, stride; // heads of a request, bytes of a head's row
+};
+__device__ __forceinline__ void clear_meet_words(const MeetWords &m, int b)
+{
+    for (int i = threadIdx.x; i < m.heads; i += blockDim.x)
+        *(uint32_t *)((char *)m.out + ((int64_t)b * m.heads + i) * m.stride) = 0u;
+}
+
+// Where and from what a pass's items are planned (plan.h).
+struct PlanParams {
+    u32x4 *items; // [max_items], or nullptr: nothing to plan
+    const int32_t *seq_lens;
+    int B, max_seq_len, max_parts, max_items;
+    float heads_per_slot; // kv-heads (pairs of them) by the workgroups the chip holds
+};
+
 struct AppendParams {
     void *k_cache, *v_cache;
     float *k_scale, *v_scale;
@@ -106,6 +129,8 @@ struct AppendParams {
     int max_pages, num_pages, page_size, Hkv, d, B;
     uint32_t *clear_words; // control area the first workgroup clears on its way (adr_decode_step), or nullptr
     int n_clear_words;
+    MeetWords meet;        // of the attention pass behind this append
+    PlanParams plan;       // the attention pass behind this append, where it is planned
     BoundsRecord *bounds;  // debug builds only
 };
 
@@ -291,11 +316,10 @@ __device__ __forceinline__ int row_partition(int L, int partition_tokens, int ma
 // and nothing of this call reads it.  (At the kernel's start every workgroup without a partition would pay for
 // the question, 84 against 79 us with 64 K of them, and in the append kernel it stands ahead of the
 // look-up of the position: 11.9 against 11.4 us for a step of one request.)
-__device__ __forceinline__ void clear_control(const DecodeParams &p)
+__device__ __forceinline__ void clear_control(uint32_t *control, int words)
 {
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < p.clear_words; i += blockDim.x)
-            p.control[i] = 0u;
+    for (int i = threadIdx.x; i < words; i += blockDim.x)
+        control[i] = 0u;
 }
 
 // Combine the kWaves per-wave partial results staged in LDS and write either

@@ -58,8 +58,10 @@
 //       set e is assembled from those four registers with byte permutes.
 //       Result layout: lane (r, j) holds O[head 4j+i][8r + e].
 #include "mfma_fp8.h"
+#include "plan.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace adr {
 
@@ -92,6 +94,8 @@ static int grid_stride(int64_t rows, int max_parts)
     const int n = (int)std::min<int64_t>(max_parts, most);
     return n > 1 ? (n | 1) : n;
 }
+
+constexpr int kNoMore = 1 << 20; // added to a partition's number: past any row's last
 
 constexpr int kChiplets = 8; // of the GPU; the hardware deals workgroups out to them in turn
 
@@ -268,8 +272,159 @@ __device__ __forceinline__ void attend_two_fp8(WaveState &st, float (&sc)[8], u3
     }
 }
 
-template <bool FP8, bool PAIR, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2)))
+// Where a workgroup's item comes from and where the partitions of a split row meet.  Variants of their own, because
+// what one of them needs costs the others scalar registers: with all in one kernel a step of one
+// request took 10.6 us instead of 10.1.
+enum class Items {
+    by_row,      // numbered by row and stride; the partitions are merged by a kernel of its own
+    by_row_meet, // numbered the same; the wave that brings a row's last partition merges it
+    planned      // listed (plan.h), merged the same
+};
+
+// The kernel's argument block, read where it is asked for: what a partition's end needs of the parameters does not
+// occupy scalar registers through the loop over its tiles (held from the start they did not fit where rows
+// meet: 25 to 60 of them went through vector lanes, 0.5 to 1 us per launch).
+typedef const __attribute__((address_space(4))) DecodeParams *LateParams;
+template <Items ITEMS>
+__device__ __forceinline__ LateParams late_params()
+{
+    LateParams p = (LateParams)__builtin_amdgcn_kernarg_segment_ptr();
+    if (ITEMS != Items::by_row)
+        asm volatile("" : "+s"(p));
+    return p;
+}
+
+// ---- merging a split row inside the pass -----------------------------------------------------------
+
+// Partial results that another workgroup reads in the same launch: written through to, and read from, the
+// memory all chiplets see (sc1, device scope), so that neither side has to write back or invalidate
+// an L2.
+constexpr int kDeviceScope = 16;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(const float *base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7fffffff, 0x00020000);
+}
+__device__ __forceinline__ void store_shared(f32x4 x, __amdgpu_buffer_rsrc_t rsrc, int offset)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rsrc, offset, 0, kDeviceScope);
+}
+__device__ __forceinline__ f32x4 load_shared(__amdgpu_buffer_rsrc_t rsrc, int offset)
+{
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, kDeviceScope));
+}
+
+// One wave's end of a partition of a split row.  In every partition's workgroup wave w holds the same elements of
+// the row's result (four per thread and round), so the waves of a row meet one by one, without a
+// barrier: a wave waits until its own partial results are in memory and counts itself in; true for the one that
+// finds all others there.  Nobody waits for anybody.  The count lies in the first word of the wave's own
+// elements of `out`, which the merged row overwrites.
+template <int HD>
+__device__ __forceinline__ bool arrive(LateParams p, int b, int first_head, int n_parts)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint32_t before = 0;
+    if ((threadIdx.x & 63) == 0) {
+        const int64_t head = (int64_t)b * p->Hq + first_head + wave * 64 / (HD / 4);
+        before = __hip_atomic_fetch_add((uint32_t *)((char *)p->out + head * HD * (p->out_f32 ? 4 : 2)), 1u, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+    }
+    before = __builtin_amdgcn_readfirstlane(before);
+    asm volatile("" ::: "memory");
+    return before + 1 == (uint32_t)n_parts;
+}
+
+// The wave's share of a row, merged from its partitions in a fixed order, whichever wave it is: in S slices of every
+// S-th partition, CH of a slice loaded together, as lse_merge_kernel does it with S and CH (the same
+// bits).
+template <int HD, int NW, int S, int CH>
+__device__ __forceinline__ void merge_share(LateParams p, int b, int first_head, int heads, int n_parts)
+{
+    constexpr int QUADS = HD / 4;
+    for (int idx = threadIdx.x; idx < heads * QUADS; idx += NW * 64) {
+        const int head = first_head + idx / QUADS;
+        const int c4 = (idx % QUADS) * 4;
+        float top[S], total[S];
+        f32x4 acc[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            top[s] = -INFINITY;
+            total[s] = 0.f;
+            acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i0 = s; i0 < n_parts; i0 += S * CH) {
+                const int64_t row = ((int64_t)b * p->max_parts + i0) * p->Hq;
+                const __amdgpu_buffer_rsrc_t o_rsrc = partial_rsrc(p->part_o + row * HD), lse_rsrc = partial_rsrc(p->part_lse + row);
+                float ls[CH];
+                f32x4 xs[CH];
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    ls[u] = -INFINITY;
+                    xs[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (i0 + u * S < n_parts) {
+                        const int at = u * S * p->Hq + head;
+                        ls[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rsrc, at * 4, 0, kDeviceScope));
+                        xs[u] = load_shared(o_rsrc, (at * HD + c4) * 4);
+                    }
+                }
+                float cm = -INFINITY;
+#pragma unroll
+                for (int u = 0; u < CH; ++u)
+                    cm = fmaxf(cm, ls[u]);
+                const float nt = fmaxf(top[s], cm);
+                if (nt > -INFINITY) {
+                    const float rs = fast_exp2((top[s] - nt) * kLog2e); // 0 when nothing was seen before
+                    acc[s] *= rs;
+                    total[s] *= rs;
+#pragma unroll
+                    for (int u = 0; u < CH; ++u) {
+                        const float w = fast_exp2((ls[u] - nt) * kLog2e);
+                        if (w > 0.f) {
+                            acc[s] += w * xs[u];
+                            total[s] += w;
+                        }
+                    }
+                    top[s] = nt;
+                }
+            }
+        }
+        if constexpr (S > 1) {
+            float all = top[0];
+#pragma unroll
+            for (int s = 1; s < S; ++s)
+                all = fmaxf(all, top[s]);
+            if (all > -INFINITY) {
+                const float w0 = fast_exp2((top[0] - all) * kLog2e);
+                acc[0] *= w0;
+                total[0] *= w0;
+#pragma unroll
+                for (int s = 1; s < S; ++s) {
+                    const float w = fast_exp2((top[s] - all) * kLog2e);
+                    if (w > 0.f) {
+                        acc[0] += w * acc[s];
+                        total[0] += w * total[s];
+                    }
+                }
+                top[0] = all;
+            }
+        }
+        const f32x4 o = acc[0] * (total[0] > 0.f ? 1.f / total[0] : 0.f);
+        const int64_t row = (int64_t)b * p->Hq + head;
+        if (p->out_f32) {
+            *(f32x4 *)((float *)p->out + row * HD + c4) = o;
+        } else {
+            u32x2 packed;
+            packed[0] = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
+            packed[1] = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
+            *(u32x2 *)((uint16_t *)p->out + row * HD + c4) = packed;
+        }
+        if (p->lse && c4 == 0)
+            p->lse[row] = total[0] > 0.f ? top[0] + fast_log2(total[0]) * kLn2 : -INFINITY;
+    }
+}
+
+template <bool FP8, bool PAIR, int NW, Items ITEMS>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2, NW == 4 ? 3 : 8)))
 void decode_mfma_kernel(const DecodeParams p)
 {
     constexpr int HD = PAIR ? D / 2 : D;           // elements of one head
@@ -286,7 +441,7 @@ void decode_mfma_kernel(const DecodeParams p)
     const int j = lane >> 4;
     const bool upper = PAIR && r >= G;
 
-    const int stride = p.grid_stride;
+    const int stride = ITEMS == Items::planned ? kNoMore : p.grid_stride;
     // Which (row of the cache h, partition, request) this workgroup starts with.  Consecutive workgroups go
     // to the eight chiplets in turn.  bf16: kv-heads fastest, so that a page's heads are read side by
     // side by different chiplets.  fp8: the kv-heads of a partition one after the other on one chiplet --
@@ -302,21 +457,34 @@ void decode_mfma_kernel(const DecodeParams p)
         h = blockIdx.x % H;
         unit = blockIdx.x / H;
     }
-    const int first_part = unit % stride;
-    const int b = unit / stride;
-    if (FP8 && b >= p.B)
-        return;
+    typedef const __attribute__((address_space(4))) int32_t *const_ptr;
+    int b, L, pt, first_part, n_parts;
+    if constexpr (ITEMS == Items::planned) {
+        const u32x4 item = ((const __attribute__((address_space(4))) u32x4 *)p.items)[unit];
+        if (item[0] == kNoRow)
+            return;
+        b = item[0];
+        L = item[1];
+        pt = item[2];
+        first_part = item[3] & 0xffffu;
+        n_parts = item[3] >> 16;
+    } else {
+        first_part = unit % stride;
+        b = unit / stride;
+        if (FP8 && b >= p.B)
+            return;
 
-    const int L = max(min(((const __attribute__((address_space(4))) int32_t *)p.seq_lens)[b], p.max_seq_len), 0);
-    // No partition is shorter than `least`: without dividing, most workgroups that have none leave here
-    // (64 K of them: 77 us with the divisions, 65 without).
-    const unsigned least = p.cut > 0 ? p.cut : p.partition_tokens;
-    if (first_part > 0 && first_part * least >= (unsigned)L)
-        return;
-    const int pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut, p.cut_share);
-    const int n_parts = parts_of(L, pt);
-    if (first_part >= n_parts)
-        return;
+        L = max(min(((const_ptr)p.seq_lens)[b], p.max_seq_len), 0);
+        // No partition is shorter than `least`: without dividing, most workgroups that have none leave here
+        // (64 K of them: 77 us with the divisions, 65 without).
+        const unsigned least = p.cut > 0 ? p.cut : p.partition_tokens;
+        if (first_part > 0 && first_part * least >= (unsigned)L)
+            return;
+        pt = row_partition(L, p.partition_tokens, p.max_parts, p.cut, p.cut_share);
+        n_parts = parts_of(L, pt);
+        if (first_part >= n_parts)
+            return;
+    }
     TileIds<NW, FP8, PAIR> ids;
     auto start = [&](int part) { // this wave's tiles of a partition
         const int t0 = part * pt, t1 = pt > 0 ? min(L, t0 + pt) : L;
@@ -476,6 +644,7 @@ void decode_mfma_kernel(const DecodeParams p)
             }
         }
 
+        const LateParams late = late_params<ITEMS>();
         // The wave's share of the result takes the place of its own K tiles (no load is on its way to
         // them any more, and no other wave reads them).  [R][D] floats, R <= 16.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -528,23 +697,36 @@ void decode_mfma_kernel(const DecodeParams p)
             const float lse = den > 0.f ? (M + fast_log2(den)) * kLn2 : -INFINITY;
             const int head = h * R + g;
             if (n_parts == 1) {
-                const int64_t row = (int64_t)b * p.Hq + head;
-                if (p.out_f32) {
-                    *(f32x4 *)((float *)p.out + row * HD + c4) = o;
+                const int64_t row = (int64_t)b * late->Hq + head;
+                if (late->out_f32) {
+                    *(f32x4 *)((float *)late->out + row * HD + c4) = o;
                 } else {
                     u32x2 packed;
                     packed[0] = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
                     packed[1] = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
-                    *(u32x2 *)((uint16_t *)p.out + row * HD + c4) = packed;
+                    *(u32x2 *)((uint16_t *)late->out + row * HD + c4) = packed;
                 }
-                if (p.lse && c4 == 0)
-                    p.lse[row] = lse;
-            } else {
-                const int64_t row = ((int64_t)b * p.max_parts + part) * p.Hq + head;
-                *(f32x4 *)(p.part_o + row * HD + c4) = o;
+                if (late->lse && c4 == 0)
+                    late->lse[row] = lse;
+            } else if (ITEMS != Items::by_row) {
+                const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq;
+                store_shared(o, partial_rsrc(late->part_o + row * HD), (head * HD + c4) * 4);
                 if (c4 == 0)
-                    p.part_lse[row] = lse;
+                    __hip_atomic_store(late->part_lse + row + head, lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq + head;
+                *(f32x4 *)(late->part_o + row * HD + c4) = o;
+                if (c4 == 0)
+                    late->part_lse[row] = lse;
             }
+        }
+        if (ITEMS != Items::by_row && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD>(late, b, h * R, n_parts)) {
+            if (ITEMS == Items::planned)
+                merge_share<HD, NW, 1, 8>(late, b, h * R, R, n_parts);
+            else if (late->meet == 1)
+                merge_share<HD, NW, 1, 16>(late, b, h * R, R, n_parts);
+            else
+                merge_share<HD, NW, 2, 8>(late, b, h * R, R, n_parts);
         }
         part += stride;
         if (part >= n_parts)
@@ -552,7 +734,10 @@ void decode_mfma_kernel(const DecodeParams p)
         start(part);
         __syncthreads(); // the next partition's K tiles go where the per-wave results lie
     }
-    clear_control(p);
+    if (blockIdx.x == 0) {
+        const LateParams late = late_params<ITEMS>();
+        clear_control(late->control, late->clear_words);
+    }
 }
 
 bool decode_mfma_supports(int d, int G, int Hkv);
@@ -565,7 +750,7 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     const bool pair = d == D / 2;
     const int64_t rows = (int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv);
     p.grid_stride = grid_stride(rows, p.max_parts);
-    int64_t units = (int64_t)p.B * p.grid_stride;
+    int64_t units = p.items ? p.max_items : (int64_t)p.B * p.grid_stride;
     if (fp8)
         units = (units + kChiplets - 1) / kChiplets * kChiplets; // (the surplus finds no request)
     const int64_t blocks = units * (rows / p.B);
@@ -580,14 +765,21 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     // and 238, 128 x 8 of up to 8192 260 and 240, heads of 64 202 and 152, fp8 171 and 157; with rows of up
     // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61).
     const bool wide = p.partition_tokens == 0 && p.max_seq_len >= 4096;
-    if (fp8 && pair)
-        wide ? go(decode_mfma_kernel<true, true, 8>, 8) : go(decode_mfma_kernel<true, true, 4>, 4);
-    else if (fp8)
-        wide ? go(decode_mfma_kernel<true, false, 8>, 8) : go(decode_mfma_kernel<true, false, 4>, 4);
-    else if (pair)
-        wide ? go(decode_mfma_kernel<false, true, 8>, 8) : go(decode_mfma_kernel<false, true, 4>, 4);
+    auto pick = [&](auto fp8_, auto pair_) {
+        constexpr bool F = fp8_.value, P = pair_.value;
+        if (wide)
+            go(decode_mfma_kernel<F, P, 8, Items::by_row>, 8);
+        else if (p.items)
+            go(decode_mfma_kernel<F, P, 4, Items::planned>, 4);
+        else if (p.meet)
+            go(decode_mfma_kernel<F, P, 4, Items::by_row_meet>, 4);
+        else
+            go(decode_mfma_kernel<F, P, 4, Items::by_row>, 4);
+    };
+    if (fp8)
+        pair ? pick(std::true_type(), std::true_type()) : pick(std::true_type(), std::false_type());
     else
-        wide ? go(decode_mfma_kernel<false, false, 8>, 8) : go(decode_mfma_kernel<false, false, 4>, 4);
+        pair ? pick(std::false_type(), std::true_type()) : pick(std::false_type(), std::false_type());
     return hipGetLastError();
 }
 

@@ -216,7 +216,8 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
     }
     __syncthreads();
     combine_waves_and_store<D>(p, sm, sl, so, G, b, kvh, part, n_parts);
-    clear_control(p);
+    if (blockIdx.x == 0)
+        clear_control(p.control, p.clear_words);
 }
 
 #define ADR_VALU_CASE(DD, GG)                                                                     \

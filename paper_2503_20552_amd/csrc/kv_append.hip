@@ -1,5 +1,5 @@
 // Append of the decode step's new K/V token into its cache page.
-#include "adr_device.h"
+#include "plan.h"
 
 namespace adr {
 
@@ -10,6 +10,15 @@ __device__ __forceinline__ void clear_control(const AppendParams &p)
     if (p.clear_words && blockIdx.x == 0)
         for (int i = threadIdx.x; i < p.n_clear_words; i += blockDim.x)
             p.clear_words[i] = 0u;
+}
+
+// What the attention kernel behind needs of row b: its items in the pass's plan, and the words it counts a split
+// row's arrivals in.
+template <int T>
+__device__ __forceinline__ void prepare_pass(const PlanParams &plan, const MeetWords &meet, int b)
+{
+    if (meet.out && (!plan.items || plan_row<T>(plan, b) > 1))
+        clear_meet_words(meet, b);
 }
 
 // The page a row's token goes to, or -1 when the row is skipped (a padded row, a position past
@@ -46,6 +55,7 @@ __global__ __launch_bounds__(128) void kv_append_bf16_kernel(const AppendParams 
     const u32x4 k0 = *(const u32x4 *)(p.k_new + src + first);
     const u32x4 v0 = *(const u32x4 *)(p.v_new + src + first);
     clear_control(p);
+    prepare_pass<128>(p.plan, p.meet, b);
     const int pos = append_position(p, b);
     const int page = append_page(p, b, pos, threadIdx.x == 0);
     if (page < 0)
@@ -94,6 +104,8 @@ __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
 {
     const int b = blockIdx.x / p.Hkv, h = blockIdx.x % p.Hkv;
     clear_control(p);
+    if (h == 0)
+        prepare_pass<64>(p.plan, p.meet, b);
     const int pos = append_position(p, b);
     const int page = append_page(p, b, pos, threadIdx.x == 0 && h == 0);
     if (page < 0)
@@ -135,6 +147,18 @@ __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
             dst[lane] = (uint8_t)f32_to_e4m3(x[0] * inv);
         }
     }
+}
+
+// The same ahead of a pass that nothing is appended for.
+__global__ __launch_bounds__(128) void plan_kernel(const PlanParams p, const MeetWords meet)
+{
+    prepare_pass<128>(p, meet, blockIdx.x);
+}
+
+hipError_t launch_plan(const PlanParams &p, const MeetWords &meet, int B, hipStream_t stream)
+{
+    plan_kernel<<<dim3(B), 128, 0, stream>>>(p, meet);
+    return hipGetLastError();
 }
 
 hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream)

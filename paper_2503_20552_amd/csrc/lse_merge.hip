@@ -154,21 +154,26 @@ static void launch_merge(const MergeParams &p, int slices, hipStream_t stream)
         go(lse_merge_kernel<D, 1, 16>, 1);
 }
 
+// Slices per row: one per six partitions a row may have, as long as the blocks this makes (most of
+// them may find a row of few partitions and leave) stay within 256 rows per partition, of which no more
+// than 48 count (a bound far above the lengths allows any number: 8192 rows of one partition, 128
+// allowed, 2.3 us more with four slices than with one).  us, one slice
+// and the rule's: 32 rows of 118 partitions 12.3 and 4.8, 512 rows 14.6 and 6.0, 1280 rows of up to
+// 33 4.8 and 4.1, 4096 rows 6.5 and 6.1; 8192 rows of up to 9 or 33 have one (4.6, 10.6; with
+// four 8.5, 11.2).  adr_lse_merge, which knows no bound, has one.
+int merge_slices(int64_t rows, int max_parts)
+{
+    int slices = 1;
+    while (slices < 8 && slices * 2 * 6 <= max_parts && rows * slices * 2 <= (int64_t)256 * std::min(max_parts, 48))
+        slices *= 2;
+    return slices;
+}
+
 hipError_t launch_lse_merge(const MergeParams &p, hipStream_t stream)
 {
     if ((int64_t)p.B * p.heads == 0)
         return hipSuccess;
-    // Slices per row: one per six partitions a row may have, as long as the blocks this makes (most of
-    // them may find a row of few partitions and leave) stay within 256 rows per partition, of which no more
-    // than 48 count (a bound far above the lengths allows any number: 8192 rows of one partition, 128
-    // allowed, 2.3 us more with four slices than with one).  us, one slice
-    // and the rule's: 32 rows of 118 partitions 12.3 and 4.8, 512 rows 14.6 and 6.0, 1280 rows of up to
-    // 33 4.8 and 4.1, 4096 rows 6.5 and 6.1; 8192 rows of up to 9 or 33 have one (4.6, 10.6; with
-    // four 8.5, 11.2).  adr_lse_merge, which knows no bound, has one.
-    int slices = 1;
-    const int64_t rows = (int64_t)p.B * p.heads;
-    while (slices < 8 && slices * 2 * 6 <= p.max_parts && rows * slices * 2 <= (int64_t)256 * std::min(p.max_parts, 48))
-        slices *= 2;
+    const int slices = merge_slices((int64_t)p.B * p.heads, p.max_parts);
     if (p.d == 128)
         launch_merge<128>(p, slices, stream);
     else if (p.d == 64)

@@ -1,0 +1,191 @@
+"""Passes that are planned on the device (requests ordered by length, cut by the tokens the batch has, rows merged by the
+wave that brings their last partition) and small steps that merge the same way: against the oracle, on workspaces and
+outputs full of NaN, at the edges of the rule, under bounds far above the lengths, and with `out` in q's place."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_20552_amd as adr
+import oracle
+import workloads as W
+from gpu_util import ATOL, compare, dev, oracle_attention, say
+from test_gpu_item_kernel import make, widen
+
+gpu = pytest.mark.gpu
+NAN = float("nan")
+
+
+def run(b, cache, part, bound, entry="step", dtype=torch.float32, in_place=False, new=None):
+    """(out, lse) of one call; a step appends the token that stands in the (bf16) cache already, unless `new` are given."""
+    wl, q = b.wl, dev(b.q)
+    out = q if in_place else torch.full(b.q.shape, NAN, dtype=dtype, device="cuda:0")
+    lse = torch.full(b.q.shape[:2], NAN, device="cuda:0")
+    ws = torch.full((adr.adr_decode_workspace_bytes(*b.q.shape, bound, part) // 4,), NAN, device="cuda:0")
+    table, lens = dev(b.block_table), dev(b.seq_lens)
+    if entry == "step":
+        if new is None:
+            at = np.maximum(b.seq_lens - 1, 0)
+            page, slot = b.block_table[np.arange(wl.B), at // wl.page_size], at % wl.page_size
+            new = [dev(t.cpu()[page, slot]) for t in (b.k_cache, b.v_cache)]
+        adr.adr_decode_step(out, q, *new, cache, table, lens, wl.scale, bound, part, ws, lse)
+    else:
+        adr.adr_decode_attention(out, q, cache, table, lens, wl.scale, bound, part, ws, lse)
+    torch.cuda.synchronize()
+    assert adr.adr_decode_read_status(ws, *b.q.shape, bound, part) == 0
+    return out, lse
+
+
+def lengths(B, longest, kind):
+    rng = np.random.default_rng(B + longest)
+    n = {"mixed": rng.integers(0, min(200, longest + 1), B), "same": np.full(B, longest), "one": np.ones(B)}[kind].astype(np.int64)
+    edges = [longest, 0, 1, 15, 16, 17, 127, 128, 129, 255, 256, 257, longest - 1, longest]
+    if kind == "mixed":
+        n[:len(edges)] = np.minimum(edges, longest)
+    elif kind == "one":
+        n[B // 2] = longest                        # a single long row among rows of one token
+    return rng.permutation(n)
+
+
+CASES = [(96, 8, 4, 128), (95, 8, 4, 128), (768, 1, 4, 128), (2048, 1, 2, 128), (2049, 1, 2, 128), (24, 32, 1, 128),
+         (48, 16, 16, 128), (96, 16, 2, 64), (192, 8, 1, 64), (100, 8, 8, 128)]
+
+
+@gpu
+@pytest.mark.parametrize("B,Hkv,G,d", CASES)
+@pytest.mark.parametrize("kind", ["mixed", "one"])
+@pytest.mark.parametrize("entry", ["step", "attention"])
+def test_planned_passes(B, Hkv, G, d, kind, entry):
+    longest = 700
+    b = make(71 + B, G * Hkv, Hkv, d, lengths(B, longest, kind))
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    say("planned B=%d Hkv=%d G=%d d=%d %s %s" % (B, Hkv, G, d, kind, entry))
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    for bound in (longest, 8192):
+        if bound > longest:
+            widen(b, bound)
+        out, lse = run(b, cache, 128, bound, entry)
+        assert compare(out, lse, ref, ref_lse, what="bound %d" % bound)[0] <= ATOL
+        again, again_lse = run(b, cache, 128, bound, entry)
+        assert torch.equal(out, again) and torch.equal(lse, again_lse)
+
+
+@gpu
+@pytest.mark.parametrize("d,G,Hkv", [(128, 4, 8), (64, 2, 16)])
+@pytest.mark.parametrize("places", [3, 4, 5, 33])
+@pytest.mark.parametrize("entry", ["step", "attention"])
+def test_planned_fp8_and_few_places(d, G, Hkv, places, entry):
+    """Three partitions allowed: not planned; four: the list takes one's place and long rows have three."""
+    part = 64
+    b = make(73 + places, G * Hkv, Hkv, d, lengths(100, places * part, "mixed"))
+    b.k_cache, ks = W.quantize_pool_fp8(b.k_cache, b.used)
+    b.v_cache, vs = W.quantize_pool_fp8(b.v_cache, b.used)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache), dev(ks), dev(vs))
+    say("planned fp8 d=%d places=%d %s" % (d, places, entry))
+    new = [torch.randn(100, Hkv, d, generator=torch.Generator().manual_seed(i)).to(torch.bfloat16) for i in range(2)]
+    if entry == "step":
+        host = [W.bits(t).copy() for t in (b.k_cache, b.v_cache, ks, vs)]
+        oracle.kv_append(*host[:2], *map(W.bits, new), b.block_table, b.seq_lens - 1, k_scale=host[2], v_scale=host[3])
+    out, lse = run(b, cache, part, places * part, entry, new=[dev(t) for t in new])
+    if entry == "step":
+        for got, want in zip((cache.k, cache.v, cache.k_scale, cache.v_scale), host):
+            assert np.array_equal(W.bits(got).view(np.uint8), want.view(np.uint8))
+        b.k_cache, b.v_cache, ks, vs = (t.cpu() for t in (cache.k, cache.v, cache.k_scale, cache.v_scale))
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale,
+                                    k_scale=W.bits(ks), v_scale=W.bits(vs))
+    assert compare(out, lse, ref, ref_lse, what="fp8")[0] <= ATOL
+
+
+@gpu
+@pytest.mark.parametrize("B,kind", [(1, "same"), (3, "mixed"), (100, "mixed")])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("longest", [513, 1100, 1537, 5000])
+def test_steps_that_merge_inside_the_pass(B, kind, dtype, longest):
+    """Also with `out` in q's place, where nothing may be counted in it."""
+    b = make(79 + B, 32, 8, 128, lengths(max(B, 14), longest, kind)[:B] if kind == "mixed" else [longest] * B)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    say("merged inside B=%d %s %s longest=%d" % (B, kind, dtype, longest))
+    bound = max(longest, int(b.seq_lens.max()))
+    widen(b, bound)
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    out, lse = run(b, cache, 512, bound, dtype=dtype)
+    compare(out, lse, ref, ref_lse, what="step")
+    if B < 96:  # not planned: the two calls give the same bits
+        two, two_lse = run(b, cache, 512, bound, "attention", dtype=dtype)
+        assert torch.equal(out, two) and torch.equal(lse, two_lse)
+    for entry in ("step", "attention"):
+        out, lse = run(b, cache, 512, bound, entry, in_place=True)
+        compare(out, lse, ref, ref_lse, what="in place, " + entry)
+
+
+@gpu
+def test_a_plan_follows_the_lengths_of_each_replay():
+    """One recorded step, replayed for other lengths; every replay against an eager call on other buffers."""
+    longest = 900
+    b = make(83, 32, 8, 128, lengths(100, longest, "same"))
+    wl, part = b.wl, 128
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    q, table, new = dev(b.q), dev(b.block_table), [dev(torch.zeros(100, 8, 128), torch.bfloat16) for _ in range(2)]
+    lens = dev(b.seq_lens)
+    outs = [torch.full(b.q.shape, NAN, device="cuda:0") for _ in range(2)]
+    wss = [torch.full((adr.adr_decode_workspace_bytes(*b.q.shape, longest, part) // 4,), NAN, device="cuda:0") for _ in range(2)]
+    say("planned step recorded")
+    def step(i):
+        adr.adr_decode_step(outs[i], q, *new, cache, table, lens, wl.scale, longest, part, wss[i])
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        step(0)
+    rng = np.random.default_rng(5)
+    for replay in range(4):
+        lens.copy_(dev(rng.integers(0, longest + 1, 100).astype(np.int32)))
+        graph.replay()
+        torch.cuda.synchronize()
+        step(1)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]), "replay %d" % replay
+        assert torch.isfinite(outs[0]).all()
+
+
+def test_the_step_choice_names_the_planned_passes():
+    import ctypes
+    from test_abi_host import FAKE, cache
+    lib = adr.load_library()
+    def both(c, B, Hq, part=512, bound=8192, flags=0):
+        return tuple(f(ctypes.byref(c), B, Hq, bound, part, flags) for f in (lib.adr_decode_kernel_choice, lib.adr_decode_step_kernel_choice))
+    R, I, V = adr.KERNEL_MFMA, adr.KERNEL_MFMA_GRID, adr.KERNEL_VALU
+    gqa = cache(Hkv=8)
+    assert both(gqa, 256, 32) == both(gqa, 2048, 32) == (R, I) and both(gqa, 2049, 32) == (R, R)
+    assert both(gqa, 256, 32, bound=1 << 20) == (R, I) and both(gqa, 256, 32, part=4096) == (R, R)
+    assert both(gqa, 256, 32, flags=R) == (R, R) and both(gqa, 256, 32, flags=adr.GRID_CUS(64)) == (R, R)
+    assert both(gqa, 256, 32, flags=adr.PARTIALS_ONLY) == both(gqa, 256, 32, flags=adr.SINGLE_PARTITION_ITEMS) == (R, R)
+    assert both(gqa, 95, 32) == both(gqa, 96, 32) == (I, I) and both(cache(Hkv=1, d=64), 2000, 8) == (V, V)
+    assert both(gqa, 256, 31)[1] < 0
+
+
+def test_planned_lists_fit_their_places():
+    """The list's arithmetic (plan.h: plan_parts, plan_places) in numpy: items never outnumber the places, which lie in the
+    one partition per row that they take; every row's partitions cover it, at most as many as it has places for."""
+    f32, rng = np.float32, np.random.default_rng(11)
+    for _ in range(3000):
+        H = int(rng.choice([1, 2, 4, 8, 32, 64]))
+        B = int(np.clip(int(np.exp(rng.uniform(0, np.log(2048)))), -(-768 // H), 2048))
+        bound = int(np.exp(rng.uniform(np.log(64), np.log(1 << int(rng.integers(10, 30))))))
+        kind = rng.integers(4)
+        L = (np.full(B, bound) if kind == 0 else rng.integers(0, bound + 1, B) if kind == 1 else
+             np.exp(rng.uniform(0, math.log(bound), B)).astype(np.int64) if kind == 2 else np.where(np.arange(B) % 10, 1, bound)).astype(np.int64)
+        places = min(max(-(-bound // 16) - 1, 3), 4096) if rng.integers(2) else int(rng.integers(3, 40))
+        tiles = np.minimum(-(-L // 16), 1 << 20)
+        total = int(tiles.sum())
+        per_slot = f32(f32(H) / f32(768))
+        most = int(np.ceil(f32(total) * (f32(1.25) * per_slot)))
+        if most > 256:
+            most = max(int(np.ceil(f32(total) * (f32(0.125) * per_slot))), 256)
+        most = max(most, 8)
+        n = np.where(tiles <= most, 1, np.minimum(-(-tiles // most), places))
+        tokens = np.where(n > 1, -(-(-(-L // n)) // 128) * 128, L)
+        n = np.where(tiles <= most, 1, -(-L // np.maximum(tokens, 1)))
+        assert (n >= 1).all() and (n <= places).all() and (n * tokens >= L).all() and ((n - 1) * tokens <= np.maximum(L - 1, 0)).all()
+        room = B + max(int(768 / (1.25 * H)), min(int(768 / (0.125 * H)), B * min(-(-bound // 16), 1 << 20) // 256)) + 2
+        assert n.sum() <= -(-room // 8) * 8
