@@ -231,7 +231,8 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  * one workgroup per item serves them in that order, also where adr_decode_attention takes the
  * resident kernel (which ADR_KERNEL_MFMA names; ADR_GRID_CUS keeps it, too): `out` then equals the
  * two calls' up to the order of the floating-point sums.  adr_decode_attention plans such passes
- * the same where it would take one workgroup per item anyway.
+ * the same where it would take one workgroup per item anyway.  A step of 256 pairs or more with at
+ * least eight partitions allowed is planned too (the two calls are not, with the same consequence).
  *
  * The append kernel runs first, then the attention kernels, all on `stream`; the call saves the
  * caller the positions array (it is seq_lens - 1) and one trip through the binding.  k_new /

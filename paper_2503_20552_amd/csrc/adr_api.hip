@@ -379,9 +379,9 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
 // Is a split pass planned on the device (plan.h), and served by one workgroup per item then?  Where there are
 // at least as many rows as the chip holds workgroups: us a step, in the batch's order and planned, 256 requests x 8
 // kv-heads of median length 1500 406 (the resident kernel) and 379, fp8 223 and 208, of 3000 tokens 525 and 498, 160 of
-// up to 3000 178 and 163, 128 of heavy-tailed lengths 78 and 69, 1500 of median 200 408 and 350; with 296 to 600
-// rows the two are within 2 % either way (49.0 and 49.5, 110.4 and 111.5, 125.5 and 126.5, fp8 57 and 61).
-// The list takes the place of one partition per row, so that there must be some.
+// up to 3000 178 and 163, 128 of heavy-tailed lengths 78 and 69, 1500 of median 200 408 and 350.  With 256 rows or more
+// (plan.h: kFew...; figures there) where an append kernel plans on its way and eight partitions are allowed: with
+// four, of which the list takes one's place, 80 short requests 23.2 and 25.1.
 // Without an append kernel to plan on its way a kernel of its own does, and passes for the resident kernel stay
 // with it (adr_decode_kernel_choice).
 bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B, int Hq, int max_seq_len,
@@ -392,14 +392,19 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     const int64_t max_parts = max_parts_for(max_seq_len, partition_tokens);
     if (kernel == KERNEL_VALU || (kernel == KERNEL_STREAM && (!step || (flags >> 16))) ||
         (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_DEBUG_EXPIRE_WAITS)) ||
-        B > 2048 || (int64_t)B * H < adr::kSlots || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
+        B > 2048 || (int64_t)B * H < (step && max_parts >= 8 ? adr::kSlots / 3 : adr::kSlots) || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
+        return false;
+    p.part_counts = nullptr;
+    p.few = (int64_t)B * H < adr::kSlots;
+    p.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
+    if (p.few && p.even_tiles == 0) // (whole rows)
         return false;
     p.heads_per_slot = (float)H / adr::kSlots;
     p.B = B;
     p.max_seq_len = max_seq_len;
     p.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
-    p.max_items = (int)adr::plan_places(B, H, max_seq_len);
-    return (size_t)p.max_items * sizeof(adr::u32x4) <= (size_t)B * Hq * cache->d * sizeof(float);
+    p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.few);
+    return (size_t)p.max_items * sizeof(adr::u32x4) + (size_t)B * sizeof(int32_t) <= (size_t)B * Hq * cache->d * sizeof(float);
 }
 
 constexpr unsigned kFlagBits = 0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_WORKSPACE_READY |
@@ -486,6 +491,9 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         cut = {partition_tokens, list.max_parts, 0, 0};
         list.items = (adr::u32x4 *)((char *)workspace + (size_t)B * list.max_parts * Hq * d * sizeof(float));
         list.seq_lens = seq_lens;
+        meets = !list.few;
+        if (!meets)
+            list.part_counts = (int32_t *)(list.items + list.max_items);
     } else {
         cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
         split = split && cut.max_parts > 1;
@@ -606,6 +614,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         mp.max_seq_len = max_seq_len;
         mp.cut = p.cut;
         mp.cut_share = p.cut_share;
+        mp.part_counts = list.items ? list.part_counts : nullptr;
         mp.B = B;
         mp.heads = Hq;
         mp.d = d;
@@ -687,6 +696,7 @@ int adr_decode_merge(void *out, adr_dtype out_dtype, float *lse, const int32_t *
     mp.max_seq_len = max_seq_len;
     mp.cut = 0;
     mp.cut_share = 0;
+    mp.part_counts = nullptr;
     mp.B = B;
     mp.heads = Hq;
     mp.d = d;
@@ -720,6 +730,7 @@ int adr_lse_merge(void *out, adr_dtype out_dtype, float *lse_out, const float *p
     mp.max_seq_len = 0;
     mp.cut = 0;
     mp.cut_share = 0;
+    mp.part_counts = nullptr;
     mp.B = B;
     mp.heads = heads;
     mp.d = d;

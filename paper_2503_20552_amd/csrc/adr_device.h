@@ -91,6 +91,7 @@ struct MergeParams {
     int max_parts, max_seq_len;  //   and rows with <= 1 partition are left alone
     int cut;                     //   (row_partition)
     uint32_t cut_share;
+    const int32_t *part_counts;  //   of a planned pass (plan.h), or nullptr
     int B, heads, d, out_f32;
     const uint32_t *status;      // call status block of the pass that wrote the partials, or nullptr: when
                                  // its expired-waits word is not zero every row gets NaN
@@ -111,8 +112,11 @@ __device__ __forceinline__ void clear_meet_words(const MeetWords &m, int b)
 // Where and from what a pass's items are planned (plan.h).
 struct PlanParams {
     u32x4 *items; // [max_items], or nullptr: nothing to plan
+    int32_t *part_counts; // [B]: partitions of each row, for the merge kernel; nullptr where rows meet inside the pass
     const int32_t *seq_lens;
     int B, max_seq_len, max_parts, max_items;
+    int few;      // fewer rows than the chip holds workgroups: cut by kFew...,
+    int even_tiles; //   rows of one length in partitions of that many tiles
     float heads_per_slot; // kv-heads (pairs of them) by the workgroups the chip holds
 };
 

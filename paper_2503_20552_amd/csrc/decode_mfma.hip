@@ -278,7 +278,8 @@ __device__ __forceinline__ void attend_two_fp8(WaveState &st, float (&sc)[8], u3
 enum class Items {
     by_row,      // numbered by row and stride; the partitions are merged by a kernel of its own
     by_row_meet, // numbered the same; the wave that brings a row's last partition merges it
-    planned      // listed (plan.h), merged the same
+    planned_meet, // listed (plan.h), merged the same
+    planned      // listed, merged by the kernel of its own
 };
 
 // The kernel's argument block, read where it is asked for: what a partition's end needs of the parameters does not
@@ -289,7 +290,7 @@ template <Items ITEMS>
 __device__ __forceinline__ LateParams late_params()
 {
     LateParams p = (LateParams)__builtin_amdgcn_kernarg_segment_ptr();
-    if (ITEMS != Items::by_row)
+    if (ITEMS == Items::by_row_meet || ITEMS == Items::planned_meet)
         asm volatile("" : "+s"(p));
     return p;
 }
@@ -427,6 +428,7 @@ template <bool FP8, bool PAIR, int NW, Items ITEMS>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2, NW == 4 ? 3 : 8)))
 void decode_mfma_kernel(const DecodeParams p)
 {
+    constexpr bool kMeet = ITEMS == Items::by_row_meet || ITEMS == Items::planned_meet;
     constexpr int HD = PAIR ? D / 2 : D;           // elements of one head
     const int G = p.G;
     const int H = PAIR ? p.Hkv >> 1 : p.Hkv;       // rows of D elements per token
@@ -441,7 +443,7 @@ void decode_mfma_kernel(const DecodeParams p)
     const int j = lane >> 4;
     const bool upper = PAIR && r >= G;
 
-    const int stride = ITEMS == Items::planned ? kNoMore : p.grid_stride;
+    const int stride = ITEMS >= Items::planned_meet ? kNoMore : p.grid_stride;
     // Which (row of the cache h, partition, request) this workgroup starts with.  Consecutive workgroups go
     // to the eight chiplets in turn.  bf16: kv-heads fastest, so that a page's heads are read side by
     // side by different chiplets.  fp8: the kv-heads of a partition one after the other on one chiplet --
@@ -459,7 +461,7 @@ void decode_mfma_kernel(const DecodeParams p)
     }
     typedef const __attribute__((address_space(4))) int32_t *const_ptr;
     int b, L, pt, first_part, n_parts;
-    if constexpr (ITEMS == Items::planned) {
+    if constexpr (ITEMS >= Items::planned_meet) {
         const u32x4 item = ((const __attribute__((address_space(4))) u32x4 *)p.items)[unit];
         if (item[0] == kNoRow)
             return;
@@ -708,7 +710,7 @@ void decode_mfma_kernel(const DecodeParams p)
                 }
                 if (late->lse && c4 == 0)
                     late->lse[row] = lse;
-            } else if (ITEMS != Items::by_row) {
+            } else if (kMeet) {
                 const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq;
                 store_shared(o, partial_rsrc(late->part_o + row * HD), (head * HD + c4) * 4);
                 if (c4 == 0)
@@ -720,8 +722,8 @@ void decode_mfma_kernel(const DecodeParams p)
                     late->part_lse[row] = lse;
             }
         }
-        if (ITEMS != Items::by_row && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD>(late, b, h * R, n_parts)) {
-            if (ITEMS == Items::planned)
+        if (kMeet && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD>(late, b, h * R, n_parts)) {
+            if (ITEMS == Items::planned_meet)
                 merge_share<HD, NW, 1, 8>(late, b, h * R, R, n_parts);
             else if (late->meet == 1)
                 merge_share<HD, NW, 1, 16>(late, b, h * R, R, n_parts);
@@ -770,7 +772,7 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
         if (wide)
             go(decode_mfma_kernel<F, P, 8, Items::by_row>, 8);
         else if (p.items)
-            go(decode_mfma_kernel<F, P, 4, Items::planned>, 4);
+            p.meet ? go(decode_mfma_kernel<F, P, 4, Items::planned_meet>, 4) : go(decode_mfma_kernel<F, P, 4, Items::planned>, 4);
         else if (p.meet)
             go(decode_mfma_kernel<F, P, 4, Items::by_row_meet>, 4);
         else

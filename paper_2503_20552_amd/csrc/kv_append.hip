@@ -17,7 +17,8 @@ __device__ __forceinline__ void clear_control(const AppendParams &p)
 template <int T>
 __device__ __forceinline__ void prepare_pass(const PlanParams &plan, const MeetWords &meet, int b)
 {
-    if (meet.out && (!plan.items || plan_row<T>(plan, b) > 1))
+    const bool split = !plan.items || plan_row<T>(plan, b) > 1;
+    if (meet.out && split)
         clear_meet_words(meet, b);
 }
 

@@ -38,7 +38,8 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const MergeParams p)
         count = p.part_offsets[b + 1] - first;
     } else {
         const int L = max(min(p.seq_lens[b], p.max_seq_len), 0);
-        count = parts_of(L, row_partition(L, p.partition_tokens, p.max_parts, p.cut, p.cut_share));
+        count = p.part_counts ? p.part_counts[b]
+                              : parts_of(L, row_partition(L, p.partition_tokens, p.max_parts, p.cut, p.cut_share));
         first = b * p.max_parts;
     }
     // The pass that wrote the partials reported a broken hand-shake between its waves: no row of

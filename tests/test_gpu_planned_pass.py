@@ -120,6 +120,23 @@ def test_steps_that_merge_inside_the_pass(B, kind, dtype, longest):
 
 
 @gpu
+@pytest.mark.parametrize("B,Hkv,G,d", [(32, 8, 4, 128), (31, 8, 4, 128), (95, 8, 8, 128), (256, 1, 4, 128), (64, 8, 4, 64)])
+@pytest.mark.parametrize("kind", ["mixed", "same", "one"])
+@pytest.mark.parametrize("allowed", [7, 8, 40])
+def test_planned_steps_of_fewer_rows(B, Hkv, G, d, kind, allowed):
+    """256 rows to 767, planned from eight partitions allowed on, merged by the merge kernel; rows of one length too."""
+    longest = 128 * allowed
+    b = make(89 + B, G * Hkv, Hkv, d, lengths(B, longest, kind))
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    say("planned step B=%d Hkv=%d G=%d d=%d %s allowed=%d" % (B, Hkv, G, d, kind, allowed))
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    out, lse = run(b, cache, 128, longest)
+    assert compare(out, lse, ref, ref_lse, what="step")[0] <= ATOL
+    again, again_lse = run(b, cache, 128, longest)
+    assert torch.equal(out, again) and torch.equal(lse, again_lse)
+
+
+@gpu
 def test_a_plan_follows_the_lengths_of_each_replay():
     """One recorded step, replayed for other lengths; every replay against an eager call on other buffers."""
     longest = 900
@@ -165,27 +182,41 @@ def test_the_step_choice_names_the_planned_passes():
 
 
 def test_planned_lists_fit_their_places():
-    """The list's arithmetic (plan.h: plan_parts, plan_places) in numpy: items never outnumber the places, which lie in the
-    one partition per row that they take; every row's partitions cover it, at most as many as it has places for."""
+    """The list's arithmetic (plan.h: plan_cut, plan_parts, plan_places) in numpy: items never outnumber the places; every
+    row's partitions cover it, at most as many as it has places for."""
     f32, rng = np.float32, np.random.default_rng(11)
-    for _ in range(3000):
+    for case in range(4000):
+        few = case % 2 == 1
         H = int(rng.choice([1, 2, 4, 8, 32, 64]))
-        B = int(np.clip(int(np.exp(rng.uniform(0, np.log(2048)))), -(-768 // H), 2048))
-        bound = int(np.exp(rng.uniform(np.log(64), np.log(1 << int(rng.integers(10, 30))))))
-        kind = rng.integers(4)
+        B = int(rng.integers(-(-256 // H), -(-768 // H))) if few else int(np.clip(int(np.exp(rng.uniform(0, np.log(2048)))), -(-768 // H), 2048))
+        bound = int(np.exp(rng.uniform(np.log(128), np.log(1 << int(rng.integers(10, 30))))))
+        kind = rng.integers(5)
         L = (np.full(B, bound) if kind == 0 else rng.integers(0, bound + 1, B) if kind == 1 else
-             np.exp(rng.uniform(0, math.log(bound), B)).astype(np.int64) if kind == 2 else np.where(np.arange(B) % 10, 1, bound)).astype(np.int64)
+             np.exp(rng.uniform(0, math.log(bound), B)).astype(np.int64) if kind == 2 else
+             np.full(B, rng.integers(1, bound + 1)) if kind == 3 else np.where(np.arange(B) % 10, 1, bound)).astype(np.int64)
         places = min(max(-(-bound // 16) - 1, 3), 4096) if rng.integers(2) else int(rng.integers(3, 40))
         tiles = np.minimum(-(-L // 16), 1 << 20)
-        total = int(tiles.sum())
-        per_slot = f32(f32(H) / f32(768))
-        most = int(np.ceil(f32(total) * (f32(1.25) * per_slot)))
-        if most > 256:
-            most = max(int(np.ceil(f32(total) * (f32(0.125) * per_slot))), 256)
-        most = max(most, 8)
-        n = np.where(tiles <= most, 1, np.minimum(-(-tiles // most), places))
-        tokens = np.where(n > 1, -(-(-(-L // n)) // 128) * 128, L)
+        total, per_slot = int(tiles.sum()), f32(f32(H) / f32(768))
+        slot = f32(f32(total) * per_slot)
+        grain = 128
+        if few:
+            most = max(int(np.ceil(f32(0.75) * slot)), 16)
+            n = -(-tiles // most)
+            if f32(tiles.max()) * f32(B) <= f32(1.1) * f32(total):
+                cut = min(max((min(bound, 8192) * B * H // 4800 + 64) // 128 * 128, 128), 1024)   # pass_cut's
+                most = max(cut // 16, int(np.ceil(f32(tiles.max()) * f32(B) * f32(per_slot * f32(768) / f32(4800)))))
+                grain, n = 64, -(-tiles // most)
+            else:
+                n = np.minimum(n, np.maximum(5, -(-tiles // max(int(np.ceil(f32(2) * slot)), most))))
+        else:
+            most = int(np.ceil(f32(1.25) * slot))
+            if most > 256:
+                most = max(int(np.ceil(f32(0.125) * slot)), 256)
+            most = max(most, 8)
+            n = -(-tiles // most)
+        n = np.where(tiles <= most, 1, np.minimum(n, places))
+        tokens = np.where(n > 1, -(-(-(-L // n)) // grain) * grain, L)
         n = np.where(tiles <= most, 1, -(-L // np.maximum(tokens, 1)))
         assert (n >= 1).all() and (n <= places).all() and (n * tokens >= L).all() and ((n - 1) * tokens <= np.maximum(L - 1, 0)).all()
-        room = B + max(int(768 / (1.25 * H)), min(int(768 / (0.125 * H)), B * min(-(-bound // 16), 1 << 20) // 256)) + 2
-        assert n.sum() <= -(-room // 8) * 8
+        most_items = int(4800 / H) + 1 if few else max(int(768 / (1.25 * H)), min(int(768 / (0.125 * H)), B * min(-(-bound // 16), 1 << 20) // 256))
+        assert n.sum() <= -(-(B + most_items + 2) // 8) * 8, (few, H, B, bound, kind)
