@@ -49,6 +49,10 @@ __device__ __forceinline__ int append_page(const AppendParams &p, int b, int pos
 // kernel is two memory round trips deep, not three.
 __global__ __launch_bounds__(128) void kv_append_bf16_kernel(const AppendParams p)
 {
+    if ((int)blockIdx.x >= p.B) {
+        prepare_pass<128>(p.plan, p.meet, blockIdx.x - p.B);
+        return;
+    }
     const int b = blockIdx.x;
     const int row = p.Hkv * p.d; // elements
     const int64_t src = (int64_t)b * p.new_row_stride;
@@ -56,7 +60,8 @@ __global__ __launch_bounds__(128) void kv_append_bf16_kernel(const AppendParams 
     const u32x4 k0 = *(const u32x4 *)(p.k_new + src + first);
     const u32x4 v0 = *(const u32x4 *)(p.v_new + src + first);
     clear_control(p);
-    prepare_pass<128>(p.plan, p.meet, b);
+    if (p.meet.out && !p.plan.items)
+        clear_meet_words(p.meet, b);
     const int pos = append_position(p, b);
     const int page = append_page(p, b, pos, threadIdx.x == 0);
     if (page < 0)
@@ -103,10 +108,14 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float x)
 template <int D>
 __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
 {
+    if ((int)blockIdx.x >= p.B * p.Hkv) {
+        prepare_pass<64>(p.plan, p.meet, blockIdx.x - p.B * p.Hkv);
+        return;
+    }
     const int b = blockIdx.x / p.Hkv, h = blockIdx.x % p.Hkv;
     clear_control(p);
-    if (h == 0)
-        prepare_pass<64>(p.plan, p.meet, b);
+    if (p.meet.out && !p.plan.items && h == 0)
+        clear_meet_words(p.meet, b);
     const int pos = append_position(p, b);
     const int page = append_page(p, b, pos, threadIdx.x == 0 && h == 0);
     if (page < 0)
@@ -166,12 +175,15 @@ hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream)
 {
     if (p.B == 0)
         return hipSuccess;
+    // A planned pass has a workgroup per row behind the append's own (in the same ones, one after the other, the kernel
+    // took 8.6 us at 256 requests of an fp8 cache instead of 4.7).
+    const int plan = p.plan.items ? p.B : 0;
     if (!fp8)
-        kv_append_bf16_kernel<<<dim3(p.B), 128, 0, stream>>>(p);
+        kv_append_bf16_kernel<<<dim3(p.B + plan), 128, 0, stream>>>(p);
     else if (p.d == 128)
-        kv_append_fp8_kernel<128><<<dim3(p.B * p.Hkv), 64, 0, stream>>>(p);
+        kv_append_fp8_kernel<128><<<dim3(p.B * p.Hkv + plan), 64, 0, stream>>>(p);
     else
-        kv_append_fp8_kernel<64><<<dim3(p.B * p.Hkv), 64, 0, stream>>>(p);
+        kv_append_fp8_kernel<64><<<dim3(p.B * p.Hkv + plan), 64, 0, stream>>>(p);
     return hipGetLastError();
 }
 
