@@ -162,8 +162,7 @@ size_t adr_decode_workspace_bytes(int B, int Hq, int d, int max_seq_len, int par
  * t over the first seq_lens[b] cached tokens of request b, K_t/V_t taken from
  * kv-head h/G (Sec. 2.1 step (2); the kernel the executor of Sec. 3.1 runs).
  *
- *   out        [B][Hq][d], bf16 or fp32 (out_dtype), contiguous.  Holds counters of the call
- *              before it holds the result (not where it overlaps q or the new tokens).
+ *   out        [B][Hq][d], bf16 or fp32 (out_dtype), contiguous.
  *   lse        optional fp32 [B][Hq]: natural-log log-sum-exp of the scaled scores.
  *   q          bf16 [B][Hq][d], request rows q_row_stride ELEMENTS apart.
  *   seq_lens   int32 [B]: tokens attended (the length AFTER the append, so the
@@ -427,8 +426,8 @@ int adr_stream_fault_count(uint64_t *count);
  * Which kernel a pass of this shape and these flags runs on: ADR_KERNEL_VALU, ADR_KERNEL_MFMA
  * (the resident matrix-core kernel) or ADR_KERNEL_MFMA_GRID, or minus an adr_status when the
  * arguments are rejected.  The same decision adr_decode_attention takes;
- * adr_decode_step_kernel_choice tells adr_decode_step's (an `out` that overlaps q or the new tokens
- * left aside: such a call runs as adr_decode_attention's).  adr_kernel_name gives
+ * adr_decode_step_kernel_choice tells adr_decode_step's (an `out` that overlaps q,
+ * other than in q's very place, left aside: such a call runs as adr_decode_attention's).  adr_kernel_name gives
  * the kernel's name as profilers show it (without template arguments); "" for other values.
  */
 int adr_decode_kernel_choice(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int partition_tokens,

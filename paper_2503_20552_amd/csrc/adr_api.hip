@@ -10,7 +10,7 @@
 
 namespace adr {
 hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream);
-hipError_t launch_plan(const PlanParams &p, const MeetWords &meet, int B, hipStream_t stream);
+hipError_t launch_plan(const PlanParams &p, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
 hipError_t launch_decode_stream(const DecodeParams &p, int d, bool fp8, hipStream_t stream);
@@ -230,7 +230,7 @@ int adr_kv_append(const adr_kv_cache *cache, const void *k_new, const void *v_ne
     p.B = B;
     p.clear_words = nullptr;
     p.n_clear_words = 0;
-    p.meet.out = nullptr;
+    p.meet.part_lse = nullptr;
     p.plan.items = nullptr;
     if (bounds_record(&p.bounds) != ADR_OK)
         return ADR_ERR_LAUNCH;
@@ -395,6 +395,8 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
         B > 2048 || (int64_t)B * H < (step && max_parts >= 8 ? adr::kSlots / 3 : adr::kSlots) || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
         return false;
     p.part_counts = nullptr;
+    p.arrivals = nullptr;
+    p.heads = Hq;
     p.few = (int64_t)B * H < adr::kSlots;
     p.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
     if (p.few && p.even_tiles == 0) // (whole rows)
@@ -404,7 +406,9 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.max_seq_len = max_seq_len;
     p.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
     p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.few);
-    return (size_t)p.max_items * sizeof(adr::u32x4) + (size_t)B * sizeof(int32_t) <= (size_t)B * Hq * cache->d * sizeof(float);
+    // (behind the list: the merge kernel's partition counts, or the arrivals)
+    const size_t behind = p.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * sizeof(uint32_t);
+    return (size_t)p.max_items * sizeof(adr::u32x4) + behind <= (size_t)B * Hq * cache->d * sizeof(float);
 }
 
 constexpr unsigned kFlagBits = 0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_WORKSPACE_READY |
@@ -473,16 +477,13 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         return ADR_ERR_WORKSPACE;
     if (B == 0)
         return ADR_OK;
-    // One workgroup per item: the wave that brings a row's last partition may merge it (decode_mfma.hip).  The arrivals
-    // are counted in `out`, which must not be an input then (an executor may well attend in place).
-    adr::MeetWords meet = {out, Hq, d * (out_dtype == ADR_F32 ? 4 : 2)};
-    const size_t out_bytes = (size_t)B * Hq * meet.stride;
+    // One workgroup per item: the wave that brings a row's last partition may merge it (decode_mfma.hip), while the
+    // queries of other rows are still to be read.  `out` may stand in q's place (an executor may well attend in
+    // place: a head's result then replaces its own query, which nobody reads any more), but not across it.
+    const size_t out_bytes = (size_t)B * Hq * d * (out_dtype == ADR_F32 ? 4 : 2);
+    const bool in_place = out == q && out_dtype == ADR_BF16 && q_row_stride == (int64_t)Hq * d;
     bool meets = split && !(flags & ADR_PARTIALS_ONLY) &&
-                 !overlap(out, out_bytes, q, ((size_t)(B - 1) * q_row_stride + (size_t)Hq * d) * 2);
-    if (nt && meets) {
-        const size_t new_bytes = ((size_t)(B - 1) * nt->row_stride + (size_t)cache->Hkv * d) * 2;
-        meets = !overlap(out, out_bytes, nt->k, new_bytes) && !overlap(out, out_bytes, nt->v, new_bytes);
-    }
+                 (in_place || !overlap(out, out_bytes, q, ((size_t)(B - 1) * q_row_stride + (size_t)Hq * d) * 2));
     PassCut cut;
     adr::PlanParams list;
     list.items = nullptr;
@@ -492,22 +493,24 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         list.items = (adr::u32x4 *)((char *)workspace + (size_t)B * list.max_parts * Hq * d * sizeof(float));
         list.seq_lens = seq_lens;
         meets = !list.few;
-        if (!meets)
+        if (meets)
+            list.arrivals = (uint32_t *)(list.items + list.max_items);
+        else
             list.part_counts = (int32_t *)(list.items + list.max_items);
     } else {
         cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
         split = split && cut.max_parts > 1;
-        // Without a plan, where an append kernel clears the words on its way and the chip holds all items at once: an
+        // Without a plan, where an append kernel clears the words on its way and each item has a compute unit to itself: an
         // item of a split row keeps its place until its results are in memory and counted, 3 us with the
         // memory busy, and elsewhere others wait for that place (us a step, merged by a kernel of its own and
-        // inside: one request of 2000 tokens 10.1 and 9.5, of 8000 13.7 and 13.0; 37 of median 1000 51.2 and 54.5, fp8 256 of
-        // 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
+        // inside: one request x 8 kv-heads of 1500 tokens 9.7 and 9.5, of 8000 13.7 and 13.5, three of 2000 13.2 and 12.4; with 256
+        // items, two of 2000 11.0 and 11.0, of 8000 19.8 and 19.9; beyond, three of 8000 23.7 and 24.2, 37 of median 1000 51.2
+        // and 54.5, fp8 256 of 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
         // (24 of them: 15.2 and 15.7, three rows of 24 33.5 and 36.9).
+        const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv);
         meets = meets && split && nt && kernel == KERNEL_GRID && cut.max_parts <= 16 &&
-                (int64_t)B * cache->Hkv * cut.max_parts <= adr::kSlots;
+                pairs * cut.max_parts <= adr::kSlots / 3 && pairs * adr::result_waves(G) <= adr::kMeetWords;
     }
-    if (!meets)
-        meet.out = nullptr;
 
     adr::DecodeParams p;
     p.q = (const uint16_t *)q;
@@ -553,12 +556,15 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     // block, and behind every call that was not told it is (adr.h: a later call may then vouch for it, or
     // the status be read).  A kernel that never touches it clears it on its way; ahead of the resident
     // one the append kernel does, or else a small kernel.
+    const bool counts = meets && !list.items;
     const bool clear_control = p.control && !(flags & ADR_WORKSPACE_READY);
     const bool clear_ahead = clear_control && kernel == KERNEL_STREAM;
     p.clear_words = clear_control && !clear_ahead ? plan.control_words() : 0;
 
     p.meet = !meets ? 0 : list.items ? 1 : adr::merge_slices((int64_t)B * Hq, cut.max_parts);
     p.items = list.items;
+    p.meet_mask = p.max_parts >= 16 ? 15 : p.max_parts >= 8 ? 7 : p.max_parts >= 4 ? 3 : p.max_parts >= 2 ? 1 : 0;
+    p.arrivals = list.items ? list.arrivals : nullptr;
     p.max_items = list.items ? list.max_items : 0;
 
     // The new token goes in first: the append kernel, with the token index taken from seq_lens.
@@ -583,7 +589,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         ap.B = B;
         ap.clear_words = clear_ahead ? p.control : nullptr; // on its way, for the kernels behind it
         ap.n_clear_words = clear_ahead ? plan.control_words() : 0;
-        ap.meet = meet;
+        ap.meet = {counts ? p.part_lse : nullptr, p.max_parts, p.meet_mask, Hq};
         ap.plan = list;
         ap.bounds = p.bounds;
         if (adr::launch_kv_append(ap, fp8, (hipStream_t)stream) != hipSuccess)
@@ -593,7 +599,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         if (hipGetLastError() != hipSuccess)
             return ADR_ERR_LAUNCH;
     } else if (meets) {
-        if (adr::launch_plan(list, meet, B, (hipStream_t)stream) != hipSuccess)
+        if (adr::launch_plan(list, (hipStream_t)stream) != hipSuccess)
             return ADR_ERR_LAUNCH;
     }
     hipError_t e = kernel == KERNEL_STREAM ? adr::launch_decode_stream(p, d, fp8, (hipStream_t)stream)

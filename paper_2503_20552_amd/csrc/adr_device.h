@@ -38,6 +38,15 @@ enum {
     kLaunchExpired = 2,      //   bounded waits that expired in this launch
 };
 
+// A small pass of the one-workgroup-per-item kernel that merges its rows itself keeps a word here for each wave of a
+// (request, kv-head) pair, behind the status (arrive() in decode_mfma.hip), and leaves it zero when the row is merged.
+constexpr int kMeetWords = 2 * kControlBlockWords - 1; // (of the two blocks every call has)
+// Waves of a workgroup that hold elements of its result, four a thread: of G heads of 128 or 2 G heads of 64.
+__host__ __device__ __forceinline__ int result_waves(int G)
+{
+    return G < 2 * kWaves ? (G + 1) / 2 : kWaves;
+}
+
 // What a debug build (-DADR_DEBUG_BOUNDS) records about table entries and positions that fall
 // outside the pool or the table: how many, and the first one.
 struct BoundsRecord {
@@ -74,7 +83,9 @@ struct DecodeParams {
     int clear_words;      // of `control`, zeroed by a kernel that does not use it (clear_control)
     int spin_limit;       // polls before a wait on another wave is declared failed
     int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
-    int meet;             //   > 0: the last partition of a row to arrive merges it, in that many slices (arrivals are counted in `out`)
+    int meet;             //   > 0: the last partition of a row to arrive merges it, in that many slices
+    int meet_mask;        //     (MeetWords)
+    uint32_t *arrivals;   //     where a planned pass counts the arrivals, [B][Hq], zeroed ahead (others: see arrive())
     const u32x4 *items;   //   its items in the order they are to be taken (plan.h), or nullptr: by row and stride
     int max_items;        //     places in `items`
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
@@ -97,22 +108,29 @@ struct MergeParams {
                                  // its expired-waits word is not zero every row gets NaN
 };
 
-// Where a split pass counts the partitions of a row that have arrived: the first word of each head's row of `out`, which
-// the wave that merges the row overwrites at last.  Zeroed ahead of the attention kernel.
+// Where a small pass that merges its rows itself counts their arrivals (arrive() in decode_mfma.hip): in the lse of a head
+// in one of the request's places in the workspace, neighbouring heads in different ones, hence in different lines.  The
+// words of all heads are zeroed ahead of the attention kernel.
+__device__ __forceinline__ int meet_place(int head, int mask)
+{
+    return (head >> 1) & mask;
+}
 struct MeetWords {
-    void *out;       // or nullptr: nothing is counted
-    int heads, stride; // heads of a request, bytes of a head's row
+    float *part_lse; // or nullptr: nothing is counted there
+    int places, mask, heads; // places of a request, and a power of two of them less one
 };
 __device__ __forceinline__ void clear_meet_words(const MeetWords &m, int b)
 {
     for (int i = threadIdx.x; i < m.heads; i += blockDim.x)
-        *(uint32_t *)((char *)m.out + ((int64_t)b * m.heads + i) * m.stride) = 0u;
+        m.part_lse[((int64_t)b * m.places + meet_place(i, m.mask)) * m.heads + i] = 0.f;
 }
 
 // Where and from what a pass's items are planned (plan.h).
 struct PlanParams {
     u32x4 *items; // [max_items], or nullptr: nothing to plan
     int32_t *part_counts; // [B]: partitions of each row, for the merge kernel; nullptr where rows meet inside the pass
+    uint32_t *arrivals;   // there: [B][heads], zeroed for split rows
+    int heads;
     const int32_t *seq_lens;
     int B, max_seq_len, max_parts, max_items;
     int few;      // fewer rows than the chip holds workgroups: cut by kFew...,
@@ -134,7 +152,7 @@ struct AppendParams {
     uint32_t *clear_words; // control area the first workgroup clears on its way (adr_decode_step), or nullptr
     int n_clear_words;
     MeetWords meet;        // of the attention pass behind this append
-    PlanParams plan;       // the attention pass behind this append, where it is planned
+    PlanParams plan;       //   where it is planned
     BoundsRecord *bounds;  // debug builds only
 };
 
@@ -320,10 +338,12 @@ __device__ __forceinline__ int row_partition(int L, int partition_tokens, int ma
 // and nothing of this call reads it.  (At the kernel's start every workgroup without a partition would pay for
 // the question, 84 against 79 us with 64 K of them, and in the append kernel it stands ahead of the
 // look-up of the position: 11.9 against 11.4 us for a step of one request.)
-__device__ __forceinline__ void clear_control(uint32_t *control, int words)
+// (`in_use`: words behind the status that the pass itself leaves zero.)
+__device__ __forceinline__ void clear_control(uint32_t *control, int words, int in_use = 0)
 {
     for (int i = threadIdx.x; i < words; i += blockDim.x)
-        control[i] = 0u;
+        if (i == 0 || i > in_use)
+            control[i] = 0u;
 }
 
 // Combine the kWaves per-wave partial results staged in LDS and write either

@@ -318,31 +318,52 @@ __device__ __forceinline__ f32x4 load_shared(__amdgpu_buffer_rsrc_t rsrc, int of
 // One wave's end of a partition of a split row.  In every partition's workgroup wave w holds the same elements of
 // the row's result (four per thread and round), so the waves of a row meet one by one, without a
 // barrier: a wave waits until its own partial results are in memory and counts itself in; true for the one that
-// finds all others there.  Nobody waits for anybody.  The count lies in the first word of the wave's own
-// elements of `out`, which the merged row overwrites.
-template <int HD>
+// finds all others there.  Nobody waits for anybody.
+// The counts lie in the call's workspace (not in `out`, which may be any memory a kernel can store to).  A planned pass has
+// words of their own for them in `arrivals`.  Other passes may fill every place of the workspace: there a count takes
+// the lse of the wave's first head in one place of its row (meet_place), and that partition's lse goes to the wave's
+// word in the control area (meet_word), which whoever merges the row, or attends it whole, leaves zero.  (The counts
+// themselves in the control area, whose four lines then take all arrivals of the pass one by one, 10 ns each: one
+// request of 2000 tokens 12.4 us, 10.5 spread over the lines, 9.9 here.)
+template <int HD, bool PLANNED>
 __device__ __forceinline__ bool arrive(LateParams p, int b, int first_head, int n_parts)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int head = first_head + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 / (HD / 4);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint32_t before = 0;
     if ((threadIdx.x & 63) == 0) {
-        const int64_t head = (int64_t)b * p->Hq + first_head + wave * 64 / (HD / 4);
-        before = __hip_atomic_fetch_add((uint32_t *)((char *)p->out + head * HD * (p->out_f32 ? 4 : 2)), 1u, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t *count = PLANNED ? p->arrivals + (int64_t)b * p->Hq + head
+                                  : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
+        before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     before = __builtin_amdgcn_readfirstlane(before);
     asm volatile("" ::: "memory");
     return before + 1 == (uint32_t)n_parts;
 }
+template <int HD>
+__device__ __forceinline__ float *meet_word(LateParams p, int b, int h)
+{
+    const int H = HD == D ? p->Hkv : p->Hkv >> 1;
+    return (float *)p->control + 1 + (b * H + h) * result_waves(p->G) + (threadIdx.x >> 6);
+}
+// Where partition `part` of head `head` leaves its lse; `first`: it is the wave's first head.
+template <int HD>
+__device__ __forceinline__ float *lse_word(LateParams p, int b, int h, int part, int head, bool first)
+{
+    return first && part == meet_place(head, p->meet_mask) ? meet_word<HD>(p, b, h)
+                                                           : p->part_lse + ((int64_t)b * p->max_parts + part) * p->Hq + head;
+}
 
 // The wave's share of a row, merged from its partitions in a fixed order, whichever wave it is: in S slices of every
 // S-th partition, CH of a slice loaded together, as lse_merge_kernel does it with S and CH (the same
 // bits).
-template <int HD, int NW, int S, int CH>
-__device__ __forceinline__ void merge_share(LateParams p, int b, int first_head, int heads, int n_parts)
+template <int HD, bool PLANNED, int NW, int S, int CH>
+__device__ __forceinline__ void merge_share(LateParams p, int b, int h, int first_head, int heads, int n_parts)
 {
     constexpr int QUADS = HD / 4;
+    const int counted = first_head + (int)(threadIdx.x >> 6) * 64 / QUADS; // the wave's first head, whose lse stands elsewhere
+    float *const moved = meet_word<HD>(p, b, h);
+    const int moved_from = PLANNED ? -1 : meet_place(counted, p->meet_mask); //   in that place (lse_word)
     for (int idx = threadIdx.x; idx < heads * QUADS; idx += NW * 64) {
         const int head = first_head + idx / QUADS;
         const int c4 = (idx % QUADS) * 4;
@@ -364,7 +385,11 @@ __device__ __forceinline__ void merge_share(LateParams p, int b, int first_head,
                     xs[u] = f32x4{0.f, 0.f, 0.f, 0.f};
                     if (i0 + u * S < n_parts) {
                         const int at = u * S * p->Hq + head;
-                        ls[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rsrc, at * 4, 0, kDeviceScope));
+                        if (PLANNED)
+                            ls[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rsrc, at * 4, 0, kDeviceScope));
+                        else
+                            ls[u] = __hip_atomic_load(head == counted && i0 + u * S == moved_from ? moved : p->part_lse + row + at,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         xs[u] = load_shared(o_rsrc, (at * HD + c4) * 4);
                     }
                 }
@@ -422,6 +447,8 @@ __device__ __forceinline__ void merge_share(LateParams p, int b, int first_head,
         if (p->lse && c4 == 0)
             p->lse[row] = total[0] > 0.f ? top[0] + fast_log2(total[0]) * kLn2 : -INFINITY;
     }
+    if (!PLANNED && (threadIdx.x & 63) == 0) // (for later launches: not written through, which would be waited for, 0.2 us)
+        *moved = 0.f;
 }
 
 template <bool FP8, bool PAIR, int NW, Items ITEMS>
@@ -710,11 +737,15 @@ void decode_mfma_kernel(const DecodeParams p)
                 }
                 if (late->lse && c4 == 0)
                     late->lse[row] = lse;
+                if (ITEMS == Items::by_row_meet && lane == 0)
+                    *meet_word<HD>(late, b, h) = 0.f;
             } else if (kMeet) {
                 const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq;
                 store_shared(o, partial_rsrc(late->part_o + row * HD), (head * HD + c4) * 4);
                 if (c4 == 0)
-                    __hip_atomic_store(late->part_lse + row + head, lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(ITEMS == Items::planned_meet ? late->part_lse + row + head
+                                                                    : lse_word<HD>(late, b, h, part, head, lane == 0 && idx == (int)threadIdx.x),
+                                       lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else {
                 const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq + head;
                 *(f32x4 *)(late->part_o + row * HD + c4) = o;
@@ -722,14 +753,16 @@ void decode_mfma_kernel(const DecodeParams p)
                     late->part_lse[row] = lse;
             }
         }
-        if (kMeet && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD>(late, b, h * R, n_parts)) {
+        if (kMeet && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD, ITEMS == Items::planned_meet>(late, b, h * R, n_parts)) {
             if (ITEMS == Items::planned_meet)
-                merge_share<HD, NW, 1, 8>(late, b, h * R, R, n_parts);
-            else if (late->meet == 1)
-                merge_share<HD, NW, 1, 16>(late, b, h * R, R, n_parts);
+                merge_share<HD, true, NW, 1, 8>(late, b, h, h * R, R, n_parts);
+            else if (late->meet == 1) // (up to twelve partitions then: merge_slices)
+                merge_share<HD, false, NW, 1, 12>(late, b, h, h * R, R, n_parts);
             else
-                merge_share<HD, NW, 2, 8>(late, b, h * R, R, n_parts);
+                merge_share<HD, false, NW, 2, 8>(late, b, h, h * R, R, n_parts);
         }
+        if (ITEMS != Items::by_row) // (one partition to a workgroup; what the loop holds is free in what stands above)
+            break;
         part += stride;
         if (part >= n_parts)
             break;
@@ -738,7 +771,8 @@ void decode_mfma_kernel(const DecodeParams p)
     }
     if (blockIdx.x == 0) {
         const LateParams late = late_params<ITEMS>();
-        clear_control(late->control, late->clear_words);
+        const int in_use = ITEMS == Items::by_row_meet ? late->B * H * result_waves(late->G) : 0;
+        clear_control(late->control, late->clear_words, in_use);
     }
 }
 

@@ -22,16 +22,6 @@ __device__ __forceinline__ void clear_control(const AppendParams &p)
             p.clear_words[i] = 0u;
 }
 
-// What a planned attention kernel behind needs of row b: its items in the pass's plan, and the words it counts a split
-// row's arrivals in.
-template <int T>
-__device__ __forceinline__ void prepare_pass(const PlanParams &plan, const MeetWords &meet, int b)
-{
-    const bool split = plan_row<T>(plan, b) > 1;
-    if (meet.out && split)
-        clear_meet_words(meet, b);
-}
-
 // The page a row's token goes to, or -1 when the row is skipped (a padded row, a position past
 // the row's table, a page id outside the pool; a debug build records the latter two, once per
 // row: `report` is true in one thread of the row's workgroups).
@@ -61,7 +51,7 @@ template <Pass PASS>
 __global__ __launch_bounds__(128) void kv_append_bf16_kernel(const AppendParams p)
 {
     if (PASS == Pass::planned && (int)blockIdx.x >= p.B) {
-        prepare_pass<128>(p.plan, p.meet, blockIdx.x - p.B);
+        plan_row<128>(p.plan, blockIdx.x - p.B);
         return;
     }
     const int b = blockIdx.x;
@@ -120,7 +110,7 @@ template <int D, Pass PASS>
 __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
 {
     if (PASS == Pass::planned && (int)blockIdx.x >= p.B * p.Hkv) {
-        prepare_pass<64>(p.plan, p.meet, blockIdx.x - p.B * p.Hkv);
+        plan_row<64>(p.plan, blockIdx.x - p.B * p.Hkv);
         return;
     }
     const int b = blockIdx.x / p.Hkv, h = blockIdx.x % p.Hkv;
@@ -171,14 +161,14 @@ __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
 }
 
 // The same ahead of a pass that nothing is appended for.
-__global__ __launch_bounds__(128) void plan_kernel(const PlanParams p, const MeetWords meet)
+__global__ __launch_bounds__(128) void plan_kernel(const PlanParams p)
 {
-    prepare_pass<128>(p, meet, blockIdx.x);
+    plan_row<128>(p, blockIdx.x);
 }
 
-hipError_t launch_plan(const PlanParams &p, const MeetWords &meet, int B, hipStream_t stream)
+hipError_t launch_plan(const PlanParams &p, hipStream_t stream)
 {
-    plan_kernel<<<dim3(B), 128, 0, stream>>>(p, meet);
+    plan_kernel<<<dim3(p.B), 128, 0, stream>>>(p);
     return hipGetLastError();
 }
 
@@ -200,7 +190,7 @@ hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream)
     };
     if (p.plan.items)
         go(std::integral_constant<Pass, Pass::planned>());
-    else if (p.meet.out)
+    else if (p.meet.part_lse)
         go(std::integral_constant<Pass, Pass::meets>());
     else
         go(std::integral_constant<Pass, Pass::other>());

@@ -121,9 +121,10 @@ __device__ __forceinline__ int plan_parts(int L, const PlanCut &c, int max_parts
     return (L + tokens - 1) / tokens;
 }
 
-// Row b's items: {row, its length, tokens per partition, partition | partitions << 16}.  Returns the partitions.
+// Row b's items, {row, its length, tokens per partition, partition | partitions << 16}, and the words its partitions'
+// arrivals are counted in, or their number for the merge kernel.
 template <int T>
-__device__ __forceinline__ int plan_row(const PlanParams &p, int b)
+__device__ __forceinline__ void plan_row(const PlanParams &p, int b)
 {
     const auto length = [&](int i) { return max(min(p.seq_lens[i], p.max_seq_len), 0); };
     const int mine = length(b);
@@ -153,7 +154,9 @@ __device__ __forceinline__ int plan_row(const PlanParams &p, int b)
         p.items[ahead + j] = u32x4{j < (uint32_t)n ? (uint32_t)b : kNoRow, (uint32_t)mine, (uint32_t)tokens, j | (uint32_t)n << 16};
     if (p.part_counts && threadIdx.x == 0)
         p.part_counts[b] = n;
-    return n;
+    if (p.arrivals && n > 1)
+        for (int i = threadIdx.x; i < p.heads; i += T)
+            p.arrivals[(int64_t)b * p.heads + i] = 0u;
 }
 
 } // namespace adr

@@ -102,7 +102,7 @@ def test_planned_fp8_and_few_places(d, G, Hkv, places, entry):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("longest", [513, 1100, 1537, 5000])
 def test_steps_that_merge_inside_the_pass(B, kind, dtype, longest):
-    """Also with `out` in q's place, where nothing may be counted in it."""
+    """Also with `out` in q's place."""
     b = make(79 + B, 32, 8, 128, lengths(max(B, 14), longest, kind)[:B] if kind == "mixed" else [longest] * B)
     cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
     say("merged inside B=%d %s %s longest=%d" % (B, kind, dtype, longest))
@@ -163,6 +163,62 @@ def test_a_plan_follows_the_lengths_of_each_replay():
         torch.cuda.synchronize()
         assert torch.equal(outs[0], outs[1]), "replay %d" % replay
         assert torch.isfinite(outs[0]).all()
+
+
+@gpu
+@pytest.mark.parametrize("B,longest", [(2, 3000), (40, 4096), (100, 700)])
+@pytest.mark.parametrize("entry", ["step", "attention"])
+def test_out_in_the_place_of_an_input(B, longest, entry):
+    """`out` in q's very place, over the new tokens, and in pinned host memory: the bits it has in memory of its own."""
+    b = make(97 + B, 32, 8, 128, lengths(max(B, 14), longest, "mixed")[:B])
+    b.seq_lens[0] = longest
+    b = make(97 + B, 32, 8, 128, b.seq_lens)
+    cache, part = adr.KVCache(dev(b.k_cache), dev(b.v_cache)), 128 if B == 100 else 512
+    say("out in an input's place B=%d %s" % (B, entry))
+    plain, lse = run(b, cache, part, longest, entry, dtype=torch.bfloat16)
+    out, in_place_lse = run(b, cache, part, longest, entry, in_place=True)
+    assert torch.equal(out, plain) and torch.equal(in_place_lse, lse)
+    table, lens, ws = dev(b.block_table), dev(b.seq_lens), torch.empty(adr.adr_decode_workspace_bytes(*b.q.shape, longest, part), dtype=torch.uint8, device="cuda:0")
+    host = torch.zeros(b.q.shape, dtype=torch.bfloat16, pin_memory=True)
+    if entry == "attention":
+        adr.adr_decode_attention(host, dev(b.q), cache, table, lens, b.wl.scale, longest, part, ws)
+    else:
+        at = np.maximum(b.seq_lens - 1, 0)
+        page, slot = b.block_table[np.arange(B), at // 16], at % 16
+        over = torch.zeros(b.q.shape, dtype=torch.bfloat16, device="cuda:0")
+        new = over[:, 3:11], over[:, 17:25]
+        for t, c in zip(new, (b.k_cache, b.v_cache)):
+            t.copy_(dev(c.cpu()[page, slot]))
+        adr.adr_decode_step(host, dev(b.q), *(t.clone() for t in new), cache, table, lens, b.wl.scale, longest, part, ws)
+        adr.adr_decode_step(over, dev(b.q), *new, cache, table, lens, b.wl.scale, longest, part, ws)
+        assert torch.equal(over, plain)
+    torch.cuda.synchronize()
+    assert torch.equal(host, plain.cpu())
+
+
+@gpu
+@pytest.mark.parametrize("B,Hkv,G,d,places", [(1, 8, 16, 128, 16), (24, 8, 4, 128, 4), (31, 8, 4, 128, 3), (32, 8, 4, 128, 3),
+                                              (15, 8, 8, 128, 6), (16, 8, 8, 128, 6), (20, 8, 4, 64, 4), (3, 2, 1, 128, 7)])
+def test_small_steps_count_in_the_control_area(B, Hkv, G, d, places):
+    """Up to 508 arrivals are counted at once, four to a word; the area is zero behind every call, vouched for or not, and
+    the results are the two calls' bit for bit (also where they would be too many: 32 x 8 pairs, 16 x 8 in groups of eight)."""
+    part = 256
+    longest = part * places
+    b = make(101 + B, G * Hkv, Hkv, d, [longest] + list(range(longest - 1, longest - 1 - 37 * (B - 1), -37))[:B - 1])
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    say("arrivals B=%d Hkv=%d G=%d d=%d" % (B, Hkv, G, d))
+    two, two_lse = run(b, cache, part, longest, "attention")
+    at = b.seq_lens - 1
+    page, slot = b.block_table[np.arange(B), at // 16], at % 16
+    new = [dev(c.cpu()[page, slot]) for c in (b.k_cache, b.v_cache)]
+    q, table, lens = dev(b.q), dev(b.block_table), dev(b.seq_lens)
+    ws = torch.full((adr.adr_decode_workspace_bytes(*b.q.shape, longest, part) // 4,), NAN, device="cuda:0")
+    for flags in (0, adr.WORKSPACE_READY, adr.WORKSPACE_READY, 0):
+        out, lse = torch.full(b.q.shape, NAN, device="cuda:0"), torch.full(b.q.shape[:2], NAN, device="cuda:0")
+        adr.adr_decode_step(out, q, *new, cache, table, lens, b.wl.scale, longest, part, ws, lse, flags)
+        torch.cuda.synchronize()
+        assert torch.equal(out, two) and torch.equal(lse, two_lse)
+        assert (ws[-128:].view(torch.int32) == 0).all()
 
 
 def test_the_step_choice_names_the_planned_passes():
