@@ -447,10 +447,13 @@ const char *adr_kernel_name(int kernel);
 typedef struct adr_bounds_record {
     uint32_t count; /* out-of-range reads / appends seen */
     int32_t kind;   /* first one: 0 none, 1 attention read a page id outside [0, num_pages),
-                       2 append position outside the row's table, 3 append page id outside the pool */
+                       2 append position outside the row's table, 3 append page id outside the pool,
+                       4 more items planned than fit the list of a pass (never expected) */
     int32_t row;    /* its request row */
-    int32_t index;  /* kind 1, 3: index into the row's table; kind 2: the position */
-    int32_t value;  /* kind 1, 3: the page id found; kind 2: tokens the table can describe */
+    int32_t index;  /* kind 1, 3: index into the row's table; kind 2: the position;
+                       kind 4: items up to the row's last */
+    int32_t value;  /* kind 1, 3: the page id found; kind 2: tokens the table can describe;
+                       kind 4: places of the list */
 } adr_bounds_record;
 int adr_debug_bounds_status(adr_bounds_record *record, int reset);
 

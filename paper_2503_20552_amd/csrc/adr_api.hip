@@ -392,22 +392,22 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     const int64_t max_parts = max_parts_for(max_seq_len, partition_tokens);
     if (kernel == KERNEL_VALU || (kernel == KERNEL_STREAM && (!step || (flags >> 16))) ||
         (flags & (0xFu | ADR_PARTIALS_ONLY | ADR_SINGLE_PARTITION_ITEMS | ADR_DEBUG_EXPIRE_WAITS)) ||
-        B > 2048 || (int64_t)B * H < (step && max_parts >= 8 ? adr::kSlots / 3 : adr::kSlots) || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
+        B > adr::kPlanRows || (int64_t)B * H < (step && max_parts >= 8 ? adr::kSlots / 3 : adr::kSlots) || max_parts < 4 || !adr::decode_mfma_supports(cache->d, Hq / cache->Hkv, cache->Hkv))
         return false;
     p.part_counts = nullptr;
     p.arrivals = nullptr;
     p.heads = Hq;
-    p.few = (int64_t)B * H < adr::kSlots;
-    p.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
-    if (p.few && p.even_tiles == 0) // (whole rows)
+    p.rule.few = (int64_t)B * H < adr::kSlots;
+    p.rule.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
+    if (p.rule.few && p.rule.even_tiles == 0) // (whole rows)
         return false;
-    p.heads_per_slot = (float)H / adr::kSlots;
+    p.rule.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
+    p.rule.heads_per_slot = (float)H / adr::kSlots;
     p.B = B;
     p.max_seq_len = max_seq_len;
-    p.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
-    p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.few);
+    p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule.few);
     // (behind the list: the merge kernel's partition counts, or the arrivals)
-    const size_t behind = p.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * sizeof(uint32_t);
+    const size_t behind = p.rule.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * sizeof(uint32_t);
     return (size_t)p.max_items * sizeof(adr::u32x4) + behind <= (size_t)B * Hq * cache->d * sizeof(float);
 }
 
@@ -489,10 +489,10 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     list.items = nullptr;
     if (meets && plan_pass(list, cache, kernel, B, Hq, max_seq_len, partition_tokens, flags, nt != nullptr)) {
         kernel = KERNEL_GRID;
-        cut = {partition_tokens, list.max_parts, 0, 0};
-        list.items = (adr::u32x4 *)((char *)workspace + (size_t)B * list.max_parts * Hq * d * sizeof(float));
+        cut = {partition_tokens, list.rule.max_parts, 0, 0};
+        list.items = (adr::u32x4 *)((char *)workspace + (size_t)B * list.rule.max_parts * Hq * d * sizeof(float));
         list.seq_lens = seq_lens;
-        meets = !list.few;
+        meets = !list.rule.few;
         if (meets)
             list.arrivals = (uint32_t *)(list.items + list.max_items);
         else
@@ -551,6 +551,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     p.grid_cus = (int)((flags >> 16) & 0xFFFu);
     if (bounds_record(&p.bounds) != ADR_OK)
         return ADR_ERR_LAUNCH;
+    list.bounds = p.bounds;
 
     // The control area must be all zero when the resident kernel starts, when a merge reads the status
     // block, and behind every call that was not told it is (adr.h: a later call may then vouch for it, or

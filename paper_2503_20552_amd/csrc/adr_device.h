@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan_cut.h"
+
 namespace adr {
 
 constexpr int kPageSize = 16;       // tokens per tile, the kernels' unit of work: a cache page of 16 << page_shift
@@ -52,7 +54,7 @@ __host__ __device__ __forceinline__ int result_waves(int G)
 struct BoundsRecord {
     uint32_t count;
     int32_t kind; // 0 none, 1 attention: page id outside the pool, 2 append: position outside the table,
-                  // 3 append: page id outside the pool
+                  // 3 append: page id outside the pool, 4 plan: more items than its list has places
     int32_t row, index, value;
 };
 
@@ -132,10 +134,9 @@ struct PlanParams {
     uint32_t *arrivals;   // there: [B][heads], zeroed for split rows
     int heads;
     const int32_t *seq_lens;
-    int B, max_seq_len, max_parts, max_items;
-    int few;      // fewer rows than the chip holds workgroups: cut by kFew...,
-    int even_tiles; //   rows of one length in partitions of that many tiles
-    float heads_per_slot; // kv-heads (pairs of them) by the workgroups the chip holds
+    int B, max_seq_len, max_items;
+    PlanRule rule;
+    BoundsRecord *bounds; // debug builds only
 };
 
 struct AppendParams {

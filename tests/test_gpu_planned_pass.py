@@ -1,7 +1,10 @@
 """Passes that are planned on the device (requests ordered by length, cut by the tokens the batch has, rows merged by the
 wave that brings their last partition) and small steps that merge the same way: against the oracle, on workspaces and
 outputs full of NaN, at the edges of the rule, under bounds far above the lengths, and with `out` in q's place."""
+import ctypes
 import math
+import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -222,7 +225,6 @@ def test_small_steps_count_in_the_control_area(B, Hkv, G, d, places):
 
 
 def test_the_step_choice_names_the_planned_passes():
-    import ctypes
     from test_abi_host import FAKE, cache
     lib = adr.load_library()
     def both(c, B, Hq, part=512, bound=8192, flags=0):
@@ -237,42 +239,58 @@ def test_the_step_choice_names_the_planned_passes():
     assert both(gqa, 256, 31)[1] < 0
 
 
-def test_planned_lists_fit_their_places():
-    """The list's arithmetic (plan.h: plan_cut, plan_parts, plan_places) in numpy: items never outnumber the places; every
-    row's partitions cover it, at most as many as it has places for."""
-    f32, rng = np.float32, np.random.default_rng(11)
+SHIM = r"""
+#include "plan_cut.h"
+// The rows of a pass as plan.h cuts them: partitions and tokens of each, and the places of the list.
+extern "C" long cut_rows(int few, int even_tiles, int max_parts, int H, int B, int bound, const int *L, int *parts, int *tokens)
+{
+    const adr::PlanRule rule = {few, even_tiles, max_parts, (float)H / adr::kSlots};
+    uint32_t all = 0, longest = 0;
+    for (int b = 0; b < B; ++b) {
+        all += adr::plan_tiles(L[b]);
+        longest = adr::larger(longest, adr::plan_tiles(L[b]));
+    }
+    const adr::PlanCut cut = adr::plan_cut(rule, B, all, longest);
+    for (int b = 0; b < B; ++b)
+        parts[b] = adr::plan_parts(L[b], cut, max_parts, tokens[b]);
+    return (long)adr::plan_places(B, H, bound, few);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def cut_rows(tmp_path_factory):
+    """plan_cut.h compiled for the host: (rule, lengths) -> (partitions and tokens of each row, places of the list)."""
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    csrc = os.path.join(os.path.dirname(os.path.abspath(adr.__file__)), "csrc")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off", "-I" + csrc, str(d / "shim.cpp"), "-o", str(d / "shim.so")])
+    fn = ctypes.CDLL(str(d / "shim.so")).cut_rows
+    fn.restype = ctypes.c_long
+    def call(few, even_tiles, max_parts, H, bound, L):
+        L = np.ascontiguousarray(L, dtype=np.int32)
+        n, tokens = np.zeros_like(L), np.zeros_like(L)
+        at = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+        places = fn(int(few), int(even_tiles), int(max_parts), int(H), len(L), int(bound), at(L), at(n), at(tokens))
+        return n.astype(np.int64), tokens.astype(np.int64), places
+    return call
+
+
+def test_planned_lists_fit_their_places(cut_rows):
+    """Items never outnumber the places of their list; every row's partitions cover it, at most as many as it has places for."""
+    rng = np.random.default_rng(11)
     for case in range(4000):
         few = case % 2 == 1
         H = int(rng.choice([1, 2, 4, 8, 32, 64]))
         B = int(rng.integers(-(-256 // H), -(-768 // H))) if few else int(np.clip(int(np.exp(rng.uniform(0, np.log(2048)))), -(-768 // H), 2048))
-        bound = int(np.exp(rng.uniform(np.log(128), np.log(1 << int(rng.integers(10, 30))))))
-        kind = rng.integers(5)
+        bound = int(np.exp(rng.uniform(np.log(128), np.log((1 << int(rng.integers(10, 32))) - 1))))
+        kind = rng.integers(6)
         L = (np.full(B, bound) if kind == 0 else rng.integers(0, bound + 1, B) if kind == 1 else
              np.exp(rng.uniform(0, math.log(bound), B)).astype(np.int64) if kind == 2 else
-             np.full(B, rng.integers(1, bound + 1)) if kind == 3 else np.where(np.arange(B) % 10, 1, bound)).astype(np.int64)
+             np.full(B, rng.integers(1, bound + 1)) if kind == 3 else np.where(np.arange(B) % 10, 1, bound) if kind == 4 else
+             np.where(np.arange(B) % 3, bound, 0)).astype(np.int64)
         places = min(max(-(-bound // 16) - 1, 3), 4096) if rng.integers(2) else int(rng.integers(3, 40))
-        tiles = np.minimum(-(-L // 16), 1 << 20)
-        total, per_slot = int(tiles.sum()), f32(f32(H) / f32(768))
-        slot = f32(f32(total) * per_slot)
-        grain = 128
-        if few:
-            most = max(int(np.ceil(f32(0.75) * slot)), 16)
-            n = -(-tiles // most)
-            if f32(tiles.max()) * f32(B) <= f32(1.1) * f32(total):
-                cut = min(max((min(bound, 8192) * B * H // 4800 + 64) // 128 * 128, 128), 1024)   # pass_cut's
-                most = max(cut // 16, int(np.ceil(f32(tiles.max()) * f32(B) * f32(per_slot * f32(768) / f32(4800)))))
-                grain, n = 64, -(-tiles // most)
-            else:
-                n = np.minimum(n, np.maximum(5, -(-tiles // max(int(np.ceil(f32(2) * slot)), most))))
-        else:
-            most = int(np.ceil(f32(1.25) * slot))
-            if most > 256:
-                most = max(int(np.ceil(f32(0.125) * slot)), 256)
-            most = max(most, 8)
-            n = -(-tiles // most)
-        n = np.where(tiles <= most, 1, np.minimum(n, places))
-        tokens = np.where(n > 1, -(-(-(-L // n)) // grain) * grain, L)
-        n = np.where(tiles <= most, 1, -(-L // np.maximum(tokens, 1)))
-        assert (n >= 1).all() and (n <= places).all() and (n * tokens >= L).all() and ((n - 1) * tokens <= np.maximum(L - 1, 0)).all()
-        most_items = int(4800 / H) + 1 if few else max(int(768 / (1.25 * H)), min(int(768 / (0.125 * H)), B * min(-(-bound // 16), 1 << 20) // 256))
-        assert n.sum() <= -(-(B + most_items + 2) // 8) * 8, (few, H, B, bound, kind)
+        n, tokens, room = cut_rows(few, rng.integers(8, 65), places, H, bound, L)
+        assert (n >= 1).all() and (n <= places).all(), (few, H, B, bound, kind)
+        assert (n * tokens >= L).all() and ((n - 1) * tokens <= np.maximum(L - 1, 0)).all(), (few, H, B, bound, kind)
+        assert n.sum() <= room and room % 8 == 0, (few, H, B, bound, kind)
