@@ -401,6 +401,7 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.rule.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
     if (p.rule.few && p.rule.even_tiles == 0) // (whole rows)
         return false;
+    p.rule.fill_rounds = cache->dtype == ADR_BF16;
     p.rule.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
     p.rule.heads_per_slot = (float)H / adr::kSlots;
     p.B = B;

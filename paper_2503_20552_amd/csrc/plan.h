@@ -20,28 +20,29 @@ static_assert(kPlanTile == kPageSize && kPlanGrain == kCutLeast, "");
 
 constexpr uint32_t kNoRow = 0xffffffffu; // in place of an item's row: past the last item
 
-// Over a workgroup of T threads, in every thread: the sum of a, and b by `op` (from 0 on).
-template <int T, typename Op>
-__device__ __forceinline__ void group_reduce(uint32_t &a, uint32_t &b, Op op)
+// Over a workgroup of T threads, in every thread: the sums of v[0] to v[N - 2], and v[N - 1] by `op` (from 0 on).
+template <int T, int N, typename Op>
+__device__ __forceinline__ void group_reduce(uint32_t (&v)[N], Op op)
 {
+    const auto add = [&](uint32_t (&to)[N], int i, uint32_t x) { to[i] = i + 1 < N ? to[i] + x : op(to[i], x); };
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        a += (uint32_t)__shfl_xor((int)a, off);
-        b = op(b, (uint32_t)__shfl_xor((int)b, off));
-    }
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            add(v, i, (uint32_t)__shfl_xor((int)v[i], off));
     if constexpr (T > 64) {
-        __shared__ uint32_t parts[T / 64][2];
-        __syncthreads(); // (an earlier call's have been read)
-        if ((threadIdx.x & 63) == 0) {
-            parts[threadIdx.x / 64][0] = a;
-            parts[threadIdx.x / 64][1] = b;
-        }
-        __syncthreads();
-        a = b = 0;
+        __shared__ uint32_t parts[T / 64][N];
+        if ((threadIdx.x & 63) == 0)
 #pragma unroll
-        for (int w = 0; w < T / 64; ++w) {
-            a += parts[w][0];
-            b = op(b, parts[w][1]);
+            for (int i = 0; i < N; ++i)
+                parts[threadIdx.x / 64][i] = v[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            v[i] = 0;
+#pragma unroll
+            for (int w = 0; w < T / 64; ++w)
+                add(v, i, parts[w][i]);
         }
     }
 }
@@ -53,25 +54,27 @@ __device__ __forceinline__ void plan_row(const PlanParams &p, int b)
 {
     const auto length = [&](int i) { return max(min(p.seq_lens[i], p.max_seq_len), 0); };
     const int mine = length(b);
-    uint32_t all = 0, longest = 0;
+    uint32_t lengths[3] = {0, 0, 0}; // all tiles, rows with tokens, the longest row's tiles
     for (int i = threadIdx.x; i < p.B; i += T) {
         const uint32_t tiles = plan_tiles(length(i));
-        all += tiles;
-        longest = max(longest, tiles);
+        lengths[0] += tiles;
+        lengths[1] += tiles > 0;
+        lengths[2] = max(lengths[2], tiles);
     }
-    group_reduce<T>(all, longest, [](uint32_t x, uint32_t y) { return max(x, y); });
-    const PlanCut cut = plan_cut(p.rule, p.B, all, longest);
-    uint32_t ahead = 0, behind = 0;
+    group_reduce<T>(lengths, [](uint32_t x, uint32_t y) { return max(x, y); });
+    const PlanCut cut = plan_cut(p.rule, lengths[1], lengths[0], lengths[2]);
+    uint32_t around[2] = {0, 0}; // items ahead of the row's and behind them
     int tokens;
     for (int i = threadIdx.x; i < p.B; i += T) {
         const int L = length(i);
         const uint32_t n = plan_parts(L, cut, p.rule.max_parts, tokens);
         if (L > mine || (L == mine && i < b))
-            ahead += n;
+            around[0] += n;
         else if (i != b)
-            behind += n;
+            around[1] += n;
     }
-    group_reduce<T>(ahead, behind, [](uint32_t x, uint32_t y) { return x + y; });
+    group_reduce<T>(around, [](uint32_t x, uint32_t y) { return x + y; });
+    const uint32_t ahead = around[0], behind = around[1];
     const int n = plan_parts(mine, cut, p.rule.max_parts, tokens);
     if (ahead + n > (uint32_t)p.max_items && threadIdx.x == 0) // (no lengths do that: plan_places)
         record_out_of_bounds(p.bounds, 4, b, ahead + n, p.max_items);

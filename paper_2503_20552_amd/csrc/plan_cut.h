@@ -28,11 +28,15 @@ constexpr float kShareMost = 1.25f, kShareLeast = 0.125f;
 // kFewShare and no less than kFewTiles, kFewParts of a row as long as none is longer than kFewLong.  Rows are merged
 // by a kernel of their own here: nearly every item would keep its place until it is counted (a step of 37
 // requests x 8 kv-heads 49 and 52 us).
-// Rows of one length, or nearly (the longest no more than kFewEven times the mean), come in rounds whatever their
-// order, and the last round should be a small one: they are cut as without a plan, into no more than kEvenItems.
+// Rows of one length, or nearly (the longest no more than kFewEven times the mean; empty rows, which fill up a recorded
+// batch, are no part of it), come in rounds whatever their order.  They are cut as without a plan, into no more than
+// kEvenItems, unless longer partitions fill at least half of a last round that is not the first (us a step, cut as without a
+// plan and in longer partitions, rounds of those: 33 of 6000 tokens 142 and 147, 1.4; two layers of 16 in a batch of 64 153 and
+// 162, 0.8; 48 in a batch of 64 420 and 412, 1.5; 51 of 4956 182 and 174, 1.6; 80 of 4000 225 and 211, 1.7; 60 of 7121 308 and
+// 292, 1.9).  An fp8 cache is behind in longer ones throughout (50 of 7000 134 and 140, 1.6; 55 of 7538 158 and 160, 1.7).
 // us a step, in the batch's order and planned: eight layers of 40 requests of median length 1000, replayed, 413 and
 // 389, 128 of median 1500, heads of 64, 111 and 107, 75 of the same, pages of 64, 125 and 122, 80 of heavy-tailed
-// lengths 61.5 and 54; 33 of 6000 tokens 142 and, without the exception, 150.
+// lengths 61.5 and 54.
 constexpr uint32_t kFewTiles = 16, kFewParts = 5, kEvenItems = 4800;
 constexpr float kFewShare = 0.75f, kFewLong = 2.f, kFewEven = 1.1f;
 
@@ -48,7 +52,8 @@ ADR_BOTH uint32_t plan_tiles(int L)
 // What the host knows of a pass.
 struct PlanRule {
     int few;              // fewer rows than the chip holds workgroups: cut by kFew...,
-    int even_tiles;       //   rows of one length in partitions of that many tiles
+    int even_tiles;       //   rows of one length in partitions of that many tiles,
+    int fill_rounds;      //   or in longer ones that fill a round (a bf16 cache)
     int max_parts;        // partitions of a row at most
     float heads_per_slot; // kv-heads (pairs of them) by the workgroups the chip holds
 };
@@ -72,20 +77,31 @@ struct PlanCut {
     uint32_t most, longest, parts;
     uint32_t grain; // tokens a partition is a multiple of: two tiles for each of four waves, or one
 };
+// Partitions of a row of that many tiles.
+ADR_BOTH uint32_t plan_parts(uint32_t tiles, const PlanCut &c)
+{
+    const uint32_t n = (tiles + c.most - 1) / c.most;
+    return c.parts ? smaller(n, larger(c.parts, (tiles + c.longest - 1) / c.longest)) : n;
+}
+// `rows` with tokens, which have `all` tiles.
 ADR_BOTH PlanCut plan_cut(const PlanRule &p, int rows, uint32_t all, uint32_t longest_row)
 {
     const float slot = (float)all * p.heads_per_slot;
     PlanCut c = {(uint32_t)ceilf(kShareMost * slot), 1u, 0u, (uint32_t)kPlanGrain};
     if (p.few) {
         c.most = larger((uint32_t)ceilf(kFewShare * slot), kFewTiles);
+        c.longest = larger((uint32_t)ceilf(kFewLong * slot), c.most);
         c.parts = kFewParts;
         if ((float)longest_row * (float)rows <= kFewEven * (float)all) {
-            c.most = larger((uint32_t)p.even_tiles, (uint32_t)ceilf((float)longest_row * (float)rows * (p.heads_per_slot * kSlots / kEvenItems)));
-            c.parts = 0;
-            c.grain = kPlanGrain / 2;
-            return c;
+            const uint32_t even = larger((uint32_t)p.even_tiles, (uint32_t)ceilf((float)longest_row * (float)rows * (p.heads_per_slot * kSlots / kEvenItems)));
+            const uint32_t n = plan_parts(longest_row, c);
+            const float rounds = (float)(rows * (int)n) * p.heads_per_slot;
+            if (!p.fill_rounds || longest_row <= n * even || rounds < 1.f || rounds - floorf(rounds) < 0.5f) {
+                c.most = even;
+                c.parts = 0;
+                c.grain = kPlanGrain / 2;
+            }
         }
-        c.longest = larger((uint32_t)ceilf(kFewLong * slot), c.most);
         return c;
     }
     if (c.most > kPlanTiles)
@@ -101,10 +117,7 @@ ADR_BOTH int plan_parts(int L, const PlanCut &c, int max_parts, int &tokens)
     tokens = L;
     if (tiles <= c.most)
         return 1;
-    uint32_t n = (tiles + c.most - 1) / c.most;
-    if (c.parts)
-        n = smaller(n, larger(c.parts, (tiles + c.longest - 1) / c.longest));
-    n = smaller(n, (uint32_t)max_parts);
+    const uint32_t n = smaller(plan_parts(tiles, c), (uint32_t)max_parts);
     tokens = (int)((((uint32_t)L + n - 1) / n + c.grain - 1) / c.grain * c.grain);
     return (int)(((uint32_t)L + tokens - 1) / tokens);
 }
