@@ -403,10 +403,11 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
         return false;
     p.rule.fill_rounds = cache->dtype == ADR_BF16;
     p.rule.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
+    p.rule.whole = kernel == KERNEL_STREAM ? adr::kManyTiles : adr::kPlanTiles;
     p.rule.heads_per_slot = (float)H / adr::kSlots;
     p.B = B;
     p.max_seq_len = max_seq_len;
-    p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule.few);
+    p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule);
     // (behind the list: the merge kernel's partition counts, or the arrivals)
     const size_t behind = p.rule.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * sizeof(uint32_t);
     return (size_t)p.max_items * sizeof(adr::u32x4) + behind <= (size_t)B * Hq * cache->d * sizeof(float);

@@ -21,7 +21,11 @@ constexpr int kSlots = 768; // workgroups the chip holds at once, three to a com
 // somewhere).  us a step with shares of 0.5 / 0.75 / 1 / 1.25 / 1.5 / 2: 128 requests x 8 kv-heads, heavy-tailed
 // lengths 77 / 74 / 72 / 69 / 73 / 70, 160 of up to 3000 tokens 174 / 172 / 167 / 164 / 164 / 166, 256 of
 // median length 1500 385 / 380 / 380 / 380 / 379 / 384.
-constexpr uint32_t kPlanTiles = 256;
+// Passes that the resident kernel served, of many rows: up to kManyTiles (at 256 they fell behind it; us a step, resident, 256
+// and 512: 512 requests of 5000 tokens 1636 1670 1611, of median 5000 2187 2174 2145, 256 of 8000 1320 1329 1295, of median
+// 4000 982 963 953, of median 1500 400 374 371).  Others not: 24 requests x 32 kv-heads, one of 131072 tokens, 369 and
+// 403, 100 x 8 of 9000 616 and 629, fp8 256 of 6000 528 and 531.
+constexpr uint32_t kPlanTiles = 256, kManyTiles = 512;
 constexpr float kShareMost = 1.25f, kShareLeast = 0.125f;
 
 // With fewer rows than places most rows are cut, and long ones must not stand alone at the end: partitions of
@@ -55,16 +59,17 @@ struct PlanRule {
     int even_tiles;       //   rows of one length in partitions of that many tiles,
     int fill_rounds;      //   or in longer ones that fill a round (a bf16 cache)
     int max_parts;        // partitions of a row at most
+    uint32_t whole;       // kPlanTiles or kManyTiles
     float heads_per_slot; // kv-heads (pairs of them) by the workgroups the chip holds
 };
 
 // Places in the list that can be taken, kv-heads counted once: one per row and one per whole partition of all tokens.
-ADR_BOTH int64_t plan_places(int B, int H, int max_seq_len, bool few)
+ADR_BOTH int64_t plan_places(int B, int H, int max_seq_len, const PlanRule &p)
 {
     const int64_t tiles = (int64_t)B * plan_tiles(max_seq_len);
     const int64_t least = (int64_t)(kSlots / (kShareLeast * H)), most = (int64_t)(kSlots / (kShareMost * H));
-    const int64_t long_ones = least < tiles / kPlanTiles ? least : tiles / kPlanTiles;
-    const int64_t places = few ? (int64_t)(kEvenItems / H + 1) : most > long_ones ? most : long_ones;
+    const int64_t long_ones = least < tiles / p.whole ? least : tiles / p.whole;
+    const int64_t places = p.few ? (int64_t)(kEvenItems / H + 1) : most > long_ones ? most : long_ones;
     return (B + places + 2 + 7) / 8 * 8;
 }
 
@@ -104,8 +109,8 @@ ADR_BOTH PlanCut plan_cut(const PlanRule &p, int rows, uint32_t all, uint32_t lo
         }
         return c;
     }
-    if (c.most > kPlanTiles)
-        c.most = larger((uint32_t)ceilf(kShareLeast * slot), kPlanTiles);
+    if (c.most > p.whole)
+        c.most = larger((uint32_t)ceilf(kShareLeast * slot), p.whole);
     c.most = larger(c.most, (uint32_t)(kPlanGrain / kPlanTile));
     return c;
 }

@@ -242,9 +242,9 @@ def test_the_step_choice_names_the_planned_passes():
 SHIM = r"""
 #include "plan_cut.h"
 // The rows of a pass as plan.h cuts them: partitions and tokens of each, and the places of the list.
-extern "C" long cut_rows(int few, int even_tiles, int fill_rounds, int max_parts, int H, int B, int bound, const int *L, int *parts, int *tokens)
+extern "C" long cut_rows(int few, int even_tiles, int fill_rounds, int whole, int max_parts, int H, int B, int bound, const int *L, int *parts, int *tokens)
 {
-    const adr::PlanRule rule = {few, even_tiles, fill_rounds, max_parts, (float)H / adr::kSlots};
+    const adr::PlanRule rule = {few, even_tiles, fill_rounds, max_parts, (uint32_t)whole, (float)H / adr::kSlots};
     uint32_t all = 0, longest = 0;
     int rows = 0;
     for (int b = 0; b < B; ++b) {
@@ -255,7 +255,7 @@ extern "C" long cut_rows(int few, int even_tiles, int fill_rounds, int max_parts
     const adr::PlanCut cut = adr::plan_cut(rule, rows, all, longest);
     for (int b = 0; b < B; ++b)
         parts[b] = adr::plan_parts(L[b], cut, max_parts, tokens[b]);
-    return (long)adr::plan_places(B, H, bound, few);
+    return (long)adr::plan_places(B, H, bound, rule);
 }
 """
 
@@ -269,11 +269,11 @@ def cut_rows(tmp_path_factory):
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off", "-I" + csrc, str(d / "shim.cpp"), "-o", str(d / "shim.so")])
     fn = ctypes.CDLL(str(d / "shim.so")).cut_rows
     fn.restype = ctypes.c_long
-    def call(few, even_tiles, fill_rounds, max_parts, H, bound, L):
+    def call(few, even_tiles, fill_rounds, max_parts, H, bound, L, whole=256):
         L = np.ascontiguousarray(L, dtype=np.int32)
         n, tokens = np.zeros_like(L), np.zeros_like(L)
         at = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-        places = fn(int(few), int(even_tiles), int(fill_rounds), int(max_parts), int(H), len(L), int(bound), at(L), at(n), at(tokens))
+        places = fn(int(few), int(even_tiles), int(fill_rounds), int(whole), int(max_parts), int(H), len(L), int(bound), at(L), at(n), at(tokens))
         return n.astype(np.int64), tokens.astype(np.int64), places
     return call
 
@@ -292,7 +292,7 @@ def test_planned_lists_fit_their_places(cut_rows):
              np.full(B, rng.integers(1, bound + 1)) if kind == 3 else np.where(np.arange(B) % 10, 1, bound) if kind == 4 else
              np.where(np.arange(B) % 3, bound, 0)).astype(np.int64)
         places = min(max(-(-bound // 16) - 1, 3), 4096) if rng.integers(2) else int(rng.integers(3, 40))
-        n, tokens, room = cut_rows(few, rng.integers(8, 65), rng.integers(2), places, H, bound, L)
+        n, tokens, room = cut_rows(few, rng.integers(8, 65), rng.integers(2), places, H, bound, L, whole=256 << rng.integers(2))
         assert (n >= 1).all() and (n <= places).all(), (few, H, B, bound, kind)
         assert (n * tokens >= L).all() and ((n - 1) * tokens <= np.maximum(L - 1, 0)).all(), (few, H, B, bound, kind)
         assert n.sum() <= room and room % 8 == 0, (few, H, B, bound, kind)
@@ -312,3 +312,11 @@ def test_rows_that_fill_up_a_batch_do_not_change_its_cut(cut_rows, fill_rounds):
     tokens = lambda rows, length, even_tiles: int(cut_rows(1, even_tiles, fill_rounds, 63, 8, 8192, [length] * rows)[1][0])
     assert tokens(33, 6000, 24) == 384 and tokens(60, 1000, 48) == 512
     assert tokens(48, 6000, 32) == (2048 if fill_rounds else 512)
+
+
+def test_rows_of_passes_that_the_resident_kernel_served_stay_whole(cut_rows):
+    """512 requests of 5000 tokens and 256 of 8000, 8 kv-heads: whole rows up to 512 tiles there, halves elsewhere."""
+    for rows, length in ((512, 5000), (256, 8000)):
+        for whole, parts in ((256, 2), (512, 1)):
+            n, tokens, _ = cut_rows(0, 0, 1, 15, 8, length, [length] * rows, whole=whole)
+            assert (n == parts).all() and (n * tokens >= length).all()
