@@ -409,7 +409,7 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.max_seq_len = max_seq_len;
     p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule);
     // (behind the list: the merge kernel's partition counts, or the arrivals)
-    const size_t behind = p.rule.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * sizeof(uint32_t);
+    const size_t behind = p.rule.few ? (size_t)B * sizeof(int32_t) : (size_t)B * Hq * adr::kArrivalWords * sizeof(uint32_t);
     return (size_t)p.max_items * sizeof(adr::u32x4) + behind <= (size_t)B * Hq * cache->d * sizeof(float);
 }
 

@@ -49,6 +49,10 @@ __host__ __device__ __forceinline__ int result_waves(int G)
     return G < 2 * kWaves ? (G + 1) / 2 : kWaves;
 }
 
+// Words from one count of a planned pass's arrivals to the next: a line each, since those on one line are taken one by
+// one, 10 ns each (768 requests x 1 kv-head, one of 131072 tokens: 45.3 us with all counts of a row in one line).
+constexpr int kArrivalWords = 32;
+
 // What a debug build (-DADR_DEBUG_BOUNDS) records about table entries and positions that fall
 // outside the pool or the table: how many, and the first one.
 struct BoundsRecord {
@@ -87,7 +91,8 @@ struct DecodeParams {
     int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
     int meet;             //   > 0: the last partition of a row to arrive merges it, in that many slices
     int meet_mask;        //     (MeetWords)
-    uint32_t *arrivals;   //     where a planned pass counts the arrivals, [B][Hq], zeroed ahead (others: see arrive())
+    uint32_t *arrivals;   //     where a planned pass counts the arrivals, [B][Hq] kArrivalWords apart, zeroed ahead
+                          //     (others: see arrive())
     const u32x4 *items;   //   its items in the order they are to be taken (plan.h), or nullptr: by row and stride
     int max_items;        //     places in `items`
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
@@ -131,7 +136,7 @@ __device__ __forceinline__ void clear_meet_words(const MeetWords &m, int b)
 struct PlanParams {
     u32x4 *items; // [max_items], or nullptr: nothing to plan
     int32_t *part_counts; // [B]: partitions of each row, for the merge kernel; nullptr where rows meet inside the pass
-    uint32_t *arrivals;   // there: [B][heads], zeroed for split rows
+    uint32_t *arrivals;   // there: [B][heads], kArrivalWords apart, zeroed for split rows
     int heads;
     const int32_t *seq_lens;
     int B, max_seq_len, max_items;

@@ -332,7 +332,7 @@ __device__ __forceinline__ bool arrive(LateParams p, int b, int first_head, int 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint32_t before = 0;
     if ((threadIdx.x & 63) == 0) {
-        uint32_t *count = PLANNED ? p->arrivals + (int64_t)b * p->Hq + head
+        uint32_t *count = PLANNED ? p->arrivals + ((int64_t)b * p->Hq + head) * kArrivalWords
                                   : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
         before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -86,7 +86,7 @@ __device__ __forceinline__ void plan_row(const PlanParams &p, int b)
         p.part_counts[b] = n;
     if (p.arrivals && n > 1)
         for (int i = threadIdx.x; i < p.heads; i += T)
-            p.arrivals[(int64_t)b * p.heads + i] = 0u;
+            p.arrivals[((int64_t)b * p.heads + i) * kArrivalWords] = 0u;
 }
 
 } // namespace adr
