@@ -383,7 +383,12 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
 // (plan.h: kFew...; figures there) where an append kernel plans on its way and eight partitions are allowed: with
 // four, of which the list takes one's place, 80 short requests 23.2 and 25.1.
 // Without an append kernel to plan on its way a kernel of its own does, and passes for the resident kernel stay
-// with it (adr_decode_kernel_choice).
+// with it (adr_decode_kernel_choice).  That kernel's 4 us are for nothing where the rows would stay whole in a short pass, and
+// where they are of one length; so rows that stay whole without a plan are planned from a bound of kWholeBound tokens
+// for each place on (us adr_kv_append and adr_decode_attention without and with a plan, rows of one length / up to it: 800 rows of
+// 400 34.2 37.4 / -, 1024 of 900 81.7 85.1 / 48.0 49.1, 2048 of 300 56.8 57.0 / 33.6 33.9; 2048 of 1000 172 176 / 98 92, of 1600
+// 279 278 / 153 141, of 2000 345 349 / 190 175, fp8 1280 of 1500 93.6 96.3 / 58.0 54.8).
+constexpr int64_t kWholeBound = 2000;
 bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B, int Hq, int max_seq_len,
                int partition_tokens, unsigned flags, bool step)
 {
@@ -399,7 +404,8 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.heads = Hq;
     p.rule.few = (int64_t)B * H < adr::kSlots;
     p.rule.even_tiles = pass_cut(cache, KERNEL_GRID, B, max_seq_len, partition_tokens, flags).cut / adr::kPageSize;
-    if (p.rule.few && p.rule.even_tiles == 0) // (whole rows)
+    const bool whole_rows = p.rule.even_tiles == 0;
+    if (whole_rows && (p.rule.few || (!step && (int64_t)B * H * max_seq_len < kWholeBound * adr::kSlots)))
         return false;
     p.rule.fill_rounds = cache->dtype == ADR_BF16;
     p.rule.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);

@@ -224,6 +224,32 @@ def test_small_steps_count_in_the_control_area(B, Hkv, G, d, places):
         assert (ws[-128:].view(torch.int32) == 0).all()
 
 
+@gpu
+@pytest.mark.parametrize("entry,B,longest,part,kernels", [
+    ("attention", 100, 400, 64, 1), ("attention", 128, 900, 128, 1), ("attention", 190, 1000, 128, 1),  # whole rows, short passes
+    ("attention", 193, 1000, 128, 2), ("attention", 96, 700, 128, 2),                                   # a plan ahead
+    ("step", 100, 400, 64, 2), ("step", 96, 700, 128, 2), ("step", 96, 700, 256, 3), ("step", 48, 1024, 128, 3)])
+def test_launches_of_a_call(entry, B, longest, part, kernels):
+    """The kernels a call records: no plan of its own for an attention pass whose rows stay whole anyway and are short."""
+    cache = adr.KVCache(*(torch.zeros(longest // 16 + 1, 16, 8, 128, dtype=torch.bfloat16, device="cuda:0") for _ in range(2)))
+    q = torch.zeros(B, 32, 128, dtype=torch.bfloat16, device="cuda:0")
+    out, new = torch.zeros_like(q), torch.zeros(B, 8, 128, dtype=torch.bfloat16, device="cuda:0")
+    table = torch.zeros(B, longest // 16 + 1, dtype=torch.int32, device="cuda:0")
+    lens = torch.full((B,), longest, dtype=torch.int32, device="cuda:0")
+    ws = torch.zeros(adr.adr_decode_workspace_bytes(B, 32, 128, longest, part), dtype=torch.uint8, device="cuda:0")
+    say("launches of %s B=%d" % (entry, B))
+    graph, stream = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        if entry == "step":
+            adr.adr_decode_step(out, q, new, new, cache, table, lens, 0.1, longest, part, ws)
+        else:
+            adr.adr_decode_attention(out, q, cache, table, lens, 0.1, longest, part, ws)
+    nodes = ctypes.c_size_t(0)
+    count = adr.load_library().hipGraphGetNodes  # (the HIP runtime that the library itself is bound to)
+    assert count(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0 and nodes.value == kernels
+
+
 def test_the_step_choice_names_the_planned_passes():
     from test_abi_host import FAKE, cache
     lib = adr.load_library()
