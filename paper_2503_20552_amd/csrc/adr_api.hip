@@ -278,7 +278,8 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     //     one workgroup per item       6     18     44    197            72
     //     resident workgroups         30     35     54    206            79
     // From 2048 on the two meet (397 and 398 with G = 4) and the resident kernel pulls ahead as rows
-    // grow (1610 against 1650 with 4096 pairs of mean length 5000), except in groups of one
+    // grow (1610 against 1650 with 4096 pairs of mean length 5000; adr_decode_step, which plans its passes, serves up
+    // to 2048 requests by item all the same, plan_pass: 1652 and 1628), except in groups of one
     // head, where items of a partition each stay ahead up to 4096 pairs (236 against 248 at 2048), and
     // for rows of up to 2048 tokens, which are then items as they are (2048 rows of 1500 tokens 241
     // against 268, of median 200 74 against 82).
@@ -377,11 +378,15 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
 }
 
 // Is a split pass planned on the device (plan.h), and served by one workgroup per item then?  Where there are
-// at least as many rows as the chip holds workgroups: us a step, in the batch's order and planned, 256 requests x 8
-// kv-heads of median length 1500 406 (the resident kernel) and 379, fp8 223 and 208, of 3000 tokens 525 and 498, 160 of
-// up to 3000 178 and 163, 128 of heavy-tailed lengths 78 and 69, 1500 of median 200 408 and 350.  With 256 rows or more
-// (plan.h: kFew...; figures there) where an append kernel plans on its way and eight partitions are allowed: with
-// four, of which the list takes one's place, 80 short requests 23.2 and 25.1.
+// at least as many rows as the chip holds workgroups: us a step, without a plan and with one, 256 requests x 8
+// kv-heads of median length 1500 400 (the resident kernel) and 372, fp8 218 and 198, of 3000 tokens 528 and 509, 128 of
+// 3000 285 and 260, of heavy-tailed lengths 77 and 68, one of 131072 tokens among 95 of 500 169 and 126; 768 x 1, one of
+// 1000000 among rows of 64, 366 and 150 (a wave goes through its 559 partitions, eight at a time).
+// With a third as many rows (plan_cut.h: kFew...; figures there) where an append kernel plans on its way and eight
+// partitions are allowed.  There the mean is ahead and single shapes are not: of 256 to 304 rows 0.92 to 1.05 of the time
+// without a plan, 0.995 in the mean of 64 shapes (of 320 and more 0.87 to 1.02); with four to seven partitions
+// allowed 0.95 to 1.04, 0.996 over 32 shapes of 288 to 640 rows.
+// No more than kPlanRows requests (plan_cut.h): 2048 x 1 of median length 700 take 292 without a plan and 194, 2049 307.
 // Without an append kernel to plan on its way a kernel of its own does, and passes for the resident kernel stay
 // with it (adr_decode_kernel_choice).  That kernel's 4 us are for nothing where the rows would stay whole in a short pass, and
 // where they are of one length; so rows that stay whole without a plan are planned from a bound of kWholeBound tokens

@@ -80,7 +80,7 @@ ADR_BOTH uint32_t smaller(uint32_t a, uint32_t b) { return a < b ? a : b; }
 // those have `longest` tiles or less.
 struct PlanCut {
     uint32_t most, longest, parts;
-    uint32_t grain; // tokens a partition is a multiple of: two tiles for each of four waves, or one
+    uint32_t grain; // tokens a partition is a multiple of, a power of two: two tiles for each of four waves, or one
 };
 // Partitions of a row of that many tiles.
 ADR_BOTH uint32_t plan_parts(uint32_t tiles, const PlanCut &c)
@@ -123,7 +123,7 @@ ADR_BOTH int plan_parts(int L, const PlanCut &c, int max_parts, int &tokens)
     if (tiles <= c.most)
         return 1;
     const uint32_t n = smaller(plan_parts(tiles, c), (uint32_t)max_parts);
-    tokens = (int)((((uint32_t)L + n - 1) / n + c.grain - 1) / c.grain * c.grain);
+    tokens = (int)((((uint32_t)L + n - 1) / n + c.grain - 1) & ~(c.grain - 1));
     return (int)(((uint32_t)L + tokens - 1) / tokens);
 }
 
