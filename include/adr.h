@@ -151,8 +151,8 @@ int adr_kv_append(const adr_kv_cache *cache, const void *k_new, const void *v_ne
 /* Bytes of workspace for a call of adr_decode_attention / adr_decode_step; depends only on host
  * scalars (0 for sizes that are not positive).  The workspace holds the partitions' results of a
  * split pass (nothing when partition_tokens == 0) and, in its last 256 * (1 + ceil(B / 512))
- * bytes, the call's control area: a status block and the counters the resident kernel hands
- * work out with.  A split pass needs the workspace; an unsplit one may do without (see
+ * bytes, the call's control area: a status block, the counters the resident kernel hands
+ * work out with, and words that a small step keeps while it merges its rows.  A split pass needs the workspace; an unsplit one may do without (see
  * "Concurrency" above).  The contents need no initialisation by the caller. */
 size_t adr_decode_workspace_bytes(int B, int Hq, int d, int max_seq_len, int partition_tokens);
 
@@ -214,7 +214,8 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
 /*
  * adr_decode_step -- one decode step of the executor (Sec. 2.1 steps (1)-(2), Sec. 3.2.1): the
  * new token's K/V join the cache and the row attends over all its tokens, the new one included.
- * Same result, in `out`, `lse` and the cache, as
+ * Same result, in `out`, `lse` and the cache (in `out` and `lse` of a planned pass, see below, up to the
+ * order of the floating-point sums), as
  *     adr_kv_append(cache, k_new, v_new, new_row_stride, block_table, max_pages_per_req, pos, B, stream)
  *     with pos[b] = seq_lens[b] - 1, or -1 (append nothing) for an empty row and for a row with
  *     seq_lens[b] > max_seq_len: such a row is attended up to the bound, where an older token sits,
@@ -224,14 +225,15 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  *                 q|k|v buffer are fine), 16-byte aligned; read only.
  *   everything else as in adr_decode_attention; seq_lens is the length AFTER the append.
  *
- * In a split pass of 768 (request, kv-head) pairs or more (pairs of kv-heads where d = 64) and at
- * most 2048 requests, under ADR_KERNEL_AUTO and with at least four partitions allowed, the append
- * kernel also orders the requests by length and cuts them by the tokens the batch really has, and
- * one workgroup per item serves them in that order, also where adr_decode_attention takes the
- * resident kernel (which ADR_KERNEL_MFMA names; ADR_GRID_CUS keeps it, too): `out` then equals the
- * two calls' up to the order of the floating-point sums.  adr_decode_attention plans such passes
- * the same where it would take one workgroup per item anyway.  A step of 256 pairs or more with at
- * least eight partitions allowed is planned too (the two calls are not, with the same consequence).
+ * Planned passes: in a split pass of 256 (request, kv-head) pairs or more (pairs of kv-heads where
+ * d = 64) and at most 2048 requests, under ADR_KERNEL_AUTO and with at least eight partitions allowed
+ * (four from 768 pairs on), the append kernel also orders the requests by length and cuts them by the
+ * tokens the batch really has, and one workgroup per item serves them in that order, also where
+ * adr_decode_attention takes the resident kernel (which ADR_KERNEL_MFMA names; ADR_GRID_CUS keeps
+ * it, too).  adr_decode_attention plans passes of 768 pairs or more the same where it would take one
+ * workgroup per item anyway, but not short ones whose rows stay whole.  `out` may stand in q's very
+ * place (bf16, rows Hq * d elements apart); an `out` that overlaps q otherwise is served without a
+ * plan, as far as such a call is defined at all.
  *
  * The append kernel runs first, then the attention kernels, all on `stream`; the call saves the
  * caller the positions array (it is seq_lens - 1) and one trip through the binding.  k_new /

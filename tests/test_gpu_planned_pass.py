@@ -169,6 +169,45 @@ def test_a_plan_follows_the_lengths_of_each_replay():
 
 
 @gpu
+@pytest.mark.parametrize("page_size", [32, 64])
+@pytest.mark.parametrize("B,Hkv,G,d,longest", [(100, 8, 4, 128, 700), (100, 16, 2, 64, 700), (40, 8, 4, 128, 1024), (3, 8, 4, 128, 900)])
+@pytest.mark.parametrize("entry", ["step", "attention"])
+def test_larger_pages(page_size, B, Hkv, G, d, longest, entry):
+    """Pages of two and four tiles, whose partitions may begin inside a page, in every kind of pass."""
+    b = make(107 + B, G * Hkv, Hkv, d, lengths(max(B, 14), longest, "mixed")[:B], page_size=page_size)
+    b.seq_lens[0] = longest
+    b = make(107 + B, G * Hkv, Hkv, d, b.seq_lens, page_size=page_size)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
+    say("pages of %d B=%d d=%d %s" % (page_size, B, d, entry))
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    out, lse = run(b, cache, 128, longest, entry)
+    assert compare(out, lse, ref, ref_lse, what="pages of %d" % page_size)[0] <= ATOL
+
+
+@gpu
+@pytest.mark.parametrize("B,Hkv,G,d,longest", [(100, 8, 4, 128, 700), (100, 16, 2, 64, 700), (40, 8, 4, 128, 1024), (3, 8, 4, 128, 900), (3, 8, 2, 64, 900)])
+@pytest.mark.parametrize("where", [0, 1, -1])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_values_that_are_not_finite_meet(B, Hkv, G, d, longest, where, dtype):
+    """Infinities and NaN in the values of one token, in a row's first, second or last partition: they come through the
+    merge in their own columns and nowhere else."""
+    b = make(109 + B, G * Hkv, Hkv, d, lengths(max(B, 14), longest, "mixed")[:B])
+    b.seq_lens[0] = longest
+    b = make(109 + B, G * Hkv, Hkv, d, b.seq_lens)
+    ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
+    at = {0: 3, 1: longest // 3, -1: longest - 2}[where]
+    b.v_cache[b.block_table[0, at // 16], at % 16, :, 5] = float("inf")
+    b.v_cache[b.block_table[0, at // 16], at % 16, :, 6] = -float("inf")
+    b.v_cache[b.block_table[0, at // 16], at % 16, :, 7] = NAN
+    say("not finite B=%d d=%d at %d" % (B, d, at))
+    out, lse = run(b, adr.KVCache(dev(b.k_cache), dev(b.v_cache)), 128, longest, "step", dtype)
+    assert (out[0, :, 5] == float("inf")).all() and (out[0, :, 6] == -float("inf")).all() and torch.isnan(out[0, :, 7]).all()
+    out[0, :, 5:8] = torch.as_tensor(ref[0, :, 5:8]).to(out)
+    # (bf16: half a unit in the last place of values below 8)
+    assert compare(out, lse, ref, ref_lse, what="the rest")[0] <= (ATOL if dtype == torch.float32 else ATOL + 2.0 ** -6)
+
+
+@gpu
 @pytest.mark.parametrize("B,longest", [(2, 3000), (40, 4096), (100, 700)])
 @pytest.mark.parametrize("entry", ["step", "attention"])
 def test_out_in_the_place_of_an_input(B, longest, entry):
