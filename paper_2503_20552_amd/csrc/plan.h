@@ -53,48 +53,27 @@ __device__ __forceinline__ void group_reduce(uint32_t (&v)[N], Op op)
 template <int T>
 __device__ __forceinline__ void plan_row(const PlanParams &p, int b)
 {
-    const auto clamp = [&](int L) { return max(min(L, p.max_seq_len), 0); };
-    const int mine = clamp(p.seq_lens[b]);
-    // All lengths, kBatch of a thread's loaded side by side, and the first batch once for both sweeps: each trip to them is
-    // a microsecond in the append kernel's chain (one by one, a step of 288 requests x 1 kv-head, fp8, 42.3 us and
-    // not 41.4).
-    constexpr int kBatch = 8;
-    int first[kBatch];
-    const auto load = [&](int (&L)[kBatch], int i0) {
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            L[u] = i0 + u * T < p.B ? p.seq_lens[i0 + u * T] : 0;
-    };
-    const auto sweep = [&](auto each) {
-        for (int i0 = threadIdx.x; i0 < p.B; i0 += kBatch * T) {
-            int L[kBatch];
-            if (i0 >= kBatch * T)
-                load(L, i0);
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u)
-                if (i0 + u * T < p.B)
-                    each(i0 + u * T, clamp(i0 < kBatch * T ? first[u] : L[u]));
-        }
-    };
-    load(first, threadIdx.x);
+    const auto length = [&](int i) { return max(min(p.seq_lens[i], p.max_seq_len), 0); };
+    const int mine = length(b);
     uint32_t lengths[3] = {0, 0, 0}; // all tiles, rows with tokens, the longest row's tiles
-    sweep([&](int, int L) {
-        const uint32_t tiles = plan_tiles(L);
+    for (int i = threadIdx.x; i < p.B; i += T) {
+        const uint32_t tiles = plan_tiles(length(i));
         lengths[0] += tiles;
         lengths[1] += tiles > 0;
         lengths[2] = max(lengths[2], tiles);
-    });
+    }
     group_reduce<T>(lengths, [](uint32_t x, uint32_t y) { return max(x, y); });
     const PlanCut cut = plan_cut(p.rule, lengths[1], lengths[0], lengths[2]);
     uint32_t around[2] = {0, 0}; // items ahead of the row's and behind them
     int tokens;
-    sweep([&](int i, int L) {
+    for (int i = threadIdx.x; i < p.B; i += T) {
+        const int L = length(i);
         const uint32_t n = plan_parts(L, cut, p.rule.max_parts, tokens);
         if (L > mine || (L == mine && i < b))
             around[0] += n;
         else if (i != b)
             around[1] += n;
-    });
+    }
     group_reduce<T>(around, [](uint32_t x, uint32_t y) { return x + y; });
     const uint32_t ahead = around[0], behind = around[1];
     const int n = plan_parts(mine, cut, p.rule.max_parts, tokens);
