@@ -329,13 +329,12 @@ template <int HD, bool PLANNED>
 __device__ __forceinline__ bool arrive(LateParams p, int b, int first_head, int n_parts)
 {
     const int head = first_head + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 / (HD / 4);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint32_t *const count = PLANNED ? p->arrivals + ((int64_t)b * p->Hq + head) * kArrivalWords
+                                    : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
+    asm volatile("s_waitcnt vmcnt(0)" ::"s"(count) : "memory"); // (the address is there by then)
     uint32_t before = 0;
-    if ((threadIdx.x & 63) == 0) {
-        uint32_t *count = PLANNED ? p->arrivals + ((int64_t)b * p->Hq + head) * kArrivalWords
-                                  : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
+    if ((threadIdx.x & 63) == 0)
         before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     before = __builtin_amdgcn_readfirstlane(before);
     asm volatile("" ::: "memory");
     return before + 1 == (uint32_t)n_parts;
@@ -786,6 +785,8 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     const bool pair = d == D / 2;
     const int64_t rows = (int64_t)p.B * (pair ? p.Hkv / 2 : p.Hkv);
     p.grid_stride = grid_stride(rows, p.max_parts);
+    if (p.meet && !p.items && p.grid_stride < p.max_parts)
+        return hipErrorInvalidValue; // a workgroup of a pass that merges inside takes one partition
     int64_t units = p.items ? p.max_items : (int64_t)p.B * p.grid_stride;
     if (fp8)
         units = (units + kChiplets - 1) / kChiplets * kChiplets; // (the surplus finds no request)
