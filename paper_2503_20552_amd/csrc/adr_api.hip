@@ -498,6 +498,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     bool meets = split && !(flags & ADR_PARTIALS_ONLY) &&
                  (in_place || !overlap(out, out_bytes, q, ((size_t)(B - 1) * q_row_stride + (size_t)Hq * d) * 2));
     PassCut cut;
+    bool meet_bytes = false;
     adr::PlanParams list;
     list.items = nullptr;
     if (meets && plan_pass(list, cache, kernel, B, Hq, max_seq_len, partition_tokens, flags, nt != nullptr)) {
@@ -520,9 +521,14 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         // items, two of 2000 11.0 and 11.0, of 8000 19.8 and 19.9; beyond, three of 8000 23.7 and 24.2, 37 of median 1000 51.2
         // and 54.5, fp8 256 of 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
         // (24 of them: 15.2 and 15.7, three rows of 24 33.5 and 36.9).
-        const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv);
-        meets = meets && split && nt && kernel == KERNEL_GRID && cut.max_parts <= 16 &&
-                pairs * cut.max_parts <= adr::kSlots / 3 && pairs * adr::result_waves(G) <= adr::kMeetWords;
+        // Rows of few partitions merge inside up to 768 items, too: what the bound makes room for is mostly empty there (23
+        // requests x 4 kv-heads, 3112 tokens in all under a bound of 1024, 17.7 and 14.7).
+        const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv), waves = pairs * adr::result_waves(G);
+        meets = meets && split && nt && kernel == KERNEL_GRID;
+        if (meets && !(cut.max_parts <= 16 && pairs * cut.max_parts <= adr::kSlots / 3 && waves <= adr::kMeetWords)) {
+            meets = cut.max_parts <= 4 && (int64_t)B * cache->Hkv * cut.max_parts <= adr::kSlots && waves <= adr::kMeetBytes;
+            meet_bytes = waves > adr::kMeetWords;
+        }
     }
 
     adr::DecodeParams p;
@@ -569,15 +575,17 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     // The control area must be all zero when the resident kernel starts, when a merge reads the status
     // block, and behind every call that was not told it is (adr.h: a later call may then vouch for it, or
     // the status be read).  A kernel that never touches it clears it on its way; ahead of the resident
-    // one the append kernel does, or else a small kernel.
+    // one, and of counts in bytes, the append kernel does, or else a small kernel.
     const bool counts = meets && !list.items;
+    meet_bytes = meet_bytes && counts;
     const bool clear_control = p.control && !(flags & ADR_WORKSPACE_READY);
-    const bool clear_ahead = clear_control && kernel == KERNEL_STREAM;
+    const bool clear_ahead = clear_control && (kernel == KERNEL_STREAM || meet_bytes);
     p.clear_words = clear_control && !clear_ahead ? plan.control_words() : 0;
 
     p.meet = !meets ? 0 : list.items ? 1 : adr::merge_slices((int64_t)B * Hq, cut.max_parts);
     p.items = list.items;
     p.meet_mask = p.max_parts >= 16 ? 15 : p.max_parts >= 8 ? 7 : p.max_parts >= 4 ? 3 : p.max_parts >= 2 ? 1 : 0;
+    p.meet_bytes = meet_bytes;
     p.arrivals = list.items ? list.arrivals : nullptr;
     p.max_items = list.items ? list.max_items : 0;
 
@@ -603,7 +611,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         ap.B = B;
         ap.clear_words = clear_ahead ? p.control : nullptr; // on its way, for the kernels behind it
         ap.n_clear_words = clear_ahead ? plan.control_words() : 0;
-        ap.meet = {counts ? p.part_lse : nullptr, p.max_parts, p.meet_mask, Hq};
+        ap.meet = {counts && !meet_bytes ? p.part_lse : nullptr, p.max_parts, p.meet_mask, Hq};
         ap.plan = list;
         ap.bounds = p.bounds;
         if (adr::launch_kv_append(ap, fp8, (hipStream_t)stream) != hipSuccess)

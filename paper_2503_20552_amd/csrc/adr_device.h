@@ -41,8 +41,10 @@ enum {
 };
 
 // A small pass of the one-workgroup-per-item kernel that merges its rows itself keeps a word here for each wave of a
-// (request, kv-head) pair, behind the status (arrive() in decode_mfma.hip), and leaves it zero when the row is merged.
+// (request, kv-head) pair, behind the status (arrive() in decode_mfma.hip), or a byte, which is zero ahead of the
+// kernel, and leaves it zero when the row is merged.
 constexpr int kMeetWords = 2 * kControlBlockWords - 1; // (of the two blocks every call has)
+constexpr int kMeetBytes = 4 * kMeetWords;
 // Waves of a workgroup that hold elements of its result, four a thread: of G heads of 128 or 2 G heads of 64.
 __host__ __device__ __forceinline__ int result_waves(int G)
 {
@@ -91,6 +93,7 @@ struct DecodeParams {
     int grid_stride;      // one-workgroup-per-item kernel: workgroups per row and kv-head (set at its launch)
     int meet;             //   > 0: the last partition of a row to arrive merges it, in that many slices
     int meet_mask;        //     (MeetWords)
+    int meet_bytes;       //     1: its arrivals are counted in bytes of the control area
     uint32_t *arrivals;   //     where a planned pass counts the arrivals, [B][Hq] kArrivalWords apart, zeroed ahead
                           //     (others: see arrive())
     const u32x4 *items;   //   its items in the order they are to be taken (plan.h), or nullptr: by row and stride

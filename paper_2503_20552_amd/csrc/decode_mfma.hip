@@ -322,35 +322,48 @@ __device__ __forceinline__ f32x4 load_shared(__amdgpu_buffer_rsrc_t rsrc, int of
 // The counts lie in the call's workspace (not in `out`, which may be any memory a kernel can store to).  A planned pass has
 // words of their own for them in `arrivals`.  Other passes may fill every place of the workspace: there a count takes
 // the lse of the wave's first head in one place of its row (meet_place), and that partition's lse goes to the wave's
-// word in the control area (meet_word), which whoever merges the row, or attends it whole, leaves zero.  (The counts
-// themselves in the control area, whose four lines then take all arrivals of the pass one by one, 10 ns each: one
-// request of 2000 tokens 12.4 us, 10.5 spread over the lines, 9.9 here.)
-template <int HD, bool PLANNED>
-__device__ __forceinline__ bool arrive(LateParams p, int b, int first_head, int n_parts)
+// word in the control area (meet_word), which whoever merges the row, or attends it whole, leaves zero.  Where there are
+// more waves than words the counts themselves are bytes of the control area, neighbours in different lines: its four lines
+// then take all arrivals of the pass one by one, 10 ns each (one request of 2000 tokens, 256 arrivals: 10.5 us, 9.9 with the
+// counts in places of their own), so for rows of few partitions only.
+template <int HD>
+__device__ __forceinline__ int meet_index(LateParams p, int b, int h)
 {
-    const int head = first_head + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 / (HD / 4);
-    uint32_t *const count = PLANNED ? p->arrivals + ((int64_t)b * p->Hq + head) * kArrivalWords
-                                    : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
-    asm volatile("s_waitcnt vmcnt(0)" ::"s"(count) : "memory"); // (the address is there by then)
-    uint32_t before = 0;
-    if ((threadIdx.x & 63) == 0)
-        before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    before = __builtin_amdgcn_readfirstlane(before);
-    asm volatile("" ::: "memory");
-    return before + 1 == (uint32_t)n_parts;
+    const int H = HD == D ? p->Hkv : p->Hkv >> 1;
+    return (b * H + h) * result_waves(p->G) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 template <int HD>
 __device__ __forceinline__ float *meet_word(LateParams p, int b, int h)
 {
-    const int H = HD == D ? p->Hkv : p->Hkv >> 1;
-    return (float *)p->control + 1 + (b * H + h) * result_waves(p->G) + (threadIdx.x >> 6);
+    return (float *)p->control + 1 + meet_index<HD>(p, b, h);
+}
+template <int HD, bool PLANNED>
+__device__ __forceinline__ bool arrive(LateParams p, int b, int h, int first_head, int n_parts)
+{
+    const int head = first_head + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 / (HD / 4);
+    const bool bytes = !PLANNED && p->meet_bytes;
+    const int i = bytes ? meet_index<HD>(p, b, h) : 0, shift = i / kMeetWords * 8;
+    uint32_t *const count = PLANNED ? p->arrivals + ((int64_t)b * p->Hq + head) * kArrivalWords
+                            : bytes ? p->control + 1 + i * 32 % kMeetWords
+                                    : (uint32_t *)(p->part_lse + ((int64_t)b * p->max_parts + meet_place(head, p->meet_mask)) * p->Hq + head);
+    asm volatile("s_waitcnt vmcnt(0)" ::"s"(count) : "memory"); // (the address is there by then)
+    uint32_t before = 0;
+    if ((threadIdx.x & 63) == 0)
+        before = __hip_atomic_fetch_add(count, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = __builtin_amdgcn_readfirstlane(before);
+    asm volatile("" ::: "memory");
+    const bool last = (bytes ? before >> shift & 0xffu : before) + 1 == (uint32_t)n_parts;
+    if (bytes && last && (threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_sub(count, (uint32_t)n_parts << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
 }
 // Where partition `part` of head `head` leaves its lse; `first`: it is the wave's first head.
 template <int HD>
 __device__ __forceinline__ float *lse_word(LateParams p, int b, int h, int part, int head, bool first)
 {
-    return first && part == meet_place(head, p->meet_mask) ? meet_word<HD>(p, b, h)
-                                                           : p->part_lse + ((int64_t)b * p->max_parts + part) * p->Hq + head;
+    return first && !p->meet_bytes && part == meet_place(head, p->meet_mask)
+               ? meet_word<HD>(p, b, h)
+               : p->part_lse + ((int64_t)b * p->max_parts + part) * p->Hq + head;
 }
 
 // The wave's share of a row, merged from its partitions in a fixed order, whichever wave it is: in S slices of every
@@ -361,8 +374,9 @@ __device__ __forceinline__ void merge_share(LateParams p, int b, int h, int firs
 {
     constexpr int QUADS = HD / 4;
     const int counted = first_head + (int)(threadIdx.x >> 6) * 64 / QUADS; // the wave's first head, whose lse stands elsewhere
+    const bool moves = !PLANNED && !p->meet_bytes;
     float *const moved = meet_word<HD>(p, b, h);
-    const int moved_from = PLANNED ? -1 : meet_place(counted, p->meet_mask); //   in that place (lse_word)
+    const int moved_from = !moves ? -1 : meet_place(counted, p->meet_mask); //   in that place (lse_word)
     for (int idx = threadIdx.x; idx < heads * QUADS; idx += NW * 64) {
         const int head = first_head + idx / QUADS;
         const int c4 = (idx % QUADS) * 4;
@@ -446,7 +460,7 @@ __device__ __forceinline__ void merge_share(LateParams p, int b, int h, int firs
         if (p->lse && c4 == 0)
             p->lse[row] = total[0] > 0.f ? top[0] + fast_log2(total[0]) * kLn2 : -INFINITY;
     }
-    if (!PLANNED && (threadIdx.x & 63) == 0) // (for later launches: not written through, which would be waited for, 0.2 us)
+    if (moves && (threadIdx.x & 63) == 0) // (for later launches: not written through, which would be waited for, 0.2 us)
         *moved = 0.f;
 }
 
@@ -736,7 +750,7 @@ void decode_mfma_kernel(const DecodeParams p)
                 }
                 if (late->lse && c4 == 0)
                     late->lse[row] = lse;
-                if (ITEMS == Items::by_row_meet && lane == 0)
+                if (ITEMS == Items::by_row_meet && !late->meet_bytes && lane == 0)
                     *meet_word<HD>(late, b, h) = 0.f;
             } else if (kMeet) {
                 const int64_t row = ((int64_t)b * late->max_parts + part) * late->Hq;
@@ -752,7 +766,7 @@ void decode_mfma_kernel(const DecodeParams p)
                     late->part_lse[row] = lse;
             }
         }
-        if (kMeet && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD, ITEMS == Items::planned_meet>(late, b, h * R, n_parts)) {
+        if (kMeet && n_parts > 1 && wave * 64 < R * QUADS && arrive<HD, ITEMS == Items::planned_meet>(late, b, h, h * R, n_parts)) {
             if (ITEMS == Items::planned_meet)
                 merge_share<HD, true, NW, 1, 8>(late, b, h, h * R, R, n_parts);
             else if (late->meet == 1) // (up to twelve partitions then: merge_slices)
