@@ -485,20 +485,28 @@ void decode_mfma_kernel(const DecodeParams p)
 
     const int stride = ITEMS >= Items::planned_meet ? kNoMore : p.grid_stride;
     // Which (row of the cache h, partition, request) this workgroup starts with.  Consecutive workgroups go
-    // to the eight chiplets in turn.  bf16: kv-heads fastest, so that a page's heads are read side by
-    // side by different chiplets.  fp8: the kv-heads of a partition one after the other on one chiplet --
-    // with eight kv-heads the other order gives a chiplet the same 128 bytes of every 1024, and it
-    // costs 250 against 221 us at 255 requests, 130 against 116 at 128, 141 against 129 at 60
-    // requests of 32 kv-heads (bf16, 256 bytes a piece, is 1 to 2 % faster the first way).
+    // to the eight chiplets in turn, those of a chiplet to its four shader engines.  bf16: kv-heads fastest, so that a
+    // page's heads are read side by side by different chiplets.  fp8: the kv-heads of a partition one after the other
+    // on one chiplet -- with eight kv-heads the other order gives a chiplet the same 128 bytes of every 1024, and it
+    // costs 250 against 221 us at 255 requests, 130 against 116 at 128, 141 against 129 at 60 requests of 32 kv-heads.
+    // Which head comes first changes from partition to partition: the heads are not read at one rate (pieces at
+    // bytes 384 to 511 of every 1024 take a fifth longer in bf16, a third in fp8, whichever chiplet reads them), and a
+    // chiplet or an engine that always had the same ones would end late or, since workgroups are handed out in turn,
+    // hold up the others (fp8: half of the places empty from the middle of the pass on).  The sum of the
+    // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
+    // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
+    // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
     unsigned unit, h;
     if constexpr (FP8) {
-        const unsigned turn = blockIdx.x / kChiplets;
-        h = turn % H;
-        unit = turn / H * kChiplets + blockIdx.x % kChiplets;
+        const unsigned in_chiplet = blockIdx.x / kChiplets;
+        h = in_chiplet % H;
+        unit = in_chiplet / H * kChiplets + blockIdx.x % kChiplets;
     } else {
         h = blockIdx.x % H;
         unit = blockIdx.x / H;
     }
+    const unsigned turn = FP8 ? unit / kChiplets : unit;
+    h = (h + turn + turn / 4 + turn / 16 + turn / 64) % H;
     typedef const __attribute__((address_space(4))) int32_t *const_ptr;
     int b, L, pt, first_part, n_parts;
     if constexpr (ITEMS >= Items::planned_meet) {
