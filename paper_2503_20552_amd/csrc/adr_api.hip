@@ -416,6 +416,7 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.rule.max_parts = (int)std::min<int64_t>(max_parts - 1, 4096);
     p.rule.whole = kernel == KERNEL_STREAM ? adr::kManyTiles : adr::kPlanTiles;
     p.rule.heads_per_slot = (float)H / adr::kSlots;
+    p.by_items = cache->dtype == ADR_BF16;
     p.B = B;
     p.max_seq_len = max_seq_len;
     p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule);
