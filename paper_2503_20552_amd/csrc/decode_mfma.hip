@@ -95,6 +95,7 @@ static int grid_stride(int64_t rows, int max_parts)
     return n > 1 ? (n | 1) : n;
 }
 
+constexpr int kLdsBytes = 160 * 1024; // of a compute unit
 constexpr int kNoMore = 1 << 20; // added to a partition's number: past any row's last
 
 constexpr int kChiplets = 8; // of the GPU; the hardware deals workgroups out to them in turn
@@ -816,8 +817,15 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     if (blocks > 0x7fffffffLL)
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
+    // Planned passes of a bf16 cache run two workgroups to a compute unit, not three (the LDS they ask for holds them to that):
+    // two keep the memory busy, and with three every load waits 8 to 9 us behind the others', the first loads of an item one
+    // after the other.  us a step, three and two: 256 requests x 8 kv-heads 369.6 and 367.0, 64 x 32 232.2 and 230.2, heavy-tailed
+    // lengths 66.2 and 65.6, 39.5 and 38.4, heads of 64 101.1 and 99.7, eight layers of 40 requests 380 and 376, 50 of up to 2000
+    // 75.3 and 73.9 (37 requests, the other way round, 48.6 and 48.9); one: 366, 230, 69, 43, 100, 402, 73.  fp8 (half the bytes in flight) 188 with three or two, 207 with one;
+    // passes without a plan are of either kind (16 requests of 2000 28.7 and 29.4, 28 of up to 6000 64.4 and 63.3).
     auto go = [&](auto kernel, int waves) {
-        kernel<<<grid, waves * 64, (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float)), stream>>>(p);
+        const size_t lds = (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float));
+        kernel<<<grid, waves * 64, p.items && !fp8 ? std::max(lds, (size_t)kLdsBytes / 2) : lds, stream>>>(p);
     };
     // Eight waves to an item where whole rows are items and may be long: a row is then at the mercy of
     // the few waves that share it (us, 4 and 8 waves: 64 requests x 32 kv-heads of up to 4096 tokens 277
