@@ -235,9 +235,11 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  * place (bf16, rows Hq * d elements apart); an `out` that overlaps q otherwise is served without a
  * plan, as far as such a call is defined at all.
  *
- * The append kernel runs first, then the attention kernels, all on `stream`; the call saves the
- * caller the positions array (it is seq_lens - 1) and one trip through the binding.  k_new /
- * v_new must not alias the cache.
+ * The append kernel runs first, then the attention kernels, all on `stream`.  Passes of up to 64
+ * requests and fewer than 768 pairs that are not planned, served by one workgroup per item, append
+ * inside the attention kernel instead, to the same bits (an `out` or `lse` over k_new / v_new keeps the
+ * append kernel).  The call saves the caller the positions array (it is seq_lens - 1) and one trip through
+ * the binding.  k_new / v_new must not alias the cache.
  */
 int adr_decode_step(void *out, adr_dtype out_dtype, float *lse, const void *q, int64_t q_row_stride,
                     const void *k_new, const void *v_new, int64_t new_row_stride,

@@ -499,7 +499,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     bool meets = split && !(flags & ADR_PARTIALS_ONLY) &&
                  (in_place || !overlap(out, out_bytes, q, ((size_t)(B - 1) * q_row_stride + (size_t)Hq * d) * 2));
     PassCut cut;
-    bool meet_bytes = false;
+    bool meet_bytes = false, appends = false;
     adr::PlanParams list;
     list.items = nullptr;
     if (meets && plan_pass(list, cache, kernel, B, Hq, max_seq_len, partition_tokens, flags, nt != nullptr)) {
@@ -515,6 +515,18 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     } else {
         cut = pass_cut(cache, kernel, B, max_seq_len, split ? partition_tokens : 0, flags);
         split = split && cut.max_parts > 1;
+        const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv), waves = pairs * adr::result_waves(G);
+        // Small steps append inside the attention pass (NewTokens in decode_mfma.hip), unless that would read new tokens where
+        // others have written their results.  us a step, with an append kernel and inside: one request x 8 kv-heads of 2000 tokens
+        // 10.0 and 8.8, three of 300 10.5 and 8.8, eight of 300 under a bound of 512 8.2 and 6.9, 24 of median length 1000 32.1
+        // and 30.2, 28 of up to 6000 64.9 and 62.8, fp8 three of 2000 13.5 and 11.6.  (One of 100 tokens under a bound of 8192 6.9
+        // and 7.3: its row is not split, and the merge kernel is launched all the same.)  Up to 64 requests: their pages stand
+        // in one register; and to as many rows as the chip holds workgroups, beyond which 1.7 us count for little.
+        if (nt && kernel == KERNEL_GRID && B <= 64 && pairs < adr::kSlots) {
+            const size_t new_bytes = ((size_t)(B - 1) * nt->row_stride + (size_t)cache->Hkv * d) * 2, lse_bytes = lse ? (size_t)B * Hq * sizeof(float) : 0;
+            appends = !overlap(out, out_bytes, nt->k, new_bytes) && !overlap(out, out_bytes, nt->v, new_bytes) &&
+                      !overlap(lse, lse_bytes, nt->k, new_bytes) && !overlap(lse, lse_bytes, nt->v, new_bytes);
+        }
         // Without a plan, where an append kernel clears the words on its way and each item has a compute unit to itself: an
         // item of a split row keeps its place until its results are in memory and counted, 3 us with the
         // memory busy, and elsewhere others wait for that place (us a step, merged by a kernel of its own and
@@ -523,9 +535,9 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         // and 54.5, fp8 256 of 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
         // (24 of them: 15.2 and 15.7, three rows of 24 33.5 and 36.9).
         // Rows of few partitions merge inside up to 768 items, too: what the bound makes room for is mostly empty there (23
-        // requests x 4 kv-heads, 3112 tokens in all under a bound of 1024, 17.7 and 14.7).
-        const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv), waves = pairs * adr::result_waves(G);
-        meets = meets && split && nt && kernel == KERNEL_GRID;
+        // requests x 4 kv-heads, 3112 tokens in all under a bound of 1024, 17.7 and 14.7).  A pass that appends itself has
+        // nobody to clear the words and takes the merge kernel (that one 10.1 and 9.2, one of 8000 13.6 and 12.1).
+        meets = meets && split && nt && kernel == KERNEL_GRID && !appends;
         if (meets && !(cut.max_parts <= 16 && pairs * cut.max_parts <= adr::kSlots / 3 && waves <= adr::kMeetWords)) {
             meets = cut.max_parts <= 4 && (int64_t)B * cache->Hkv * cut.max_parts <= adr::kSlots && waves <= adr::kMeetBytes;
             meet_bytes = waves > adr::kMeetWords;
@@ -591,6 +603,13 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
     p.max_items = list.items ? list.max_items : 0;
 
     // The new token goes in first: the append kernel, with the token index taken from seq_lens.
+    p.k_new = p.v_new = nullptr;
+    if (appends) {
+        p.k_new = (const uint16_t *)nt->k;
+        p.v_new = (const uint16_t *)nt->v;
+        p.new_row_stride = nt->row_stride;
+        nt = nullptr;
+    }
     if (nt) {
         adr::AppendParams ap;
         ap.k_cache = cache->k;

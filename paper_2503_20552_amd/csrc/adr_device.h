@@ -98,6 +98,8 @@ struct DecodeParams {
                           //     (others: see arrive())
     const u32x4 *items;   //   its items in the order they are to be taken (plan.h), or nullptr: by row and stride
     int max_items;        //     places in `items`
+    const uint16_t *k_new, *v_new; // the step's new tokens, which the pass appends itself, or nullptr
+    int64_t new_row_stride;        //   elements between their request rows
     int grid_cus;         // > 0: size the resident kernel's grid for this many compute units
     BoundsRecord *bounds; // debug builds: where out-of-range entries are recorded (else nullptr)
 };
@@ -204,6 +206,38 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f)
         return (u >> 16) | 0x40u;
     u += 0x7fffu + ((u >> 16) & 1u);
     return u >> 16;
+}
+
+// fp32 -> OCP E4M3 byte, round to nearest even, saturating at +-448, NaN -> 0x7F.
+__device__ __forceinline__ uint32_t f32_to_e4m3(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    const uint32_t sign = (u >> 24) & 0x80u;
+    const uint32_t a = u & 0x7fffffffu;
+    if (a > 0x7f800000u)
+        return 0x7Fu;
+    const float ax = __uint_as_float(a);
+    if (ax >= 464.0f) // halfway between 448 and the next (absent) step: everything above saturates
+        return sign | 0x7Eu;
+    uint32_t code;
+    if (ax < 0.015625f) { // below 2^-6: subnormal codes, spacing 2^-9
+        // adding 2^14 leaves ax/2^-9 rounded (to nearest even) in the low mantissa bits
+        const float t = ax * 512.0f + 12582912.0f; // 1.5 * 2^23
+        code = __float_as_uint(t) - 0x4B400000u;   // 0 .. 8 (8 = the smallest normal)
+    } else {
+        // keep 3 mantissa bits: round the fp32 mantissa at bit 20, nearest even
+        const uint32_t rounded = a + 0x7FFFFu + ((a >> 20) & 1u);
+        code = (rounded >> 20) - ((127u - 7u) << 3);
+        if (code > 0x7Eu)
+            code = 0x7Eu;
+    }
+    return sign | code;
+}
+
+// Scale of a page whose first token has that largest magnitude.
+__device__ __forceinline__ float new_page_scale(float amax)
+{
+    return fmaxf(amax, 9.5367431640625e-07f) * (2.0f / 448.0f); // (2^-20)
 }
 
 // Two fp32 -> two bf16, round to nearest even (one instruction on gfx950).

@@ -273,6 +273,138 @@ __device__ __forceinline__ void attend_two_fp8(WaveState &st, float (&sc)[8], u3
     }
 }
 
+// The kernel's argument block, read where it is asked for: what a partition's end needs of the parameters does not
+// occupy scalar registers through the loop over its tiles (held from the start they did not fit where rows
+// meet: 25 to 60 of them went through vector lanes, 0.5 to 1 us per launch).
+typedef const __attribute__((address_space(4))) DecodeParams *LateParams;
+__device__ __forceinline__ LateParams late_params_of_append()
+{
+    LateParams p = (LateParams)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// ---- a step's new tokens --------------------------------------------------------------------------
+
+// A pass that appends the step's new tokens itself (APPEND; up to 64 requests): where a tile belongs to a page that any request
+// appends to, the new token takes its slot's place in the wave's copy of the tile, and the wave that attends a row's last tile
+// also stores it in the cache.  So every row sees every new token, whichever requests share pages, as if the append had
+// come first, and no launch of its own is waited for.  The pages stand in a register, a request to a lane, and are compared with each
+// tile's.  (Fetched for each row with the first loads of its items, the new tokens came later: 9.4 and 9.9 us for three requests
+// of 300 tokens; at 256 requests' pages in four registers: the same.)
+template <bool FP8, bool PAIR, int NW>
+struct NewTokens {
+    int page; // of the new token of the lane's request, or -1
+
+    __device__ __forceinline__ void ask(const DecodeParams &p, int length)
+    {
+        const int b = threadIdx.x & 63;
+        page = -1;
+        if (b < p.B && length > 0 && length <= p.max_seq_len) { // (append_position, append_page)
+            const int at = (length - 1) >> (4 + p.page_shift);
+            page = p.block_table[(int64_t)b * p.max_pages + at];
+            if ((unsigned)page >= (unsigned)p.num_pages) {
+                if (blockIdx.x == 0 && threadIdx.x < 64)
+                    record_out_of_bounds(p.bounds, 3, b, at, page);
+                page = -1;
+            }
+        }
+    }
+    // The pages are waited for here (behind the first tile's loads).
+    __device__ __forceinline__ void settle() { asm volatile("" : "+v"(page)); }
+    // Nothing asked for beside the tiles is pending where their loop goes on: the compiler would otherwise wait there, for every
+    // tile, for all loads in flight (20 requests in whole rows 26.6 us a step, 35.6 so).
+    static __device__ __forceinline__ void wait_for_all_loads()
+    {
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0), no other counter
+#endif
+    }
+    // put(request, slot in the page) for each request whose new token goes to that page.
+    template <typename Put>
+    __device__ __forceinline__ void each(LateParams p, int of, Put put) const
+    {
+        for (uint64_t m = __ballot(page == of); m; m &= m - 1) {
+            const int b = __ffsll((unsigned long long)m) - 1;
+            const int pos = ((const __attribute__((address_space(4))) int32_t *)p->seq_lens)[b] - 1;
+            put(b, pos & ((kPageSize << p->page_shift) - 1));
+        }
+        wait_for_all_loads();
+    }
+
+    // bf16: a tile of the pool, K in LDS and V in registers (load_page).  last: it is row b's last tile.
+    __device__ __forceinline__ void put_bf16(LateParams p, int h, int tile, char *ktile, PageRegs &regs, int row, bool last) const
+    {
+        const int lane = threadIdx.x & 63, r = lane & 15, j = lane >> 4;
+        const int H = PAIR ? p->Hkv >> 1 : p->Hkv;
+        each(p, tile >> p->page_shift, [&](int b, int in_page) {
+            if (in_page / kPageSize != (tile & ((1 << p->page_shift) - 1)))
+                return;
+            const int slot = in_page % kPageSize;
+            const int64_t src = (int64_t)b * p->new_row_stride + h * D + r * 8;
+            const u32x4 k = *(const u32x4 *)(p->k_new + src), v = *(const u32x4 *)(p->v_new + src);
+            if (j == 0)
+                *(u32x4 *)(ktile + slot * (D * 2) + ((r ^ slot) * 16)) = k;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u == (slot & 3) && j == slot >> 2)
+                    regs.v[u] = v;
+            if (b == row && last && j == 0) {
+                const int64_t dst = (((int64_t)tile * kPageSize + slot) * H + h) * D + r * 8;
+                *(u32x4 *)((uint16_t *)p->k_cache + dst) = k;
+                *(u32x4 *)((uint16_t *)p->v_cache + dst) = v;
+            }
+        });
+    }
+
+    // fp8: tile number t of a stage (K, K, V, V), and the scales its scores and weights take.  A token in slot 0 of its
+    // page also sets the page's scales, for all tiles of the page.
+    __device__ __forceinline__ void put_fp8(LateParams p, int h, int tile, int t, char *stage, float &ks, float &vs, int row, bool last) const
+    {
+        const int lane = threadIdx.x & 63;
+        const int H = PAIR ? p->Hkv >> 1 : p->Hkv;
+        const bool upper = PAIR && (lane & 15) >= p->G;
+        const int of = tile >> p->page_shift;
+        each(p, of, [&](int b, int in_page) {
+            const bool here = in_page / kPageSize == (tile & ((1 << p->page_shift) - 1));
+            if (!here && in_page != 0)
+                return;
+            const int slot = in_page % kPageSize;
+            const bool keep = b == row && last;
+            const int64_t src = (int64_t)b * p->new_row_stride + h * D + lane * 2;
+            const int64_t scale_at = (int64_t)of * p->Hkv + (PAIR ? 2 * h + lane / 32 : h);
+#pragma unroll
+            for (int which = 0; which < 2; ++which) {
+                const uint32_t two = *(const uint32_t *)((which ? p->v_new : p->k_new) + src);
+                const float x0 = bf16_lo(two), x1 = bf16_hi(two);
+                float *const scales = (float *)(which ? p->v_scale : p->k_scale);
+                float scale;
+                if (in_page == 0) {
+                    float amax = fmaxf(fabsf(x0), fabsf(x1));
+#pragma unroll
+                    for (int off = 1; off < (PAIR ? 32 : 64); off <<= 1)
+                        amax = fmaxf(amax, __shfl_xor(amax, off));
+                    scale = new_page_scale(amax);
+                    if (keep && lane % (PAIR ? 32 : 64) == 0)
+                        scales[scale_at] = scale;
+                    const float s0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale), 0));
+                    const float s1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale), 32));
+                    (which ? vs : ks) = upper ? s1 : s0;
+                } else {
+                    scale = scales[scale_at];
+                }
+                if (here) {
+                    const float inv = 1.0f / scale;
+                    const uint16_t bytes = (uint16_t)(f32_to_e4m3(x0 * inv) | (f32_to_e4m3(x1 * inv) << 8));
+                    *(uint16_t *)(stage + (2 * which + t) * kFp8TileBytes + slot * D + (((lane >> 3) ^ (slot & 7)) * 16) + (lane & 7) * 2) = bytes;
+                    if (keep)
+                        *(uint16_t *)((uint8_t *)(which ? p->v_cache : p->k_cache) + (((int64_t)tile * kPageSize + slot) * H + h) * D + lane * 2) = bytes;
+                }
+            }
+        });
+    }
+};
+
 // Where a workgroup's item comes from and where the partitions of a split row meet.  Variants of their own, because
 // what one of them needs costs the others scalar registers: with all in one kernel a step of one
 // request took 10.6 us instead of 10.1.
@@ -283,10 +415,6 @@ enum class Items {
     planned      // listed, merged by the kernel of its own
 };
 
-// The kernel's argument block, read where it is asked for: what a partition's end needs of the parameters does not
-// occupy scalar registers through the loop over its tiles (held from the start they did not fit where rows
-// meet: 25 to 60 of them went through vector lanes, 0.5 to 1 us per launch).
-typedef const __attribute__((address_space(4))) DecodeParams *LateParams;
 template <Items ITEMS>
 __device__ __forceinline__ LateParams late_params()
 {
@@ -465,7 +593,7 @@ __device__ __forceinline__ void merge_share(LateParams p, int b, int h, int firs
         *moved = 0.f;
 }
 
-template <bool FP8, bool PAIR, int NW, Items ITEMS>
+template <bool FP8, bool PAIR, int NW, Items ITEMS, bool APPEND>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2, NW == 4 ? 3 : 8)))
 void decode_mfma_kernel(const DecodeParams p)
 {
@@ -485,6 +613,9 @@ void decode_mfma_kernel(const DecodeParams p)
     const bool upper = PAIR && r >= G;
 
     const int stride = ITEMS >= Items::planned_meet ? kNoMore : p.grid_stride;
+    int length = 0; // of the lane's request (asked for before anything else is waited for)
+    if constexpr (APPEND)
+        length = p.seq_lens[min(lane, p.B - 1)];
     // Which (row of the cache h, partition, request) this workgroup starts with.  Consecutive workgroups go
     // to the eight chiplets in turn, those of a chiplet to its four shader engines.  bf16: kv-heads fastest, so that a
     // page's heads are read side by side by different chiplets.  fp8: the kv-heads of a partition one after the other
@@ -543,6 +674,9 @@ void decode_mfma_kernel(const DecodeParams p)
         ids.start(p, b, t0 / kPageSize + wave, tiles > 0 ? (tiles + NW - 1) / NW : 0);
     };
     start(first_part);
+    NewTokens<FP8, PAIR, NW> fresh;
+    if constexpr (APPEND)
+        fresh.ask(p, length);
 
     // B operand of QK^T: head r's query, chunk order matching the K loads.  (Columns past the last head
     // repeat it, and a column of a pair holds its query in the other kv-head's chunks too: nobody reads
@@ -611,9 +745,10 @@ void decode_mfma_kernel(const DecodeParams p)
         if constexpr (!FP8) if (count > 0) {
             PageRegs A, B;
             u32x4 ka[4];
-            auto issue = [&](int n, PageRegs &regs, char *tile) {
+            int tile_a = 0, tile_b = 0; // where the two lie in the pool
+            auto issue = [&](int n, PageRegs &regs, char *tile, int &page) {
                 uint32_t range = 0;
-                int page = 0;
+                page = 0;
                 if (n < count) {
                     const int t = ids.first + n * NW;
                     page = pool_tile_checked(ids.entry(p, h, n), t, p.num_pages, p.page_shift, p.bounds, b);
@@ -623,17 +758,25 @@ void decode_mfma_kernel(const DecodeParams p)
                           k_lane, v_lane, tok_bytes);
             };
             int tok = t0 + wave * kPageSize + 4 * j;
-            issue(0, A, mine);
+            const auto touch = [&](int n, int tile, char *ktile, PageRegs &regs) {
+                if (APPEND && __any(fresh.page == tile >> p.page_shift))
+                    fresh.put_bf16(late_params_of_append(), h, tile, ktile, regs, b, ids.first + n * NW == (L - 1) / kPageSize);
+            };
+            issue(0, A, mine, tile_a);
+            if constexpr (APPEND)
+                fresh.settle();
             for (int n = 0;;) {
-                issue(n + 1, B, mine + kTileBytes);
+                issue(n + 1, B, mine + kTileBytes, tile_b);
                 wait_older_page();
+                touch(n, tile_a, mine, A);
                 read_k_operand(ka, mine, k_read);
                 attend_page<PAIR>(st, A, ka, qb, p.scale_log2e, 1.f, tok, t1, j, upper);
                 tok += NW * kPageSize;
                 if (++n >= count)
                     break;
-                issue(n + 1, A, mine);
+                issue(n + 1, A, mine, tile_a);
                 wait_older_page();
+                touch(n, tile_b, mine + kTileBytes, B);
                 read_k_operand(ka, mine + kTileBytes, k_read);
                 attend_page<PAIR>(st, B, ka, qb, p.scale_log2e, 1.f, tok, t1, j, upper);
                 tok += NW * kPageSize;
@@ -646,11 +789,13 @@ void decode_mfma_kernel(const DecodeParams p)
         // next two tiles are on their way while these are attended (twelve waves to a compute unit
         // keep up to 96 KB in flight).
         if constexpr (FP8) if (count > 0) {
+            int tiles[2]; // where the two lie in the pool
             auto issue = [&](int n) {
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     uint32_t range = 0;
-                    int page = 0;
+                    int &page = tiles[t];
+                    page = 0;
                     if (n + t < count) {
                         page = pool_tile_checked(ids.entry(p, h, n + t), ids.first + (n + t) * NW, p.num_pages,
                                                  p.page_shift, p.bounds, b);
@@ -663,9 +808,24 @@ void decode_mfma_kernel(const DecodeParams p)
             ids.load_scales(p, h, ids.now, lane, ids.scale_now);
             issue(0);
             ids.settle(ids.scale_now);
+            if constexpr (APPEND)
+                fresh.settle();
             int tok = t0 + wave * kPageSize + 4 * j;
             for (int n = 0; n < count; n += 2) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                // The scales of these two tiles (zero for a tile that is none), before the ids move on.
+                // (n is even, so tile n + 1 belongs to the same sixty-four lanes.)
+                float ks[2], vs[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    ks[t] = PAIR && upper ? ids.scale(ids.SCALES - 2, n + t) : ids.scale(0, n + t);
+                    vs[t] = PAIR && upper ? ids.scale(ids.SCALES - 1, n + t) : ids.scale(1, n + t);
+                }
+                if constexpr (APPEND)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        if (n + t < count && __any(fresh.page == tiles[t] >> p.page_shift))
+                            fresh.put_fp8(late_params_of_append(), h, tiles[t], t, mine, ks[t], vs[t], b, ids.first + (n + t) * NW == (L - 1) / kPageSize);
                 u32x2 ka[4], kb[4], v8[8];
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
@@ -674,14 +834,8 @@ void decode_mfma_kernel(const DecodeParams p)
                 }
                 lds_read_tr8_x8_wait(v_tr, v8);
                 settle_k(ka, kb);
-                // The scales of these two tiles (zero for a tile that is none), before the ids move on.
-                // (n is even, so tile n + 1 belongs to the same sixty-four lanes.)
-                float ks[2], vs[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    ks[t] = p.scale_log2e * (PAIR && upper ? ids.scale(ids.SCALES - 2, n + t) : ids.scale(0, n + t));
-                    vs[t] = PAIR && upper ? ids.scale(ids.SCALES - 1, n + t) : ids.scale(1, n + t);
-                }
+                ks[0] *= p.scale_log2e;
+                ks[1] *= p.scale_log2e;
                 issue(n + 2);
                 const f32x4 sa = scores_fp8<PAIR>(ka, qb, upper), sb = scores_fp8<PAIR>(kb, qb, upper);
                 float sc[8];
@@ -835,13 +989,13 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     auto pick = [&](auto fp8_, auto pair_) {
         constexpr bool F = fp8_.value, P = pair_.value;
         if (wide)
-            go(decode_mfma_kernel<F, P, 8, Items::by_row>, 8);
+            p.k_new ? go(decode_mfma_kernel<F, P, 8, Items::by_row, true>, 8) : go(decode_mfma_kernel<F, P, 8, Items::by_row, false>, 8);
         else if (p.items)
-            p.meet ? go(decode_mfma_kernel<F, P, 4, Items::planned_meet>, 4) : go(decode_mfma_kernel<F, P, 4, Items::planned>, 4);
+            p.meet ? go(decode_mfma_kernel<F, P, 4, Items::planned_meet, false>, 4) : go(decode_mfma_kernel<F, P, 4, Items::planned, false>, 4);
         else if (p.meet)
-            go(decode_mfma_kernel<F, P, 4, Items::by_row_meet>, 4);
+            go(decode_mfma_kernel<F, P, 4, Items::by_row_meet, false>, 4);
         else
-            go(decode_mfma_kernel<F, P, 4, Items::by_row>, 4);
+            p.k_new ? go(decode_mfma_kernel<F, P, 4, Items::by_row, true>, 4) : go(decode_mfma_kernel<F, P, 4, Items::by_row, false>, 4);
     };
     if (fp8)
         pair ? pick(std::true_type(), std::true_type()) : pick(std::true_type(), std::false_type());

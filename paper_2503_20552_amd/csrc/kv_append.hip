@@ -78,32 +78,6 @@ __global__ __launch_bounds__(128) void kv_append_bf16_kernel(const AppendParams 
     }
 }
 
-// fp32 -> OCP E4M3 byte, round to nearest even, saturating at +-448, NaN -> 0x7F.
-__device__ __forceinline__ uint32_t f32_to_e4m3(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    const uint32_t a = u & 0x7fffffffu;
-    if (a > 0x7f800000u)
-        return 0x7Fu;
-    const float ax = __uint_as_float(a);
-    if (ax >= 464.0f) // halfway between 448 and the next (absent) step: everything above saturates
-        return sign | 0x7Eu;
-    uint32_t code;
-    if (ax < 0.015625f) { // below 2^-6: subnormal codes, spacing 2^-9
-        // adding 2^14 leaves ax/2^-9 rounded (to nearest even) in the low mantissa bits
-        const float t = ax * 512.0f + 12582912.0f; // 1.5 * 2^23
-        code = __float_as_uint(t) - 0x4B400000u;   // 0 .. 8 (8 = the smallest normal)
-    } else {
-        // keep 3 mantissa bits: round the fp32 mantissa at bit 20, nearest even
-        const uint32_t rounded = a + 0x7FFFFu + ((a >> 20) & 1u);
-        code = (rounded >> 20) - ((127u - 7u) << 3);
-        if (code > 0x7Eu)
-            code = 0x7Eu;
-    }
-    return sign | code;
-}
-
 // fp8 cache: one wave per (request, kv-head).  Lane i owns elements 2i, 2i+1
 // (d = 128) or element i (d = 64).
 template <int D, Pass PASS>
@@ -143,8 +117,7 @@ __global__ __launch_bounds__(64) void kv_append_fp8_kernel(const AppendParams p)
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1)
                 amax = fmaxf(amax, __shfl_xor(amax, off));
-            amax = fmaxf(amax, 9.5367431640625e-07f); // 2^-20
-            scale = amax * (2.0f / 448.0f);
+            scale = new_page_scale(amax);
             if (lane == 0)
                 scales[(int64_t)page * p.Hkv + h] = scale;
         } else {

@@ -1,0 +1,73 @@
+"""Steps that append the new tokens inside the attention pass (up to 64 requests): against the two calls, bit for bit, with
+requests that share pages in every way a table allows: a page some request appends to read by others before, at and behind the
+new token's slot, a row's own page in its table twice, entries outside the pool, rows beyond the bound."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_20552_amd as adr
+import workloads as W
+from gpu_util import dev, say
+
+pytestmark = pytest.mark.gpu
+
+
+def shared_pages(seed, B, page, longest, pages):
+    """Lengths and a table over a small pool.  No two requests append to one slot, and none beside a token that sets its page's scales."""
+    rng = np.random.default_rng(seed)
+    L = rng.integers(0, longest + 1, B)
+    edges = [1, page, page + 1, longest, 0, 2 * page, longest - 1, 17]
+    L[:len(edges)] = np.minimum(edges, longest)[:B]
+    table = rng.integers(0, pages, (B, -(-longest // page)))
+    first, slots = set(), set()
+    for b in range(B):
+        if L[b] == 0:
+            continue
+        at, slot = divmod(int(L[b]) - 1, page)
+        free = [p for p in rng.permutation(pages) if p not in first and (p, slot) not in slots and (slot or not any(q == p for q, _ in slots))]
+        if not free:
+            L[b] = 0
+            continue
+        table[b, at] = free[0]
+        slots.add((free[0], slot))
+        if slot == 0:
+            first.add(free[0])
+        if b % 3 == 1 and at:
+            table[b, rng.integers(0, at)] = free[0]      # the page it appends to, earlier in its own table
+    if B > 4:
+        table[4, 0] = -3                                 # clamped to page 0, and nothing is appended where the last one is
+        table[2, (max(int(L[2]), 1) - 1) // page] = pages + 9
+    return L.astype(np.int32), table.astype(np.int32)
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", [(128, 4, 2, False), (64, 2, 4, False), (128, 4, 2, True), (64, 2, 4, True), (128, 16, 1, False)])
+@pytest.mark.parametrize("B,longest", [(1, 40), (3, 700), (64, 300), (65, 300)])
+@pytest.mark.parametrize("page,part", [(16, 0), (16, 64), (64, 512)])
+def test_requests_that_share_pages(d, G, Hkv, fp8, B, longest, page, part):
+    pages, Hq, scale = 2 * B + 9, G * Hkv, d ** -0.5
+    gen = torch.Generator().manual_seed(B + longest)
+    data = [torch.randn(pages, page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    scales = [None, None]
+    if fp8:
+        data, scales = map(list, zip(*(W.quantize_pool_fp8(t, np.ones(pages, dtype=bool)) for t in data)))
+    q, k_new, v_new = (dev(torch.randn(B, h, d, generator=gen), torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    for seed in range(3):
+        L, table = shared_pages(seed, B, page, longest, pages)
+        bound = longest - 3 if seed == 2 else longest    # rows beyond it are cut short and append nothing
+        lens, entries = dev(L), dev(table)
+        say("shared pages B=%d d=%d fp8=%s page=%d part=%d seed=%d" % (B, d, fp8, page, part, seed))
+        got = []
+        for one_call in (True, False):
+            cache = adr.KVCache(*([dev(t) for t in data] + [None if s is None else dev(s) for s in scales]))
+            out, lse = torch.full((B, Hq, d), float("nan"), device="cuda:0"), torch.full((B, Hq), float("nan"), device="cuda:0")
+            ws = torch.full((max(adr.adr_decode_workspace_bytes(B, Hq, d, bound, part), 4) // 4,), float("nan"), device="cuda:0")
+            if one_call:
+                adr.adr_decode_step(out, q, k_new, v_new, cache, entries, lens, scale, bound, part, ws, lse)
+            else:
+                adr.adr_kv_append(cache, k_new, v_new, entries, dev(np.where(L > bound, -1, L - 1).astype(np.int32)))
+                adr.adr_decode_attention(out, q, cache, entries, lens, scale, bound, part, ws, lse)
+            torch.cuda.synchronize()
+            got.append([out, lse, cache.k, cache.v] + ([cache.k_scale, cache.v_scale] if fp8 else []))
+        for a, b in zip(*got):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), "seed %d" % seed
+        assert torch.isfinite(got[0][0]).all()
