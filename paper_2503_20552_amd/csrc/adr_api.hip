@@ -302,11 +302,12 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // and 239; four requests of 300 tokens in groups of four 9 and 12; small fp8 passes in groups of two 5 %
     // behind, large ones 20 % ahead) and in large passes of groups of one (fp8
     // 113 and 207, bf16 195 and 223).  Small passes of groups of one are the vector ALUs': with few
-    // items a workgroup's own chain of steps is all there is, and theirs is shorter (four requests x 8
-    // kv-heads of up to 512 tokens 10.2 and 8.6, fp8 11.8 and 9.4; one of 2000 in partitions of 512 12.9
-    // and 11.2).  Up to 32768 tokens that holds for 244 of 252 shapes measured, by 15 % in the median; with
-    // twice as many an fp8 cache is behind in one of four, and from 4096 tokens on whole rows get eight waves
-    // (31 against 46).
+    // items a workgroup's own chain of steps is all there is, and theirs is shorter (append and attention, four
+    // requests x 8 kv-heads of 512 tokens 10.6 and 7.8, fp8 13.0 and 9.4; one of 2000 24 and 15, in partitions of
+    // 256 11.0 and 10.6; the two meet below 256 tokens, 7.5, and there and in partitions of 256 a step, which the item kernel
+    // needs one launch less for, is up to 2 us ahead by item.  The weights, which the vector ALUs keep in fp32, are
+    // the same up to the line all the same.)  With twice as many tokens an fp8 cache was behind in one of four
+    // shapes, by four waves an item.
     const bool few = d == 64 && G == 1 && pairs * max_seq_len <= 32768 && max_seq_len < 4096;
     if (!few && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;

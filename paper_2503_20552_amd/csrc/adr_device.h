@@ -390,23 +390,23 @@ __device__ __forceinline__ void clear_control(uint32_t *control, int words, int 
             control[i] = 0u;
 }
 
-// Combine the kWaves per-wave partial results staged in LDS and write either
+// Combine the NW per-wave partial results staged in LDS and write either
 // the final output row or this partition's (normalised o, lse) pair.
-// sm/sl: [kWaves][G] running max (base 2) and denominator; so: [kWaves][G][D].
-template <int D>
+// sm/sl: [NW][G] running max (base 2) and denominator; so: [NW][G][D].
+template <int D, int NW = kWaves>
 __device__ __forceinline__ void combine_waves_and_store(const DecodeParams &p, const float *sm,
                                                         const float *sl, const float *so, int G,
                                                         int b, int kvh, int part, int n_parts)
 {
-    for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
+    for (int idx = threadIdx.x; idx < G * D; idx += NW * 64) {
         const int g = idx / D, dd = idx - g * D;
         float M = sm[g];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w)
+        for (int w = 1; w < NW; ++w)
             M = fmaxf(M, sm[w * G + g]);
         float acc = 0.f, den = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < NW; ++w) {
             const float f = fast_exp2(sm[w * G + g] - M);
             acc += f * so[(w * G + g) * D + dd];
             den += f * sl[w * G + g];

@@ -1,8 +1,8 @@
 // Decode attention with vector-ALU dot products (any supported shape, bf16 or
 // fp8-e4m3 cache).
 //
-// One workgroup of 4 waves per (request, kv-head, partition).  Wave w streams
-// pages w, w+4, ... of the partition.  A cache row (one token, one kv-head) is
+// One workgroup of NW waves per (request, kv-head, partition).  Wave w streams
+// tiles w, w+NW, ... of the partition.  A cache row (one token, one kv-head) is
 // D bf16 = D/8 chunks of 16 bytes; lane l owns chunk l % (D/8) and token slot
 // l / (D/8) of each 16-byte-per-lane load, so one load instruction fetches
 // 64/(D/8) complete, contiguous rows.  All G q-heads of the group consume the
@@ -13,7 +13,17 @@
 // An fp8 cache keeps the same lane <-> element mapping: a lane's eight elements
 // are 8 bytes, widened by the hardware converter; the page's K scale multiplies
 // the scores and its V scale the weights that enter the V sum.
+//
+// What bounds it, in the small passes of groups of one head of 64 that it is chosen for: the chain of
+// loads a wave goes through, a few of 32 workgroups' turns.  So the pages of a wave's first 64 tiles
+// come in one load beside the length (they used to come a tile at a time, each ahead of its tile), such
+// groups take two tiles a turn, and eight waves share an item.  us, append and attention, four waves and
+// a tile a turn and now: one request x 8 kv-heads of 512 tokens 8.2 and 7.3 (fp8 9.5 and 8.2), of 1024
+// 11.2 and 8.3, of 2000 17.2 and 11.7 (fp8 27 and 15), of 4000 33 and 22; four waves with the rest of it 7.9,
+// 10.3, 15.4, 31; sixteen 7.7, 8.4, 11.3, 19, and behind eight below 512 tokens and with fp8.
 #include "adr_device.h"
+
+#include <type_traits>
 
 namespace adr {
 
@@ -52,12 +62,13 @@ template <> struct Row8<true> {
     }
 };
 
-template <int D, int G, bool FP8>
-__global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParams p)
+template <int D, int G, bool FP8, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_valu_kernel(const DecodeParams p)
 {
     constexpr int LPT = D / 8;          // lanes per token row
     constexpr int TPL = 64 / LPT;       // token rows per load instruction
     constexpr int U = kPageSize / TPL;  // load instructions per page
+    constexpr int AT_ONCE = D == 64 && G == 1 ? 2 : 1; // tiles of a turn
 
     const int Hkv = p.Hkv;
     // (an odd number of workgroups per row and kv-head: consecutive workgroups go to the compute
@@ -67,15 +78,23 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
     const int part = (blockIdx.x / Hkv) % stride;
     const int b = blockIdx.x / (Hkv * stride);
 
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = p.partition_tokens > 0 ? part * p.partition_tokens : 0;
+    const int32_t *bt = p.block_table + (int64_t)b * p.max_pages;
+    // The pages of the wave's next 64 tiles, one to a lane (0 beyond the table).
+    auto pages_from = [&](int tile) {
+        const int at = (tile + lane * NW) >> p.page_shift;
+        return at < p.max_pages ? bt[at] : 0;
+    };
+    int tile = t0 / kPageSize + wave;
+    int pages = pages_from(tile);
+
     const int L = min(p.seq_lens[b], p.max_seq_len);
     const int n_parts = parts_of(L, p.partition_tokens);
     if (part >= n_parts)
         return;
-    const int t0 = p.partition_tokens > 0 ? part * p.partition_tokens : 0;
     const int t1 = p.partition_tokens > 0 ? min(L, t0 + p.partition_tokens) : L;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane % LPT;
     const int j = lane / LPT;
 
@@ -103,31 +122,37 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
     }
 
     const int64_t tok_stride = (int64_t)Hkv * D; // elements between tokens of a page
-    const int32_t *bt = p.block_table + (int64_t)b * p.max_pages;
     const int pg_end = (t1 + kPageSize - 1) / kPageSize;
 
-    for (int pg = t0 / kPageSize + wave; pg < pg_end; pg += kWaves) {
-        const int page = pool_tile_checked(bt[pg >> p.page_shift], pg, p.num_pages, p.page_shift, p.bounds, b); // a 16-token tile
-        const int64_t base = ((int64_t)page * kPageSize * Hkv + kvh) * D + c * 8;
-        Row8<FP8> kr[U], vr[U];
+    // N tiles, tile, tile + NW, ..., whose pages the lanes from `from` on hold.
+    auto turn = [&](auto n, int from) {
+        constexpr int N = decltype(n)::value, R = N * U; // load instructions of K and of V
+        Row8<FP8> kr[R], vr[R];
+        float k_scale[N], v_scale[N];
+        int64_t base[N];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            kr[u].load(p.k_cache, base + (u * TPL + j) * tok_stride);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            vr[u].load(p.v_cache, base + (u * TPL + j) * tok_stride);
-        float k_scale = 1.f, v_scale = 1.f;
-        if (FP8) {
-            k_scale = p.k_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
-            v_scale = p.v_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+        for (int i = 0; i < N; ++i) {
+            const int page = pool_tile_checked(__builtin_amdgcn_readlane(pages, from + i), tile + i * NW, p.num_pages, p.page_shift, p.bounds, b); // a 16-token tile
+            base[i] = ((int64_t)page * kPageSize * Hkv + kvh) * D + c * 8;
+            k_scale[i] = v_scale[i] = 1.f;
+            if (FP8) {
+                k_scale[i] = p.k_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+                v_scale[i] = p.v_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+            }
         }
-
-        float s[U][G];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < R; ++u)
+            kr[u].load(p.k_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            vr[u].load(p.v_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
+
+        float s[R][G];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
             float kf[8];
             kr[u].widen(kf);
-            const bool valid = pg * kPageSize + u * TPL + j < t1;
+            const bool valid = (tile + u / U * NW) * kPageSize + u % U * TPL + j < t1;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float dot = 0.f;
@@ -136,44 +161,58 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
                     dot = fmaf(qf[g][e], kf[e], dot);
                 dot = group_sum<LPT>(dot);
                 if (FP8)
-                    dot *= k_scale;
+                    dot *= k_scale[u / U];
                 s[u][g] = valid ? dot : -INFINITY; // select, so garbage in unwritten slots never spreads
             }
             if (!valid)
                 vr[u].clear();
         }
-        float vf[U][8];
+        float vf[R][8];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < R; ++u)
             vr[u].widen(vf[u]);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             float mn = m[g];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < R; ++u)
                 mn = fmaxf(mn, s[u][g]);
             const float alpha = fast_exp2(m[g] - mn);
             m[g] = mn;
-            float pw[U], ps = 0.f;
+            float pw[R], ps = 0.f;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < R; ++u) {
                 pw[u] = fast_exp2(s[u][g] - mn);
                 ps += pw[u];
             }
             l[g] = l[g] * alpha + ps;
             if (FP8) {
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    pw[u] *= v_scale;
+                for (int u = 0; u < R; ++u)
+                    pw[u] *= v_scale[u / U];
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float acc = o[g][e] * alpha;
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                for (int u = 0; u < R; ++u)
                     acc = fmaf(pw[u], vf[u][e], acc);
                 o[g][e] = acc;
             }
+        }
+        tile += N * NW;
+    };
+    for (int from = 0; tile < pg_end;) {
+        if (from == 64) {
+            pages = pages_from(tile);
+            from = 0;
+        }
+        if (AT_ONCE == 2 && tile + NW < pg_end) {
+            turn(std::integral_constant<int, AT_ONCE>{}, from); // (`from` stays even: a turn of one is the last)
+            from += AT_ONCE;
+        } else {
+            turn(std::integral_constant<int, 1>{}, from);
+            ++from;
         }
     }
 
@@ -201,7 +240,7 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
         l[g] = ls;
     }
 
-    __shared__ float sm[kWaves * G], sl[kWaves * G], so[kWaves * G * D];
+    __shared__ float sm[NW * G], sl[NW * G], so[NW * G * D];
     if (j == 0) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -215,17 +254,17 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const DecodeParam
         }
     }
     __syncthreads();
-    combine_waves_and_store<D>(p, sm, sl, so, G, b, kvh, part, n_parts);
+    combine_waves_and_store<D, NW>(p, sm, sl, so, G, b, kvh, part, n_parts);
     if (blockIdx.x == 0)
         clear_control(p.control, p.clear_words);
 }
 
-#define ADR_VALU_CASE(DD, GG)                                                                     \
+#define ADR_VALU_CASE(DD, GG, NW)                                                                 \
     if (d == DD && G == GG) {                                                                     \
         if (fp8)                                                                                  \
-            decode_valu_kernel<DD, GG, true><<<grid, kThreads, 0, stream>>>(p);                   \
+            decode_valu_kernel<DD, GG, true, NW><<<grid, NW * 64, 0, stream>>>(p);                \
         else                                                                                      \
-            decode_valu_kernel<DD, GG, false><<<grid, kThreads, 0, stream>>>(p);                  \
+            decode_valu_kernel<DD, GG, false, NW><<<grid, NW * 64, 0, stream>>>(p);               \
         return hipGetLastError();                                                                 \
     }
 
@@ -233,14 +272,14 @@ hipError_t launch_decode_valu(const DecodeParams &p, int d, bool fp8, hipStream_
 {
     const int G = p.G;
     const dim3 grid((unsigned)((int64_t)p.B * p.Hkv * (p.max_parts > 1 ? (p.max_parts | 1) : 1)));
-    ADR_VALU_CASE(128, 1)
-    ADR_VALU_CASE(128, 2)
-    ADR_VALU_CASE(128, 4)
-    ADR_VALU_CASE(128, 8)
-    ADR_VALU_CASE(64, 1)
-    ADR_VALU_CASE(64, 2)
-    ADR_VALU_CASE(64, 4)
-    ADR_VALU_CASE(64, 8)
+    ADR_VALU_CASE(128, 1, kWaves)
+    ADR_VALU_CASE(128, 2, kWaves)
+    ADR_VALU_CASE(128, 4, kWaves)
+    ADR_VALU_CASE(128, 8, kWaves)
+    ADR_VALU_CASE(64, 1, 2 * kWaves)
+    ADR_VALU_CASE(64, 2, kWaves)
+    ADR_VALU_CASE(64, 4, kWaves)
+    ADR_VALU_CASE(64, 8, kWaves)
     return hipErrorInvalidValue;
 }
 
