@@ -305,8 +305,8 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // items a workgroup's own chain of steps is all there is, and theirs is shorter (append and attention, four
     // requests x 8 kv-heads of 512 tokens 10.6 and 7.8, fp8 13.0 and 9.4; one of 2000 24 and 15, in partitions of
     // 256 11.0 and 10.6; the two meet below 256 tokens, 7.5, and there and in partitions of 256 a step, which the item kernel
-    // needs one launch less for, is up to 2 us ahead by item.  The weights, which the vector ALUs keep in fp32, are
-    // the same up to the line all the same.)  With twice as many tokens an fp8 cache was behind in one of four
+    // needs one launch less for, is up to 2 us ahead by item; the vector ALUs, which keep the weights in
+    // fp32, serve it all the same).  With twice as many tokens an fp8 cache was behind in one of four
     // shapes, by four waves an item.
     const bool few = d == 64 && G == 1 && pairs * max_seq_len <= 32768 && max_seq_len < 4096;
     if (!few && adr::decode_mfma_supports(d, G, cache->Hkv))

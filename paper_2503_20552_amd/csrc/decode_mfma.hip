@@ -621,13 +621,6 @@ void decode_mfma_kernel(const DecodeParams p)
     // page's heads are read side by side by different chiplets.  fp8: the kv-heads of a partition one after the other
     // on one chiplet -- with eight kv-heads the other order gives a chiplet the same 128 bytes of every 1024, and it
     // costs 250 against 221 us at 255 requests, 130 against 116 at 128, 141 against 129 at 60 requests of 32 kv-heads.
-    // Which head comes first changes from partition to partition: the heads are not read at one rate (pieces at
-    // bytes 384 to 511 of every 1024 take a fifth longer in bf16, a third in fp8, whichever chiplet reads them), and a
-    // chiplet or an engine that always had the same ones would end late or, since workgroups are handed out in turn,
-    // hold up the others (fp8: half of the places empty from the middle of the pass on).  The sum of the
-    // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
-    // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
-    // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
     unsigned unit, h;
     if constexpr (FP8) {
         const unsigned in_chiplet = blockIdx.x / kChiplets;
@@ -637,8 +630,6 @@ void decode_mfma_kernel(const DecodeParams p)
         h = blockIdx.x % H;
         unit = blockIdx.x / H;
     }
-    const unsigned turn = FP8 ? unit / kChiplets : unit;
-    h = (h + turn + turn / 4 + turn / 16 + turn / 64) % H;
     typedef const __attribute__((address_space(4))) int32_t *const_ptr;
     int b, L, pt, first_part, n_parts;
     if constexpr (ITEMS >= Items::planned_meet) {
@@ -666,6 +657,26 @@ void decode_mfma_kernel(const DecodeParams p)
         n_parts = parts_of(L, pt);
         if (first_part >= n_parts)
             return;
+    }
+    // Which head comes first changes from partition to partition: the heads are not read at one rate (pieces at
+    // bytes 384 to 511 of every 1024 take a fifth longer in bf16, a third in fp8, whichever chiplet reads them), and a
+    // chiplet or an engine that always had the same ones would end late or, since workgroups are handed out in turn,
+    // hold up the others (fp8: half of the places empty from the middle of the pass on).  The sum of the
+    // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
+    // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
+    // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
+    // Not where a pass of a bf16 cache has its workgroups on the chip all at once, one to a compute unit or, of the shorter items
+    // that rows cut by the library are, two: nothing then waits behind a slow one, and heads in place are ahead (in turn and in place, one request
+    // of 8000 tokens x 8 kv-heads 13.7 and 12.1, 3 of 300 9.4 and 8.8, 20 of 300 14.3 and 12.4; whole rows 8 x 1000 tokens 14.2 and 13.1, 32 x 2000 45.0 and
+    // 41.9, heads of 64 8 x 1000 14.8 and 12.0; with 320 whole rows 33.1 and 33.8, 16 requests of 2000 in partitions of 128 27.7
+    // and 29.2).  Each row goes by its own number of partitions.  Nor with fewer than four heads, which share the slow
+    // bytes evenly or not at all (400 requests x 2 149 and 145, 1000 x 2 356 and 348; 200 x 4 147 and 149, 500 x 4 353 and 362).
+    bool in_turn = FP8 || H >= 4;
+    if constexpr (!FP8 && ITEMS < Items::planned_meet)
+        in_turn = in_turn && (unsigned)p.B * H * n_parts > (n_parts == 1 ? 256u : 512u);
+    if (in_turn) {
+        const unsigned turn = FP8 ? unit / kChiplets : unit;
+        h = (h + turn + turn / 4 + turn / 16 + turn / 64) % H;
     }
     TileIds<NW, FP8, PAIR> ids;
     auto start = [&](int part) { // this wave's tiles of a partition
@@ -984,7 +995,7 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     // Eight waves to an item where whole rows are items and may be long: a row is then at the mercy of
     // the few waves that share it (us, 4 and 8 waves: 64 requests x 32 kv-heads of up to 4096 tokens 277
     // and 238, 128 x 8 of up to 8192 260 and 240, heads of 64 202 and 152, fp8 171 and 157; with rows of up
-    // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61).
+    // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61). 
     const bool wide = p.partition_tokens == 0 && p.max_seq_len >= 4096;
     auto pick = [&](auto fp8_, auto pair_) {
         constexpr bool F = fp8_.value, P = pair_.value;
