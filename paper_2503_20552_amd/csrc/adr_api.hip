@@ -302,12 +302,12 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // and 239; four requests of 300 tokens in groups of four 9 and 12; small fp8 passes in groups of two 5 %
     // behind, large ones 20 % ahead) and in large passes of groups of one (fp8
     // 113 and 207, bf16 195 and 223).  Small passes of groups of one are the vector ALUs': with few
-    // items a workgroup's own chain of steps is all there is, and theirs is shorter (append and attention, four
-    // requests x 8 kv-heads of 512 tokens 10.6 and 7.8, fp8 13.0 and 9.4; one of 2000 24 and 15, in partitions of
-    // 256 11.0 and 10.6; the two meet below 256 tokens, 7.5, and there and in partitions of 256 a step, which the item kernel
-    // needs one launch less for, is up to 2 us ahead by item; the vector ALUs, which keep the weights in
-    // fp32, serve it all the same).  With twice as many tokens an fp8 cache was behind in one of four
-    // shapes, by four waves an item.
+    // items a workgroup's own chain of steps is all there is, and theirs is shorter (append and attention, by item and
+    // on the vector ALUs, four requests x 8 kv-heads of 512 tokens 9.4 and 7.5, of 1000 14.2 and 9.8, one of 2000 23.8
+    // and 13.1, 8 of 256 in fp8 9.8 and 7.9; one of 2000 in partitions of 256 11.0 and 10.6).  The two meet below
+    // 256 tokens, 7.5, and there a step, which the item kernel needs one launch less for, is up to 2 us ahead by
+    // item; the vector ALUs, which keep the weights in fp32, serve it all the same.  The line itself lies where an fp8
+    // cache was behind in one shape of four, by items of four waves: 32768 tokens, and 4096 a row.
     const bool few = d == 64 && G == 1 && pairs * max_seq_len <= 32768 && max_seq_len < 4096;
     if (!few && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;

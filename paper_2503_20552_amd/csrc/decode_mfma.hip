@@ -995,8 +995,12 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     // Eight waves to an item where whole rows are items and may be long: a row is then at the mercy of
     // the few waves that share it (us, 4 and 8 waves: 64 requests x 32 kv-heads of up to 4096 tokens 277
     // and 238, 128 x 8 of up to 8192 260 and 240, heads of 64 202 and 152, fp8 171 and 157; with rows of up
-    // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61). 
-    const bool wide = p.partition_tokens == 0 && p.max_seq_len >= 4096;
+    // to 1600 tokens four are ahead: 30 and 33, fp8 45 and 61).  And where there are fewer rows than compute units, however short:
+    // a unit has one row then, and nothing else to run (one request x 8 kv-heads of up to 300 tokens 5.7 and 5.4, 600 6.7 and 5.9,
+    // 2000 12.3 and 10.4, 4000 20.3 and 15.8; 16 x 8 of up to 1000 12.8 and 12.4, 2000 24.6 and 24.1, fp8 12.5 and 11.4, 20.2 and 18.5;
+    // heads of 64 in pairs, 16 x 4 22.4 and 19.6, 32 x 4 24.7 and 24.4; with 256 rows bf16 is the same with either, with 512 of up to 600
+    // tokens 17.9 and 20.3, fp8 12.6 and 17.1).
+    const bool wide = p.partition_tokens == 0 && (p.max_seq_len >= 4096 || rows < 256);
     auto pick = [&](auto fp8_, auto pair_) {
         constexpr bool F = fp8_.value, P = pair_.value;
         if (wide)
