@@ -15,7 +15,7 @@
 // the scores and its V scale the weights that enter the V sum.
 //
 // What bounds it, in the small passes of groups of one head of 64 that it is chosen for: the chain of
-// loads a wave goes through, a few of 32 workgroups' turns.  So the pages of a wave's first 64 tiles
+// loads a wave goes through.  So the pages of a wave's first 64 tiles
 // come in one load beside the length (they used to come a tile at a time, each ahead of its tile), such
 // groups take two tiles a turn, and eight waves share an item.  us, append and attention, four waves and
 // a tile a turn and now: one request x 8 kv-heads of 512 tokens 8.2 and 7.3 (fp8 9.5 and 8.2), of 1024
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(NW * 64) void decode_valu_kernel(const DecodeParams
     constexpr int LPT = D / 8;          // lanes per token row
     constexpr int TPL = 64 / LPT;       // token rows per load instruction
     constexpr int U = kPageSize / TPL;  // load instructions per page
-    constexpr int AT_ONCE = D == 64 && G == 1 ? 2 : 1; // tiles of a turn
+    constexpr bool BY_TWO = D == 64 && G == 1; // two tiles a turn, their pages asked for ahead
 
     const int Hkv = p.Hkv;
     // (an odd number of workgroups per row and kv-head: consecutive workgroups go to the compute
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(NW * 64) void decode_valu_kernel(const DecodeParams
         return at < p.max_pages ? bt[at] : 0;
     };
     int tile = t0 / kPageSize + wave;
-    int pages = pages_from(tile);
+    int pages = BY_TWO ? pages_from(tile) : 0;
 
     const int L = min(p.seq_lens[b], p.max_seq_len);
     const int n_parts = parts_of(L, p.partition_tokens);
@@ -124,95 +124,147 @@ __global__ __launch_bounds__(NW * 64) void decode_valu_kernel(const DecodeParams
     const int64_t tok_stride = (int64_t)Hkv * D; // elements between tokens of a page
     const int pg_end = (t1 + kPageSize - 1) / kPageSize;
 
-    // N tiles, tile, tile + NW, ..., whose pages the lanes from `from` on hold.
-    auto turn = [&](auto n, int from) {
-        constexpr int N = decltype(n)::value, R = N * U; // load instructions of K and of V
-        Row8<FP8> kr[R], vr[R];
-        float k_scale[N], v_scale[N];
-        int64_t base[N];
+    if constexpr (BY_TWO) {
+        // N tiles, tile, tile + NW, ..., whose pages the lanes from `from` on hold.
+        auto turn = [&](auto n, int from) {
+            constexpr int N = decltype(n)::value, R = N * U; // load instructions of K and of V
+            Row8<FP8> kr[R], vr[R];
+            float k_scale[N], v_scale[N];
+            int64_t base[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int page = pool_tile_checked(__builtin_amdgcn_readlane(pages, from + i), tile + i * NW, p.num_pages, p.page_shift, p.bounds, b); // a 16-token tile
-            base[i] = ((int64_t)page * kPageSize * Hkv + kvh) * D + c * 8;
-            k_scale[i] = v_scale[i] = 1.f;
-            if (FP8) {
-                k_scale[i] = p.k_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
-                v_scale[i] = p.v_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+            for (int i = 0; i < N; ++i) {
+                const int page = pool_tile_checked(__builtin_amdgcn_readlane(pages, from + i), tile + i * NW, p.num_pages, p.page_shift, p.bounds, b); // a 16-token tile
+                base[i] = ((int64_t)page * kPageSize * Hkv + kvh) * D + c * 8;
+                k_scale[i] = v_scale[i] = 1.f;
+                if (FP8) {
+                    k_scale[i] = p.k_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+                    v_scale[i] = p.v_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+                }
             }
-        }
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-            kr[u].load(p.k_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-            vr[u].load(p.v_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
-
-        float s[R][G];
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-            float kf[8];
-            kr[u].widen(kf);
-            const bool valid = (tile + u / U * NW) * kPageSize + u % U * TPL + j < t1;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float dot = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    dot = fmaf(qf[g][e], kf[e], dot);
-                dot = group_sum<LPT>(dot);
-                if (FP8)
-                    dot *= k_scale[u / U];
-                s[u][g] = valid ? dot : -INFINITY; // select, so garbage in unwritten slots never spreads
-            }
-            if (!valid)
-                vr[u].clear();
-        }
-        float vf[R][8];
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-            vr[u].widen(vf[u]);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float mn = m[g];
 #pragma unroll
             for (int u = 0; u < R; ++u)
-                mn = fmaxf(mn, s[u][g]);
-            const float alpha = fast_exp2(m[g] - mn);
-            m[g] = mn;
-            float pw[R], ps = 0.f;
+                kr[u].load(p.k_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                vr[u].load(p.v_cache, base[u / U] + (u % U * TPL + j) * tok_stride);
+
+            float s[R], mn = m[0];
 #pragma unroll
             for (int u = 0; u < R; ++u) {
-                pw[u] = fast_exp2(s[u][g] - mn);
-                ps += pw[u];
+                float kf[8], dot = 0.f;
+                kr[u].widen(kf);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    dot = fmaf(qf[0][e], kf[e], dot);
+                dot = group_sum<LPT>(dot) * (FP8 ? k_scale[u / U] : 1.f);
+                const bool valid = (tile + u / U * NW) * kPageSize + u % U * TPL + j < t1;
+                s[u] = valid ? dot : -INFINITY; // select, so garbage in unwritten slots never spreads
+                if (!valid)
+                    vr[u].clear();
+                mn = fmaxf(mn, s[u]);
             }
-            l[g] = l[g] * alpha + ps;
+            const float alpha = fast_exp2(m[0] - mn);
+            m[0] = mn;
+            l[0] *= alpha;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                o[0][e] *= alpha;
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const float w = fast_exp2(s[u] - mn), pw = FP8 ? w * v_scale[u / U] : w;
+                float vf[8];
+                vr[u].widen(vf);
+                l[0] += w;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    o[0][e] = fmaf(pw, vf[e], o[0][e]);
+            }
+            tile += N * NW;
+        };
+        for (int from = 0; tile < pg_end;) {
+            if (from == 64) {
+                pages = pages_from(tile);
+                from = 0;
+            }
+            if (tile + NW < pg_end) {
+                turn(std::integral_constant<int, 2>{}, from);
+                from += 2;
+            } else { // (the last: `from` stays even)
+                turn(std::integral_constant<int, 1>{}, from);
+            }
+        }
+    } else {
+        // (Larger groups keep their registers for the heads.  With the pages of 64 tiles in one load fp8 groups of four were behind, 305
+        // requests 67 and 71 us, 88 of up to 10000 tokens 169 and 173.)
+        for (int pg = t0 / kPageSize + wave; pg < pg_end; pg += NW) {
+            const int page = pool_tile_checked(bt[pg >> p.page_shift], pg, p.num_pages, p.page_shift, p.bounds, b); // a 16-token tile
+            const int64_t base = ((int64_t)page * kPageSize * Hkv + kvh) * D + c * 8;
+            Row8<FP8> kr[U], vr[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                kr[u].load(p.k_cache, base + (u * TPL + j) * tok_stride);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                vr[u].load(p.v_cache, base + (u * TPL + j) * tok_stride);
+            float k_scale = 1.f, v_scale = 1.f;
             if (FP8) {
-#pragma unroll
-                for (int u = 0; u < R; ++u)
-                    pw[u] *= v_scale[u / U];
+                k_scale = p.k_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
+                v_scale = p.v_scale[(int64_t)(page >> p.page_shift) * Hkv + kvh];
             }
+
+            float s[U][G];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float acc = o[g][e] * alpha;
+            for (int u = 0; u < U; ++u) {
+                float kf[8];
+                kr[u].widen(kf);
+                const bool valid = pg * kPageSize + u * TPL + j < t1;
 #pragma unroll
-                for (int u = 0; u < R; ++u)
-                    acc = fmaf(pw[u], vf[u][e], acc);
-                o[g][e] = acc;
+                for (int g = 0; g < G; ++g) {
+                    float dot = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        dot = fmaf(qf[g][e], kf[e], dot);
+                    dot = group_sum<LPT>(dot);
+                    if (FP8)
+                        dot *= k_scale;
+                    s[u][g] = valid ? dot : -INFINITY; // select, so garbage in unwritten slots never spreads
+                }
+                if (!valid)
+                    vr[u].clear();
             }
-        }
-        tile += N * NW;
-    };
-    for (int from = 0; tile < pg_end;) {
-        if (from == 64) {
-            pages = pages_from(tile);
-            from = 0;
-        }
-        if (AT_ONCE == 2 && tile + NW < pg_end) {
-            turn(std::integral_constant<int, AT_ONCE>{}, from); // (`from` stays even: a turn of one is the last)
-            from += AT_ONCE;
-        } else {
-            turn(std::integral_constant<int, 1>{}, from);
-            ++from;
+            float vf[U][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                vr[u].widen(vf[u]);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float mn = m[g];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    mn = fmaxf(mn, s[u][g]);
+                const float alpha = fast_exp2(m[g] - mn);
+                m[g] = mn;
+                float pw[U], ps = 0.f;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    pw[u] = fast_exp2(s[u][g] - mn);
+                    ps += pw[u];
+                }
+                l[g] = l[g] * alpha + ps;
+                if (FP8) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        pw[u] *= v_scale;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float acc = o[g][e] * alpha;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        acc = fmaf(pw[u], vf[u][e], acc);
+                    o[g][e] = acc;
+                }
+            }
         }
     }
 
