@@ -665,15 +665,18 @@ void decode_mfma_kernel(const DecodeParams p)
     // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
     // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
     // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
-    // Not where a pass of a bf16 cache has its workgroups on the chip all at once, one to a compute unit or, of the shorter items
-    // that rows cut by the library are, two: nothing then waits behind a slow one, and heads in place are ahead (in turn and in place, one request
-    // of 8000 tokens x 8 kv-heads 13.7 and 12.1, 3 of 300 9.4 and 8.8, 20 of 300 14.3 and 12.4; whole rows 8 x 1000 tokens 14.2 and 13.1, 32 x 2000 45.0 and
-    // 41.9, heads of 64 8 x 1000 14.8 and 12.0; with 320 whole rows 33.1 and 33.8, 16 requests of 2000 in partitions of 128 27.7
-    // and 29.2).  Each row goes by its own number of partitions.  Nor with fewer than four heads, which share the slow
+    // Not in a pass of a bf16 cache with few items (one to a compute unit) or few tokens: it is on the chip all at once,
+    // nothing waits behind a slow one, and heads in place are ahead (in turn and in place, one request of 8000 tokens x 8 kv-heads 13.7
+    // and 12.1, 3 of 300 9.4 and 8.8, 20 of 300 14.3 and 12.4; whole rows 8 x 1000 tokens 14.2 and 13.1, 32 x 2000 45.0 and
+    // 41.9, heads of 64 8 x 1000 14.8 and 12.0; 512 of up to 224 9.3 and 8.7, of up to 400 13.4 and 13.3, of up to 700 20.7 and 21.4; 320 of 1000
+    // 33.1 and 33.8; 16 requests of 2000 in partitions of 128 27.7 and 29.2).  Each row goes by its own length.
+    // Nor with fewer than four heads, which share the slow
     // bytes evenly or not at all (400 requests x 2 149 and 145, 1000 x 2 356 and 348; 200 x 4 147 and 149, 500 x 4 353 and 362).
     bool in_turn = FP8 || H >= 4;
-    if constexpr (!FP8 && ITEMS < Items::planned_meet)
-        in_turn = in_turn && (unsigned)p.B * H * n_parts > (n_parts == 1 ? 256u : 512u);
+    if constexpr (!FP8 && ITEMS < Items::planned_meet) {
+        const unsigned rows = (unsigned)p.B * H;
+        in_turn = in_turn && rows * n_parts > 256 && (uint64_t)rows * L > 98304;
+    }
     if (in_turn) {
         const unsigned turn = FP8 ? unit / kChiplets : unit;
         h = (h + turn + turn / 4 + turn / 16 + turn / 64) % H;
