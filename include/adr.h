@@ -227,7 +227,7 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  *
  * Planned passes: in a split pass of 256 (request, kv-head) pairs or more (pairs of kv-heads where
  * d = 64) and at most 2048 requests, under ADR_KERNEL_AUTO and with at least eight partitions allowed
- * (four from 768 pairs on), the append kernel also orders the requests by length and cuts them by the
+ * (four from 768 pairs on), the append kernel also lists the pass's items by length and cuts them by the
  * tokens the batch really has, and one workgroup per item serves them in that order, also where
  * adr_decode_attention takes the resident kernel (which ADR_KERNEL_MFMA names; ADR_GRID_CUS keeps
  * it, too).  adr_decode_attention plans passes of 768 pairs or more the same where it would take one

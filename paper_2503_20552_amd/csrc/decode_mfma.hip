@@ -1,13 +1,13 @@
 // Decode attention with the QK^T and PV contractions on the matrix cores
 // (bf16 or fp8 cache; d = 128 with any group size G <= 16, and d = 64 with two kv-heads taken together).
 //
-// One workgroup of 4 waves per (request, kv-head, partition); wave w streams
+// One workgroup of 4 waves (8 for some whole rows) per (request, kv-head, partition); wave w streams
 // tiles w, w+4, ... .  A tile is 16 tokens = one MFMA tile edge (a cache page is one or
 // more of them).  Lane l is (r, j) = (l % 16, l / 16).
 //
-// What bounds it: HBM while it runs (three workgroups to a compute unit keep 96 to 192 KB in flight),
-// and per item a chain of round trips (length, page table, first tile) of about 2 us that the other
-// two workgroups cover only in part.  Three workgroups need the kernel in 168 registers, which the
+// What bounds it: HBM while it runs (three workgroups to a compute unit keep 96 to 192 KB in flight,
+// and two are enough for the planned passes of a bf16 cache, see launch_decode_mfma), and per item a chain of round trips (length,
+// page table, first tile) of about 2 us that the others cover only in part.  Three workgroups need the kernel in 168 registers, which the
 // compiler does not try for by itself (159 + 36 accumulation registers, two workgroups): 410 against
 // 424 us at 256 requests x 8 kv-heads in partitions of 512 tokens, 71 against 76 us at 128
 // requests of 64 heads.  A resident variant (the same loop, three workgroups per unit taking
