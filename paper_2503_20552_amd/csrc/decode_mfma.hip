@@ -5,9 +5,9 @@
 // tiles w, w+4, ... .  A tile is 16 tokens = one MFMA tile edge (a cache page is one or
 // more of them).  Lane l is (r, j) = (l % 16, l / 16).
 //
-// What bounds it: HBM while it runs (three workgroups to a compute unit keep 96 to 192 KB in flight,
-// and two are enough for the planned passes of a bf16 cache, see launch_decode_mfma), and per item a chain of round trips (length,
-// page table, first tile) of about 2 us that the others cover only in part.  Three workgroups need the kernel in 168 registers, which the
+// What bounds it: HBM while it runs (three workgroups to a compute unit keep 96 to 192 KB in flight),
+// and per item a chain of round trips (length, page table, first tile) of about 2 us that the other
+// two workgroups cover only in part.  Three workgroups need the kernel in 168 registers, which the
 // compiler does not try for by itself (159 + 36 accumulation registers, two workgroups): 410 against
 // 424 us at 256 requests x 8 kv-heads in partitions of 512 tokens, 71 against 76 us at 128
 // requests of 64 heads.  A resident variant (the same loop, three workgroups per unit taking
@@ -95,7 +95,6 @@ static int grid_stride(int64_t rows, int max_parts)
     return n > 1 ? (n | 1) : n;
 }
 
-constexpr int kLdsBytes = 160 * 1024; // of a compute unit
 constexpr int kNoMore = 1 << 20; // added to a partition's number: past any row's last
 
 constexpr int kChiplets = 8; // of the GPU; the hardware deals workgroups out to them in turn
@@ -985,15 +984,13 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     if (blocks > 0x7fffffffLL)
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
-    // Planned passes of a bf16 cache run two workgroups to a compute unit, not three (the LDS they ask for holds them to that):
-    // two keep the memory busy, and with three every load waits 8 to 9 us behind the others', the first loads of an item one
-    // after the other.  us a step, three and two: 256 requests x 8 kv-heads 369.6 and 367.0, 64 x 32 232.2 and 230.2, heavy-tailed
-    // lengths 66.2 and 65.6, 39.5 and 38.4, heads of 64 101.1 and 99.7, eight layers of 40 requests 380 and 376, 50 of up to 2000
-    // 75.3 and 73.9 (37 requests, the other way round, 48.6 and 48.9); one: 366, 230, 69, 43, 100, 402, 73.  fp8 (half the bytes in flight) 188 with three or two, 207 with one;
-    // passes without a plan are of either kind (16 requests of 2000 28.7 and 29.4, 28 of up to 6000 64.4 and 63.3).
+    // Three workgroups to a compute unit everywhere.  Planned passes of a bf16 cache held to two (by the LDS they ask for) are
+    // 0.3 to 1 % faster where rows are long (us a step, three and two: 256 requests x 8 kv-heads of median length 1500 370 and 367,
+    // 64 x 32 233.6 and 231.9, heads of 64 101.0 and 99.8, 48 of median 4000 201.8 and 197.7; 37 requests 46.4 and 46.8), but an
+    // item of a short row is all latency, and a third fewer of them at once show: 512 requests of 1 token 23.7 and
+    // 30.9, 256 of 20 15.6 and 18.8, 64 of 100 12.2 and 14.5, 32 of 700 23.0 and 24.9.  The bound does not tell which.
     auto go = [&](auto kernel, int waves) {
-        const size_t lds = (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float));
-        kernel<<<grid, waves * 64, p.items && !fp8 ? std::max(lds, (size_t)kLdsBytes / 2) : lds, stream>>>(p);
+        kernel<<<grid, waves * 64, (size_t)waves * (kWaveBytes + 16 * 2 * sizeof(float)), stream>>>(p);
     };
     // Eight waves to an item where whole rows are items and may be long: a row is then at the mercy of
     // the few waves that share it (us, 4 and 8 waves: 64 requests x 32 kv-heads of up to 4096 tokens 277

@@ -14,7 +14,7 @@
 namespace adr {
 
 constexpr int kPlanTile = 16, kPlanGrain = 128; // tokens of a tile; two tiles for each of four waves
-constexpr int kSlots = 768; // workgroups the shares below are counted in: three to a compute unit, as the fp8 kernel runs (bf16: two)
+constexpr int kSlots = 768; // workgroups the chip holds at once, three to a compute unit
 
 // Tiles of a partition, as a share of what a slot has to do if all do the same: kShareMost of it, or, where that
 // is more than kPlanTiles, as little as kShareLeast (a pass of few and very long rows must be cut
