@@ -395,6 +395,11 @@ PassCut pass_cut(const adr_kv_cache *cache, int kernel, int B, int max_seq_len, 
 // 400 34.2 37.4 / -, 1024 of 900 81.7 85.1 / 48.0 49.1, 2048 of 300 56.8 57.0 / 33.6 33.9; 2048 of 1000 172 176 / 98 92, of 1600
 // 279 278 / 153 141, of 2000 345 349 / 190 175, fp8 1280 of 1500 93.6 96.3 / 58.0 54.8).
 constexpr int64_t kWholeBound = 2000;
+// Tokens of a planned pass, over all kv-heads, from which the heads go in turn (decode_mfma.hip: a shorter pass is on the chip all at
+// once).  us a step, in turn and in place: 32 requests x 8 kv-heads of 300 tokens 13.4 and 12.7, 48 of 100 11.8 and 11.3, 128 of 20 10.7
+// and 10.3, 8 of 1000 x 4 among 56 of one token 14.6 and 13.8; 64 x 8 of 300 18.9 and 19.1, 256 of 100 24.9 and 25.2, 32 of 700
+// 23.1 and 24.1; fp8 48 of 300 14.0 and 14.6, 32 of 300 12.0 and 11.8, 512 of 1 27.3 and 26.9.
+constexpr uint32_t kTurnTokens[2] = {131072, 65536}; // bf16, fp8
 bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B, int Hq, int max_seq_len,
                int partition_tokens, unsigned flags, bool step)
 {
@@ -418,6 +423,7 @@ bool plan_pass(adr::PlanParams &p, const adr_kv_cache *cache, int kernel, int B,
     p.rule.whole = kernel == KERNEL_STREAM ? adr::kManyTiles : adr::kPlanTiles;
     p.rule.heads_per_slot = (float)H / adr::kSlots;
     p.by_items = cache->dtype == ADR_BF16;
+    p.turn_tiles = cache->dtype == ADR_BF16 && H < 4 ? ~0u : kTurnTokens[cache->dtype != ADR_BF16] / (adr::kPageSize * H);
     p.B = B;
     p.max_seq_len = max_seq_len;
     p.max_items = (int)adr::plan_places(B, H, max_seq_len, p.rule);

@@ -145,6 +145,7 @@ struct PlanParams {
     int heads;
     const int32_t *seq_lens;
     int B, max_seq_len, max_items;
+    uint32_t turn_tiles;  // the kv-heads go in turn from that many tiles on
     int by_items;         // ordered by the items' own lengths, not by the rows'
     PlanRule rule;
     BoundsRecord *bounds; // debug builds only

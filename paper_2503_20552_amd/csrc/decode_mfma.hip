@@ -95,6 +95,7 @@ static int grid_stride(int64_t rows, int max_parts)
     return n > 1 ? (n | 1) : n;
 }
 
+constexpr unsigned kTurnRowTokens = 163840; // from that many on, if all rows were as long, its kv-heads go in turn (see the kernel)
 constexpr int kNoMore = 1 << 20; // added to a partition's number: past any row's last
 
 constexpr int kChiplets = 8; // of the GPU; the hardware deals workgroups out to them in turn
@@ -631,11 +632,13 @@ void decode_mfma_kernel(const DecodeParams p)
     }
     typedef const __attribute__((address_space(4))) int32_t *const_ptr;
     int b, L, pt, first_part, n_parts;
+    bool in_turn;
     if constexpr (ITEMS >= Items::planned_meet) {
         const u32x4 item = ((const __attribute__((address_space(4))) u32x4 *)p.items)[unit];
         if (item[0] == kNoRow)
             return;
-        b = item[0];
+        b = item[0] & ~kInTurn;
+        in_turn = item[0] & kInTurn;
         L = item[1];
         pt = item[2];
         first_part = item[3] & 0xffffu;
@@ -656,6 +659,8 @@ void decode_mfma_kernel(const DecodeParams p)
         n_parts = parts_of(L, pt);
         if (first_part >= n_parts)
             return;
+        const unsigned rows = (unsigned)p.B * H;
+        in_turn = FP8 || (H >= 4 && rows * n_parts > 256 && (uint64_t)rows * L > kTurnRowTokens);
     }
     // Which head comes first changes from partition to partition: the heads are not read at one rate (pieces at
     // bytes 384 to 511 of every 1024 take a fifth longer in bf16, a third in fp8, whichever chiplet reads them), and a
@@ -664,18 +669,15 @@ void decode_mfma_kernel(const DecodeParams p)
     // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
     // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
     // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
-    // Not in a pass of a bf16 cache with few items (one to a compute unit) or few tokens: it is on the chip all at once,
-    // nothing waits behind a slow one, and heads in place are ahead (in turn and in place, one request of 8000 tokens x 8 kv-heads 13.7
-    // and 12.1, 3 of 300 9.4 and 8.8, 20 of 300 14.3 and 12.4; whole rows 8 x 1000 tokens 14.2 and 13.1, 32 x 2000 45.0 and
-    // 41.9, heads of 64 8 x 1000 14.8 and 12.0; 512 of up to 224 9.3 and 8.7, of up to 400 13.4 and 13.3, of up to 700 20.7 and 21.4; 320 of 1000
-    // 33.1 and 33.8; 16 requests of 2000 in partitions of 128 27.7 and 29.2).  Each row goes by its own length.
-    // Nor with fewer than four heads, which share the slow
+    // Not in a short pass: it is on the chip all at once, nothing waits behind a slow head, and heads in place are ahead.  A
+    // planned pass goes by the tokens it has (the list says so; adr_api.hip, plan_pass).  Of a bf16 cache without a plan each row goes
+    // by its own length: in place with one item to a compute unit or fewer (in turn and in place, one request of 8000 tokens x 8
+    // kv-heads 13.7 and 12.1, 3 of 300 9.4 and 8.8, 20 of 300 14.3 and 12.4; whole rows 8 x 1000 tokens 14.2 and 13.1, 32 x 2000 45.0
+    // and 41.9, heads of 64 8 x 1000 14.8 and 12.0), and below kTurnRowTokens in a pass of rows as long (whole rows, 512 of up to 224 tokens
+    // 10.2 and 10.0, 384 of up to 400 11.7 and 11.2, 296 of up to 400 11.0 and 10.8; 640 of 300 19.6 and 20.0, 800 of 224 20.0
+    // and 20.6, 1600 of 120 21.6 and 22.1, 1120 of up to 600 33.6 and 36.2).
+    // Nor of a bf16 cache with fewer than four heads, which share the slow
     // bytes evenly or not at all (400 requests x 2 149 and 145, 1000 x 2 356 and 348; 200 x 4 147 and 149, 500 x 4 353 and 362).
-    bool in_turn = FP8 || H >= 4;
-    if constexpr (!FP8 && ITEMS < Items::planned_meet) {
-        const unsigned rows = (unsigned)p.B * H;
-        in_turn = in_turn && rows * n_parts > 256 && (uint64_t)rows * L > 98304;
-    }
     if (in_turn) {
         const unsigned turn = FP8 ? unit / kChiplets : unit;
         h = (h + turn + turn / 4 + turn / 16 + turn / 64) % H;

@@ -22,6 +22,7 @@ namespace adr {
 static_assert(kPlanTile == kPageSize && kPlanGrain == kCutLeast, "");
 
 constexpr uint32_t kNoRow = 0xffffffffu; // in place of an item's row: past the last item
+constexpr uint32_t kInTurn = 1u << 31; // beside it: the kv-heads go in turn (decode_mfma.hip)
 
 // Over a workgroup of T threads, in every thread: the sums of v[0] to v[N - 2], and v[N - 1] by `op` (from 0 on).
 template <int T, int N, typename Op>
@@ -87,9 +88,10 @@ __device__ __forceinline__ void plan_row(const PlanParams &p, int b)
     if (ahead + n > (uint32_t)p.max_items && threadIdx.x == 0) // (no lengths do that: plan_places)
         record_out_of_bounds(p.bounds, 4, b, ahead + n, p.max_items);
     // (The last row's workgroup also marks what is left of the list.)
+    const uint32_t row = b | (lengths[0] >= p.turn_tiles ? kInTurn : 0u);
     const uint32_t end = min(behind ? ahead + n : (uint32_t)p.max_items, (uint32_t)p.max_items);
     for (uint32_t j = threadIdx.x; ahead + j < end; j += T)
-        p.items[ahead + j] = u32x4{j < n ? (uint32_t)b : kNoRow, (uint32_t)mine, (uint32_t)tokens, j | n << 16};
+        p.items[ahead + j] = u32x4{j < n ? row : kNoRow, (uint32_t)mine, (uint32_t)tokens, j | n << 16};
     if (p.part_counts && threadIdx.x == 0)
         p.part_counts[b] = n;
     if (p.arrivals && n > 1)

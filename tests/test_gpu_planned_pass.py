@@ -75,6 +75,31 @@ def test_planned_passes(B, Hkv, G, d, kind, entry):
 
 
 @gpu
+@pytest.mark.parametrize("B,Hkv,d", [(96, 8, 128), (64, 4, 128), (200, 4, 128), (100, 12, 128), (96, 16, 64)])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_heads_go_in_turn_from_so_many_tokens_on(B, Hkv, d, fp8, more):
+    """A tile less than what the pass's heads go in turn from, as many, and one more; each head of each row once."""
+    H = Hkv if d == 128 else Hkv // 2
+    tiles = (65536 if fp8 else 131072) // (16 * H) + more
+    per_row = np.full(B, tiles // B)
+    per_row[:tiles % B] += 1
+    b = make(113 + B + more, 2 * Hkv, Hkv, d, 16 * per_row - np.arange(B) % 7)
+    widen(b, 4096)
+    scales = [None, None]
+    if fp8:
+        b.k_cache, scales[0] = W.quantize_pool_fp8(b.k_cache, b.used)
+        b.v_cache, scales[1] = W.quantize_pool_fp8(b.v_cache, b.used)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache), *(None if t is None else dev(t) for t in scales))
+    new = [dev(torch.randn(B, Hkv, d, generator=torch.Generator().manual_seed(i)), torch.bfloat16) for i in range(2)]
+    say("heads in turn B=%d Hkv=%d d=%d fp8=%s %+d" % (B, Hkv, d, fp8, more))
+    out, lse = run(b, cache, 128, 4096, new=new)
+    ref_kw = dict(k_scale=W.bits(cache.k_scale), v_scale=W.bits(cache.v_scale)) if fp8 else {}
+    ref, ref_lse = oracle_attention(b.q, cache.k.cpu(), cache.v.cpu(), b.block_table, b.seq_lens, b.wl.scale, **ref_kw)
+    assert compare(out, lse, ref, ref_lse, what="in turn")[0] <= ATOL
+
+
+@gpu
 @pytest.mark.parametrize("d,G,Hkv", [(128, 4, 8), (64, 2, 16)])
 @pytest.mark.parametrize("places", [3, 4, 5, 33])
 @pytest.mark.parametrize("entry", ["step", "attention"])
