@@ -71,3 +71,51 @@ def test_requests_that_share_pages(d, G, Hkv, fp8, B, longest, page, part):
         for a, b in zip(*got):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), "seed %d" % seed
         assert torch.isfinite(got[0][0]).all()
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", [(128, 4, 2, False), (64, 2, 4, False), (128, 4, 2, True), (64, 2, 4, True)])
+@pytest.mark.parametrize("page,part", [(16, 0), (16, 64), (64, 512)])
+def test_requests_that_append_to_one_slot(d, G, Hkv, fp8, page, part):
+    """Rows that fill up a batch may all be one token on one page: the last one's token stands for all, in the cache and in what
+    every row attends, as if each had brought that token."""
+    B, longest = 64, 700
+    rng = np.random.default_rng(page + d)
+    L = np.where(np.arange(B) % 8 == 3, rng.integers(page + 2, longest + 1, B), 1)
+    L[[5, 21, 62]] = page + 2                            # three rows behind a page that all of them share
+    L[0] = longest
+    need = -(-L // page)
+    table = np.zeros((B, -(-longest // page)), dtype=np.int64)
+    at = 3
+    for b in range(B):
+        if L[b] == 1:
+            table[b] = 0
+        elif b in (5, 21, 62):
+            table[b, :2] = 1, 2
+        else:
+            table[b, :need[b]] = at + np.arange(need[b])
+            at += need[b]
+    gen = torch.Generator().manual_seed(d)
+    data = [torch.randn(at, page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    scales = [None, None]
+    if fp8:
+        data, scales = map(list, zip(*(W.quantize_pool_fp8(t, np.ones(at, dtype=bool)) for t in data)))
+    q, k_new, v_new = (dev(torch.randn(B, h, d, generator=gen), torch.bfloat16) for h in (G * Hkv, Hkv, Hkv))
+    bring = np.arange(B)
+    bring[L == 1] = np.nonzero(L == 1)[0][-1]
+    bring[[5, 21, 62]] = 62
+    lens, entries, scale = dev(L.astype(np.int32)), dev(table.astype(np.int32)), d ** -0.5
+    say("one slot d=%d fp8=%s page=%d part=%d" % (d, fp8, page, part))
+    got = []
+    for one_call in (True, False):
+        cache = adr.KVCache(*([dev(t) for t in data] + [None if s is None else dev(s) for s in scales]))
+        out, lse = torch.full((B, G * Hkv, d), float("nan"), device="cuda:0"), torch.full((B, G * Hkv), float("nan"), device="cuda:0")
+        ws = torch.full((max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, longest, part), 4) // 4,), float("nan"), device="cuda:0")
+        if one_call:
+            adr.adr_decode_step(out, q, k_new, v_new, cache, entries, lens, scale, longest, part, ws, lse)
+        else:
+            adr.adr_kv_append(cache, k_new[bring].contiguous(), v_new[bring].contiguous(), entries, lens - 1)
+            adr.adr_decode_attention(out, q, cache, entries, lens, scale, longest, part, ws, lse)
+        torch.cuda.synchronize()
+        got.append([out, lse, cache.k, cache.v] + ([cache.k_scale, cache.v_scale] if fp8 else []))
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
