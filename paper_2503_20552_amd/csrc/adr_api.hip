@@ -524,7 +524,7 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         split = split && cut.max_parts > 1;
         const int64_t pairs = (int64_t)B * (d == 64 ? cache->Hkv / 2 : cache->Hkv), waves = pairs * adr::result_waves(G);
         // Small steps append inside the attention pass (NewTokens in decode_mfma.hip), unless that would read new tokens where
-        // others have written their results.  us a step, with an append kernel and inside: one request x 8 kv-heads of 2000 tokens
+        // results or partial results have been written.  us a step, with an append kernel and inside: one request x 8 kv-heads of 2000 tokens
         // 10.0 and 8.8, three of 300 10.5 and 8.8, eight of 300 under a bound of 512 8.2 and 6.9, 24 of median length 1000 32.1
         // and 30.2, 28 of up to 6000 64.9 and 62.8, fp8 three of 2000 13.5 and 11.6.  (One of 100 tokens under a bound of 8192 6.9
         // and 7.3: its row is not split, and the merge kernel is launched all the same.)  Up to 64 requests: their pages stand
@@ -533,8 +533,10 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         // tokens 42.8 and 41.9, fp8 heads of 64 of 12000 75.1 and 78.3, of 30000 179 and 191).
         if (nt && kernel == KERNEL_GRID && B <= 64 && pairs < adr::kSlots && (split || max_seq_len < 4096)) {
             const size_t new_bytes = ((size_t)(B - 1) * nt->row_stride + (size_t)cache->Hkv * d) * 2, lse_bytes = lse ? (size_t)B * Hq * sizeof(float) : 0;
-            appends = !overlap(out, out_bytes, nt->k, new_bytes) && !overlap(out, out_bytes, nt->v, new_bytes) &&
-                      !overlap(lse, lse_bytes, nt->k, new_bytes) && !overlap(lse, lse_bytes, nt->v, new_bytes);
+            const auto apart = [&](const void *written, size_t bytes) {
+                return !overlap(written, bytes, nt->k, new_bytes) && !overlap(written, bytes, nt->v, new_bytes);
+            };
+            appends = apart(out, out_bytes) && apart(lse, lse_bytes) && apart(workspace, workspace_fits ? plan.total() : 0);
         }
         // Without a plan, where an append kernel clears the words on its way and each item has a compute unit to itself: an
         // item of a split row keeps its place until its results are in memory and counted, 3 us with the

@@ -2,6 +2,7 @@
 ABI on cuda:0 and through the fp64 oracle on the same bytes, and compare."""
 from __future__ import annotations
 
+import ctypes
 import sys
 
 import numpy as np
@@ -76,3 +77,15 @@ def oracle_attention(q, k_cache, v_cache, block_table, seq_lens, scale, rows=Non
                                           np.asarray(block_table, dtype=np.int32),
                                           np.asarray(seq_lens, dtype=np.int32), scale, rows=rows, **kw)
     return out, lse
+
+
+def kernels_recorded(call) -> int:
+    """Kernels that `call` launches, as the nodes of a graph it is recorded into."""
+    graph, stream = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    nodes = ctypes.c_size_t(0)
+    count = adr.load_library().hipGraphGetNodes  # (the HIP runtime that the library itself is bound to)
+    assert count(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    return nodes.value

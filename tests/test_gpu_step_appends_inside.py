@@ -7,7 +7,7 @@ import torch
 
 import paper_2503_20552_amd as adr
 import workloads as W
-from gpu_util import dev, say
+from gpu_util import dev, kernels_recorded, say
 
 pytestmark = pytest.mark.gpu
 
@@ -117,5 +117,42 @@ def test_requests_that_append_to_one_slot(d, G, Hkv, fp8, page, part):
             adr.adr_decode_attention(out, q, cache, entries, lens, scale, longest, part, ws, lse)
         torch.cuda.synchronize()
         got.append([out, lse, cache.k, cache.v] + ([cache.k_scale, cache.v_scale] if fp8 else []))
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("B,part,over,kernels", [
+    (64, 0, None, 1), (65, 0, None, 2), (64, 256, None, 2), (65, 256, None, 3),   # with the append inside and, from 65 on, without
+    (64, 0, "out", 2), (64, 256, "out", 3), (64, 0, "lse", 2), (64, 256, "lse", 3), (64, 256, "workspace", 3)])
+def test_which_steps_append_inside(B, part, over, kernels):
+    """The kernels of a step, and its results where they take the place of the new tokens, which must all be read before."""
+    Hkv, G, d, page, bound = 2, 16, 128, 16, 300 if part == 0 else 1000
+    rng = np.random.default_rng(B)
+    L = rng.integers(1, bound + 1, B).astype(np.int32)
+    wide = -(-bound // page)
+    table = rng.permutation(B * wide).reshape(B, wide).astype(np.int32)
+    gen = torch.Generator().manual_seed(B + part)
+    data = [torch.randn(B * wide, page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    q, k_new, v_new = (dev(torch.randn(B, h, d, generator=gen), torch.bfloat16) for h in (G * Hkv, Hkv, Hkv))
+    lens, entries, ws_bytes = dev(L), dev(table), max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, bound, part), 256)
+    say("step route B=%d part=%d over=%s" % (B, part, over))
+    got = []
+    for apart in (True, False):
+        cache = adr.KVCache(*(dev(t) for t in data))
+        ws = torch.full((ws_bytes // 4,), float("nan"), device="cuda:0")
+        out, lse = torch.zeros(B, G * Hkv, d, dtype=torch.bfloat16, device="cuda:0"), torch.zeros(B, G * Hkv, device="cuda:0")
+        new = [k_new.clone(), v_new.clone()]
+        if not apart and over:
+            memory = {"out": out.view(-1), "lse": torch.zeros(B * Hkv * d, dtype=torch.bfloat16, device="cuda:0"), "workspace": ws.view(torch.bfloat16)}[over]
+            if over == "lse":
+                lse = memory.view(torch.float32)[:lse.numel()].view(lse.shape)
+            new[1] = memory[:v_new.numel()].view(v_new.shape)
+            new[1].copy_(v_new)
+        call = lambda: adr.adr_decode_step(out, q, *new, cache, entries, lens, d ** -0.5, bound, part, ws, lse)
+        call()
+        torch.cuda.synchronize()
+        got.append([out, lse, cache.k, cache.v])
+        nodes = kernels_recorded(call)
+    assert nodes == kernels
     for a, b in zip(*got):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
