@@ -238,8 +238,9 @@ int adr_decode_attention_static(void *out, adr_dtype out_dtype, float *lse, cons
  * The append kernel runs first, then the attention kernels, all on `stream`.  Passes of up to 64
  * requests and fewer than 768 pairs that are not planned, served by one workgroup per item, append
  * inside the attention kernel instead, to the same bits (k_new or v_new that share memory with `out`,
- * `lse` or the workspace keep the append kernel, and so do unsplit passes with max_seq_len of 4096 or
- * more).  The call saves the caller the positions array (it is seq_lens - 1) and one trip through
+ * `lse` or the workspace keep the append kernel, and so do passes of an fp8 cache whose partitions may
+ * be long: unsplit ones from max_seq_len 4096 on, those of up to four partitions from 2048 tokens a partition on (d = 64:
+ * 1024), others from 8192 on).  The call saves the caller the positions array (it is seq_lens - 1) and one trip through
  * the binding.  k_new / v_new must not alias the cache.
  */
 int adr_decode_step(void *out, adr_dtype out_dtype, float *lse, const void *q, int64_t q_row_stride,

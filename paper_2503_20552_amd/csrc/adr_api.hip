@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <limits.h>
 
 namespace adr {
 hipError_t launch_kv_append(const AppendParams &p, bool fp8, hipStream_t stream);
@@ -526,12 +527,18 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
         // Small steps append inside the attention pass (NewTokens in decode_mfma.hip), unless that would read new tokens where
         // results or partial results have been written.  us a step, with an append kernel and inside: one request x 8 kv-heads of 2000 tokens
         // 10.0 and 8.8, three of 300 10.5 and 8.8, eight of 300 under a bound of 512 8.2 and 6.9, 24 of median length 1000 32.1
-        // and 30.2, 28 of up to 6000 64.9 and 62.8, fp8 three of 2000 13.5 and 11.6.  (One of 100 tokens under a bound of 8192 6.9
-        // and 7.3: its row is not split, and the merge kernel is launched all the same.)  Up to 64 requests: their pages stand
-        // in one register; and to as many rows as the chip holds workgroups, beyond which 1.7 us count for little.  Not
-        // where long rows stay whole: comparing pages for each of a wave's many tiles costs what the launch did (4 whole rows of 6000
-        // tokens 42.8 and 41.9, fp8 heads of 64 of 12000 75.1 and 78.3, of 30000 179 and 191).
-        if (nt && kernel == KERNEL_GRID && B <= 64 && pairs < adr::kSlots && (split || max_seq_len < 4096)) {
+        // and 30.2, 28 of up to 6000 64.9 and 62.8, fp8 three of 2000 13.5 and 11.6.  One thing is slower, and the arguments do not tell it
+        // from the others: up to three requests that all have 128 tokens or fewer, under bounds that would let them be split; they merged inside the
+        // pass before, and nothing was to merge (replayed 5.8 and 6.2 us, called one by one 6.9 and 7.3; from 130 tokens on 8.3 and 7.5).
+        // Up to 64 requests: their pages stand in one register; and to as many rows as the chip holds workgroups, beyond which 1.7 us
+        // count for little.  Comparing pages costs a wave of an fp8 cache some 0.02 us a tile, and `longest` is what its partition may
+        // have: whole rows (eight waves) of 4000 tokens 32.4 and 30.5, of 6000 in heads of 64 41.8 and 42.5, of 30000 179 and 191; up
+        // to four partitions, which an append kernel's pass may merge inside: heads of 64 in partitions of 512 tokens 13.8 and 13.5, of
+        // 1536 22.4 and 22.7, of 8192 76 and 78, heads of 128 of 1536 20.6 and 20.3, of 2560 26.3 and 26.6; more of them: four rows of 16000
+        // tokens in partitions of up to 4096 27.9 and 26.6.  (bf16, twice the bytes a tile: whole rows of 6000 42.4 and 41.7, of 30000 256 and 255.)
+        const int longest = !split ? max_seq_len : cut.cut ? (max_seq_len + cut.max_parts - 1) / cut.max_parts : cut.tokens;
+        const int too_long = !fp8 ? INT_MAX : !split ? 4096 : cut.max_parts > 4 ? 8192 : d == 64 ? 1024 : 2048;
+        if (nt && kernel == KERNEL_GRID && B <= 64 && pairs < adr::kSlots && longest < too_long) {
             const size_t new_bytes = ((size_t)(B - 1) * nt->row_stride + (size_t)cache->Hkv * d) * 2, lse_bytes = lse ? (size_t)B * Hq * sizeof(float) : 0;
             const auto apart = [&](const void *written, size_t bytes) {
                 return !overlap(written, bytes, nt->k, new_bytes) && !overlap(written, bytes, nt->v, new_bytes);

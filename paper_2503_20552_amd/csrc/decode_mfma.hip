@@ -290,8 +290,9 @@ __device__ __forceinline__ LateParams late_params_of_append()
 // appends to, the new token takes its slot's place in the wave's copy of the tile, and the wave that attends a row's last tile
 // also stores it in the cache.  So every row sees every new token, whichever requests share pages, as if the append had
 // come first, and no launch of its own is waited for.  The pages stand in a register, a request to a lane, and are compared with each
-// tile's.  (Fetched for each row with the first loads of its items, the new tokens came later: 9.4 and 9.9 us for three requests
-// of 300 tokens; at 256 requests' pages in four registers: the same.)
+// tile's.  (The answer is nearly always no, and the compiler is told so: 24 requests x 4 kv-heads of 64 of an fp8 cache in two partitions of
+// 2048 tokens 28.8 us, 27.9 so.  Fetched for each row with the first loads of its items, the new tokens came later: 9.4 and 9.9 us for
+// three requests of 300 tokens; asked for ahead of the row's last tile, no sooner; at 256 requests' pages in four registers: the same.)
 template <bool FP8, bool PAIR, int NW>
 struct NewTokens {
     int page; // of the new token of the lane's request, or -1
@@ -784,7 +785,7 @@ void decode_mfma_kernel(const DecodeParams p)
             };
             int tok = t0 + wave * kPageSize + 4 * j;
             const auto touch = [&](int n, int tile, char *ktile, PageRegs &regs) {
-                if (APPEND && __any(fresh.page == tile >> p.page_shift))
+                if (APPEND && __builtin_expect(__any(fresh.page == tile >> p.page_shift), 0))
                     fresh.put_bf16(late_params_of_append(), h, tile, ktile, regs, b, ids.first + n * NW == (L - 1) / kPageSize);
             };
             issue(0, A, mine, tile_a);
@@ -849,7 +850,7 @@ void decode_mfma_kernel(const DecodeParams p)
                 if constexpr (APPEND)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
-                        if (n + t < count && __any(fresh.page == tiles[t] >> p.page_shift))
+                        if (n + t < count && __builtin_expect(__any(fresh.page == tiles[t] >> p.page_shift), 0))
                             fresh.put_fp8(late_params_of_append(), h, tiles[t], t, mine, ks[t], vs[t], b, ids.first + (n + t) * NW == (L - 1) / kPageSize);
                 u32x2 ka[4], kb[4], v8[8];
 #pragma unroll

@@ -156,3 +156,23 @@ def test_which_steps_append_inside(B, part, over, kernels):
     assert nodes == kernels
     for a, b in zip(*got):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("d,Hkv,fp8,bound,part,kernels", [
+    (128, 8, True, 4095, 0, 1), (128, 8, True, 4096, 0, 2), (128, 8, False, 4096, 0, 1), (64, 16, True, 4096, 0, 2), (64, 16, False, 9000, 0, 1),
+    (128, 8, True, 4094, 2048, 2), (128, 8, True, 4096, 2048, 3), (128, 8, False, 4096, 2048, 2), (64, 16, True, 2046, 1024, 2), (64, 16, True, 2048, 1024, 3),
+    (64, 16, False, 2048, 1024, 2), (128, 8, True, 40000, 8000, 2), (128, 8, True, 49152, 8192, 3), (64, 16, True, 5120, 1024, 2)])
+def test_long_partitions_of_an_fp8_cache_keep_the_append_kernel(d, Hkv, fp8, bound, part, kernels):
+    """By what a partition may have at most; so many rows that none merge inside the pass."""
+    B, G = 48, 16 if d == 128 else 8
+    shape = (bound // 16 + 1, 16, Hkv, d)
+    if fp8:
+        cache = adr.KVCache(*(torch.zeros(shape, dtype=torch.uint8, device="cuda:0") for _ in range(2)), *(torch.ones(shape[0], Hkv, device="cuda:0") for _ in range(2)))
+    else:
+        cache = adr.KVCache(*(torch.zeros(shape, dtype=torch.bfloat16, device="cuda:0") for _ in range(2)))
+    q, new = (torch.zeros(B, h, d, dtype=torch.bfloat16, device="cuda:0") for h in (G * Hkv, Hkv))
+    out, lens = torch.zeros_like(q), torch.full((B,), 17, dtype=torch.int32, device="cuda:0")
+    table = torch.arange(shape[0], dtype=torch.int32, device="cuda:0").repeat(B, 1)
+    ws = torch.zeros(max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, bound, part), 256), dtype=torch.uint8, device="cuda:0")
+    say("append kernel of long partitions d=%d fp8=%s bound=%d part=%d" % (d, fp8, bound, part))
+    assert kernels_recorded(lambda: adr.adr_decode_step(out, q, new, new, cache, table, lens, d ** -0.5, bound, part, ws)) == kernels
