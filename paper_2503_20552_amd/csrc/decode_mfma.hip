@@ -1012,8 +1012,11 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     // a unit has one row then, and nothing else to run (one request x 8 kv-heads of up to 300 tokens 5.7 and 5.4, 600 6.7 and 5.9,
     // 2000 12.3 and 10.4, 4000 20.3 and 15.8; 16 x 8 of up to 1000 12.8 and 12.4, 2000 24.6 and 24.1, fp8 12.5 and 11.4, 20.2 and 18.5;
     // heads of 64 in pairs, 16 x 4 22.4 and 19.6, 32 x 4 24.7 and 24.4; with 256 rows bf16 is the same with either, with 512 of up to 600
-    // tokens 17.9 and 20.3, fp8 12.6 and 17.1).
-    const bool wide = p.partition_tokens == 0 && (p.max_seq_len >= 4096 || rows < 256);
+    // tokens 17.9 and 20.3, fp8 12.6 and 17.1).  Not where all rows are of 128 tokens or fewer, which leaves a wave one tile at most
+    // and twice the results to combine (ten steps replayed: one request x 8 of 40 tokens 46.1 and 47.4, of 126 50.8 and 51.9, fp8 57.6 and
+    // 64.5; five of 150 tokens 30.8 and 29.4, fp8 35.2 and 32.2).  And fp8 rows of 128 bytes leave some units to spare: 31 x 8 of 2000 tokens
+    // 26.6 and 28.9, of 4000 49.0 and 53.8, of median 1000 38.5 and 36.8; 24 x 8 are level or ahead.
+    const bool wide = p.partition_tokens == 0 && (p.max_seq_len >= 4096 || (rows < (fp8 && !pair ? 224 : 256) && p.max_seq_len > 8 * kPageSize));
     auto pick = [&](auto fp8_, auto pair_) {
         constexpr bool F = fp8_.value, P = pair_.value;
         if (wide)

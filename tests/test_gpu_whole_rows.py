@@ -15,3 +15,13 @@ def test_whole_rows_by_item(B, Hkv, d, longest, fp8):
     lens = np.minimum(np.resize(EDGES + [longest, longest - 1, 255, 256, 257], B), longest)
     check(make(B + longest, 2 * Hkv, Hkv, d, lens), "whole rows %d x %d d=%d up to %d fp8=%s" % (B, Hkv, d, longest, fp8),
           fp8=fp8, partition_tokens=0)
+
+
+@pytest.mark.parametrize("B,Hkv,d", [(3, 8, 128), (223, 1, 128), (28, 8, 128), (31, 8, 64)])
+@pytest.mark.parametrize("longest", [128, 129])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_short_whole_rows_by_item(B, Hkv, d, longest, fp8):
+    """A tile for each of eight waves, and the first of a second round; fewer fp8 rows than leave some compute units to spare."""
+    lens = np.minimum(np.resize([longest, 1, 0, 127, 16, 17, longest - 1, 65], B), longest)
+    check(make(B + longest, 2 * Hkv, Hkv, d, lens), "short whole rows %d x %d d=%d up to %d fp8=%s" % (B, Hkv, d, longest, fp8),
+          fp8=fp8, partition_tokens=0)
