@@ -24,3 +24,17 @@ def test_partitions(page_size, pages):
     n = page_size * pages
     b = make(7, 4, 4, 64, [0, 1, n, n + 1, 2 * n + 17, 1000], page_size)
     check(b, "valu partitions of %d page=%d" % (n, page_size), partition_tokens=n, flags=adr.KERNEL_VALU)
+
+
+@pytest.mark.parametrize("longest", [1, 63, 64, 65])
+@pytest.mark.parametrize("page_size,fp8", [(16, False), (64, True), (16, True)])
+def test_rows_of_a_tile_a_wave(longest, page_size, fp8):
+    """Both sides of the line between four waves and eight, in whole rows and in partitions of 64 tokens."""
+    b = make(11 + longest, 6, 6, 64, [min(n, longest) for n in (longest, 0, 1, 15, 16, 17, 33, 48, 49, longest - 1)], page_size)
+    check(b, "valu rows of up to %d page=%d fp8=%s" % (longest, page_size, fp8), fp8=fp8, partition_tokens=0, flags=adr.KERNEL_VALU)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_partitions_of_a_tile_a_wave(fp8):
+    b = make(13, 6, 6, 64, [0, 1, 63, 64, 65, 127, 129, 1000])
+    check(b, "valu partitions of 64 fp8=%s" % fp8, fp8=fp8, partition_tokens=64, flags=adr.KERNEL_VALU)
