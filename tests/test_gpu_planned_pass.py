@@ -1,5 +1,5 @@
 """Passes that are planned on the device (requests ordered by length, cut by the tokens the batch has, rows merged by the
-wave that brings their last partition) and small steps that merge the same way: against the oracle, on workspaces and
+wave that brings their last partition) and unplanned steps that merge the same way: against the oracle, on workspaces and
 outputs full of NaN, at the edges of the rule, under bounds far above the lengths, and with `out` in q's place."""
 import ctypes
 import math
@@ -13,7 +13,7 @@ import torch
 import paper_2503_20552_amd as adr
 import oracle
 import workloads as W
-from gpu_util import ATOL, compare, dev, oracle_attention, say
+from gpu_util import ATOL, compare, dev, kernels_recorded, oracle_attention, say
 from test_gpu_item_kernel import make, widen
 
 gpu = pytest.mark.gpu
@@ -129,11 +129,11 @@ def test_planned_fp8_and_few_places(d, G, Hkv, places, entry):
 @pytest.mark.parametrize("B,kind", [(1, "same"), (3, "mixed"), (100, "mixed")])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("longest", [513, 1100, 1537, 5000])
-def test_steps_that_merge_inside_the_pass(B, kind, dtype, longest):
-    """Also with `out` in q's place."""
+def test_split_steps_small_and_planned(B, kind, dtype, longest):
+    """Steps that append inside and are merged by the merge kernel, and planned ones whose rows meet; also with `out` in q's place."""
     b = make(79 + B, 32, 8, 128, lengths(max(B, 14), longest, kind)[:B] if kind == "mixed" else [longest] * B)
     cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
-    say("merged inside B=%d %s %s longest=%d" % (B, kind, dtype, longest))
+    say("split step B=%d %s %s longest=%d" % (B, kind, dtype, longest))
     bound = max(longest, int(b.seq_lens.max()))
     widen(b, bound)
     ref, ref_lse = oracle_attention(b.q, b.k_cache, b.v_cache, b.block_table, b.seq_lens, b.wl.scale)
@@ -210,10 +210,11 @@ def test_larger_pages(page_size, B, Hkv, G, d, longest, entry):
 
 
 @gpu
-@pytest.mark.parametrize("B,Hkv,G,d,longest", [(100, 8, 4, 128, 700), (100, 16, 2, 64, 700), (40, 8, 4, 128, 1024), (3, 8, 4, 128, 900), (3, 8, 2, 64, 900)])
+@pytest.mark.parametrize("B,Hkv,G,d,longest,part", [(100, 8, 4, 128, 700, 128), (100, 16, 2, 64, 700, 128), (40, 8, 4, 128, 1024, 128), (3, 8, 4, 128, 900, 128),
+                                                    (3, 8, 2, 64, 900, 128), (80, 1, 2, 128, 900, 512), (100, 2, 4, 128, 900, 512)])
 @pytest.mark.parametrize("where", [0, 1, -1])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_values_that_are_not_finite_meet(B, Hkv, G, d, longest, where, dtype):
+def test_values_that_are_not_finite_meet(B, Hkv, G, d, longest, part, where, dtype):
     """Infinities and NaN in the values of one token, in a row's first, second or last partition: they come through the
     merge in their own columns and nowhere else."""
     b = make(109 + B, G * Hkv, Hkv, d, lengths(max(B, 14), longest, "mixed")[:B])
@@ -225,7 +226,7 @@ def test_values_that_are_not_finite_meet(B, Hkv, G, d, longest, where, dtype):
     b.v_cache[b.block_table[0, at // 16], at % 16, :, 6] = -float("inf")
     b.v_cache[b.block_table[0, at // 16], at % 16, :, 7] = NAN
     say("not finite B=%d d=%d at %d" % (B, d, at))
-    out, lse = run(b, adr.KVCache(dev(b.k_cache), dev(b.v_cache)), 128, longest, "step", dtype)
+    out, lse = run(b, adr.KVCache(dev(b.k_cache), dev(b.v_cache)), part, longest, "step", dtype)
     assert (out[0, :, 5] == float("inf")).all() and (out[0, :, 6] == -float("inf")).all() and torch.isnan(out[0, :, 7]).all()
     out[0, :, 5:8] = torch.as_tensor(ref[0, :, 5:8]).to(out)
     # (bf16: half a unit in the last place of values below 8)
@@ -263,30 +264,45 @@ def test_out_in_the_place_of_an_input(B, longest, entry):
     assert torch.equal(host, plain.cpu())
 
 
+# Steps that count arrivals: `over` has the new tokens in the memory of `out`, which keeps small ones from appending inside the
+# attention pass; beyond 64 requests none does.  Kernels: append and attention, and the merge where they would be too many.
+COUNTED = [(True, 1, 8, 16, 128, 16, 2), (True, 15, 8, 1, 128, 2, 2), (True, 16, 8, 1, 128, 2, 2), (True, 24, 8, 4, 128, 4, 2),
+           (True, 31, 8, 4, 128, 3, 2), (True, 32, 8, 4, 128, 3, 3), (True, 15, 8, 8, 128, 4, 2), (True, 16, 8, 8, 128, 4, 3),
+           (True, 15, 8, 8, 128, 6, 3), (True, 24, 16, 4, 64, 2, 2), (True, 48, 8, 1, 128, 2, 2), (True, 20, 8, 4, 64, 4, 2), (True, 3, 2, 1, 128, 7, 2),
+           (False, 65, 1, 1, 128, 3, 2), (False, 80, 1, 2, 128, 2, 2), (False, 80, 2, 2, 64, 3, 2), (False, 127, 1, 1, 128, 2, 2),   # words
+           (False, 128, 1, 1, 128, 2, 2), (False, 96, 1, 4, 128, 4, 2), (False, 97, 2, 1, 128, 3, 2), (False, 66, 3, 4, 128, 2, 2),  # bytes
+           (False, 127, 2, 4, 128, 2, 2), (False, 128, 2, 4, 128, 2, 3), (False, 100, 4, 4, 64, 2, 3)]
+
+
 @gpu
-@pytest.mark.parametrize("B,Hkv,G,d,places", [(1, 8, 16, 128, 16), (15, 8, 1, 128, 2), (16, 8, 1, 128, 2), (24, 8, 4, 128, 4), (31, 8, 4, 128, 3),
-                                              (32, 8, 4, 128, 3), (15, 8, 8, 128, 4), (16, 8, 8, 128, 4), (15, 8, 8, 128, 6), (24, 16, 4, 64, 2),
-                                              (48, 8, 1, 128, 2), (20, 8, 4, 64, 4), (3, 2, 1, 128, 7)])
-def test_small_steps_count_in_the_control_area(B, Hkv, G, d, places):
+@pytest.mark.parametrize("over,B,Hkv,G,d,places,kernels", COUNTED)
+@pytest.mark.parametrize("fp8", [False, True])
+def test_small_steps_count_in_the_control_area(over, B, Hkv, G, d, places, kernels, fp8):
     """Up to 127 waves keep a word of the control area, up to 508 a byte; it is zero behind every call, vouched for or not, and
     the results are the two calls' bit for bit (also where they would be too many: 32 x 8 pairs, 16 x 8 in groups of eight)."""
     part = 512 if places == 2 else 256
     longest = part * places
-    b = make(101 + B, G * Hkv, Hkv, d, [max(longest - 37 * i, 1) for i in range(B)])
-    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache))
-    say("arrivals B=%d Hkv=%d G=%d d=%d" % (B, Hkv, G, d))
+    b = make(101 + B, G * Hkv, Hkv, d, [max(longest - 37 * i, 1 + i % 300) for i in range(B)])
+    scales, new = [None, None], [torch.randn(B, Hkv, d, generator=torch.Generator().manual_seed(i)).to(torch.bfloat16) for i in range(2)]
+    if fp8:
+        b.k_cache, scales[0] = W.quantize_pool_fp8(b.k_cache, b.used)
+        b.v_cache, scales[1] = W.quantize_pool_fp8(b.v_cache, b.used)
+    cache = adr.KVCache(dev(b.k_cache), dev(b.v_cache), *(None if t is None else dev(t) for t in scales))
+    say("arrivals B=%d Hkv=%d G=%d d=%d fp8=%s" % (B, Hkv, G, d, fp8))
+    q, table, lens, new = dev(b.q), dev(b.block_table), dev(b.seq_lens), [dev(t) for t in new]
+    adr.adr_kv_append(cache, *new, table, lens - 1)
     two, two_lse = run(b, cache, part, longest, "attention")
-    at = b.seq_lens - 1
-    page, slot = b.block_table[np.arange(B), at // 16], at % 16
-    new = [dev(c.cpu()[page, slot]) for c in (b.k_cache, b.v_cache)]
-    q, table, lens = dev(b.q), dev(b.block_table), dev(b.seq_lens)
     ws = torch.full((adr.adr_decode_workspace_bytes(*b.q.shape, longest, part) // 4,), NAN, device="cuda:0")
     for flags in (0, adr.WORKSPACE_READY, adr.WORKSPACE_READY, 0):
         out, lse = torch.full(b.q.shape, NAN, device="cuda:0"), torch.full(b.q.shape[:2], NAN, device="cuda:0")
-        adr.adr_decode_step(out, q, *new, cache, table, lens, b.wl.scale, longest, part, ws, lse, flags)
+        k_new = out.view(torch.bfloat16).view(-1)[:new[0].numel()].view(new[0].shape) if over else new[0]
+        k_new.copy_(new[0])
+        step = lambda: adr.adr_decode_step(out, q, k_new, new[1], cache, table, lens, b.wl.scale, longest, part, ws, lse, flags)
+        step()
         torch.cuda.synchronize()
         assert torch.equal(out, two) and torch.equal(lse, two_lse)
         assert (ws[-128:].view(torch.int32) == 0).all()
+    assert kernels_recorded(step) == kernels
 
 
 @gpu

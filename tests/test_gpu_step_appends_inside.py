@@ -176,3 +176,118 @@ def test_long_partitions_of_an_fp8_cache_keep_the_append_kernel(d, Hkv, fp8, bou
     ws = torch.zeros(max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, bound, part), 256), dtype=torch.uint8, device="cuda:0")
     say("append kernel of long partitions d=%d fp8=%s bound=%d part=%d" % (d, fp8, bound, part))
     assert kernels_recorded(lambda: adr.adr_decode_step(out, q, new, new, cache, table, lens, d ** -0.5, bound, part, ws)) == kernels
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", [(128, 4, 2, False), (64, 2, 4, False), (128, 4, 2, True), (64, 2, 4, True)])
+@pytest.mark.parametrize("page,part", [(16, 0), (64, 128)])
+def test_new_tokens_that_are_not_finite(d, G, Hkv, fp8, page, part):
+    """Infinities and NaN among the new tokens' elements, as the first token of a page and later in it: the two calls' bits."""
+    L = np.array([1, 5, page + 1, 3 * page + 7, 600, 40 * page // page + 1], dtype=np.int32)
+    B, wide = len(L), -(-600 // page)
+    table = np.arange(B * wide).reshape(B, wide).astype(np.int32)
+    gen = torch.Generator().manual_seed(d + page)
+    data = [torch.randn(B * wide, page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    scales = [None, None]
+    if fp8:
+        data, scales = map(list, zip(*(W.quantize_pool_fp8(t, np.ones(B * wide, dtype=bool)) for t in data)))
+    q, k_new, v_new = (dev(torch.randn(B, h, d, generator=gen), torch.bfloat16) for h in (G * Hkv, Hkv, Hkv))
+    for i, x in enumerate((float("inf"), -float("inf"), float("nan"))):
+        k_new[i::4, i % Hkv, 3 + i], v_new[i::4, (i + 1) % Hkv, 9 + i] = x, x
+    lens, entries = dev(L), dev(table)
+    say("new tokens not finite d=%d fp8=%s page=%d part=%d" % (d, fp8, page, part))
+    got = []
+    for one_call in (True, False):
+        cache = adr.KVCache(*([dev(t) for t in data] + [None if s is None else dev(s) for s in scales]))
+        out, lse = torch.zeros(B, G * Hkv, d, device="cuda:0"), torch.zeros(B, G * Hkv, device="cuda:0")
+        ws = torch.full((max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, 600, part), 4) // 4,), float("nan"), device="cuda:0")
+        if one_call:
+            adr.adr_decode_step(out, q, k_new, v_new, cache, entries, lens, d ** -0.5, 600, part, ws, lse)
+        else:
+            adr.adr_kv_append(cache, k_new, v_new, entries, lens - 1)
+            adr.adr_decode_attention(out, q, cache, entries, lens, d ** -0.5, 600, part, ws, lse)
+        torch.cuda.synchronize()
+        got.append([out, lse, cache.k, cache.v] + ([cache.k_scale, cache.v_scale] if fp8 else []))
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert torch.isfinite(got[0][0][3]).all() and not torch.isfinite(got[0][0][:3]).all()
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8,bound,part", [(128, 4, 2, False, 16384, 8192), (64, 2, 4, False, 16384, 8192), (128, 4, 2, True, 40000, 8000),
+                                                    (64, 2, 4, True, 40000, 8000), (128, 4, 2, False, 9000, 0)])
+@pytest.mark.parametrize("page", [16, 64])
+def test_waves_of_more_tiles_than_a_load_of_the_table_brings(d, G, Hkv, fp8, bound, part, page):
+    """More than 64 tiles a wave (the next ids, and an fp8 cache's scales, arrive beside the new token): the two calls' bits."""
+    L = np.array([bound, bound - page, bound // 2 + 1, 4 * 64 * 16 * max(bound // part, 1) + 1 if part else 8193, 4097, 17], dtype=np.int32)
+    B, wide = len(L), -(-bound // page)
+    need = -(-L // page)
+    table = np.zeros((B, wide), dtype=np.int32)
+    start = np.concatenate([[0], np.cumsum(need)])
+    for b in range(B):
+        table[b, :need[b]] = start[b] + np.random.default_rng(b).permutation(need[b])
+    gen = torch.Generator().manual_seed(d + page)
+    data = [torch.randn(start[-1], page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    scales = [None, None]
+    if fp8:
+        data, scales = map(list, zip(*(W.quantize_pool_fp8(t, np.ones(start[-1], dtype=bool)) for t in data)))
+    q, k_new, v_new = (dev(torch.randn(B, h, d, generator=gen), torch.bfloat16) for h in (G * Hkv, Hkv, Hkv))
+    lens, entries = dev(L), dev(table)
+    say("many tiles a wave d=%d fp8=%s bound=%d part=%d page=%d" % (d, fp8, bound, part, page))
+    got = []
+    for one_call in (True, False):
+        cache = adr.KVCache(*([dev(t) for t in data] + [None if s is None else dev(s) for s in scales]))
+        out, lse = torch.full((B, G * Hkv, d), float("nan"), device="cuda:0"), torch.full((B, G * Hkv), float("nan"), device="cuda:0")
+        ws = torch.full((max(adr.adr_decode_workspace_bytes(B, G * Hkv, d, bound, part), 4) // 4,), float("nan"), device="cuda:0")
+        step = lambda: adr.adr_decode_step(out, q, k_new, v_new, cache, entries, lens, d ** -0.5, bound, part, ws, lse)
+        if one_call:
+            step()
+        else:
+            adr.adr_kv_append(cache, k_new, v_new, entries, lens - 1)
+            adr.adr_decode_attention(out, q, cache, entries, lens, d ** -0.5, bound, part, ws, lse)
+        torch.cuda.synchronize()
+        got.append([out, lse, cache.k, cache.v] + ([cache.k_scale, cache.v_scale] if fp8 else []))
+        if one_call:
+            assert kernels_recorded(step) == (2 if part else 1)
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert torch.isfinite(got[0][0]).all()
+
+
+@pytest.mark.parametrize("d,G,Hkv,fp8", [(128, 4, 2, False), (64, 2, 4, True)])
+def test_debug_build_records_what_is_not_appended(d, G, Hkv, fp8):
+    """A step whose request 1 would append to a page outside the pool: recorded as often as by the two calls, nothing is written
+    for it, and the results are the release build's."""
+    page, L, table = 16, np.array([40, 41, 180], dtype=np.int32), np.arange(3 * 13).reshape(3, 13).astype(np.int32)
+    pages = table.size
+    table[1, 2] = pages + 7
+    gen = torch.Generator().manual_seed(d)
+    data = [torch.randn(pages, page, Hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    scales = [None, None]
+    if fp8:
+        data, scales = map(list, zip(*(W.quantize_pool_fp8(t, np.ones(pages, dtype=bool)) for t in data)))
+    q, k_new, v_new = (dev(torch.randn(3, h, d, generator=gen), torch.bfloat16) for h in (G * Hkv, Hkv, Hkv))
+    lens, entries = dev(L), dev(table)
+
+    def call(one_call):
+        cache = adr.KVCache(*([dev(t) for t in data] + [None if s is None else dev(s) for s in scales]))
+        out = torch.full((3, G * Hkv, d), float("nan"), device="cuda:0")
+        if one_call:
+            adr.adr_decode_step(out, q, k_new, v_new, cache, entries, lens, d ** -0.5, 208, 0, None)
+        else:
+            adr.adr_kv_append(cache, k_new, v_new, entries, lens - 1)
+            adr.adr_decode_attention(out, q, cache, entries, lens, d ** -0.5, 208, 0, None)
+        torch.cuda.synchronize()
+        return out, cache
+
+    say("debug record of a step d=%d fp8=%s" % (d, fp8))
+    release, _ = call(True)
+    with adr.debug_library():
+        records = []
+        for one_call in (True, False):
+            adr.adr_debug_bounds_status(reset=True)
+            out, cache = call(one_call)
+            records.append(adr.adr_debug_bounds_status(reset=True))
+            assert torch.equal(out, release)
+            assert torch.equal(cache.k[pages - 1].cpu(), data[0][pages - 1])      # (the page its entry is clamped to)
+        for r in records:
+            assert (r["row"], r["index"], r["value"]) == (1, 2, pages + 7) and r["kind"] in (1, 3)
+        assert records[0]["count"] == records[1]["count"] > 1
