@@ -303,12 +303,15 @@ int choose_kernel(const adr_kv_cache *cache, int B, int Hq, int max_seq_len, int
     // and 239; four requests of 300 tokens in groups of four 9 and 12; small fp8 passes in groups of two 5 %
     // behind, large ones 20 % ahead) and in large passes of groups of one (fp8
     // 113 and 207, bf16 195 and 223).  Small passes of groups of one are the vector ALUs': with few
-    // items a workgroup's own chain of steps is all there is, and theirs is shorter (append and attention, by item and
-    // on the vector ALUs, four requests x 8 kv-heads of 512 tokens 9.4 and 7.5, of 1000 14.2 and 9.8, one of 2000 23.8
-    // and 13.1, 8 of 256 in fp8 9.8 and 7.9; one of 2000 in partitions of 256 11.0 and 10.6).  The two meet below
-    // 256 tokens, 7.5, and there a step, which the item kernel needs one launch less for, is up to 2 us ahead by
-    // item; the vector ALUs, which keep the weights in fp32, serve it all the same.  The line itself lies where an fp8
-    // cache was behind in one shape of four, by items of four waves: 32768 tokens, and 4096 a row.
+    // items a workgroup's own chain of steps is all there is, and theirs is shorter.  us, by item and on the vector ALUs, eight
+    // waves each, whole rows of 8 kv-heads, append and attention: one request of 512 tokens 8.8 and 7.5, of 1000 11.8 and 8.6, of 2000 18.7 and 16.5,
+    // four of 512 9.1 and 7.9, of 1000 12.6 and 12.2, 16 of 512 10.3 and 9.8, 64 of 256 9.2 and 10.5; fp8 one of 1000 13.4 and 9.7,
+    // four of 2000 20.0 and 17.4, 32 of 512 11.7 and 11.0, 64 of 256 11.2 and 11.5.  The two meet in bf16 near 64000 tokens over all
+    // heads, in fp8 near 130000, with 64 requests sooner; the line was drawn below that, when both were slower, and holds for both entry
+    // points.  A step is another matter:
+    // the item kernel appends inside, and is ahead in bf16 up to 512 tokens (one of 60 4.4 and 6.8, of 200 6.2 and 6.8, of 512 7.7
+    // and 7.9, of 1000 10.8 and 10.1, four of 512 7.5 and 8.0) and in all partitions of 256 (8 of 512 9.2 and 10.5), in fp8 up to
+    // 200 (6.7 and 6.8, of 512 9.5 and 8.5).  (Neither is the less exact: pairs carry their weights in three bf16 terms, 24 bits.)
     const bool few = d == 64 && G == 1 && pairs * max_seq_len <= 32768 && max_seq_len < 4096;
     if (!few && adr::decode_mfma_supports(d, G, cache->Hkv))
         return KERNEL_GRID;
@@ -545,16 +548,17 @@ int decode_attention(void *out, adr_dtype out_dtype, float *lse, const void *q, 
             };
             appends = apart(out, out_bytes) && apart(lse, lse_bytes) && apart(workspace, workspace_fits ? plan.total() : 0);
         }
-        // Without a plan, where an append kernel clears the words on its way and each item has a compute unit to itself: an
-        // item of a split row keeps its place until its results are in memory and counted, 3 us with the
-        // memory busy, and elsewhere others wait for that place (us a step, merged by a kernel of its own and
-        // inside: one request x 8 kv-heads of 1500 tokens 9.7 and 9.5, of 8000 13.7 and 13.5, three of 2000 13.2 and 12.4; with 256
-        // items, two of 2000 11.0 and 11.0, of 8000 19.8 and 19.9; beyond, three of 8000 23.7 and 24.2, 37 of median 1000 51.2
-        // and 54.5, fp8 256 of 1500 220 and 234).  And for rows of no more than 16 partitions, which a wave goes through by itself
-        // (24 of them: 15.2 and 15.7, three rows of 24 33.5 and 36.9).
-        // Rows of few partitions merge inside up to 768 items, too: what the bound makes room for is mostly empty there (23
-        // requests x 4 kv-heads, 3112 tokens in all under a bound of 1024, 17.7 and 14.7).  A pass that appends itself has
-        // nobody to clear the words and takes the merge kernel (that one 10.1 and 9.2, one of 8000 13.6 and 12.1).
+        // Without a plan, where an append kernel clears the words on its way: steps beyond 64 requests, those of an fp8 cache in long
+        // partitions, and those whose new tokens share memory with what is written.  A pass that appends itself has nobody to clear the words.
+        // Where each item has a compute unit to itself and rows have no more than 16 partitions, which a wave goes through by itself, and up to
+        // 768 items where rows have few partitions: what the bound makes room for is mostly empty there.  Elsewhere an item of a split row
+        // keeps its place until its results are in memory and counted, 3 us with the memory busy, and others wait for that place.
+        // us a step, merged by a kernel of its own and inside (lengths uniform up to the bound): words, 65 requests x 1 kv-head
+        // of up to 600 tokens 11.5 and 10.6, 127 x 1 of 1024 16.3 and 15.7, fp8 13.4 and 11.8, 16.0 and 14.9, two long partitions of 4 x 2 in heads
+        // of 64 23.5 and 22.3; bytes, 100 x 2 of up to 600 13.8 and 13.0, of 1024 18.4 and 17.9, fp8 16.6 and 15.3; level or behind by 2 %
+        // only at their edge (190 x 1 of 2048 25.5 and 26.1, groups of eight 14.0 and 14.1).
+        // Without the limits (measured when small steps came here as well): three requests x 8 of 8000 tokens 23.7 and 24.2, 37 of median
+        // 1000 51.2 and 54.5, fp8 256 of 1500 220 and 234; three rows of 24 partitions 33.5 and 36.9.
         meets = meets && split && nt && kernel == KERNEL_GRID && !appends;
         if (meets && !(cut.max_parts <= 16 && pairs * cut.max_parts <= adr::kSlots / 3 && waves <= adr::kMeetWords)) {
             meets = cut.max_parts <= 4 && (int64_t)B * cache->Hkv * cut.max_parts <= adr::kSlots && waves <= adr::kMeetBytes;

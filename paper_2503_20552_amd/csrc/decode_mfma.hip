@@ -676,8 +676,9 @@ void decode_mfma_kernel(const DecodeParams p)
     // Which head comes first changes from partition to partition: the heads are not read at one rate (pieces at
     // bytes 384 to 511 of every 1024 take a fifth longer in bf16, a third in fp8, whichever chiplet reads them), and a
     // chiplet or an engine that always had the same ones would end late or, since workgroups are handed out in turn,
-    // hold up the others (fp8: half of the places empty from the middle of the pass on).  The sum of the
-    // digits to base four does that for any power of two of heads: us a step with the heads in place and in turn, 256 requests x 8
+    // hold up the others (fp8: half of the places empty from the middle of the pass on).  So head h stands where h + u + u/4 + u/16 + u/64
+    // would, u the unit's number (fp8: within its chiplet): every fourth, 16th and 64th unit moves it on once more, which is what meets the
+    // engines in turn.  us a step with the heads in place and in turn, 256 requests x 8
     // kv-heads of median length 1500 374 and 357, fp8 199 and 190, 64 x 32 of 1000 234 and 224, heavy-tailed lengths 68.6 and 66.3.
     // (In turn by the partition's number alone: no gain, a head of every fourth still meets the same engine.)
     // Not in a short pass: it is on the chip all at once, nothing waits behind a slow head, and heads in place are ahead.  A
@@ -1012,7 +1013,8 @@ hipError_t launch_decode_mfma(const DecodeParams &params, int d, bool fp8, hipSt
     // a unit has one row then, and nothing else to run (one request x 8 kv-heads of up to 300 tokens 5.7 and 5.4, 600 6.7 and 5.9,
     // 2000 12.3 and 10.4, 4000 20.3 and 15.8; 16 x 8 of up to 1000 12.8 and 12.4, 2000 24.6 and 24.1, fp8 12.5 and 11.4, 20.2 and 18.5;
     // heads of 64 in pairs, 16 x 4 22.4 and 19.6, 32 x 4 24.7 and 24.4; with 256 rows bf16 is the same with either, with 512 of up to 600
-    // tokens 17.9 and 20.3, fp8 12.6 and 17.1).  Not where all rows are of 128 tokens or fewer, which leaves a wave one tile at most
+    // tokens 17.9 and 20.3, fp8 12.6 and 17.1; bf16 rows of one length are 1 to 4 % behind with eight where they make 50000 to 250000 tokens in all, 96 x
+    // 1000 16.3 and 16.9, mixed ones 5 to 20 % ahead).  Not where all rows are of 128 tokens or fewer, which leaves a wave one tile at most
     // and twice the results to combine (ten steps replayed: one request x 8 of 40 tokens 46.1 and 47.4, of 126 50.8 and 51.9, fp8 57.6 and
     // 64.5; five of 150 tokens 30.8 and 29.4, fp8 35.2 and 32.2).  And fp8 rows of 128 bytes leave some units to spare: 31 x 8 of 2000 tokens
     // 26.6 and 28.9, of 4000 49.0 and 53.8, of median 1000 38.5 and 36.8; 24 x 8 are level or ahead.
