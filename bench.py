@@ -46,10 +46,10 @@ HBM_PEAK_GBS = 8000.0
 # line reports traffic null rather than a stale number.
 MEASURED_TRAFFIC_BYTES = {
     # (workload, kernel[, "fp8"]): (bytes per launch, hash of csrc/ at the time, summary under profiles/)
-    (3, 'decode_mfma_kernel'): (2317144454, '01e1d6dc37a8159a', 'profiles/traffic_of_the_benchmark_kernels.md'),
-    (3, 'decode_mfma_kernel', 'fp8'): (1171380586, '01e1d6dc37a8159a', 'profiles/traffic_of_the_benchmark_kernels.md'),
-    (4, 'decode_mfma_kernel'): (343967184, '01e1d6dc37a8159a', 'profiles/traffic_of_the_benchmark_kernels.md'),
-    (2, 'decode_mfma_kernel'): (1438523506, '01e1d6dc37a8159a', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (3, 'decode_mfma_kernel'): (2317258521, 'e9d05faf4f96d844', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (3, 'decode_mfma_kernel', 'fp8'): (1171389723, 'e9d05faf4f96d844', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (4, 'decode_mfma_kernel'): (344327160, 'e9d05faf4f96d844', 'profiles/traffic_of_the_benchmark_kernels.md'),
+    (2, 'decode_mfma_kernel'): (1438574420, 'e9d05faf4f96d844', 'profiles/traffic_of_the_benchmark_kernels.md'),
 }
 
 
